@@ -164,9 +164,10 @@ struct IcpArgs {
   void* workspace;
 };
 hipError_t launch_icp_search(const IcpArgs& a, hipStream_t stream);
-// `problems` independent n x n linear assignment problems (cost row-major, binary64), n <= kIcpMaxPartitions:
-// assign[q][i] = the column given to row i at minimal total cost
-hipError_t launch_assignment(const double* cost, int32_t* assign, int problems, int n, hipStream_t stream);
+// `problems` independent linear assignment problems (cost [problems][n][m], binary64): n rows to m columns that take
+// n / m rows each (n a multiple of m, n <= kIcpMaxPartitions), at minimal total cost.  assign[q][i] = column of row i
+// times n / m, plus the row's slot in that column (0 .. n / m - 1, every slot once).
+hipError_t launch_assignment(const double* cost, int32_t* assign, int problems, int n, int m, hipStream_t stream);
 
 // ---- output-channel permutation search ---------------------------------------------------------------
 constexpr int kOcpMaxK = 16384;   // columns one workgroup of the cost kernel holds in registers
@@ -191,7 +192,7 @@ hipError_t launch_ocp_search(const OcpArgs& a, hipStream_t stream);
 
 // clustering phase of the output-channel search: balanced K-means over the sampled channels
 struct KmeansWorkspace {
-  size_t features, dist, cost, assign, total_bytes;
+  size_t features, dist, assign, total_bytes;
 };
 KmeansWorkspace kmeans_workspace_layout(const hinm_shape& s, int n_samples);
 struct KmeansArgs {

@@ -9,21 +9,18 @@
 //                three remaining values this is sum_r m1 + min(sample_j, m2): a (min, +) contraction
 //                over the V rows, the data-parallel part of the search;
 //   assignment : samples -> partitions minimising the total cost (shortest augmenting paths with row
-//                and column potentials, one workgroup per tile);
+//                and column potentials, one wave per tile: assignment.hip);
 //   apply      : every sample moves into the slot its partition vacated.
 // The arrangement is tracked as a permutation of the slots of the incoming vector index, so the
 // saliencies are gathered from W (or rho) only once.
 #include "hinm_internal.h"
-#include "wave_reduce.h"
 
 namespace hinm {
 namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxP = kIcpMaxPartitions;
-constexpr int kSmallP = 128;  // up to here a tile's cost matrix fits in LDS
 constexpr int kCostRowsPerThread = 8;
-constexpr double kInf = 1e300;
 
 // G[t][r][slot] = saliency of W[tV + r][vec_idx[t][slot]]: the caller's rho, or |w|; order = identity
 template <int DT>
@@ -107,186 +104,6 @@ __global__ __launch_bounds__(kThreads) void icp_cost_kernel(const float* __restr
   }
 }
 
-// Linear assignment by shortest augmenting paths (rows = partitions, columns = samples), one
-// workgroup per tile.  Index 0 is the virtual start column; rows and columns are 1-based inside.
-// Every loop is bounded by the problem size, so the kernel ends for any input; if the costs are not
-// finite no augmenting path is found and the tile keeps its arrangement (identity assignment).
-// Each of the up to n^2 inner steps reads one row of the cost matrix and is one dependent chain of
-// memory latency, reduction and barriers: for n <= MAXN = 128 the matrix is held in LDS (IN_LDS) and
-// the workgroup has two waves, which makes a step about three times shorter.
-template <int MAXN, int THREADS, bool IN_LDS>
-__global__ __launch_bounds__(THREADS) void icp_assign_kernel(const double* __restrict__ cost,
-                                                             int32_t* __restrict__ assign, int n) {
-  __shared__ double u[MAXN + 1], v[MAXN + 1], minv[MAXN + 1];
-  __shared__ int p[MAXN + 1], way[MAXN + 1];
-  __shared__ uint8_t used[MAXN + 1];
-  __shared__ double red_val[THREADS / 64];
-  __shared__ int red_idx[THREADS / 64];
-  extern __shared__ __attribute__((aligned(16))) double cost_lds[];  // n * n doubles when IN_LDS
-  const int t = blockIdx.x;
-  const int tid = threadIdx.x;
-  const int lane = tid & 63, wave = tid >> 6;
-  const double* a = cost + (size_t)t * n * n;
-  if constexpr (IN_LDS) {
-    for (int e = tid; e < n * n; e += THREADS) cost_lds[e] = a[e];
-  }
-  for (int j = tid; j <= n; j += THREADS) {
-    u[j] = 0.0;
-    v[j] = 0.0;
-    p[j] = 0;
-    way[j] = 0;
-    used[j] = 0;  // until the main loop: "row j is matched"
-  }
-  __syncthreads();
-  // Start from feasible potentials and a greedy partial matching instead of from nothing: v[j] = the
-  // smallest cost in column j, u[i] = the smallest reduced cost in row i, and row i takes the column
-  // where that minimum sits (the lowest one) if it is still free.  Most rows are matched here, with n
-  // reductions; only the others need an augmenting path (up to n reductions each).
-  {
-    const double* m = IN_LDS ? cost_lds : a;
-    for (int j = 1 + tid; j <= n; j += THREADS) {
-      double lo = kInf;
-      for (int i = 0; i < n; ++i) {
-        const double x = m[(size_t)i * n + (j - 1)];
-        lo = x < lo ? x : lo;
-      }
-      v[j] = lo < kInf ? lo : 0.0;
-    }
-    __syncthreads();
-    for (int i = 1; i <= n; ++i) {
-      const double* arow = m + (size_t)(i - 1) * n;
-      double best = kInf;
-      int best_j = n + 1;
-      for (int j = 1 + tid; j <= n; j += THREADS) {
-        const double x = arow[j - 1] - v[j];
-        if (x < best) {
-          best = x;
-          best_j = j;
-        }
-      }
-      wave_argmin(best, best_j, n + 1);
-      if (lane == 0) {
-        red_val[wave] = best;
-        red_idx[wave] = best_j;
-      }
-      __syncthreads();
-      if (tid == 0) {
-        double lo = red_val[0];
-        int at = red_idx[0];
-        for (int w = 1; w < THREADS / 64; ++w)
-          if (red_val[w] < lo || (red_val[w] == lo && red_idx[w] < at)) {
-            lo = red_val[w];
-            at = red_idx[w];
-          }
-        if (lo < kInf && at <= n) {
-          u[i] = lo;
-          if (p[at] == 0) {
-            p[at] = i;
-            used[i] = 1;
-          }
-        }
-      }
-      __syncthreads();
-    }
-  }
-  // rows still to be matched, in ascending order
-  __shared__ int free_list[MAXN];
-  __shared__ int n_free;
-  if (tid == 0) {
-    int count = 0;
-    for (int i = 1; i <= n; ++i)
-      if (!used[i]) free_list[count++] = i;
-    n_free = count;
-  }
-  __syncthreads();
-  const int free_rows = n_free;
-  bool failed = false;
-  for (int f = 0; f < free_rows && !failed; ++f) {
-    const int i = free_list[f];
-    if (tid == 0) p[0] = i;
-    for (int j = tid; j <= n; j += THREADS) {
-      minv[j] = kInf;
-      used[j] = 0;
-    }
-    int j0 = 0;
-    __syncthreads();
-    for (int step = 0; step <= n; ++step) {  // every pass marks one more column used
-      if (tid == 0) used[j0] = 1;
-      __syncthreads();
-      const int i0 = p[j0];
-      const double ui0 = u[i0];
-      const double* arow = (IN_LDS ? cost_lds : a) + (size_t)(i0 - 1) * n;
-      double best = kInf;
-      int best_j = n + 1;
-      for (int j = 1 + tid; j <= n; j += THREADS) {
-        if (used[j]) continue;
-        const double cur = arow[j - 1] - ui0 - v[j];
-        double m = minv[j];
-        if (cur < m) {
-          m = cur;
-          minv[j] = cur;
-          way[j] = j0;
-        }
-        if (m < best) {  // j ascends inside a thread: the first minimum is the lowest column
-          best = m;
-          best_j = j;
-        }
-      }
-      wave_argmin(best, best_j, n + 1);
-      if (lane == 0) {
-        red_val[wave] = best;
-        red_idx[wave] = best_j;
-      }
-      __syncthreads();
-      double delta = red_val[0];
-      int j1 = red_idx[0];
-#pragma unroll
-      for (int w = 1; w < THREADS / 64; ++w) {
-        const double ob = red_val[w];
-        const int oj = red_idx[w];
-        if (ob < delta || (ob == delta && oj < j1)) {
-          delta = ob;
-          j1 = oj;
-        }
-      }
-      if (!(delta < kInf) || j1 > n) {  // same value in every thread
-        failed = true;
-        break;
-      }
-      for (int j = tid; j <= n; j += THREADS) {
-        if (used[j]) {
-          u[p[j]] += delta;  // the rows matched to used columns are distinct
-          v[j] -= delta;
-        } else {
-          minv[j] -= delta;
-        }
-      }
-      j0 = j1;
-      __syncthreads();
-      if (p[j0] == 0) break;  // a free column: the path is complete
-    }
-    if (failed) break;
-    if (tid == 0) {
-      int jj = j0;
-      for (int guard = 0; jj != 0 && guard <= n; ++guard) {
-        const int j1 = way[jj];
-        p[jj] = p[j1];
-        jj = j1;
-      }
-    }
-    __syncthreads();
-  }
-  int32_t* out = assign + (size_t)t * n;
-  if (failed) {
-    for (int i = tid; i < n; i += THREADS) out[i] = i;
-  } else {
-    for (int j = 1 + tid; j <= n; j += THREADS) {
-      const int row = p[j];
-      if (row >= 1) out[row - 1] = j - 1;
-    }
-  }
-}
-
 // Moves sample assign[i] into the slot partition i vacated, and reports the total cost of the
 // assignment (partitions added in ascending order).
 __global__ __launch_bounds__(kThreads) void icp_apply_kernel(const double* __restrict__ cost,
@@ -335,17 +152,6 @@ size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
 
 }  // namespace
 
-hipError_t launch_assignment(const double* cost, int32_t* assign, int problems, int n, hipStream_t stream) {
-  if (n <= kSmallP) {  // the cost matrix in LDS: up to 128 KB beside the solver's own arrays
-    constexpr auto kernel = icp_assign_kernel<kSmallP, 128, true>;
-    if (hipError_t e = raise_lds_limit<kernel>(kSmallP * kSmallP * (int)sizeof(double)); e != hipSuccess) return e;
-    kernel<<<problems, 128, (size_t)n * n * sizeof(double), stream>>>(cost, assign, n);
-  } else {
-    icp_assign_kernel<kMaxP, kThreads, false><<<problems, kThreads, 0, stream>>>(cost, assign, n);
-  }
-  return hipGetLastError();
-}
-
 IcpWorkspace icp_workspace_layout(const hinm_shape& s) {
   const size_t T = s.M / s.V, P = s.Kv / 4;
   IcpWorkspace w;
@@ -386,7 +192,7 @@ hipError_t launch_icp_search(const IcpArgs& a, hipStream_t stream) {
     const uint8_t* smp = a.samples + (size_t)it * T * P;
     icp_split_kernel<<<rows_grid, kThreads, 0, stream>>>(G, order, smp, S, M1, M2, s.V, s.Kv);
     icp_cost_kernel<<<cost_grid, kThreads, 0, stream>>>(S, M1, M2, cost, s.V, P);
-    e = launch_assignment(cost, assign, T, P, stream);
+    e = launch_assignment(cost, assign, T, P, P, stream);
     if (e != hipSuccess) return e;
     icp_apply_kernel<<<T, kThreads, 0, stream>>>(cost, assign, smp, order,
                                                  a.objective ? a.objective + (size_t)it * T : nullptr, s.Kv);

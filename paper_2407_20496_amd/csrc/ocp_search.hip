@@ -273,60 +273,114 @@ __global__ __launch_bounds__(kThreads) void km_init_kernel(const float* __restri
   if (k < K) C[(size_t)c * K + k] = (double)F[(size_t)c * n * K + k];
 }
 
-// d[q][c], also written n times into the square matrix the assignment solver works on
+// d[q][c] for 64 clusters (one a lane) and two points a wave.  A chain of K steps per pair is the definition (the
+// rounding of every step is pinned), so the chains have to run on operands that are at hand: 64 columns of the
+// centroids at a time go through LDS (rows padded to an odd number of doubles: no bank conflicts), the points' features
+// are wave-uniform.  384 points x 48 clusters x 768 columns: 76 us with one column of a different centroid row per
+// lane and step, 29 us here.
+constexpr int kDistColumns = 64;
+constexpr int kDistPoints = 2;  // per wave
 __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __restrict__ F,
                                                                const double* __restrict__ C,
-                                                               double* __restrict__ dist, double* __restrict__ cost,
-                                                               int T, int K, int n) {
+                                                               double* __restrict__ dist, int T, int K, int points) {
 #pragma clang fp contract(off)  // product and sum are rounded separately: that rounding is part of the definition
-  const int q = blockIdx.x;
-  const int c = blockIdx.y * kThreads + threadIdx.x;
-  if (c >= T) return;
-  const float* f = F + (size_t)q * K;
-  const double* cen = C + (size_t)c * K;
-  double acc = 0.0;
-  for (int k = 0; k < K; ++k) {
-    const double diff = (double)f[k] - cen[k];
-    const double sq = diff * diff;
-    acc = acc + sq;
+  __shared__ double tile[64][kDistColumns + 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = blockIdx.y * 64;
+  const int q0 = (blockIdx.x * (kThreads / 64) + wave) * kDistPoints;
+  const float* f[kDistPoints];
+  double acc[kDistPoints];
+#pragma unroll
+  for (int p = 0; p < kDistPoints; ++p) {
+    f[p] = F + (size_t)min(q0 + p, points - 1) * K;
+    acc[p] = 0.0;
   }
-  dist[(size_t)q * T + c] = acc;
-  double* out = cost + (size_t)q * T * n + (size_t)c * n;
-  for (int s = 0; s < n; ++s) out[s] = acc;
+  for (int k0 = 0; k0 < K; k0 += kDistColumns) {
+    const int k_lane = min(k0 + lane, K - 1);
+    double mine[64 / (kThreads / 64)];
+#pragma unroll
+    for (int r = 0; r < 64 / (kThreads / 64); ++r)
+      mine[r] = C[(size_t)min(c0 + wave + r * (kThreads / 64), T - 1) * K + k_lane];
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < 64 / (kThreads / 64); ++r) tile[wave + r * (kThreads / 64)][lane] = mine[r];
+    __syncthreads();
+    const int count = min(kDistColumns, K - k0);
+    if (count == kDistColumns) {
+#pragma unroll 16
+      for (int k = 0; k < kDistColumns; ++k) {
+        const double cen = tile[lane][k];
+#pragma unroll
+        for (int p = 0; p < kDistPoints; ++p) {
+          const double diff = (double)f[p][k0 + k] - cen;
+          const double sq = diff * diff;
+          acc[p] = acc[p] + sq;
+        }
+      }
+    } else {
+      for (int k = 0; k < count; ++k) {
+        const double cen = tile[lane][k];
+#pragma unroll
+        for (int p = 0; p < kDistPoints; ++p) {
+          const double diff = (double)f[p][k0 + k] - cen;
+          const double sq = diff * diff;
+          acc[p] = acc[p] + sq;
+        }
+      }
+    }
+  }
+  if (c0 + lane < T) {
+#pragma unroll
+    for (int p = 0; p < kDistPoints; ++p)
+      if (q0 + p < points) dist[(size_t)(q0 + p) * T + c0 + lane] = acc[p];
+  }
 }
 
-// new centroids from the assignment (point q belongs to cluster assign[q] / n); block (0, 0) also
-// reports the sum of the distances of the points to the centroids they were assigned to
+// New centroids and cluster lists from the assignment (point q belongs to cluster assign[q] / n): every workgroup
+// finds its cluster's members, in ascending item order, with one pass over the assignment and then reads their
+// features only.  Block (0, 0) also reports the sum of the distances of the points to the centroids they were
+// assigned to.
 __global__ __launch_bounds__(kThreads) void km_update_kernel(const float* __restrict__ F,
                                                              const int32_t* __restrict__ assign,
                                                              const double* __restrict__ dist, double* __restrict__ C,
+                                                             int32_t* __restrict__ clusters,
                                                              double* __restrict__ objective, int T, int K, int n) {
+  __shared__ int members[kIcpMaxPartitions];
+  __shared__ int wave_count[kThreads / 64];
   const int c = blockIdx.x;
   const int k = blockIdx.y * kThreads + threadIdx.x;
   const int points = T * n;
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  int filled = 0;
+  for (int q0 = 0; q0 < points; q0 += kThreads) {
+    const int q = q0 + threadIdx.x;
+    const bool in = q < points && clamp_index(assign[q], points) / n == c;
+    const unsigned long long mask = __ballot(in);
+    if (lane == 0) wave_count[wave] = __popcll(mask);
+    __syncthreads();
+    int at = filled + __popcll(mask & ((1ull << lane) - 1ull));
+    for (int w = 0; w < kThreads / 64; ++w) {
+      if (w < wave) at += wave_count[w];
+      filled += wave_count[w];
+    }
+    if (in) members[at] = q;
+    __syncthreads();
+  }
   if (k < K) {
     double acc = 0.0;
-    for (int q = 0; q < points; ++q)
-      if (clamp_index(assign[q], points) / n == c) acc += (double)F[(size_t)q * K + k];
+#pragma unroll 4
+    for (int e = 0; e < filled; ++e) acc += (double)F[(size_t)members[e] * K + k];
     C[(size_t)c * K + k] = acc / (double)n;
   }
+  if (blockIdx.y == 0)
+    for (int e = threadIdx.x; e < n; e += kThreads)
+      clusters[(size_t)c * n + e] = e < filled ? members[e] : c * n + e;  // the latter only after a malformed assignment
   if (objective && c == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
     double total = 0.0;
     for (int q = 0; q < points; ++q) total += dist[(size_t)q * T + clamp_index(assign[q], points) / n];
     *objective = total;
   }
-}
-
-// clusters[c] = its items in ascending order
-__global__ __launch_bounds__(kThreads) void km_clusters_kernel(const int32_t* __restrict__ assign,
-                                                               int32_t* __restrict__ clusters, int T, int n) {
-  const int c = blockIdx.x * kThreads + threadIdx.x;
-  if (c >= T) return;
-  const int points = T * n;
-  int filled = 0;
-  for (int q = 0; q < points && filled < n; ++q)
-    if (clamp_index(assign[q], points) / n == c) clusters[(size_t)c * n + filled++] = q;
-  for (; filled < n; ++filled) clusters[(size_t)c * n + filled] = c * n + filled;  // only after a malformed assignment
 }
 
 size_t align256(size_t x) { return (x + 255) & ~(size_t)255; }
@@ -339,7 +393,6 @@ KmeansWorkspace kmeans_workspace_layout(const hinm_shape& s, int n_samples) {
   size_t off = 0;
   w.features = off; off += align256(points * s.K * sizeof(float));
   w.dist = off;     off += align256(points * T * sizeof(double));
-  w.cost = off;     off += align256(points * points * sizeof(double));
   w.assign = off;   off += align256(points * sizeof(int32_t));
   w.total_bytes = off;
   return w;
@@ -352,7 +405,6 @@ hipError_t launch_ocp_cluster(const KmeansArgs& a, hipStream_t stream) {
   uint8_t* ws = static_cast<uint8_t*>(a.workspace);
   float* F = reinterpret_cast<float*>(ws + w.features);
   double* dist = reinterpret_cast<double*>(ws + w.dist);
-  double* cost = reinterpret_cast<double*>(ws + w.cost);
   int32_t* assign = reinterpret_cast<int32_t*>(ws + w.assign);
   const uint16_t* Wb = static_cast<const uint16_t*>(a.W);
   const int k_blocks = (s.K + kThreads - 1) / kThreads;
@@ -366,16 +418,16 @@ hipError_t launch_ocp_cluster(const KmeansArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   for (int r = 0; r < a.rounds; ++r) {
-    km_distance_kernel<<<dim3(points, (T + kThreads - 1) / kThreads), kThreads, 0, stream>>>(F, a.centroids, dist, cost,
-                                                                                             T, s.K, n);
+    constexpr int kPointsPerBlock = kDistPoints * (kThreads / 64);
+    km_distance_kernel<<<dim3((points + kPointsPerBlock - 1) / kPointsPerBlock, (T + 63) / 64), kThreads, 0, stream>>>(
+        F, a.centroids, dist, T, s.K, points);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_assignment(cost, assign, 1, points, stream);
+    e = launch_assignment(dist, assign, 1, points, T, stream);
     if (e != hipSuccess) return e;
-    km_update_kernel<<<dim3(T, k_blocks), kThreads, 0, stream>>>(F, assign, dist, a.centroids,
+    km_update_kernel<<<dim3(T, k_blocks), kThreads, 0, stream>>>(F, assign, dist, a.centroids, a.clusters,
                                                                  a.objective ? a.objective + r : nullptr, T, s.K, n);
   }
-  km_clusters_kernel<<<(T + kThreads - 1) / kThreads, kThreads, 0, stream>>>(assign, a.clusters, T, n);
   return hipGetLastError();
 }
 
@@ -419,7 +471,7 @@ hipError_t launch_ocp_search(const OcpArgs& a, hipStream_t stream) {
     else ocp_cost_wide_kernel<64><<<cost_grid, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
     hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
-    e = launch_assignment(cost, assign, 1, T, stream);
+    e = launch_assignment(cost, assign, 1, T, T, stream);
     if (e != hipSuccess) return e;
     ocp_moved_kernel<<<T, kThreads, 0, stream>>>(cost, assign, a.row_order, smp, cl, moved,
                                                  a.objective ? a.objective + it : nullptr, T, s.V, n);
