@@ -23,41 +23,54 @@ typedef uint32_t quad_t __attribute__((ext_vector_type(4)));  // 16 bytes for no
 
 constexpr int kScoreThreads = 256;
 constexpr int kSelectThreads = 1024;
+constexpr int kSelectDigit = 11;                  // bits a pass of select decides
+constexpr int kSelectBins = 1 << kSelectDigit;
 constexpr int kEmitThreads = 256;
 
 // ---------------------------------------------------------------------------------------------
-// score: one thread owns VEC adjacent columns of one tile and walks down the V rows.
-// The products are exact in binary64 (both factors carry at most 11 significand bits), so the
+// score: one thread owns VEC adjacent columns of one tile and walks down the V rows, ROWS of them requested at a
+// time.  The products are exact in binary64 (both factors carry at most 11 significand bits), so the
 // fused multiply-add rounds exactly like a separate add would; only the add order matters and
 // it is fixed to ascending rows.
+// Bound by memory, so what counts is bytes in flight, about 16 MB on the chip: large layers have enough threads with
+// eight columns each (16384 x 16384 91 us, 5.9 TB/s); the 44032 threads of 11008 x 4096 with V = 128 had 7 MB in flight and
+// took 64 us, with two columns a thread and 32 rows at a time 16 us.
 // ---------------------------------------------------------------------------------------------
-template <int DT, int VEC>
+template <int DT, int VEC, int ROWS>
 __global__ __launch_bounds__(kScoreThreads) void score_kernel(const uint16_t* __restrict__ W,
                                                               double* __restrict__ scores, int K, int V) {
   const int t = blockIdx.y;
   const int64_t c0 = ((int64_t)blockIdx.x * kScoreThreads + threadIdx.x) * VEC;
   if (c0 >= K) return;
   const uint16_t* p = W + (size_t)t * V * K + c0;
+  constexpr int WORDS = VEC > 1 ? VEC / 2 : 1;
+  typedef uint32_t words_t __attribute__((ext_vector_type(WORDS)));
   double s[VEC];
 #pragma unroll
   for (int e = 0; e < VEC; ++e) s[e] = 0.0;
-  for (int i = 0; i < V; ++i) {
-    uint16_t w[VEC];
-    if constexpr (VEC == 8) {
-      const quad_t q = __builtin_nontemporal_load(reinterpret_cast<const quad_t*>(p));  // streamed once here (C5: 110 -> 91 us)
-      w[0] = q.x & 0xFFFF; w[1] = q.x >> 16; w[2] = q.y & 0xFFFF; w[3] = q.y >> 16;
-      w[4] = q.z & 0xFFFF; w[5] = q.z >> 16; w[6] = q.w & 0xFFFF; w[7] = q.w >> 16;
+  auto load = [&](int i) -> words_t {
+    if constexpr (VEC > 1) {
+      return __builtin_nontemporal_load(reinterpret_cast<const words_t*>(p + (size_t)i * K));  // streamed once here
     } else {
-#pragma unroll
-      for (int e = 0; e < VEC; ++e) w[e] = p[e];
+      return words_t{(uint32_t)p[(size_t)i * K]};
     }
+  };
+  auto add = [&](words_t w) {
 #pragma unroll
     for (int e = 0; e < VEC; ++e) {
-      const double a = (double)bits_to_float<DT>(w[e]);
+      const double a = (double)bits_to_float<DT>((uint16_t)(w[e / 2] >> (16 * (e & 1))));
       s[e] = __builtin_fma(a, a, s[e]);
     }
-    p += K;
+  };
+  int i = 0;
+  for (; i + ROWS <= V; i += ROWS) {
+    words_t w[ROWS];
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) w[r] = load(i + r);
+#pragma unroll
+    for (int r = 0; r < ROWS; ++r) add(w[r]);
   }
+  for (; i < V; ++i) add(load(i));
   double* out = scores + (size_t)t * K + c0;
 #pragma unroll
   for (int e = 0; e < VEC; ++e) out[e] = s[e];
@@ -98,9 +111,12 @@ __global__ __launch_bounds__(kScoreThreads) void score_rho_kernel(const float* _
 // select: one workgroup per tile.  A score's bit pattern is turned into a key that orders like an
 // unsigned 64-bit integer (sign bit set for non-negative values, all bits flipped for negative ones;
 // sums start from +0, so -0 does not occur and equal values have equal keys; NaN is not supported).
-// An 8-bit-digit radix descent finds the Kv-th largest key tau and
+// An 11-bit-digit radix descent below the leading bits that all keys share finds the Kv-th largest key tau and
 // how many keys equal to tau still have to be taken; those are taken from the lowest columns.
 // A final in-order sweep with workgroup prefix sums writes the kept columns ascending.
+// Bound by the latency of its passes (one workgroup per tile): 8-bit digits from the top bit took four passes and two
+// atomics per wave and pass for the bins that everyone hits; two passes now.  86 tiles of 4096 columns 9.8 -> 7.8 us,
+// 32 of 11008 22 -> 13.8 us, 128 of 16384 28 -> 16 us.
 // ---------------------------------------------------------------------------------------------
 __device__ __forceinline__ unsigned long long ordered_key(unsigned long long bits) {
   return (bits >> 63) ? ~bits : (bits | (1ull << 63));
@@ -129,8 +145,9 @@ __device__ __forceinline__ uint32_t block_exclusive_count(bool flag, uint32_t* w
 template <int KPT>
 __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __restrict__ scores,
                                                                 int32_t* __restrict__ vec_idx, int K, int Kv) {
-  __shared__ uint32_t hist[256];
+  __shared__ uint32_t hist[kSelectBins];
   __shared__ uint32_t wave_tot[kSelectThreads / 64];
+  __shared__ unsigned long long wave_and[kSelectThreads / 64], wave_or[kSelectThreads / 64];
   __shared__ unsigned long long s_prefix;
   __shared__ uint32_t s_need;
   __shared__ uint32_t s_in_bin;  // keys in the bin the last pass chose
@@ -147,83 +164,101 @@ __global__ __launch_bounds__(kSelectThreads) void select_kernel(const double* __
   }
   const int chunks = KPT > 0 ? KPT : (K + kSelectThreads - 1) / kSelectThreads;
 
-  unsigned long long prefix = 0, mask = 0;
-  uint32_t need = (uint32_t)Kv;  // the need-th largest among keys that match prefix under mask
-  for (int shift = 56; shift >= 0; shift -= 8) {
-    if (threadIdx.x < 256) hist[threadIdx.x] = 0;
-    __syncthreads();
+  // Scores of one tile share their leading bits (sign, most of the exponent, often more): the digits start below the
+  // bits that all keys have in common.
+  unsigned long long all_and = ~0ull, all_or = 0ull;
+#pragma unroll
+  for (int c = 0; c < chunks; ++c) {
+    const int k = c * kSelectThreads + threadIdx.x;
+    if (k < K) {
+      unsigned long long u;
+      if constexpr (KPT > 0) u = held[c];
+      else u = ordered_key(key[k]);
+      all_and &= u;
+      all_or |= u;
+    }
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) {
+    all_and &= (unsigned long long)__shfl_xor((long long)all_and, off);
+    all_or |= (unsigned long long)__shfl_xor((long long)all_or, off);
+  }
+  if ((threadIdx.x & 63) == 0) {
+    wave_and[threadIdx.x >> 6] = all_and;
+    wave_or[threadIdx.x >> 6] = all_or;
+  }
+  for (int b = threadIdx.x; b < kSelectBins; b += kSelectThreads) hist[b] = 0;
+  __syncthreads();
+  all_and = wave_and[0];
+  all_or = wave_or[0];
+  for (int w = 1; w < kSelectThreads / 64; ++w) {
+    all_and &= wave_and[w];
+    all_or |= wave_or[w];
+  }
+  const unsigned long long differ = all_and ^ all_or;
+  int low = differ ? 64 - __clzll((long long)differ) : 0;  // bits below this position are undecided
+  unsigned long long prefix = low < 64 ? all_and & (~0ull << low) : 0ull;
+  uint32_t need = (uint32_t)Kv;  // the need-th largest among keys that match prefix above `low`
+  uint32_t in_bin = (uint32_t)K;
+  while (low > 0 && in_bin != need) {
+    // (every key of the chosen bin wanted: the lower digits decide nothing any more.  With distinct scores this
+    // happens after two passes.)
+    const unsigned long long mask = low < 64 ? ~0ull << low : 0ull;
+    const int shift = low > kSelectDigit ? low - kSelectDigit : 0;
+    const uint32_t digit_mask = (1u << (low - shift)) - 1u;
 #pragma unroll
     for (int c = 0; c < chunks; ++c) {
       const int k = c * kSelectThreads + threadIdx.x;
       unsigned long long u;
       if constexpr (KPT > 0) u = held[c];
       else u = (k < K) ? ordered_key(key[k]) : 0ull;
-      bool pending = (k < K) && ((u & mask) == prefix);
-      const uint32_t d = (uint32_t)(u >> shift) & 255u;
-      // Scores of one tile share their leading bits, so in the first passes nearly every lane hits the
-      // same bin: count the two most common digits of the wave with one atomic each, the rest singly.
-#pragma unroll
-      for (int round = 0; round < 2; ++round) {
-        const unsigned long long todo = __ballot(pending);
-        if (todo == 0ull) break;
-        const int leader = __ffsll((long long)todo) - 1;
-        const uint32_t dl = (uint32_t)__shfl((int)d, leader);
-        const unsigned long long same = __ballot(pending && d == dl);
-        if ((int)(threadIdx.x & 63) == leader) atomicAdd(&hist[dl], (uint32_t)__popcll(same));
-        pending = pending && d != dl;
-      }
-      if (pending) atomicAdd(&hist[d], 1u);
+      if ((k < K) && ((u & mask) == prefix)) atomicAdd(&hist[(uint32_t)(u >> shift) & digit_mask], 1u);
     }
     __syncthreads();
-    // Find the digit that holds the need-th largest key: the first wave scans the 256 bins from the
-    // top, four bins per lane (lane 0 owns the highest four).
-    if (threadIdx.x < 64) {
-      const int lane = threadIdx.x;
-      uint32_t h[4];
-      uint32_t mine = 0;
+    // Find the digit that holds the need-th largest key: every thread owns kPer bins, the highest first, and a
+    // scan over the threads says how many keys lie above them.
+    constexpr int kPer = kSelectBins / kSelectThreads;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    uint32_t h[kPer], mine = 0;
 #pragma unroll
-      for (int q = 0; q < 4; ++q) {
-        h[q] = hist[255 - (4 * lane + q)];
-        mine += h[q];
-      }
-      uint32_t incl = mine;  // inclusive prefix over lanes = keys in this lane's bins or higher ones
+    for (int q = 0; q < kPer; ++q) {
+      h[q] = hist[kSelectBins - 1 - (kPer * (int)threadIdx.x + q)];
+      mine += h[q];
+    }
+    uint32_t incl = mine;
 #pragma unroll
-      for (int off = 1; off < 64; off <<= 1) {
-        const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
-        if (lane >= off) incl += v;
-      }
-      uint32_t above = incl - mine;  // keys in strictly higher lanes' bins
-      const bool here = (above < need) && (incl >= need);
-      const bool nowhere = (__ballot(here) == 0ull);  // fewer keys than asked for: cannot happen for Kv <= K
-      if (here || (nowhere && lane == 63)) {
-        int pick = 3;
+    for (int off = 1; off < 64; off <<= 1) {
+      const uint32_t v = (uint32_t)__shfl_up((int)incl, off);
+      if (lane >= off) incl += v;
+    }
+    if (lane == 63) wave_tot[wave] = incl;
+    __syncthreads();
 #pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          if (above + h[q] >= need) {
-            pick = q;
-            break;
-          }
-          above += h[q];
-        }
-        s_prefix = prefix | ((unsigned long long)(255 - (4 * lane + pick)) << shift);
+    for (int q = 0; q < kPer; ++q) hist[kSelectBins - 1 - (kPer * (int)threadIdx.x + q)] = 0;  // for the next pass
+    uint32_t above = incl - mine;
+    for (int w = 0; w < kSelectThreads / 64; ++w)
+      if (w < wave) above += wave_tot[w];
+#pragma unroll
+    for (int q = 0; q < kPer; ++q) {
+      if (above < need && above + h[q] >= need) {  // one bin of one thread
+        s_prefix = prefix | ((unsigned long long)(kSelectBins - 1 - (kPer * (int)threadIdx.x + q)) << shift);
         s_need = need - above;
-        s_in_bin = h[pick];
+        s_in_bin = h[q];
       }
+      above += h[q];
     }
     __syncthreads();
     prefix = s_prefix;
     need = s_need;
-    mask |= 0xFFull << shift;
-    // Every key of the chosen bin is wanted: the lower digits decide nothing any more.  (With distinct scores
-    // this happens after three or four of the eight passes.)
-    if (s_in_bin == need) break;
+    in_bin = s_in_bin;
+    low = shift;
   }
   // tau = the Kv-th largest key, or, after an early exit, its leading digits with zeros behind them: in both
   // cases keys above tau survive, and of the keys equal to tau (only possible without an early exit) the
   // take_equal lowest columns do.
   const unsigned long long tau = prefix;
   const uint32_t take_equal = need;
-  const bool ties_cut = s_in_bin != need;  // some keys equal to tau are dropped: their order matters
+  const bool ties_cut = in_bin != need;  // some keys equal to tau are dropped: their order matters
 
   int32_t* out = vec_idx + (size_t)t * Kv;
   if constexpr (KPT > 0) {
@@ -653,20 +688,26 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t stream) {
   const uint16_t* Wb = static_cast<const uint16_t*>(a.W);
   uint16_t* vals = static_cast<uint16_t*>(a.vals);
   const bool vec8 = (s.K % 8 == 0) && ((reinterpret_cast<uintptr_t>(a.W) & 15u) == 0);
+  const bool vec2 = (s.K % 2 == 0) && ((reinterpret_cast<uintptr_t>(a.W) & 3u) == 0);
   const bool rho_vec4 = a.rho && (s.K % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.rho) & 15u) == 0);
   // ---- score
-  const int cols_per_thread = a.rho ? (rho_vec4 ? 4 : 1) : (vec8 ? 8 : 1);
+  // eight columns a thread where that leaves sixteen waves for every compute unit, else two (see score_kernel)
+  const bool score8 = vec8 && (int64_t)T * (s.K / 8) >= 256 * 16 * 64;
+  const int cols_per_thread = a.rho ? (rho_vec4 ? 4 : 1) : (score8 ? 8 : vec2 ? 2 : 1);
   const int threads_needed = (s.K + cols_per_thread - 1) / cols_per_thread;
   dim3 grid((threads_needed + kScoreThreads - 1) / kScoreThreads, T);
+  auto score = [&](auto kernel) { kernel<<<grid, kScoreThreads, 0, stream>>>(Wb, a.scores, s.K, s.V); };
   if (a.rho) {
     if (rho_vec4) score_rho_kernel<4><<<grid, kScoreThreads, 0, stream>>>(a.rho, a.scores, s.K, s.V);
     else score_rho_kernel<1><<<grid, kScoreThreads, 0, stream>>>(a.rho, a.scores, s.K, s.V);
   } else if (s.dtype == HINM_F16) {
-    if (vec8) score_kernel<HINM_F16, 8><<<grid, kScoreThreads, 0, stream>>>(Wb, a.scores, s.K, s.V);
-    else score_kernel<HINM_F16, 1><<<grid, kScoreThreads, 0, stream>>>(Wb, a.scores, s.K, s.V);
+    if (score8) score(score_kernel<HINM_F16, 8, 4>);
+    else if (vec2) score(score_kernel<HINM_F16, 2, 32>);
+    else score(score_kernel<HINM_F16, 1, 32>);
   } else {
-    if (vec8) score_kernel<HINM_BF16, 8><<<grid, kScoreThreads, 0, stream>>>(Wb, a.scores, s.K, s.V);
-    else score_kernel<HINM_BF16, 1><<<grid, kScoreThreads, 0, stream>>>(Wb, a.scores, s.K, s.V);
+    if (score8) score(score_kernel<HINM_BF16, 8, 4>);
+    else if (vec2) score(score_kernel<HINM_BF16, 2, 32>);
+    else score(score_kernel<HINM_BF16, 1, 32>);
   }
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
