@@ -14,6 +14,7 @@ _HERE = os.path.dirname(os.path.abspath(__file__))
 # HINM_LIBRARY names another build of the same library (the host-sanitized one of build.py --sanitize)
 _LIB_PATH = os.environ.get("HINM_LIBRARY") or os.path.join(_HERE, "libhinm.so")
 _lib = None
+_native = None  # the call module, bound to _lib (python_calls.cpp: marshalling of the calls a program makes often)
 
 
 class HinmError(RuntimeError):
@@ -53,7 +54,7 @@ def calib_symbols() -> Tuple[str, ...]:
 def load_library():
     """Load libhinm.so (built in-tree by ``python -m paper_2407_20496_amd.build``).
     Raises if it is missing: there is no fallback path."""
-    global _lib
+    global _lib, _native
     if _lib is not None:
         return _lib
     if not os.path.exists(_LIB_PATH):
@@ -126,6 +127,15 @@ def load_library():
     lib.hinm_status_str.restype = C.c_char_p
     lib.hinm_version.argtypes = []
     lib.hinm_version.restype = C.c_int32
+    try:
+        from . import _calls
+    except ImportError as e:
+        raise RuntimeError("the call module of this package is missing: build it with "
+                           "`python -m paper_2407_20496_amd.build`") from e
+    _calls.bind(*[C.cast(getattr(lib, f), C.c_void_p).value for f in
+                  ("hinm_pack", "hinm_prepare", "hinm_spmm", "hinm_spmm_vectors", "hinm_spmm_prepared", "hinm_chain")],
+                _dtype_code, _stream)
+    _native = _calls
     _lib = lib
     return lib
 
@@ -171,7 +181,10 @@ def _stream(stream) -> Optional[int]:
     if stream is None:
         import torch
         if torch.cuda.is_available():
-            return torch.cuda.current_stream().cuda_stream or None
+            stream = torch.cuda.current_stream().cuda_stream or None  # initialises the device layer the first time
+            if _native is not None:
+                _native.set_stream_source(torch._C._cuda_getDevice, torch._C._cuda_getCurrentRawStream)
+            return stream
         return None
     if isinstance(stream, int):
         return stream or None
@@ -192,9 +205,11 @@ def hinm_pack_sizes(M, K, V, Kv, dtype) -> Tuple[int, int, int, int]:
 
 
 def hinm_pack(M, K, V, Kv, dtype, W, vals, nm_idx, vec_idx, workspace, workspace_bytes, stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_pack(C.byref(_shape(M, K, V, Kv, dtype)), _ptr(W), _ptr(vals), _ptr(nm_idx), _ptr(vec_idx),
-                         _ptr(workspace), int(workspace_bytes), _stream(stream)), "hinm_pack")
+    if _lib is None:
+        load_library()
+    status = _native.pack(M, K, V, Kv, dtype, W, vals, nm_idx, vec_idx, workspace, workspace_bytes, stream)
+    if status:
+        raise HinmError(status, "hinm_pack")
 
 
 PACK_STATIC_MAX_SCORES = 524288
@@ -242,10 +257,11 @@ def hinm_pack_vectors(M, K, V, Kv, dtype, W, rho, tile_order, vals_v, vec_idx, w
 
 def hinm_spmm_vectors(M, K, V, Kv, dtype, N, vals_v, vec_idx, pi_in, pi_out, X, ldx, Y, ldy, flags=0,
                       stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_spmm_vectors(C.byref(_shape(M, K, V, Kv, dtype)), int(N), _ptr(vals_v), _ptr(vec_idx),
-                                 _ptr(pi_in), _ptr(pi_out), _ptr(X), int(ldx), _ptr(Y), int(ldy), int(flags),
-                                 _stream(stream)), "hinm_spmm_vectors")
+    if _lib is None:
+        load_library()
+    status = _native.spmm_vectors(M, K, V, Kv, dtype, N, vals_v, vec_idx, pi_in, pi_out, X, ldx, Y, ldy, flags, stream)
+    if status:
+        raise HinmError(status, "hinm_spmm_vectors")
 
 
 def hinm_icp_sizes(M, K, V, Kv, dtype) -> int:
@@ -306,10 +322,12 @@ def hinm_unpack(M, K, V, Kv, dtype, vals, nm_idx, vec_idx, W_out, stream=None) -
 
 def hinm_spmm(M, K, V, Kv, dtype, N, vals, nm_idx, vec_idx, pi_in, pi_out, X, ldx, Y, ldy, flags=0,
               workspace=None, workspace_bytes=0, stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_spmm(C.byref(_shape(M, K, V, Kv, dtype)), int(N), _ptr(vals), _ptr(nm_idx), _ptr(vec_idx),
-                         _ptr(pi_in), _ptr(pi_out), _ptr(X), int(ldx), _ptr(Y), int(ldy), int(flags),
-                         _ptr(workspace), int(workspace_bytes), _stream(stream)), "hinm_spmm")
+    if _lib is None:
+        load_library()
+    status = _native.spmm(M, K, V, Kv, dtype, N, vals, nm_idx, vec_idx, pi_in, pi_out, X, ldx, Y, ldy, flags,
+                          workspace, workspace_bytes, stream)
+    if status:
+        raise HinmError(status, "hinm_spmm")
 
 
 def hinm_prepare_sizes(M, K, V, Kv, dtype) -> int:
@@ -321,10 +339,11 @@ def hinm_prepare_sizes(M, K, V, Kv, dtype) -> int:
 
 def hinm_prepare(M, K, V, Kv, dtype, vals, nm_idx, vec_idx, pi_in, pi_out, prepared, prepared_bytes,
                  stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_prepare(C.byref(_shape(M, K, V, Kv, dtype)), _ptr(vals), _ptr(nm_idx), _ptr(vec_idx),
-                            _ptr(pi_in), _ptr(pi_out), _ptr(prepared), int(prepared_bytes), _stream(stream)),
-           "hinm_prepare")
+    if _lib is None:
+        load_library()
+    status = _native.prepare(M, K, V, Kv, dtype, vals, nm_idx, vec_idx, pi_in, pi_out, prepared, prepared_bytes, stream)
+    if status:
+        raise HinmError(status, "hinm_prepare")
 
 
 def hinm_spmm_prepared_workspace(M, K, V, Kv, dtype, N) -> int:
@@ -337,10 +356,12 @@ def hinm_spmm_prepared_workspace(M, K, V, Kv, dtype, N) -> int:
 
 def hinm_spmm_prepared(M, K, V, Kv, dtype, N, prepared, X, ldx, Y, ldy, flags=0, workspace=None,
                        workspace_bytes=0, stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_spmm_prepared(C.byref(_shape(M, K, V, Kv, dtype)), int(N), _ptr(prepared), _ptr(X), int(ldx),
-                                  _ptr(Y), int(ldy), int(flags), _ptr(workspace), int(workspace_bytes),
-                                  _stream(stream)), "hinm_spmm_prepared")
+    if _lib is None:
+        load_library()
+    status = _native.spmm_prepared(M, K, V, Kv, dtype, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes,
+                                   stream)
+    if status:
+        raise HinmError(status, "hinm_spmm_prepared")
 
 
 def hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ldx, ldy, flags=0) -> Tuple[str, int]:
@@ -438,6 +459,8 @@ def hinm_chain_sizes(layers: Sequence[Layer], N: int) -> int:
 
 
 def hinm_chain(layers: Sequence[Layer], N, X, ldx, Y, ldy, scratch, scratch_bytes, stream=None) -> None:
-    lib = load_library()
-    _check(lib.hinm_chain(len(layers), _layers(layers), int(N), _ptr(X), int(ldx), _ptr(Y), int(ldy),
-                          _ptr(scratch), int(scratch_bytes), _stream(stream)), "hinm_chain")
+    if _lib is None:
+        load_library()
+    status = _native.chain(layers, N, X, ldx, Y, ldy, scratch, scratch_bytes, stream)
+    if status:
+        raise HinmError(status, "hinm_chain")

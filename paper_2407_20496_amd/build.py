@@ -1,4 +1,4 @@
-"""Build libhinm.so (gfx950) in-tree with hipcc.  Used by __graft_entry__.build() and by hand:
+"""Build libhinm.so (gfx950) and the Python call module in-tree with hipcc.  Used by __graft_entry__.build() and by hand:
 
     python -m paper_2407_20496_amd.build
     python -m paper_2407_20496_amd.build --sanitize    # host code under ASan + UBSan -> _build/libhinm_sanitize.so
@@ -11,6 +11,7 @@ from __future__ import annotations
 import os
 import subprocess
 import sys
+import sysconfig
 from concurrent.futures import ThreadPoolExecutor
 
 HERE = os.path.dirname(os.path.abspath(__file__))
@@ -64,10 +65,27 @@ def _compile(src: str, sanitize: bool = False) -> str:
     return obj
 
 
+CALLS = os.path.join(HERE, "_calls" + (sysconfig.get_config_var("EXT_SUFFIX") or ".so"))
+
+
+def _build_calls() -> str:
+    """The Python call module: host code only, built with the host compiler and linked to nothing (it gets the library's
+    entry points at run time; hipcc would link a second HIP runtime into the process)."""
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-shared", "-Wall",
+           "-I", os.path.join(ROOT, "include"), "-I", sysconfig.get_paths()["include"],
+           os.path.join(CSRC, "python_calls.cpp"), "-o", CALLS]
+    res = subprocess.run(cmd, capture_output=True, text=True)
+    if res.returncode != 0:
+        raise RuntimeError("building python_calls.cpp failed:\n" + res.stderr)
+    return CALLS
+
+
 def build(verbose: bool = True, sanitize: bool = False) -> str:
     os.makedirs(OBJ_DIR, exist_ok=True)
     with ThreadPoolExecutor(max_workers=min(8, len(SOURCES))) as ex:
+        calls = ex.submit(_build_calls)
         objs = list(ex.map(lambda src: _compile(src, sanitize), SOURCES))
+        calls.result()
     lib = SANITIZE_LIB if sanitize else LIB
     cmd = [HIPCC, "--offload-arch=gfx950", "-shared", "-fPIC", "-o", lib, *objs]
     if sanitize:
