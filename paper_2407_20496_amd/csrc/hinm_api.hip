@@ -48,9 +48,11 @@ hinm_status run_spmm(const SpmmArgs& a, uint32_t flags, hipStream_t stream) {
     if (a.N > 16 || !spmm_skinny_supported(a)) return HINM_ERR_UNSUPPORTED;
     e = launch_spmm_skinny(a, stream);
   } else {
-    // by shape: few columns -> k-split skinny kernel (bandwidth-bound on the packed weights);
-    // otherwise the tile kernel; shapes neither covers fall back to the plain kernel.
-    if (a.N <= 16 && spmm_skinny_supported(a)) e = launch_spmm_skinny(a, stream);
+    // by shape: a moderate number of columns -> wave-private kernel; one column, or sixteen on a small layer -> k-split
+    // skinny kernel (bandwidth-bound on the packed weights); otherwise the tile kernel; shapes none covers fall back to
+    // the plain kernel.
+    if (spmm_mid_canonical_preferred(a)) e = launch_spmm_mid_canonical(a, stream);
+    else if (a.N <= 16 && spmm_skinny_supported(a)) e = launch_spmm_skinny(a, stream);
     else if (spmm_tile_supported(a)) e = launch_spmm_tile(a, stream);
     else if (spmm_skinny_supported(a)) e = launch_spmm_skinny(a, stream);
     else e = launch_spmm_reference(a, stream);
@@ -444,7 +446,7 @@ hinm_status hinm_spmm_prepared_workspace(const hinm_shape* shape, int32_t N, siz
 
 // Which kernel family a prepared call runs on; everything that can make the call fail is decided here, on the
 // host, before anything is launched (hinm_chain validates every layer with it before its first launch).
-enum class PreparedRoute { Rows16, Skinny, Panel, Tile };
+enum class PreparedRoute { Mid, Rows16, Skinny, Panel, Tile };
 
 static PreparedArgs prepared_args(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                   void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes) {
@@ -452,9 +454,15 @@ static PreparedArgs prepared_args(const hinm_shape* shape, int32_t N, const void
                       (int)((flags & HINM_VARIANT_MASK) >> HINM_VARIANT_SHIFT), workspace, workspace_bytes};
 }
 
-static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route) {
+// with_mid = false: as if there were no kernel for a moderate number of columns (what the measurement launches of the
+// tile kernel go by, which serve shapes that now run on that kernel too).
+static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, bool with_mid = true) {
   const hinm_shape* shape = &a.s;
   const int32_t N = a.N;
+  if (with_mid && a.tile_variant == 0 && spmm_mid_prepared_preferred(a)) {
+    *route = PreparedRoute::Mid;
+    return HINM_OK;
+  }
   // up to 16 columns: 16-row workgroups on the 16x16x64 form (measured faster than the 32-row kernel on every
   // decode shape tried, by 8-10 % with 344 row blocks of 32 and by 15-37 % with 128); variant 11 pins it for any N, 19 its form with
   // the input rows resident in LDS (16 columns only)
@@ -527,6 +535,7 @@ static hinm_status run_prepared(const hinm_shape* shape, int32_t N, const void* 
   if (st != HINM_OK) return st;
   hipError_t e = hipSuccess;
   switch (route) {
+    case PreparedRoute::Mid: e = launch_spmm_mid_prepared(a, stream); break;
     case PreparedRoute::Rows16: e = launch_spmm_rows16_prepared(a, stream); break;
     case PreparedRoute::Skinny: e = launch_spmm_skinny_prepared(a, stream); break;
     case PreparedRoute::Panel: e = launch_spmm_panel_prepared(a, stream); break;
@@ -567,7 +576,7 @@ hinm_status hinm_calib_tile_part(const hinm_shape* shape, int32_t N, const void*
   if (part != 1 && part != 2) return HINM_ERR_UNSUPPORTED;
   PreparedArgs a = prepared_args(shape, N, prepared, X, ldx, no_y, (N + 7) / 8 * 8, 0, nullptr, 0);
   PreparedRoute route;
-  st = route_prepared(a, &route);
+  st = route_prepared(a, &route, false);
   if (st != HINM_OK) return st;
   if (route != PreparedRoute::Tile) return HINM_ERR_UNSUPPORTED;
   hipError_t e = launch_spmm_tile_prepared_part(a, part, static_cast<hipStream_t>(stream));

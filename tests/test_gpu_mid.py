@@ -1,0 +1,77 @@
+"""The kernel for a moderate number of columns (csrc/spmm_mid.hip) in every block shape its dispatch takes, from both
+layer forms, against the CPU oracle: ragged columns and kept columns, waves without steps, odd numbers of steps."""
+import numpy as np
+import pytest
+
+import hinm_synth as synth
+from tests.test_gpu_prepared import _check as check_prepared
+from tests.test_gpu_spmm import _check_full as check_canonical
+
+pytestmark = pytest.mark.gpu
+
+# M, K, V, Kv, N, (32-row blocks, 32-column blocks, waves) of a workgroup
+PREPARED = [
+    (64, 256, 32, 200, 37, (1, 1, 4)),
+    (192, 640, 96, 584, 33, (1, 1, 8)),      # ten steps on eight waves
+    (128, 2048, 64, 1992, 17, (1, 1, 8)),    # 32 steps, the last one padded
+    (9600, 128, 64, 72, 20, (2, 1, 8)),      # two steps: six waves have none
+    (9600, 128, 64, 72, 2, (2, 1, 8)),
+    (4096, 320, 32, 264, 9, (1, 1, 8)),
+    (640, 640, 64, 584, 965, (2, 2, 8)),
+    (1280, 320, 64, 264, 965, (2, 2, 4)),
+    (640, 320, 64, 264, 1765, (2, 2, 4)),     # beyond 1024 columns: fewer than 1024 rows
+    (2560, 320, 64, 264, 965, (2, 2, 2)),
+    (1280, 2304, 128, 2000, 965, (4, 2, 4)),
+    (320, 1152, 32, 1032, 965, (1, 2, 8)),
+    (640, 320, 32, 264, 965, (1, 2, 4)),
+    (1152, 320, 32, 264, 965, (1, 2, 2)),
+]
+CANONICAL = [c for c in PREPARED if c[5] not in ((2, 1, 8), (4, 2, 4))] + [
+    (1280, 1152, 64, 1048, 965, (2, 4, 4)),
+    (320, 320, 160, 168, 70, (1, 1, 4)),     # tiles beyond 128 rows: packed arrays only
+    (64, 64, 32, 8, 33, (1, 1, 4)),          # a single, mostly empty step
+]
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,V,Kv,N,block", PREPARED)
+def test_mid_prepared(M, K, V, Kv, N, block, dtype):
+    import paper_2407_20496_amd as hinm
+    ld = (N + 7) // 8 * 8
+    plan, launches = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld, 0)
+    assert launches == 1 and "spmm_mid_kernel<" in plan and "RB=%d,CB=%d,NW=%d>" % block in plan
+    check_prepared(synth.small_case(M, K, V, Kv, N, dtype, 84), N, [0], relu=(N % 2 == 0), identity=(V == 96))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,V,Kv,N,block", CANONICAL)
+def test_mid_canonical(M, K, V, Kv, N, block, dtype):
+    check_canonical(synth.small_case(M, K, V, Kv, N, dtype, 85), N, [0], relu=(N % 2 == 0), identity=(V == 96), ld_pad=8)
+
+
+@pytest.mark.parametrize("prepared", [True, False])
+def test_mid_ignores_what_lies_beside_the_kept_columns(prepared):
+    """Input rows that no tile keeps, the padding columns of X and the values of the next row hold infinities and NaN:
+    none may reach an output (the ragged last step multiplies zeros there)."""
+    import torch
+    import paper_2407_20496_amd as hinm
+    from oracle import hinm_oracle as orc
+    from tests import gpu_util as gu
+    M, K, V, Kv, N = 64, 192, 32, 72, 37
+    case = synth.small_case(M, K, V, Kv, N, "f16", 86)
+    vals, nm, vec = orc.pack(case.weights(), "f16", V, Kv)
+    Wh = orc.unpack_fast(vals, nm, vec, M, K, V)
+    Xb = case.activations(N)
+    want = orc.product(Wh, Xb, "f16", None, None).astype(np.float64)
+    ld = 48
+    Xp = np.full((K, ld), 0x7C00, dtype=np.uint16)
+    Xp[:, :N] = Xb
+    unused = np.setdiff1d(np.arange(K), vec.reshape(-1))
+    Xp[unused] = 0x7E00
+    vals[1::2, 0] = 0x7C00          # every other row starts with an infinity: its outputs are not looked at
+    p = gu.upload_packed(M, K, V, Kv, "f16", vals, nm, vec)
+    if prepared:
+        got = gu.gpu_spmm_prepared(gu.gpu_prepare(p, None, None), Xb, 2, ldx=ld, ldy=ld, X_dev=gu.dev_bits(Xp))
+    else:
+        got = gu.gpu_spmm(p, Xb, None, None, 2, ldx=ld, ldy=ld, X_dev=gu.dev_bits(Xp))
+    gu.check_close(got[0::2].astype(np.float64), want[0::2], what="rows without infinities")
