@@ -75,3 +75,15 @@ def test_mid_ignores_what_lies_beside_the_kept_columns(prepared):
     else:
         got = gu.gpu_spmm(p, Xb, None, None, 2, ldx=ld, ldy=ld, X_dev=gu.dev_bits(Xp))
     gu.check_close(got[0::2].astype(np.float64), want[0::2], what="rows without infinities")
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,Kv,N,ld_pad", [
+    (48, 272, 264, 220, 0),     # ragged last step and ragged last block of columns
+    (48, 272, 264, 5, 0),       # rows of eight elements: the second half of a block lies past their end
+    (48, 272, 264, 9, 8),
+    (32, 40, 8, 17, 0),         # nothing but a ragged step
+    (32, 320, 312, 1, 0),
+])
+def test_sixteen_row_tiles_with_ragged_ends(M, K, Kv, N, ld_pad, dtype):
+    check_canonical(synth.small_case(M, K, 16, Kv, N, dtype, 88), N, [0], ld_pad=ld_pad)
