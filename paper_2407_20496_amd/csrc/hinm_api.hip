@@ -324,7 +324,11 @@ hinm_status hinm_spmm_vectors(const hinm_shape* shape, int32_t N, const void* va
                       (flags & HINM_EPI_RELU) != 0, (flags & HINM_OUT_F32) != 0, variant};
   hipError_t e;
   if (variant && !spmm_vectors_mfma_supported(a)) return HINM_ERR_UNSUPPORTED;  // a pinned kernel must fit the shape
-  if (!(flags & HINM_KERNEL_REFERENCE) && spmm_vectors_mfma_supported(a))
+  if (!(flags & HINM_KERNEL_REFERENCE) && !variant && N == 1)
+    e = launch_spmm_vectors_gemv(a, static_cast<hipStream_t>(stream));
+  else if (!(flags & HINM_KERNEL_REFERENCE) && !variant && spmm_mid_vectors_preferred(a))
+    e = launch_spmm_mid_vectors(a, static_cast<hipStream_t>(stream));
+  else if (!(flags & HINM_KERNEL_REFERENCE) && spmm_vectors_mfma_supported(a))
     e = launch_spmm_vectors_mfma(a, static_cast<hipStream_t>(stream));
   else
     e = launch_spmm_vectors_plain(a, static_cast<hipStream_t>(stream));

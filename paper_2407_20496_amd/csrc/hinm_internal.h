@@ -143,6 +143,7 @@ struct VectorsArgs {
 // Dense-MFMA tile kernels: V in {32, 64, 96, 128}, ldx % 8 == 0, ldy % 8 == 0; the direct-to-LDS ones
 // also need Kv % 64 == 0.
 bool spmm_vectors_mfma_supported(const VectorsArgs& a);
+hipError_t launch_spmm_vectors_gemv(const VectorsArgs& a, hipStream_t stream);  // N == 1, any leading dimensions
 int spmm_vectors_variant(const VectorsArgs& a);
 hipError_t launch_spmm_vectors_mfma(const VectorsArgs& a, hipStream_t stream);
 hipError_t launch_spmm_vectors_plain(const VectorsArgs& a, hipStream_t stream);
@@ -248,11 +249,13 @@ hipError_t launch_spmm_rows16_prepared(const PreparedArgs& a, hipStream_t stream
 bool spmm_rows16_resident_supported(const PreparedArgs& a);
 int spmm_rows16_prepared_blocks_per_wg(const PreparedArgs& a);  // 16-column blocks per workgroup chosen for this call (1, 2, 4)
 
-// Wave-private kernel for a moderate number of columns (spmm_mid.hip), from either layer form.  V % 32 == 0, N > 1,
+// Wave-private kernel for a moderate number of columns (spmm_mid.hip), from every layer form.  V % 32 == 0, N > 1,
 // ldx and ldy multiples of 8; `preferred` includes what it needs.
 bool spmm_mid_prepared_preferred(const PreparedArgs& a);
 hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream);
 bool spmm_mid_canonical_preferred(const SpmmArgs& a);
 hipError_t launch_spmm_mid_canonical(const SpmmArgs& a, hipStream_t stream);
+bool spmm_mid_vectors_preferred(const VectorsArgs& a);
+hipError_t launch_spmm_mid_vectors(const VectorsArgs& a, hipStream_t stream);
 
 }  // namespace hinm

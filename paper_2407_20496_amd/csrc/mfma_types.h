@@ -62,6 +62,19 @@ __device__ __forceinline__ f32x16 smfmac_32x32x32(u32x4 a, u32x8 b, f32x16 c, in
   }
 }
 
+// Operand layout of the dense 32x32x16 MFMA (lane l): A holds row l % 32, k = 8 * (l / 32) + 0..7;
+// B holds column l % 32, the same eight k; D as for the sparse 32x32 form.
+template <int DT>
+__device__ __forceinline__ f32x16 mfma_32x32x16(u32x4 a, u32x4 b, f32x16 c) {
+  if constexpr (DT == HINM_F16) {
+    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
+                                                  0);
+  } else {
+    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
+                                                   0, 0);
+  }
+}
+
 // LDS transposing read: within every group of 16 lanes the 64 16-bit elements addressed by the
 // group (lane i supplies 4 consecutive elements) are viewed as a 4 x 16 row-major block and lane c
 // receives column c, i.e. elements (row 0..3, column c).

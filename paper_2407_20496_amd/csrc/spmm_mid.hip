@@ -25,15 +25,16 @@
 namespace hinm {
 namespace {
 
-enum { kFromPrepared = 0, kFromCanonical = 1 };
+enum { kFromPrepared = 0, kFromCanonical = 1, kFromVectors = 2 };  // vectors: a layer before its 2:4 step
 
 struct MidSource {
-  const uint8_t* blocks;     // prepared: the blocks of the layer; canonical: stored values [M][Kv/2]
+  const uint8_t* blocks;     // prepared: the blocks of the layer; canonical: stored values [M][Kv/2];
+                             // vectors: [M][Kv]
   const uint8_t* nm_idx;     // canonical only
-  const int32_t* gather;     // prepared: gather table [T][Kp]; canonical: vector index [T][Kv]
-  const int32_t* pi_in;      // canonical only, may be NULL
-  const int32_t* out_rows;   // canonical: may be NULL
-  const uint8_t* zeros;      // prepared only: where padded kept columns read (canonical: kZeroRow)
+  const int32_t* gather;     // prepared: gather table [T][Kp]; else vector index [T][Kv]
+  const int32_t* pi_in;      // not prepared; may be NULL
+  const int32_t* out_rows;   // not prepared: may be NULL
+  const uint8_t* zeros;      // prepared only: where padded kept columns read (else kZeroRow)
 };
 
 // What the columns past Kv of a ragged last step read; never written.
@@ -154,7 +155,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
     return at < p.Kv ? v : -1;
   };
   auto translate = [&](int v) {
-    if (SRC != kFromCanonical || !src.pi_in) return v;
+    if (SRC == kFromPrepared || !src.pi_in) return v;
     const int c = src.pi_in[max(v, 0)];
     return v >= 0 ? c : -1;
   };
@@ -175,8 +176,8 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
 
   // ---- stored values ---------------------------------------------------------------------------------
   struct Weights {
-    u32x4 a[RB][2];
-    uint32_t idx[RB][SRC == kFromPrepared ? 1 : 2];
+    u32x4 a[RB][SRC == kFromVectors ? 4 : 2];
+    uint32_t idx[RB][SRC == kFromCanonical ? 2 : 1];
   };
   const int rb_total = p.V / 32;
   const uint8_t* a_lane;
@@ -184,6 +185,8 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
   if constexpr (SRC == kFromPrepared) {
     a_lane = src.blocks + ((size_t)t * steps * rb_total + (row0 % p.V) / 32) * kPrepBlockBytes + lane * 16;
     nm_lane = src.blocks + ((size_t)t * steps * rb_total + (row0 % p.V) / 32) * kPrepBlockBytes + kPrepIdxOffset + lane * 4;
+  } else if constexpr (SRC == kFromVectors) {
+    a_lane = src.blocks + (size_t)(row0 + i32) * p.Kv * 2 + qh * 16;
   } else {
     a_lane = src.blocks + (size_t)(row0 + i32) * p.Kv + qh * 16;         // Kv / 2 values of two bytes per row
     nm_lane = src.nm_idx + (size_t)(row0 + i32) * (p.Kv / 8) + qh * 2;
@@ -198,6 +201,16 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
         wt.a[rb][1] = *reinterpret_cast<const u32x4*>(a_lane + off + 1024);
         wt.idx[rb][0] = *reinterpret_cast<const uint32_t*>(nm_lane + off);
       }
+    } else if constexpr (SRC == kFromVectors) {  // 16-byte pieces, all of one or nothing there (Kv % 8 == 0)
+#pragma unroll
+      for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const uint8_t* a = a_lane + (size_t)rb * 64 * p.Kv + (size_t)s * 128 + q * 32;
+          const bool there = s * 64 + q * 16 + qh * 8 < p.Kv;
+          wt.a[rb][q] = *reinterpret_cast<const u32x4*>(there ? a : a_lane - qh * 16);
+          if (!there) wt.a[rb][q] = u32x4{0, 0, 0, 0};
+        }
     } else if ((s + 1) * 64 <= p.Kv) {  // rows are only 8-byte aligned, their nibbles not at all
 #pragma unroll
       for (int rb = 0; rb < RB; ++rb)
@@ -258,7 +271,10 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
     for (int rb = 0; rb < RB; ++rb)
 #pragma unroll
       for (int cb = 0; cb < CB; ++cb) {
-        if constexpr (SRC == kFromPrepared)
+        if constexpr (SRC == kFromVectors) {
+          acc[rb][cb] = mfma_32x32x16<DT>(wt.a[rb][2 * Q], u32x4{b[cb][0], b[cb][1], b[cb][2], b[cb][3]}, acc[rb][cb]);
+          acc[rb][cb] = mfma_32x32x16<DT>(wt.a[rb][2 * Q + 1], u32x4{b[cb][4], b[cb][5], b[cb][6], b[cb][7]}, acc[rb][cb]);
+        } else if constexpr (SRC == kFromPrepared)
           acc[rb][cb] = smfmac_32x32x32<DT, Q>(wt.a[rb][Q], b[cb], acc[rb][cb], (int)wt.idx[rb][0]);
         else
           acc[rb][cb] = smfmac_32x32x32<DT, 0>(wt.a[rb][Q], b[cb], acc[rb][cb], (int)wt.idx[rb][Q]);
@@ -274,10 +290,10 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
   // ---- the wave's steps --------------------------------------------------------------------------------
   if (mine > 0) {
     Weights w0, w1;
-    int vec1 = load_entry(1);  // entries of step j + 1; canonical: j + 2 before translation
+    int vec1 = load_entry(1);  // rows of step j + 1; with a table to translate through, its entries of j + 2
     int row_now = translate(load_entry(0));
     int row_next = translate(vec1);
-    int vec_next = SRC == kFromCanonical ? load_entry(2) : 0;
+    int vec_next = SRC != kFromPrepared ? load_entry(2) : 0;
     load_weights(0, w0);
     issue_rows(0, row_now);
     // Step j: request the rows of j + 1, wait until only those are outstanding (whatever else was requested
@@ -287,7 +303,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_mid_kernel(MidSource src, const 
       __builtin_amdgcn_sched_barrier(0);
       wait_copies_outstanding<C::COPIES>();
       __builtin_amdgcn_sched_barrier(0);
-      if constexpr (SRC == kFromCanonical) {
+      if constexpr (SRC != kFromPrepared) {
         row_next = translate(vec_next);
         vec_next = load_entry(j + 3);
       } else {
@@ -450,7 +466,7 @@ int64_t plain_blocks(int M, int V, int N) {
 
 template <int DT, int SRC>
 hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
-  const MidPlan m = plan_mid(c.M, c.V, c.Kv, c.N, SRC == kFromCanonical);
+  const MidPlan m = plan_mid(c.M, c.V, c.Kv, c.N, SRC != kFromPrepared);
   if constexpr (SRC == kFromPrepared) {
     if (m.rb == 4) return launch_cfg<DT, SRC, 4, 2, 4>(c, stream);
     if (m.rb == 2 && m.cb == 1) return launch_cfg<DT, SRC, 2, 1, 8>(c, stream);
@@ -516,6 +532,25 @@ hipError_t launch_spmm_mid_canonical(const SpmmArgs& a, hipStream_t stream) {
                   a.out_f32, nullptr};
   return a.s.dtype == HINM_F16 ? launch_planned<HINM_F16, kFromCanonical>(c, stream)
                                : launch_planned<HINM_BF16, kFromCanonical>(c, stream);
+}
+
+// The layer before its 2:4 step has twice the values per kept column.  Whole 64-column steps: as on the packed arrays.
+// Otherwise the tile kernel is the register-staged one, which is ahead from about 1024 blocks on (2688 x 680, V = 64,
+// Kv = 168, N = 1764, 1176 blocks: 15.8 against 16.6 us; 2752 x 1608, N = 3675, 2494 blocks: 43 and 58; 640 x 3872,
+// V = 128, N = 1726, 270 blocks: 74 and 24) and ends at tiles of 128 rows.
+bool spmm_mid_vectors_preferred(const VectorsArgs& a) {
+  if (a.s.V % 32 != 0 || a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
+  const int64_t blocks = plain_blocks(a.s.M, a.s.V, a.N);
+  if (blocks >= (1 << 28)) return false;
+  return a.N <= 64 || a.s.V > 128 || blocks <= (a.s.Kv % 64 != 0 ? 1024 : 640);
+}
+
+hipError_t launch_spmm_mid_vectors(const VectorsArgs& a, hipStream_t stream) {
+  const MidCall c{{static_cast<const uint8_t*>(a.vals_v), nullptr, a.vec_idx, a.pi_in, a.pi_out, nullptr},
+                  a.s.M, a.s.K, a.s.V, a.s.Kv, a.N, static_cast<const uint16_t*>(a.X), a.ldx, a.Y, a.ldy, a.relu,
+                  a.out_f32, nullptr};
+  return a.s.dtype == HINM_F16 ? launch_planned<HINM_F16, kFromVectors>(c, stream)
+                               : launch_planned<HINM_BF16, kFromVectors>(c, stream);
 }
 
 }  // namespace hinm

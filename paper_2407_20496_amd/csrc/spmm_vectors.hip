@@ -28,19 +28,6 @@
 namespace hinm {
 namespace {
 
-// Operand layout of the dense 32x32x16 MFMA (lane l): A holds row l % 32, k = 8 * (l / 32) + 0..7;
-// B holds column l % 32, the same eight k; D as for the sparse 32x32 form.
-template <int DT>
-__device__ __forceinline__ f32x16 mfma_32x32x16(u32x4 a, u32x4 b, f32x16 c) {
-  if constexpr (DT == HINM_F16) {
-    return __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(f16x8, a), __builtin_bit_cast(f16x8, b), c, 0, 0,
-                                                  0);
-  } else {
-    return __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c, 0,
-                                                   0, 0);
-  }
-}
-
 constexpr int kNB = 256;  // columns per workgroup
 constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
@@ -403,6 +390,83 @@ __global__ __launch_bounds__(NB / WC * 64) void spmm_vectors_dma_kernel(
                                                                   [&](int row) -> int64_t { const int r = t * V + row; return pi_out ? pi_out[r] : r; });
 }
 
+// A single column: bound by streaming the stored values once.  A workgroup of four waves owns 4 RW rows of a tile; the
+// tile's input elements are gathered into LDS (a chunk of the kept columns at a time), every wave multiplies RW rows
+// with them, 16 bytes of a row per lane, and adds its lanes' sums in a fixed order.  The first pieces of the rows are
+// requested before the index chain.  One thread per output element, which served this before, reads 2 bytes of a row
+// per lane and cache line and walks it alone (5984 x 5144, V = 32, Kv = 2576: 939 -> 12.2 us, 2.5 TB/s; 1792 x 3440,
+// V = 128, Kv = 1720: 435 -> 6.0; 640 x 856, Kv = 216: 42 -> 2.9).
+constexpr int kGemvChunk = 8192;  // kept columns in LDS: 16 KB
+
+template <int DT, int RW>
+__global__ __launch_bounds__(256) void spmm_vectors_gemv_kernel(
+    const uint16_t* __restrict__ vals_v, const int32_t* __restrict__ vec_idx, const int32_t* __restrict__ pi_in,
+    const int32_t* __restrict__ pi_out, const uint16_t* __restrict__ X, int64_t ldx, void* __restrict__ Y, int64_t ldy,
+    int V, int Kv, int groups_per_tile, bool relu, bool out_f32) {
+  __shared__ __attribute__((aligned(16))) uint16_t xs[kGemvChunk];
+  const int t = blockIdx.x / groups_per_tile;
+  const int lane = threadIdx.x & 63;
+  const int first = (int)(blockIdx.x % groups_per_tile) * (4 * RW) + (int)(threadIdx.x >> 6) * RW;  // row of the tile
+  const int32_t* vi = vec_idx + (size_t)t * Kv;
+  const uint16_t* row[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) row[r] = vals_v + ((size_t)t * V + min(first + r, V - 1)) * Kv;  // past the tile: its last row
+  u32x4 ahead[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) ahead[r] = *reinterpret_cast<const u32x4*>(row[r] + min(lane * 8, Kv - 8));
+  float acc[RW];
+#pragma unroll
+  for (int r = 0; r < RW; ++r) acc[r] = 0.f;
+
+  for (int c0 = 0; c0 < Kv; c0 += kGemvChunk) {
+    const int len = min(kGemvChunk, Kv - c0);
+    if (c0 > 0) __syncthreads();
+    constexpr int kBatch = 4;
+    for (int j0 = threadIdx.x; j0 < len; j0 += 256 * kBatch) {
+      int c[kBatch];
+      uint16_t x[kBatch];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) c[b] = vi[c0 + min(j0 + 256 * b, len - 1)];
+      if (pi_in) {
+#pragma unroll
+        for (int b = 0; b < kBatch; ++b) c[b] = pi_in[c[b]];
+      }
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b) x[b] = X[(int64_t)c[b] * ldx];
+#pragma unroll
+      for (int b = 0; b < kBatch; ++b)
+        if (j0 + 256 * b < len) xs[j0 + 256 * b] = x[b];
+    }
+    __syncthreads();
+    for (int k = lane * 8; k < len; k += 512) {  // Kv % 8 == 0: whole pieces
+      const u32x4 xv = *reinterpret_cast<const u32x4*>(xs + k);
+#pragma unroll
+      for (int r = 0; r < RW; ++r) {
+        const u32x4 v = ahead[r];
+        ahead[r] = *reinterpret_cast<const u32x4*>(row[r] + min(k + 512 < kGemvChunk ? c0 + k + 512 : c0 + kGemvChunk + lane * 8, Kv - 8));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          acc[r] = fmaf(bits_to_float<DT>((uint16_t)(v[e] & 0xFFFFu)), bits_to_float<DT>((uint16_t)(xv[e] & 0xFFFFu)), acc[r]);
+          acc[r] = fmaf(bits_to_float<DT>((uint16_t)(v[e] >> 16)), bits_to_float<DT>((uint16_t)(xv[e] >> 16)), acc[r]);
+        }
+      }
+    }
+  }
+#pragma unroll
+  for (int r = 0; r < RW; ++r) {
+    float sum = acc[r];
+#pragma unroll
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d);
+    if (lane == 0 && first + r < V) {
+      const int m = t * V + first + r;
+      const int64_t out = (int64_t)(pi_out ? pi_out[m] : m) * ldy;
+      if (relu) sum = sum > 0.f ? sum : 0.f;
+      if (out_f32) static_cast<float*>(Y)[out] = sum;
+      else static_cast<uint16_t*>(Y)[out] = float_to_bits<DT>(sum);
+    }
+  }
+}
+
 // One thread per output element, fp32 fused multiply-adds in ascending vector-index order.
 template <int DT>
 __global__ __launch_bounds__(256) void spmm_vectors_plain_kernel(
@@ -508,6 +572,26 @@ bool spmm_vectors_mfma_supported(const VectorsArgs& a) {
 
 hipError_t launch_spmm_vectors_mfma(const VectorsArgs& a, hipStream_t stream) {
   return a.s.dtype == HINM_F16 ? launch_dt<HINM_F16>(a, stream) : launch_dt<HINM_BF16>(a, stream);
+}
+
+template <int DT>
+void launch_gemv(const VectorsArgs& a, hipStream_t stream) {
+  auto launch = [&](auto kernel, int rows) {
+    const int groups = (a.s.V + rows - 1) / rows;
+    kernel<<<dim3((unsigned)(a.s.M / a.s.V * groups)), 256, 0, stream>>>(
+        static_cast<const uint16_t*>(a.vals_v), a.vec_idx, a.pi_in, a.pi_out, static_cast<const uint16_t*>(a.X), a.ldx,
+        a.Y, a.ldy, a.s.V, a.s.Kv, groups, a.relu, a.out_f32);
+  };
+  // four rows per wave share a read of the gathered elements; fewer where the grid would not cover the chip twice
+  if (a.s.M / 16 >= 512) launch(spmm_vectors_gemv_kernel<DT, 4>, 16);
+  else if (a.s.M / 8 >= 256) launch(spmm_vectors_gemv_kernel<DT, 2>, 8);
+  else launch(spmm_vectors_gemv_kernel<DT, 1>, 4);
+}
+
+hipError_t launch_spmm_vectors_gemv(const VectorsArgs& a, hipStream_t stream) {
+  if (a.s.dtype == HINM_F16) launch_gemv<HINM_F16>(a, stream);
+  else launch_gemv<HINM_BF16>(a, stream);
+  return hipGetLastError();
 }
 
 hipError_t launch_spmm_vectors_plain(const VectorsArgs& a, hipStream_t stream) {

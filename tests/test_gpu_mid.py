@@ -78,6 +78,22 @@ def test_mid_ignores_what_lies_beside_the_kept_columns(prepared):
 
 
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,V,Kv,N,block", CANONICAL)
+def test_mid_vectors(M, K, V, Kv, N, block, dtype):
+    from oracle import hinm_oracle as orc
+    from tests import gpu_util as gu
+    case = synth.small_case(M, K, V, Kv, N, dtype, 87)
+    pv = gu.gpu_pack_vectors(case.weights(), dtype, V, Kv)
+    Wv = orc.unpack_vectors(*orc.pack_vectors(case.weights(), dtype, V, Kv), M, K, V)
+    pin, pout = (None, None) if V == 96 else (case.pi_in(), case.pi_out())
+    Xb, relu = case.activations(N), int(N % 2 == 0)
+    want = orc.product(Wv, Xb, dtype, pin, pout, acc=np.float32, relu=bool(relu)).astype(np.float64)
+    got32 = gu.gpu_spmm_vectors(pv, Xb, pin, pout, flags=2 | relu)
+    gu.check_close(got32.astype(np.float64), want, what="layer before its 2:4 step")
+    assert np.array_equal(gu.gpu_spmm_vectors(pv, Xb, pin, pout, flags=relu), orc.round_to_storage(got32, dtype))
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("M,K,Kv,N,ld_pad", [
     (48, 272, 264, 220, 0),     # ragged last step and ragged last block of columns
     (48, 272, 264, 5, 0),       # rows of eight elements: the second half of a block lies past their end
@@ -87,3 +103,27 @@ def test_mid_ignores_what_lies_beside_the_kept_columns(prepared):
 ])
 def test_sixteen_row_tiles_with_ragged_ends(M, K, Kv, N, ld_pad, dtype):
     check_canonical(synth.small_case(M, K, 16, Kv, N, dtype, 88), N, [0], ld_pad=ld_pad)
+
+
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("M,K,V,Kv,ldx", [
+    (48, 40, 16, 8, 1),             # one piece per row
+    (60, 600, 20, 520, 8),          # rows past the tile in the last workgroup; a strided column
+    (2048, 96, 64, 72, 1),          # two rows per wave
+    (8192, 64, 128, 64, 1),         # four
+    (8, 17000, 8, 16904, 1),        # three chunks, the last ragged
+    (8, 8192, 8, 8192, 1),          # exactly one chunk
+])
+def test_vectors_single_column(M, K, V, Kv, ldx, dtype):
+    from oracle import hinm_oracle as orc
+    from tests import gpu_util as gu
+    case = synth.small_case(M, K, V, Kv, 1, dtype, 89)
+    pv = gu.gpu_pack_vectors(case.weights(), dtype, V, Kv)
+    Wv = orc.unpack_vectors(*orc.pack_vectors(case.weights(), dtype, V, Kv), M, K, V)
+    Xb = case.activations(1)
+    for pin, pout, relu in ((case.pi_in(), case.pi_out(), 1), (None, None, 0)):
+        want = orc.product(Wv, Xb, dtype, pin, pout, acc=np.float32, relu=bool(relu)).astype(np.float64)
+        got32 = gu.gpu_spmm_vectors(pv, Xb, pin, pout, flags=2 | relu, ldx=ldx, ldy=ldx)
+        gu.check_close(got32.astype(np.float64), want, what="single column")
+        got = gu.gpu_spmm_vectors(pv, Xb, pin, pout, flags=relu, ldx=ldx, ldy=ldx)
+        assert np.array_equal(got, orc.round_to_storage(got32, dtype))
