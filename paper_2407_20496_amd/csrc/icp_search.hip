@@ -20,7 +20,11 @@ namespace {
 
 constexpr int kThreads = 256;
 constexpr int kMaxP = kIcpMaxPartitions;
-constexpr int kCostRowsPerThread = 8;
+// block of the cost matrix per workgroup: 64 samples (one a lane) x 16 partitions (four a wave), 64 rows at a time
+constexpr int kCostSamples = 64;
+constexpr int kCostPartitionsPerWave = 4;
+constexpr int kCostPartitions = kCostPartitionsPerWave * (kThreads / 64);
+constexpr int kCostRows = 64;
 
 // G[t][r][slot] = saliency of W[tV + r][vec_idx[t][slot]]: the caller's rho, or |w|; order = identity
 template <int DT>
@@ -72,35 +76,66 @@ __global__ __launch_bounds__(kThreads) void icp_split_kernel(const float* __rest
 }
 
 // cost[t][i][j] = sum_r (double) m1[r][i] + (double) min(s[r][j], m2[r][i]), rows ascending.
-// One thread owns one sample j and kCostRowsPerThread consecutive partitions i; the (m1, m2) pairs
-// are the same for the whole workgroup.
+// A chain of V rows per entry, whose additions take four clocks a wave: the rows have to be at hand.  64 of them go
+// through LDS in one burst of loads (m1 converted on the way), then a wave reads one sample a lane and four broadcast
+// partitions per row.  48 tiles of 64 rows and 96 partitions: 53 us with the operands of every row loaded from L2 as
+// the chain reached them and 160 of 256 lanes beyond the last sample; 15.9 us here.
 __global__ __launch_bounds__(kThreads) void icp_cost_kernel(const float* __restrict__ S, const float* __restrict__ M1,
                                                             const float* __restrict__ M2, double* __restrict__ cost,
                                                             int V, int P) {
+  __shared__ float s_rows[kCostRows][kCostSamples];
+  __shared__ __attribute__((aligned(16))) double m1_rows[kCostRows][kCostPartitions];
+  __shared__ __attribute__((aligned(16))) float m2_rows[kCostRows][kCostPartitions];
   const int t = blockIdx.z;
-  const int i0 = blockIdx.y * kCostRowsPerThread;
-  const int j = blockIdx.x * kThreads + threadIdx.x;
+  const int i0 = blockIdx.y * kCostPartitions;
+  const int j0 = blockIdx.x * kCostSamples;
+  const int lane = threadIdx.x & 63;
+  const int mine = (threadIdx.x >> 6) * kCostPartitionsPerWave;  // this wave's partitions of the block
   const float* s_t = S + (size_t)t * V * P;
   const float* m1_t = M1 + (size_t)t * V * P;
   const float* m2_t = M2 + (size_t)t * V * P;
-  double acc[kCostRowsPerThread];
+  double acc[kCostPartitionsPerWave];
 #pragma unroll
-  for (int e = 0; e < kCostRowsPerThread; ++e) acc[e] = 0.0;
-  const int jj = j < P ? j : P - 1;  // lanes beyond P repeat the last sample and store nothing
-  for (int r = 0; r < V; ++r) {
-    const float s = s_t[(size_t)r * P + jj];
+  for (int e = 0; e < kCostPartitionsPerWave; ++e) acc[e] = 0.0;
+  for (int r0 = 0; r0 < V; r0 += kCostRows) {
+    // rows beyond the tile and samples and partitions beyond P repeat the last one; what they give is not used
+    constexpr int kSamplePieces = kCostRows * kCostSamples / kThreads;
+    constexpr int kPartitionPieces = kCostRows * kCostPartitions / kThreads;
+    float sv[kSamplePieces], m1v[kPartitionPieces], m2v[kPartitionPieces];
 #pragma unroll
-    for (int e = 0; e < kCostRowsPerThread; ++e) {
-      const int i = (i0 + e < P) ? i0 + e : P - 1;  // workgroup-uniform
-      const float m1 = m1_t[(size_t)r * P + i];
-      const float m2 = m2_t[(size_t)r * P + i];
-      acc[e] += (double)m1 + (double)__builtin_fminf(s, m2);
+    for (int q = 0; q < kSamplePieces; ++q) {
+      const int at = q * kThreads + threadIdx.x;
+      sv[q] = s_t[(size_t)min(r0 + at / kCostSamples, V - 1) * P + min(j0 + at % kCostSamples, P - 1)];
+    }
+#pragma unroll
+    for (int q = 0; q < kPartitionPieces; ++q) {
+      const int at = q * kThreads + threadIdx.x;
+      const size_t from = (size_t)min(r0 + at / kCostPartitions, V - 1) * P + min(i0 + at % kCostPartitions, P - 1);
+      m1v[q] = m1_t[from];
+      m2v[q] = m2_t[from];
+    }
+    if (r0 > 0) __syncthreads();
+#pragma unroll
+    for (int q = 0; q < kSamplePieces; ++q) (&s_rows[0][0])[q * kThreads + threadIdx.x] = sv[q];
+#pragma unroll
+    for (int q = 0; q < kPartitionPieces; ++q) {
+      (&m1_rows[0][0])[q * kThreads + threadIdx.x] = (double)m1v[q];
+      (&m2_rows[0][0])[q * kThreads + threadIdx.x] = m2v[q];
+    }
+    __syncthreads();
+    const int rows = min(kCostRows, V - r0);
+#pragma unroll 8
+    for (int r = 0; r < rows; ++r) {
+      const float s = s_rows[r][lane];
+#pragma unroll
+      for (int e = 0; e < kCostPartitionsPerWave; ++e)
+        acc[e] += m1_rows[r][mine + e] + (double)__builtin_fminf(s, m2_rows[r][mine + e]);
     }
   }
-  if (j < P) {
+  if (j0 + lane < P) {
 #pragma unroll
-    for (int e = 0; e < kCostRowsPerThread; ++e)
-      if (i0 + e < P) cost[((size_t)t * P + i0 + e) * P + j] = acc[e];
+    for (int e = 0; e < kCostPartitionsPerWave; ++e)
+      if (i0 + mine + e < P) cost[((size_t)t * P + i0 + mine + e) * P + j0 + lane] = acc[e];
   }
 }
 
@@ -187,7 +222,7 @@ hipError_t launch_icp_search(const IcpArgs& a, hipStream_t stream) {
     icp_gather_kernel<HINM_BF16><<<rows_grid, kThreads, 0, stream>>>(Wb, a.rho, a.vec_idx, G, order, s.K, s.V, s.Kv);
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
-  const dim3 cost_grid((P + kThreads - 1) / kThreads, (P + kCostRowsPerThread - 1) / kCostRowsPerThread, T);
+  const dim3 cost_grid((P + kCostSamples - 1) / kCostSamples, (P + kCostPartitions - 1) / kCostPartitions, T);
   for (int it = 0; it < a.iters; ++it) {
     const uint8_t* smp = a.samples + (size_t)it * T * P;
     icp_split_kernel<<<rows_grid, kThreads, 0, stream>>>(G, order, smp, S, M1, M2, s.V, s.Kv);
