@@ -379,7 +379,9 @@ hinm_status hinm_chain(int32_t L, const hinm_layer* layers, int32_t N, const voi
   if (!X || !Y) return HINM_ERR_NULL;
   const size_t need = (L <= 1) ? 0 : (L == 2 ? per : 2 * per);
   if (need > 0 && (!scratch || scratch_bytes < need || !aligned(scratch, 256))) return HINM_ERR_WORKSPACE;
-  const int64_t ldh = (N + 7) / 8 * 8;
+  // one column is packed: 4096 x 11008 at 50 % gathers its input from 22 KB then, not from 176 KB, and stages it in LDS
+  // (13.6 -> 8.9 us behind an 11008 x 4096 layer)
+  const int64_t ldh = N == 1 ? 1 : (N + 7) / 8 * 8;
   // validate every layer's call before launching the first one
   for (int l = 0; l < L; ++l) {
     const void* in = (l == 0) ? X : scratch;

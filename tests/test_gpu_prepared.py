@@ -301,3 +301,41 @@ def test_tile_kernel_parts_run_and_store_nothing():
     with pytest.raises(hinm.HinmError):     # a shape served by another kernel has no tile-kernel parts
         hinm.hinm_calib_tile_part(256, 512, 64, 256, "f16", 520, prep, X, 520, 1)
     _check(synth.small_case(1024, 2048, 64, 1024, 1032, "f16", 77), 1032, [0])
+
+
+@pytest.mark.parametrize("forms", ["prepared", "canonical", "mixed"])
+def test_chain_of_one_column(forms):
+    """The intermediate of a chain at one column, long enough for the second layer to stage it in LDS, against the oracle and
+    against the two calls on their own."""
+    import torch
+    import paper_2407_20496_amd as hinm
+    from tests import gpu_util as gu
+    RELU, dtype, V = 1, "bf16", 64
+    shapes = [(8448, 64, 64), (64, 8448, 4232)]     # M, K, Kv: 67 steps in the second layer, the last one ragged
+    layers, calls, keep, h = [], [], [], None
+    for l, (M, K, Kv) in enumerate(shapes):
+        case = synth.small_case(M, K, V, Kv, 1, dtype, 120 + l)
+        p = gu.gpu_pack(case.weights(), dtype, V, Kv)
+        vals, nm, vec = orc.pack(case.weights(), dtype, V, Kv)
+        pin, pout, relu = case.pi_in(), case.pi_out(), RELU if l == 0 else 0
+        form = forms if forms != "mixed" else ("canonical", "prepared")[l]
+        pr = gu.gpu_prepare(p, pin, pout) if form == "prepared" else None
+        if l == 0:
+            Xb = h = case.activations()
+        run = (lambda x, flags: gu.gpu_spmm_prepared(pr, x, flags)) if pr is not None else (
+            lambda x, flags: gu.gpu_spmm(p, x, pin, pout, flags))
+        want = orc.product(orc.unpack_fast(vals, nm, vec, M, K, V), h, dtype, pin, pout, relu=bool(relu))
+        acc = run(h, relu | 2)
+        gu.check_close(acc.astype(np.float64), want.astype(np.float64), what="layer %d on its own" % l)
+        h = run(h, relu)
+        assert np.array_equal(h, orc.round_to_storage(acc, dtype))
+        pi = (gu.dev_i32(pin), gu.dev_i32(pout))
+        keep.append((p, pr, pi))
+        layers.append(hinm.Layer(M, K, V, Kv, dtype, p.vals, p.nm_idx, p.vec_idx, pi[0], pi[1], relu,
+                                 pr.buf if pr is not None else None))
+    nbytes = hinm.hinm_chain_sizes(layers, 1)
+    scratch = torch.full((nbytes,), 0x7B, dtype=torch.uint8, device=gu.DEV)
+    Y = torch.full((64, 1), 0x7B7B, dtype=torch.int16, device=gu.DEV)
+    hinm.hinm_chain(layers, 1, gu.dev_bits(Xb), 1, Y, 1, scratch, nbytes)
+    torch.cuda.synchronize()
+    assert np.array_equal(gu.host_bits(Y), h.reshape(64, 1))
