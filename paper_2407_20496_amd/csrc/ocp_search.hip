@@ -287,13 +287,14 @@ __global__ __launch_bounds__(kThreads) void km_init_kernel(const float* __restri
   if (k < K) C[(size_t)c * K + k] = (double)F[(size_t)c * n * K + k];
 }
 
-// d[q][c] for 64 clusters (one a lane) and two points a wave.  A chain of K steps per pair is the definition (the
+// d[q][c] for 64 clusters (one a lane) and one or two points a wave.  A chain of K steps per pair is the definition (the
 // rounding of every step is pinned), so the chains have to run on operands that are at hand: 64 columns of the
 // centroids at a time go through LDS (rows padded to an odd number of doubles: no bank conflicts), the points' features
 // are wave-uniform.  384 points x 48 clusters x 768 columns: 76 us with one column of a different centroid row per
-// lane and step, 29 us here.
+// lane and step, 33 us with two points a wave and the loads of a piece behind the sums of the last, 26 us with
+// one point (96 workgroups; two points read the centroids half as often once there are 256) and a piece requested ahead.
 constexpr int kDistColumns = 64;
-constexpr int kDistPoints = 2;  // per wave
+template <int POINTS>  // per wave
 __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __restrict__ F,
                                                                const double* __restrict__ C,
                                                                double* __restrict__ dist, int T, int K, int points) {
@@ -302,31 +303,36 @@ __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __re
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c0 = blockIdx.y * 64;
-  const int q0 = (blockIdx.x * (kThreads / 64) + wave) * kDistPoints;
-  const float* f[kDistPoints];
-  double acc[kDistPoints];
+  const int q0 = (blockIdx.x * (kThreads / 64) + wave) * POINTS;
+  const float* f[POINTS];
+  double acc[POINTS];
 #pragma unroll
-  for (int p = 0; p < kDistPoints; ++p) {
+  for (int p = 0; p < POINTS; ++p) {
     f[p] = F + (size_t)min(q0 + p, points - 1) * K;
     acc[p] = 0.0;
   }
-  for (int k0 = 0; k0 < K; k0 += kDistColumns) {
+  constexpr int kPieces = 64 / (kThreads / 64);
+  double ahead[kPieces];
+  auto request = [&](int k0) {
     const int k_lane = min(k0 + lane, K - 1);
-    double mine[64 / (kThreads / 64)];
 #pragma unroll
-    for (int r = 0; r < 64 / (kThreads / 64); ++r)
-      mine[r] = C[(size_t)min(c0 + wave + r * (kThreads / 64), T - 1) * K + k_lane];
+    for (int r = 0; r < kPieces; ++r)
+      ahead[r] = C[(size_t)min(c0 + wave + r * (kThreads / 64), T - 1) * K + k_lane];
+  };
+  request(0);
+  for (int k0 = 0; k0 < K; k0 += kDistColumns) {
     __syncthreads();
 #pragma unroll
-    for (int r = 0; r < 64 / (kThreads / 64); ++r) tile[wave + r * (kThreads / 64)][lane] = mine[r];
+    for (int r = 0; r < kPieces; ++r) tile[wave + r * (kThreads / 64)][lane] = ahead[r];
     __syncthreads();
+    if (k0 + kDistColumns < K) request(k0 + kDistColumns);
     const int count = min(kDistColumns, K - k0);
     if (count == kDistColumns) {
 #pragma unroll 16
       for (int k = 0; k < kDistColumns; ++k) {
         const double cen = tile[lane][k];
 #pragma unroll
-        for (int p = 0; p < kDistPoints; ++p) {
+        for (int p = 0; p < POINTS; ++p) {
           const double diff = (double)f[p][k0 + k] - cen;
           const double sq = diff * diff;
           acc[p] = acc[p] + sq;
@@ -336,7 +342,7 @@ __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __re
       for (int k = 0; k < count; ++k) {
         const double cen = tile[lane][k];
 #pragma unroll
-        for (int p = 0; p < kDistPoints; ++p) {
+        for (int p = 0; p < POINTS; ++p) {
           const double diff = (double)f[p][k0 + k] - cen;
           const double sq = diff * diff;
           acc[p] = acc[p] + sq;
@@ -346,7 +352,7 @@ __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __re
   }
   if (c0 + lane < T) {
 #pragma unroll
-    for (int p = 0; p < kDistPoints; ++p)
+    for (int p = 0; p < POINTS; ++p)
       if (q0 + p < points) dist[(size_t)(q0 + p) * T + c0 + lane] = acc[p];
   }
 }
@@ -432,9 +438,14 @@ hipError_t launch_ocp_cluster(const KmeansArgs& a, hipStream_t stream) {
   hipError_t e = hipGetLastError();
   if (e != hipSuccess) return e;
   for (int r = 0; r < a.rounds; ++r) {
-    constexpr int kPointsPerBlock = kDistPoints * (kThreads / 64);
-    km_distance_kernel<<<dim3((points + kPointsPerBlock - 1) / kPointsPerBlock, (T + 63) / 64), kThreads, 0, stream>>>(
-        F, a.centroids, dist, T, s.K, points);
+    constexpr int kWaves = kThreads / 64;
+    const int cluster_blocks = (T + 63) / 64;
+    if ((points + 2 * kWaves - 1) / (2 * kWaves) * cluster_blocks >= 256)
+      km_distance_kernel<2><<<dim3((points + 2 * kWaves - 1) / (2 * kWaves), cluster_blocks), kThreads, 0, stream>>>(
+          F, a.centroids, dist, T, s.K, points);
+    else
+      km_distance_kernel<1><<<dim3((points + kWaves - 1) / kWaves, cluster_blocks), kThreads, 0, stream>>>(
+          F, a.centroids, dist, T, s.K, points);
     e = hipGetLastError();
     if (e != hipSuccess) return e;
     e = launch_assignment(dist, assign, 1, points, T, stream);

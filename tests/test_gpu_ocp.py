@@ -148,6 +148,7 @@ def _gpu_cluster(c, Wb, rho, row_order, sampled, rounds, centroids=None):
     (48, 40, 8, 16, 3, "f16", False),
     (64, 300, 16, 152, 5, "bf16", True),
     (40, 24, 1, 8, 1, "f16", True),
+    (1040, 72, 8, 32, 7, "f16", True),       # 910 points, 130 clusters: two points a wave
 ])
 def test_balanced_kmeans_round_by_round(M, K, V, Kv, n, dtype, scored):
     c = synth.small_case(M, K, V, Kv, 1, dtype, 101)
