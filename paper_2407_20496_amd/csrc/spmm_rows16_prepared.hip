@@ -14,6 +14,7 @@
 #include "mfma_types.h"
 #include "prepared_layout.h"
 #include "direct_lds.h"
+#include "column_pieces.h"
 
 namespace hinm {
 namespace {
@@ -152,10 +153,10 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
     x_staged = true;
   };
 
-  // XMODE 1: whether this lane's 16-byte piece of column block cb lies inside the row (ldx % 8 == 0)
-  bool piece_in_row[CB];
+  // XMODE 1: whether this lane's 16-byte piece of column block cb holds any of the N columns
+  bool piece_there[CB];
 #pragma unroll
-  for (int cb = 0; cb < CB; ++cb) piece_in_row[cb] = n0 + kCols * cb + 8 * (lane & 1) + 8 <= (int)ldx;
+  for (int cb = 0; cb < CB; ++cb) piece_there[cb] = piece_inside(n0 + kCols * cb + 8 * (lane & 1), N);
   for (int sb = s_begin; sb < s_end; sb += KB) {
     u32x4 a_reg[KB][RBW];
     int idx_reg[KB][RBW];
@@ -202,12 +203,12 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
         // rows scattered by the input-channel order costs.
         const int c_lo = __builtin_amdgcn_ds_bpermute((lane >> 1) * 4, col[u]);
         const int c_hi = __builtin_amdgcn_ds_bpermute((32 + (lane >> 1)) * 4, col[u]);
-        // (a piece of a ragged last block may lie past the end of the row: its columns are beyond N then, and
-        // it reads the zero row instead; whatever else a piece holds beyond N never reaches a stored column)
+        // (a piece of a ragged last block that holds none of the N columns may lie past the end of X: the zero row is
+        // read instead; what the last piece holds beyond N never reaches a stored column)
 #pragma unroll
         for (int cb = 0; cb < CB; ++cb) {
-          const uint16_t* r_lo = (c_lo >= 0 && piece_in_row[cb]) ? X + (size_t)c_lo * ldx + n0 + kCols * cb : reinterpret_cast<const uint16_t*>(zeros);
-          const uint16_t* r_hi = (c_hi >= 0 && piece_in_row[cb]) ? X + (size_t)c_hi * ldx + n0 + kCols * cb : reinterpret_cast<const uint16_t*>(zeros);
+          const uint16_t* r_lo = (c_lo >= 0 && piece_there[cb]) ? X + (size_t)c_lo * ldx + n0 + kCols * cb : reinterpret_cast<const uint16_t*>(zeros);
+          const uint16_t* r_hi = (c_hi >= 0 && piece_there[cb]) ? X + (size_t)c_hi * ldx + n0 + kCols * cb : reinterpret_cast<const uint16_t*>(zeros);
           b_lo[u][cb] = *reinterpret_cast<const u32x4*>(r_lo + 8 * (lane & 1));
           b_hi[u][cb] = *reinterpret_cast<const u32x4*>(r_hi + 8 * (lane & 1));
         }

@@ -13,6 +13,7 @@
 // through LDS, so results do not depend on timing.
 #include "hinm_internal.h"
 #include "mfma_types.h"
+#include "column_pieces.h"
 
 namespace hinm {
 namespace {
@@ -49,7 +50,7 @@ __device__ __forceinline__ u32x8 read_b_operand(const uint8_t* slab, int i, int 
   return b;
 }
 
-// XMODE: 1 = rows are 16-byte aligned (ld % 8 == 0; columns beyond N are computed on whatever the padding holds and
+// XMODE: 1 = rows are 16-byte aligned (ld % 8 == 0; columns beyond N are computed on whatever their piece holds and
 // never stored), 2 = N == 1.  KB = steps whose loads are issued together.  RBW = 16-row blocks per
 // workgroup (they share the gathered B operand).
 template <int DT, int NW, int XMODE, int KB, int RBW>
@@ -125,15 +126,15 @@ __global__ __launch_bounds__(NW * 64) void spmm_skinny_kernel(
       const uint16_t* xr = X + (size_t)c * ldx + n0;
       if constexpr (XMODE == 1) {
         tail_lo = *reinterpret_cast<const u32x4*>(xr);
-        if (n0 + 8 < (int)ldx) tail_hi = *reinterpret_cast<const u32x4*>(xr + 8);
+        if (piece_inside(n0 + 8, N)) tail_hi = *reinterpret_cast<const u32x4*>(xr + 8);
       } else {
         tail_lo = u32x4{(uint32_t)xr[0], 0, 0, 0};
       }
     }
   };
   if (RBW == 1 && has_tail) load_tail();  // (two row blocks leave no registers for it)
-  // this lane's half of a row's 16 columns; a half past the end of the row (columns beyond N) repeats the other
-  const int piece = (n0 + 8 * (lane & 1) < (int)ldx) ? 8 * (lane & 1) : 0;
+  // this lane's half of a row's 16 columns
+  const int piece = half_offset(n0, lane & 1, N);
 
   for (int sb = s_begin; sb < s_end; sb += KB) {
     u32x4 a_reg[KB][RBW];
