@@ -19,7 +19,11 @@
 // Measured per call, against one augmenting-path search per row from column minima on two to four waves: 48 problems
 // of 96 x 96 1.10 -> 0.104 ms, 384 and 192 points to 48 clusters (n x n before) 16.6 -> 0.15 ms on average, one of
 // 48 x 48 0.365 -> 0.040 ms, 64 of 512 x 512 (four iterations of the tile-wise search on 4096 x 4096) 161 -> 16 ms.
-// Every loop is bounded by the problem's size.  Costs that are not finite end in the identity assignment.
+// Every loop is bounded by the problem's size.  Costs may be of any finite size below 1e300: a row's smallest cost is
+// taken off the row first (a constant of a row changes no choice, but next to one of 1e39 the other rows' costs would
+// be rounded away), and the start, which works in single precision, scales what is left by the power of two of
+// its largest entry.  An infinite or undefined cost is a pair that cannot be taken; problems without an
+// assignment of finite pairs end in the identity.
 #include "hinm_internal.h"
 #include "wave_reduce.h"
 
@@ -27,7 +31,8 @@ namespace hinm {
 namespace {
 
 constexpr int kStartRounds = 12;  // 384 x 48: path steps 62 after 10 rounds, 96 x 96: 30 .. 70 after 10, 15 .. 30 after 20
-constexpr double kInf = 1e300;
+constexpr double kInf = 1e300;  // distance of a column that is closed; costs are below
+constexpr double kFar = 5e299;  // distance of a column that cannot be reached yet
 constexpr int kLdsBytes = 160 * 1024;
 
 // lane that holds the smallest x (the lowest of several), wave-uniform
@@ -85,13 +90,14 @@ struct __attribute__((aligned(16))) RowBest {
 };
 
 struct AssignLds {  // byte offsets into dynamic LDS
-  int cost, v, rows, filled, work, row_col, list, members, total;
+  int cost, v, rows, base, filled, work, row_col, list, members, total;
 };
 __host__ __device__ inline AssignLds assign_lds(int n, int m, int threads, bool with_cost) {
   AssignLds l;
   int off = 0;
   l.rows = off;     off += n * (int)sizeof(RowBest);
   l.cost = off;     off += with_cost ? n * m * 8 : 0;
+  l.base = off;     off += with_cost ? 0 : n * 8;  // what is taken off every row (a matrix in LDS has it taken off)
   l.v = off;        off += m * 8;
   l.work = off;                     // start: two floats per (row group, column); afterwards:
   l.row_col = off;                  // column of every row, -1 = free
@@ -114,6 +120,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   const AssignLds L = assign_lds(n, m, THREADS, IN_LDS);
   double* col_v = reinterpret_cast<double*>(lds + L.v);
   RowBest* rows = reinterpret_cast<RowBest*>(lds + L.rows);
+  double* base = reinterpret_cast<double*>(lds + L.base);
   int* filled = reinterpret_cast<int*>(lds + L.filled);
   float2* smallest = reinterpret_cast<float2*>(lds + L.work);
   int* row_col = reinterpret_cast<int*>(lds + L.row_col);
@@ -126,6 +133,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   const int lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   auto row_of = [&](int i) -> const double* { return (IN_LDS ? lds_cost : global_cost) + (size_t)i * m; };
+  auto base_of = [&](int i) { return IN_LDS ? 0.0 : base[i]; };
 
   // ---- start: the whole workgroup ------------------------------------------------------------------
   const int groups = THREADS / m > 0 ? THREADS / m : 1;  // row groups that share a column
@@ -135,7 +143,42 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
     for (int e = tid; e < n * m; e += THREADS) lds_cost[e] = global_cost[e];
   }
   for (int j = tid; j < m; j += THREADS) col_v[j] = 0.0;
+  if (tid == 0) filled[0] = 0;
   __syncthreads();
+  // the smallest cost of every row is taken off it; filled[0] = high word of the largest finite cost that is left
+  for (int i = wave; i < n; i += WAVES) {
+    const double* r = row_of(i);
+    double x[CPL];
+    double least = kInf;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      x[c] = r[min(64 * c + lane, m - 1)];
+      least = x[c] < least ? x[c] : least;
+    }
+    least = read_lane(least, wave_argmin_lane(least));
+    const double off = least > -kInf && least < kInf ? least : 0.0;
+    int largest = 0;
+#pragma unroll
+    for (int c = 0; c < CPL; ++c) {
+      x[c] -= off;
+      if (__builtin_fabs(x[c]) < kInf) largest = max(largest, __double2hiint(x[c]) & 0x7fffffff);
+      if constexpr (IN_LDS) {
+        if (64 * c + lane < m) lds_cost[(size_t)i * m + 64 * c + lane] = x[c];
+      }
+    }
+    largest = -wave_min(-largest);
+    if (lane == 0) {
+      if constexpr (!IN_LDS) base[i] = off;
+      atomicMax(&filled[0], largest);
+    }
+  }
+  __syncthreads();
+  // powers of two: costs times `scale` are below 2, and the start's potentials are of scaled costs
+  const int exponent = max(filled[0] >> 20, 1);
+  const double scale = __hiloint2double((2046 - exponent) << 20, 0), unscale = __hiloint2double(exponent << 20, 0);
+  auto scaled = [&](int i, double cost_ij, double vj) {
+    return __builtin_fma(IN_LDS ? cost_ij : cost_ij - base[i], scale, -vj);
+  };
 
   // best and second best column of every row; two rows at a time, their chains overlap
   auto scan_rows = [&]() {
@@ -144,13 +187,14 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       int k1[2], k2[2], c1[2];
 #pragma unroll
       for (int h = 0; h < 2; ++h) {
-        const double* r = row_of(h ? i1 : i0);
+        const int i = h ? i1 : i0;
+        const double* r = row_of(i);
         k1[h] = k2[h] = 0x7fffffff;
         c1[h] = 0;
 #pragma unroll
         for (int c = 0; c < CPL; ++c) {
           const int j = min(64 * c + lane, m - 1);
-          const int x = float_key((float)(r[j] - col_v[j]));
+          const int x = float_key((float)scaled(i, r[j], col_v[j]));
           const int key = 64 * c + lane < m ? x : 0x7fffffff;
           const bool first = key < k1[h];
           k2[h] = first ? k1[h] : min(k2[h], key);
@@ -170,7 +214,9 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       for (int h = 0; h < 2; ++h)
         if (lane == at[h]) {
           const float u1 = key_float(least[h]), u2 = key_float(second[h]);
-          rows[h ? i1 : i0] = RowBest{u1, u2 - u1, 64 * c1[h] + at[h], 0};
+          // a row without a finite cost moves no potential; one with a single one claims its column, within bounds
+          const bool any = __builtin_fabsf(u1) < 1e30f;
+          rows[h ? i1 : i0] = RowBest{any ? u1 : -3e38f, any ? fminf(u2 - u1, 4.f) : 0.f, 64 * c1[h] + at[h], 0};
         }
     }
     __syncthreads();
@@ -185,7 +231,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
 #pragma unroll 4
           for (int i = group; i < n; i += groups) {
             const RowBest rb = rows[i];
-            const float g = (float)((row_of(i)[j] - vj) - (double)rb.best) - (rb.col == j ? rb.gap : 0.f);
+            const float g = (float)(scaled(i, row_of(i)[j], vj) - (double)rb.best) - (rb.col == j ? rb.gap : 0.f);
             s2 = fminf(s2, fmaxf(s1, g));
             s1 = fminf(s1, g);
           }
@@ -244,20 +290,23 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       __syncthreads();
     }
   }
+  for (int j = tid; j < m; j += THREADS) col_v[j] *= unscale;
+  __syncthreads();
   for (int i = wave; i < n; i += WAVES) {  // now exactly
     const double* r = row_of(i);
+    const double off = base_of(i);
     double least = kInf;
     int least_c = 0;
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       const int j = min(64 * c + lane, m - 1);
-      const double x = 64 * c + lane < m ? r[j] - col_v[j] : kInf;
+      const double x = 64 * c + lane < m ? (IN_LDS ? r[j] : r[j] - off) - col_v[j] : kInf;
       const bool less = x < least;
       least = less ? x : least;
       least_c = less ? c : least_c;
     }
     const int at = wave_argmin_lane(least);
-    if (lane == at) rows[i].col = 64 * least_c + at;
+    if (lane == at) rows[i].col = least < kFar ? 64 * least_c + at : -1;
   }
   __syncthreads();
   // every row sits in its best column while there is room, lower rows first
@@ -283,7 +332,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   for (int c = 0; c < CPL; ++c) {
     const int j = 64 * c + lane;
     col[c] = min(j, m - 1);
-    v[c] = j < m ? col_v[j] : -kInf;  // columns that do not exist look infinitely expensive
+    v[c] = j < m ? col_v[j] : 0.0;
     const int count = j < m ? filled[col[c]] : 0;
     y[c] = CAPACITY ? count : (count ? members[col[c]] : -1);
   }
@@ -296,10 +345,11 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   }
   auto reduced_row = [&](int i, double (&x)[CPL]) {
     const double* r = row_of(i);
+    const double off = base_of(i);
 #pragma unroll
     for (int c = 0; c < CPL; ++c) x[c] = r[col[c]];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) x[c] -= v[c];
+    for (int c = 0; c < CPL; ++c) x[c] = (IN_LDS ? x[c] : x[c] - off) - v[c];
   };
   bool failed = false;
   for (int k = 0; k < n_free && !failed; ++k) {
@@ -311,6 +361,8 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
 #pragma unroll
     for (int c = 0; c < CPL; ++c) {
       pred[c] = start;
+      // columns that do not exist are closed; one that costs infinitely much from here may be reached through others
+      d[c] = 64 * c + lane < m ? __builtin_fmin(d[c], kFar) : kInf;
       open[c] = d[c];
     }
     int end = -1;
@@ -326,7 +378,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       }
       const int at = wave_argmin_lane(least);
       reach = read_lane(least, at);
-      if (!(reach < kInf)) break;
+      if (!(reach < kFar)) break;
       const int at_c = CPL == 1 ? 0 : __builtin_amdgcn_readlane(least_c, at);
       const int j1 = 64 * at_c + at;
       const int held = at_column(y, j1);

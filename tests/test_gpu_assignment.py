@@ -45,3 +45,77 @@ def test_columns_that_take_several_rows(T, n):
     assert obj[0] == gyro.kmeans_objective(d, label)
     # both totals are sums of T n binary64 terms from potentials rounded at 2^-53: 1e-9 is far above that
     assert obj[0] <= gyro.kmeans_objective(d, gyro.kmeans_balanced_assignment(d, n)) * (1 + 1e-9)
+
+
+def _moves(c, before, after, sampled, P):
+    """assign[i] = whose sample sits in partition i's slot now (one tile)."""
+    where = {int(before[0][4 * j + sampled[j]]): j for j in range(P)}
+    return np.array([where[int(after[0][4 * i + sampled[i]])] for i in range(P)])
+
+
+@pytest.mark.parametrize("P", [16, 258])                    # matrix in LDS and not
+@pytest.mark.parametrize("huge", ["one", "some", "all"])
+def test_costs_beyond_single_precision(P, huge):
+    """Scores near the largest float (columns marked never to be pruned): the costs of their partitions, sums over the
+    tile's rows, are beyond it.  The other partitions are assigned as well as if those were not there."""
+    V, K = 4, 4 * P
+    c = synth.small_case(V, K, V, K, 1, "f16", 500)
+    Wb = c.weights()
+    rng = np.random.default_rng(P)
+    rho = rng.random((V, K)).astype(np.float32)
+    samples = rng.integers(0, 4, size=(1, 1, P))
+    vec = np.arange(K, dtype=np.int32).reshape(1, K)
+    if huge == "all":
+        rho *= np.float32(3e38)
+    else:
+        for i in (3,) if huge == "one" else range(0, P, 3):
+            samples[0, 0, i] = 1
+            rho[:, [4 * i, 4 * i + 2, 4 * i + 3]] = 3e38
+    after, obj = _gpu_search(c, Wb, rho, vec, samples)
+    _check_iteration(c, Wb, rho, vec, after, samples[0], obj[0], [0])
+    cost = gyro.icp_cost_fast(gyro.kept_saliency(Wb, c.dtype, rho, V, vec[0], 0), samples[0, 0])
+    assert cost.max() > 1e39
+    left = cost - cost.min(axis=1, keepdims=True)           # exact where it matters: huge rows are constant or all are
+    got = gyro.assignment_cost(left, _moves(c, vec, after, samples[0, 0], P))
+    assert got <= gyro.assignment_cost(left, gyro.icp_assign(left)) * (1 + 1e-9)
+
+
+@pytest.mark.parametrize("P", [16, 258])
+@pytest.mark.parametrize("feasible", [True, False])
+def test_infinite_scores_are_pairs_that_cannot_be_taken(P, feasible):
+    V, K = 4, 4 * P
+    c = synth.small_case(V, K, V, K, 1, "f16", 501)
+    Wb = c.weights()
+    rng = np.random.default_rng(P)
+    rho = rng.random((V, K)).astype(np.float32)
+    samples = rng.integers(0, 4, size=(1, 1, P))
+    vec = np.arange(K, dtype=np.int32).reshape(1, K)
+    samples[0, 0, :8] = 1
+    for i in range(4):                                      # two of the three that stay, in row 0: only a finite sample fits
+        rho[0, [4 * i, 4 * i + 2]] = np.inf
+    for j in range(4 if feasible else 0, P if not feasible else 8):
+        rho[0, 4 * j + samples[0, 0, j]] = np.inf           # samples 4..7, or all of them
+    after, obj = _gpu_search(c, Wb, rho, vec, samples)
+    if feasible:
+        assert np.isfinite(obj[0, 0])
+        _check_iteration(c, Wb, rho, vec, after, samples[0], obj[0], [0])
+    else:
+        assert np.isinf(obj[0, 0]) and np.array_equal(after, vec)
+
+
+@pytest.mark.parametrize("T,n", [(48, 8), (130, 7)])        # matrix in LDS and not
+@pytest.mark.parametrize("scale", [1e-25, 1e25])
+def test_distances_beyond_single_precision(T, n, scale):
+    c = synth.small_case(T * n, 40, n, 16, 1, "f16", 502)
+    Wb = c.weights()
+    rng = np.random.default_rng(T)
+    rho = (rng.standard_normal((c.M, c.K)) ** 2 * scale).astype(np.float32)
+    sampled = np.stack([rng.permutation(n) for _ in range(T)]).astype(np.int32)
+    order = np.arange(c.M, dtype=np.int32)
+    clusters, _, obj = _gpu_cluster(c, Wb, rho, order, sampled, 1)
+    F = gyro.sampled_features(gyro.saliency_matrix(Wb, c.dtype, rho), order.reshape(T, n), sampled)
+    d = gyro.kmeans_distances(F, gyro.kmeans_initial_centroids(F, n))
+    label = np.empty(T * n, dtype=np.int64)
+    label[clusters.reshape(-1)] = np.repeat(np.arange(T), n)
+    assert obj[0] == gyro.kmeans_objective(d, label)
+    assert obj[0] <= gyro.kmeans_objective(d, gyro.kmeans_balanced_assignment(d, n)) * (1 + 1e-9)
