@@ -247,6 +247,8 @@ hipError_t launch_spmm_skinny_prepared(const PreparedArgs& a, hipStream_t stream
 hipError_t launch_spmm_rows16_prepared(const PreparedArgs& a, hipStream_t stream);
 // ... with all input rows resident in LDS (16 columns, K rows of 32 bytes beside the waves' slabs)
 bool spmm_rows16_resident_supported(const PreparedArgs& a);
+bool spmm_rows16_resident_preferred(const PreparedArgs& a);  // by shape
+int64_t spmm_rows16_prepared_workgroups(const PreparedArgs& a);  // of its other forms, for this call
 int spmm_rows16_prepared_blocks_per_wg(const PreparedArgs& a);  // 16-column blocks per workgroup chosen for this call (1, 2, 4)
 
 // Wave-private kernel for a moderate number of columns (spmm_mid.hip), from every layer form.  V % 32 == 0, N > 1,

@@ -489,9 +489,38 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 
 }  // namespace
 
-// Up to 16 columns the 16-row kernels read half as much of X per gathered row and win where a layer does not have
-// the rows for 64-row blocks (768 x 3072, N = 16: 4.1 against 4.9 us; 11008 x 4096 at N = 2 / 8 / 16: 13.5 / 12.0 / 9.7
-// against 9.4 / 9.0 / 8.8).  Many columns belong to the tile kernels, whose larger blocks gather less: the line lies
+// Against the 16-row kernels, up to 128 columns.  A layer is one of many in a model, so its values come from memory, not
+// from the 256 MB cache that a layer called over and over stays in: both were timed, over some 500 (layer, N) pairs.  Below,
+// "a / b -> c / d us" is the 16-row kernel and then this one, with buffers rotated past that cache / from it.  A compute
+// unit fetches from memory at a bounded rate (neither more waves per workgroup nor requests further ahead change it), so
+// what counts there is how many units take part and for how many rounds.
+//   2 .. 4 columns: the 16-row kernel has one row block per workgroup (11008 x 4096 at 50 %, N = 2: 13.3 / 12.0 ->
+//     10.6 / 5.9).
+//   5 .. 16: that kernel is ahead where its workgroups fit the chip in one round (4096 x 11008 at 50 %, N = 16: 13.7 / 12.1 ->
+//     17.5 / 8.8; 4096 x 4096: 6.3 / 4.9 -> 8.5 / 5.1; 8192 x 8192, Kv = 2048: 8.2 / 6.5 -> 9.6 / 6.2), this one with a second
+//     round (5120 x 5120: 13.4 / 11.7 -> 10.1 / 5.9; 7296 x 13240, N = 15: 37.9 / 34.7 -> 22.8 / 14.9) unless its workgroups have
+//     four waves and share units (up to 16 steps), and not against its form with the input in LDS (11008 x 4096, N = 16:
+//     9.7 / 8.4 -> 11.1 / 6.4).
+//   17 .. 64: this one from 150 blocks of 32 x 32 on (11008 x 4096, N = 32: 11.4 / 9.9 -> 11.0 / 6.2); below it where both are
+//     short, where the other's last round is no more than 3/4 full (2176 x 10488, Kv = 2624, N = 32 1.06 / 1.7 times), where
+//     it needs sixteen waves (4096 x 11008, Kv = 2752, N = 32: 10.3 / 9.0 -> 10.3 / 5.5) or two batches per wave; else the
+//     16-row kernel (2048 x 8192, V = 32, Kv = 2048, N = 32: 5.9 / 4.9 -> 8.3 / 4.5; 768 x 3072 at 50 %: 4.9 / 3.6 -> 6.4 / 4.0).
+//   65 .. 128: that kernel on the smallest layers (512 x 7048, Kv = 1760, N = 100: 5.7 / 4.6 -> 7.2 / 4.8).
+static bool beats_rows16(const PreparedArgs& a) {
+  const int S = (a.s.Kv + 63) / 64;
+  const int64_t blocks = (int64_t)(a.s.M / 32) * ((a.N + 31) / 32);
+  const int64_t others = spmm_rows16_prepared_workgroups(a);
+  const bool tall = a.s.V % 64 == 0 && a.s.M / 64 >= 150;
+  if (a.N <= 4) return tall;
+  if (a.N <= 16)
+    return !spmm_rows16_resident_preferred(a) && others > 256 && (tall ? S >= 16 : a.N > 8 && S > 16);
+  if (a.N <= 64)
+    return blocks >= 150 || (S <= 8 && a.N > 24) || S > 96 || (S > 32 && blocks >= 96) ||
+           (blocks >= 64 && others * 4 <= 3 * 256 * ((others + 255) / 256));
+  return a.N > 128 || S <= 8 || S > 32 || blocks > 64;
+}
+
+// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies
 // at four workgroups per unit (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096,
 // N = 300, 860 blocks: 25 and 38; N = 400, 1204 blocks: 44 and 36).  Layers of 1024 rows and more stay with the tile
 // kernel beyond 1024 columns although this one is faster on some of them (1024 x 1024, N = 1666: 1.8 times): the plan of
@@ -499,7 +528,7 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 // N = 3488, 440 blocks: 42 -> 24 us.
 bool spmm_mid_prepared_preferred(const PreparedArgs& a) {
   if (a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
-  if (a.N <= 16) return (a.s.V % 64 == 0 && a.s.M / 64 >= 150) || (a.N > 8 && a.s.M / 32 >= 128);
+  if (a.N <= 128 && !beats_rows16(a)) return false;
   if (a.N > 1024 && a.s.M >= 1024) return false;
   return a.N <= 64 || plain_blocks(a.s.M, a.s.V, a.N) <= (a.s.V % 64 == 0 ? 1024 : 768);
 }

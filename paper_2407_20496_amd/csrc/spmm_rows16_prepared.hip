@@ -321,7 +321,7 @@ void launch_modes(const PreparedArgs& a, const PreparedLayout& L, int blocks_per
     return;
   }
   // rows of X that start on 16-byte boundaries: vector loads for every block, the ragged last one included
-  if constexpr (NW <= 8) {  // (sixteen waves leave 128 registers per lane: not enough for several blocks)
+  if constexpr (NW <= 8 && KB <= 4) {  // (sixteen waves leave 128 registers per lane: not enough for several blocks)
     if (blocks_per_wg == 4 && a.ldx % 8 == 0) {  // (batches of two steps: four blocks of input rows per step)
       HINM_ROWS16_CB(1, 4, 2, (col_blocks + 3) / 4, x, 0, 0);
       return;
@@ -385,8 +385,10 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   const bool quad = a.N > kCols && a.s.V % 64 == 0 && a.s.M >= 2048 && (a.s.M / 64) * col_blocks >= 256;
   const bool both = a.N > 4 && (a.s.M / 32) * col_blocks >= 256;
   p.rbw = quad ? 4 : both ? 2 : 1;
-  // one batch per wave where possible (every load of the wave in flight at once): waves x batch >= steps ...
-  const int nw_steps = L.S <= 4 ? 1 : L.S <= 16 ? 4 : L.S <= 32 ? 8 : 16;
+  // one batch per wave where possible (every load of the wave in flight at once): waves x batch >= steps ... (33 to 48
+  // steps as eight waves with batches of six, up to 16 columns: 4096 x 11008, Kv = 2752, N = 16 9.4 -> 8.1 us from memory, 7.7 ->
+  // 6.4 from the cache, against sixteen with four; beyond 48 steps sixteen waves are ahead, 13.7 and 14.0 with 86)
+  const int nw_steps = L.S <= 4 ? 1 : L.S <= 16 ? 4 : L.S <= (a.N <= kCols ? 48 : 32) ? 8 : 16;
   p.nw = nw_steps;
   p.blocks_per_wg = 1;
   if (a.N > kCols) {
@@ -425,7 +427,9 @@ void launch_waves(const PreparedArgs& a, const Rows16Plan& plan, hipStream_t str
     case 1: return launch_modes<DT, 1, 4, RBW>(a, L, blocks, stream);
     case 2: return launch_modes<DT, 2, 4, RBW>(a, L, blocks, stream);
     case 4: return launch_modes<DT, 4, 4, RBW>(a, L, blocks, stream);
-    case 8: return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
+    case 8:
+      if (L.S > 32 && a.N <= kCols) return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
+      return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
     default:
       if (deep) launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);
       else launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
@@ -439,7 +443,7 @@ void launch_dt(const PreparedArgs& a, hipStream_t stream) {
   // and copying the 32 K bytes of input has to be small beside the workgroup's weights (11008 x 4096:
   // 12.4 -> 10.3 us with 2048 kept columns, 7.4 -> 7.9 us with 1024).
   const PreparedLayout L = prepared_layout(a.s);
-  if (spmm_rows16_resident_supported(a) && (a.tile_variant == 19 || (a.s.M / 64 >= 160 && L.S > 16))) {
+  if (spmm_rows16_resident_supported(a) && (a.tile_variant == 19 || spmm_rows16_resident_preferred(a))) {
     if (L.S <= 16) launch_resident<DT, 4>(a, L, stream);
     else launch_resident<DT, 8>(a, L, stream);
     return;
@@ -460,6 +464,16 @@ bool spmm_rows16_resident_supported(const PreparedArgs& a) {
   if (a.s.V % 64 != 0 || L.S > 32 || a.tile_variant == 11) return false;
   const int NW = L.S <= 16 ? 4 : 8;
   return resident_dynamic_lds_bytes(a.s.K, NW) + (size_t)NW * kSlabBytes <= 160 * 1024;
+}
+
+bool spmm_rows16_resident_preferred(const PreparedArgs& a) {
+  return spmm_rows16_resident_supported(a) && a.s.M / 64 >= 160 && prepared_layout(a.s).S > 16;
+}
+
+int64_t spmm_rows16_prepared_workgroups(const PreparedArgs& a) {
+  const Rows16Plan p = plan_rows16(a);
+  const int64_t col_blocks = (a.N + kCols - 1) / kCols;
+  return a.s.M / (kRows * p.rbw) * ((col_blocks + p.blocks_per_wg - 1) / p.blocks_per_wg);
 }
 
 hipError_t launch_spmm_rows16_prepared(const PreparedArgs& a, hipStream_t stream) {

@@ -258,3 +258,31 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     monkeypatch.setattr(binding, "_LIB_PATH", str(tmp_path / "libhinm.so"))
     with pytest.raises(RuntimeError, match="no CPU or PyTorch fallback"):
         binding.hinm_pack_sizes(256, 256, 16, 128, "f16")
+
+
+@pytest.mark.parametrize("M,K,V,Kv,N,kernel", [
+    # up to 16 columns: the 16-row kernel where its workgroups fit the chip in one round ...
+    (4096, 11008, 128, 5504, 16, "spmm_rows16_prepared_kernel"),
+    (4096, 11008, 128, 2752, 16, "spmm_rows16_prepared_kernel"),
+    (4096, 4096, 64, 2048, 9, "spmm_rows16_prepared_kernel"),
+    (8192, 8192, 64, 2048, 16, "spmm_rows16_prepared_kernel"),
+    (16384, 4096, 32, 1024, 9, "spmm_rows16_prepared_kernel"),
+    # ... or holds the layer's input in LDS, the other one with a second round
+    (11008, 4096, 128, 2048, 16, "spmm_rows16_prepared_kernel"),
+    (11008, 4096, 128, 1024, 16, "spmm_mid_kernel"),
+    (11008, 4096, 128, 2048, 15, "spmm_mid_kernel"),
+    (5120, 5120, 128, 2560, 16, "spmm_mid_kernel"),
+    (11008, 4096, 128, 2048, 2, "spmm_mid_kernel"),
+    # beyond: few blocks and a long pass stay with the 16-row kernel
+    (768, 3072, 64, 1536, 17, "spmm_rows16_prepared_kernel"),
+    (2048, 8192, 32, 2048, 64, "spmm_rows16_prepared_kernel"),
+    (4096, 4096, 64, 2048, 32, "spmm_rows16_prepared_kernel"),
+    (512, 7048, 128, 1760, 100, "spmm_rows16_prepared_kernel"),
+    (4096, 4096, 64, 2048, 64, "spmm_mid_kernel"),
+    (4096, 11008, 128, 2752, 32, "spmm_mid_kernel"),
+    (11008, 4096, 128, 2048, 100, "spmm_mid_kernel"),
+])
+def test_few_columns_run_on_the_kernel_that_is_ahead_with_weights_from_memory(M, K, V, Kv, N, kernel):
+    ld = (N + 7) // 8 * 8
+    text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "bf16", N, ld, ld)
+    assert n == 1 and text.startswith(kernel + "<"), text

@@ -12,11 +12,11 @@ pytestmark = pytest.mark.gpu
 # M, K, V, Kv, N, (32-row blocks, 32-column blocks, waves) of a workgroup
 PREPARED = [
     (64, 256, 32, 200, 37, (1, 1, 4)),
-    (192, 640, 96, 584, 33, (1, 1, 8)),      # ten steps on eight waves
-    (128, 2048, 64, 1992, 17, (1, 1, 8)),    # 32 steps, the last one padded
+    (4800, 640, 96, 584, 30, (1, 1, 8)),     # ten steps on eight waves
+    (4832, 2048, 32, 1992, 17, (1, 1, 8)),   # 32 steps, the last one padded
     (9600, 128, 64, 72, 20, (2, 1, 8)),      # two steps: six waves have none
     (9600, 128, 64, 72, 2, (2, 1, 8)),
-    (4096, 320, 32, 264, 9, (1, 1, 8)),
+    (4800, 1088, 32, 1032, 9, (1, 1, 8)),
     (640, 640, 64, 584, 965, (2, 2, 8)),
     (1280, 320, 64, 264, 965, (2, 2, 4)),
     (640, 320, 64, 264, 1765, (2, 2, 4)),     # beyond 1024 columns: fewer than 1024 rows

@@ -274,6 +274,18 @@ def test_prepared_c3_decode_full(idx):
     _check(c, c.N, [0])
 
 
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("N", [1, 5, 16])
+@pytest.mark.parametrize("Kv", [2056, 2112, 3072])
+def test_sixteen_row_kernel_with_33_to_48_steps(Kv, N, dtype):
+    """Eight waves with batches of six: one step beyond 32 (the last one padded), whole ones, and the longest pass."""
+    import paper_2407_20496_amd as hinm
+    M, K, V = 96, 3080, 32
+    ld = N if N == 1 else (N + 7) // 8 * 8
+    assert "NW=8," in hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld, 0)[0]
+    _check(synth.small_case(M, K, V, Kv, N, dtype, 79), N, [0])
+
+
 def test_tile_kernel_parts_run_and_store_nothing():
     """The measurement launches (copy stream alone, LDS reads and MFMAs alone) finish, leave X and the prepared
     layer as they were, and the product launched afterwards on the same buffers is still right."""
