@@ -81,6 +81,11 @@ hinm_status hinm_calib_gather_stream(const void* region, size_t region_bytes, in
 hinm_status hinm_calib_tile_part(const hinm_shape* shape, int32_t N, const void* prepared, const void* X,
                                  int64_t ldx, int32_t part, void* stream);
 
+/* The launch that a product with rows padded to eight elements makes straight from the packed arrays (form 0,
+ * hinm_spmm) or from a layer before its 2:4 step (form 1, hinm_spmm_vectors) if the kernel for a moderate number of
+ * columns serves it, as text; empty if another kernel does.  Needs no device. */
+hinm_status hinm_calib_mid_plan(const hinm_shape* shape, int32_t N, int32_t form, char* text, size_t text_bytes);
+
 #ifdef __cplusplus
 }
 #endif

@@ -48,7 +48,8 @@ def exported_symbols() -> Tuple[str, ...]:
 def calib_symbols() -> Tuple[str, ...]:
     """Entry points include/hinm_calib.h declares (measurement aids)."""
     return ("hinm_calib_copy", "hinm_calib_fill", "hinm_calib_read", "hinm_calib_scatter_rows", "hinm_calib_smfmac",
-            "hinm_calib_empty", "hinm_calib_lds_stream", "hinm_calib_gather_stream", "hinm_calib_tile_part")
+            "hinm_calib_empty", "hinm_calib_lds_stream", "hinm_calib_gather_stream", "hinm_calib_tile_part",
+            "hinm_calib_mid_plan")
 
 
 def load_library():
@@ -121,6 +122,7 @@ def load_library():
     lib.hinm_calib_gather_stream.argtypes = [C.c_void_p, C.c_size_t, C.c_int64, C.c_int32, C.c_int32, C.c_int32, C.c_int32,
                                              C.c_int32, C.c_void_p]
     lib.hinm_calib_tile_part.argtypes = [sp, C.c_int32, C.c_void_p, C.c_void_p, C.c_int64, C.c_int32, C.c_void_p]
+    lib.hinm_calib_mid_plan.argtypes = [sp, C.c_int32, C.c_int32, C.c_char_p, C.c_size_t]
     for name in calib_symbols():
         getattr(lib, name).restype = C.c_int
     lib.hinm_status_str.argtypes = [C.c_int]
@@ -425,6 +427,15 @@ def hinm_calib_gather_stream(region, region_bytes, row_pitch_bytes, rows, waves,
 def hinm_calib_tile_part(M, K, V, Kv, dtype, N, prepared, X, ldx, part, stream=None) -> None:
     _check(load_library().hinm_calib_tile_part(C.byref(_shape(M, K, V, Kv, dtype)), int(N), _ptr(prepared), _ptr(X),
                                                int(ldx), int(part), _stream(stream)), "hinm_calib_tile_part")
+
+
+def hinm_calib_mid_plan(M, K, V, Kv, dtype, N, form) -> str:
+    """The launch of the kernel for a moderate number of columns from the packed arrays (form 0) or from a layer before
+    its 2:4 step (form 1); empty where another kernel serves the product."""
+    buf = C.create_string_buffer(256)
+    _check(load_library().hinm_calib_mid_plan(C.byref(_shape(M, K, V, Kv, dtype)), int(N), int(form), buf, len(buf)),
+           "hinm_calib_mid_plan")
+    return buf.value.decode()
 
 
 @dataclass

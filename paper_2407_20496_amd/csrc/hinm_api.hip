@@ -590,6 +590,25 @@ hinm_status hinm_calib_tile_part(const hinm_shape* shape, int32_t N, const void*
   return e == hipSuccess ? HINM_OK : HINM_ERR_DEVICE;
 }
 
+hinm_status hinm_calib_mid_plan(const hinm_shape* shape, int32_t N, int32_t form, char* text, size_t text_bytes) {
+  hinm_status st = check_shape(shape);
+  if (st != HINM_OK) return st;
+  if (!text || text_bytes == 0) return HINM_ERR_NULL;
+  if (N <= 0 || form < 0 || form > 1) return HINM_ERR_SHAPE;
+  text[0] = 0;
+  const int64_t ld = N == 1 ? 1 : ((int64_t)N + 7) / 8 * 8;
+  LaunchPlan plan{text, text_bytes};
+  hipError_t e = hipSuccess;
+  if (form == 0) {
+    SpmmArgs a{*shape, N, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, ld, nullptr, ld, false, false, &plan};
+    if (spmm_mid_canonical_preferred(a)) e = launch_spmm_mid_canonical(a, nullptr);
+  } else {
+    VectorsArgs a{*shape, N, nullptr, nullptr, nullptr, nullptr, nullptr, ld, nullptr, ld, false, false, 0, &plan};
+    if (spmm_mid_vectors_preferred(a)) e = launch_spmm_mid_vectors(a, nullptr);
+  }
+  return e == hipSuccess ? HINM_OK : HINM_ERR_DEVICE;
+}
+
 const char* hinm_status_str(hinm_status s) {
   switch (s) {
     case HINM_OK: return "ok";

@@ -113,6 +113,7 @@ struct SpmmArgs {
   int64_t ldy;
   bool relu;
   bool out_f32;
+  LaunchPlan* plan = nullptr;  // set: record what would be launched instead (spmm_mid.hip only)
 };
 
 hipError_t launch_spmm_reference(const SpmmArgs& a, hipStream_t stream);
@@ -139,6 +140,7 @@ struct VectorsArgs {
   bool relu;
   bool out_f32;
   int variant;  // 0 = choose by shape; 1 = register-staged, 2 / 3 = direct-to-LDS with 256 / 512 columns
+  LaunchPlan* plan = nullptr;  // set: record what would be launched instead (spmm_mid.hip only)
 };
 // Dense-MFMA tile kernels: V in {32, 64, 96, 128}, ldx % 8 == 0, ldy % 8 == 0; the direct-to-LDS ones
 // also need Kv % 64 == 0.

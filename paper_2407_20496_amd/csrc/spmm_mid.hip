@@ -558,7 +558,7 @@ bool spmm_mid_canonical_preferred(const SpmmArgs& a) {
 hipError_t launch_spmm_mid_canonical(const SpmmArgs& a, hipStream_t stream) {
   const MidCall c{{static_cast<const uint8_t*>(a.vals), a.nm_idx, a.vec_idx, a.pi_in, a.pi_out, nullptr},
                   a.s.M, a.s.K, a.s.V, a.s.Kv, a.N, static_cast<const uint16_t*>(a.X), a.ldx, a.Y, a.ldy, a.relu,
-                  a.out_f32, nullptr};
+                  a.out_f32, a.plan};
   return a.s.dtype == HINM_F16 ? launch_planned<HINM_F16, kFromCanonical>(c, stream)
                                : launch_planned<HINM_BF16, kFromCanonical>(c, stream);
 }
@@ -577,7 +577,7 @@ bool spmm_mid_vectors_preferred(const VectorsArgs& a) {
 hipError_t launch_spmm_mid_vectors(const VectorsArgs& a, hipStream_t stream) {
   const MidCall c{{static_cast<const uint8_t*>(a.vals_v), nullptr, a.vec_idx, a.pi_in, a.pi_out, nullptr},
                   a.s.M, a.s.K, a.s.V, a.s.Kv, a.N, static_cast<const uint16_t*>(a.X), a.ldx, a.Y, a.ldy, a.relu,
-                  a.out_f32, nullptr};
+                  a.out_f32, a.plan};
   return a.s.dtype == HINM_F16 ? launch_planned<HINM_F16, kFromVectors>(c, stream)
                                : launch_planned<HINM_BF16, kFromVectors>(c, stream);
 }

@@ -43,9 +43,16 @@ def test_mid_prepared(M, K, V, Kv, N, block, dtype):
     check_prepared(synth.small_case(M, K, V, Kv, N, dtype, 84), N, [0], relu=(N % 2 == 0), identity=(V == 96))
 
 
+def _runs_on(block, form, M, K, V, Kv, N, dtype):
+    import paper_2407_20496_amd as hinm
+    plan = hinm.hinm_calib_mid_plan(M, K, V, Kv, dtype, N, form)
+    return "SRC=%d,RB=%d,CB=%d,NW=%d>" % (form + 1, *block) in plan
+
+
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("M,K,V,Kv,N,block", CANONICAL)
 def test_mid_canonical(M, K, V, Kv, N, block, dtype):
+    assert _runs_on(block, 0, M, K, V, Kv, N, dtype)
     check_canonical(synth.small_case(M, K, V, Kv, N, dtype, 85), N, [0], relu=(N % 2 == 0), identity=(V == 96), ld_pad=8)
 
 
@@ -80,6 +87,7 @@ def test_mid_ignores_what_lies_beside_the_kept_columns(prepared):
 @pytest.mark.parametrize("dtype", ["f16", "bf16"])
 @pytest.mark.parametrize("M,K,V,Kv,N,block", CANONICAL)
 def test_mid_vectors(M, K, V, Kv, N, block, dtype):
+    assert _runs_on(block, 1, M, K, V, Kv, N, dtype)
     from oracle import hinm_oracle as orc
     from tests import gpu_util as gu
     case = synth.small_case(M, K, V, Kv, N, dtype, 87)
