@@ -48,9 +48,9 @@ hinm_status run_spmm(const SpmmArgs& a, uint32_t flags, hipStream_t stream) {
     if (a.N > 16 || !spmm_skinny_supported(a)) return HINM_ERR_UNSUPPORTED;
     e = launch_spmm_skinny(a, stream);
   } else {
-    // by shape: a moderate number of columns -> wave-private kernel; one column, or sixteen on a small layer -> k-split
-    // skinny kernel (bandwidth-bound on the packed weights); otherwise the tile kernel; shapes none covers fall back to
-    // the plain kernel.
+    // by shape: a moderate number of columns -> wave-private kernel; one column, or up to sixteen where one round of its
+    // workgroups does -> k-split skinny kernel (bandwidth-bound on the packed weights); otherwise the tile kernel; shapes
+    // none covers fall back to the plain kernel.
     if (spmm_mid_canonical_preferred(a)) e = launch_spmm_mid_canonical(a, stream);
     else if (a.N <= 16 && spmm_skinny_supported(a)) e = launch_spmm_skinny(a, stream);
     else if (spmm_tile_supported(a)) e = launch_spmm_tile(a, stream);

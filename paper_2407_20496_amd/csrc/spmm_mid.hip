@@ -544,14 +544,18 @@ hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream) {
                                : launch_planned<HINM_BF16, kFromPrepared>(c, stream);
 }
 
-// On the packed arrays the line against the tile kernel lies at 640 blocks (8192 x 4096 at 50 %, N = 300, 640 blocks:
-// 31 against 39 us; 4096 x 4096, N = 1024, 1024 blocks: 41 against 33); that kernel's fast form needs whole 64-column
-// steps, without them this one is the better at any size.
+// Up to 16 columns the 16-row kernel is ahead where its workgroups fit the chip in one round and its waves have no more
+// than one batch of steps or so (as above, "from memory / from the cache", that kernel -> this one: 4096 x 4096 at 50 %, N = 16
+// 7.9 / 6.0 -> 11.9 / 8.1 us; 2048 x 8192, V = 32, Kv = 2048, N = 2 7.4 / 5.4 -> 11.6 / 7.6; with 320 workgroups, 5120 x 5120,
+// Kv = 1280, N = 9 11.0 / 9.5 -> 9.7 / 6.4; with 109 steps, 832 x 13960, Kv = 6976, N = 9 25.4 / 21.4 -> 28.5 / 15.5).
+// Against the tile kernel the line lies at 640 blocks (8192 x 4096 at 50 %, N = 300, 640 blocks: 31 against 39 us;
+// 4096 x 4096, N = 1024, 1024 blocks: 41 against 33); that kernel's fast form needs whole 64-column steps, without them this one
+// is the better at any size.
 bool spmm_mid_canonical_preferred(const SpmmArgs& a) {
   if (a.s.V % 32 != 0 || a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   const int64_t blocks = plain_blocks(a.s.M, a.s.V, a.N);
   if (blocks >= (1 << 28)) return false;
-  if (a.N == 16 && a.s.M < 4096) return false;  // one whole block of the 16-row kernel: 2048 x 8192 7.2 against 8.7 us
+  if (a.N <= 16 && a.s.M / 16 <= 256 && a.s.Kv <= 4096) return false;
   return a.N <= 64 || a.s.Kv % 64 != 0 || blocks <= 640;
 }
 

@@ -286,3 +286,16 @@ def test_few_columns_run_on_the_kernel_that_is_ahead_with_weights_from_memory(M,
     ld = (N + 7) // 8 * 8
     text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "bf16", N, ld, ld)
     assert n == 1 and text.startswith(kernel + "<"), text
+
+
+@pytest.mark.parametrize("M,K,V,Kv,N,mid", [
+    (4096, 4096, 64, 2048, 2, False),       # one round of 16-row workgroups: the 16-row kernel
+    (4096, 4096, 64, 2048, 16, False),
+    (2048, 8192, 32, 2048, 9, False),
+    (5120, 5120, 64, 1280, 9, True),        # a second round
+    (8192, 4096, 128, 2048, 16, True),
+    (832, 13960, 64, 6976, 9, True),        # more than 64 steps
+    (4096, 4096, 64, 2048, 17, True),
+])
+def test_packed_arrays_with_few_columns_run_on_the_kernel_that_is_ahead(M, K, V, Kv, N, mid):
+    assert bool(hinm.hinm_calib_mid_plan(M, K, V, Kv, "f16", N, 0)) == mid

@@ -108,6 +108,9 @@ def test_mid_vectors(M, K, V, Kv, N, block, dtype):
     (48, 272, 264, 9, 8),
     (32, 40, 8, 17, 0),         # nothing but a ragged step
     (32, 320, 312, 1, 0),
+    (32, 2120, 2112, 9, 0),     # eight waves with batches of six: 33 whole steps, 48 and a ragged one
+    (32, 3120, 3112, 16, 0),
+    (32, 3080, 3072, 1, 0),
 ])
 def test_sixteen_row_tiles_with_ragged_ends(M, K, Kv, N, ld_pad, dtype):
     check_canonical(synth.small_case(M, K, 16, Kv, N, dtype, 88), N, [0], ld_pad=ld_pad)
