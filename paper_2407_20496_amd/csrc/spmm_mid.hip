@@ -425,7 +425,8 @@ struct MidPlan {
 
 // The largest block of which about 150 exist (a block that is alone on its compute unit runs 2 + 0.14 S us with
 // 32 x 32 outputs and eight waves, 2.6 + 0.19 S with 64 x 64, S = 64-column steps; 64 x 64 blocks read 3/8 fewer bytes
-// per output than 64 x 32 ones).  Beyond 256 blocks of 64 x 64 several share a unit: four waves each leave room for
+// per output than 64 x 32 ones).  64 x 64 blocks from 129 on: split in two they would be more than 256 of 128 KB of LDS
+// each, a second round (3072 x 8192 at 50 %, N = 160, 144 blocks: 14.2 against 20.9 us; 2304 x 4096, N = 256 8.2 and 11.5).  Beyond 256 blocks of 64 x 64 several share a unit: four waves each leave room for
 // two, two waves for four (11008 x 4096 at 50 %, N = 256, 688 blocks: 20.5 us with two waves, 22.3 with four, 23.3
 // with eight; 16384 x 4096, N = 128, 512 blocks: 21.3, 15.5, 17.7).  Twice the block instead is worth it on long
 // passes where 150 to 256 of them exist: 128 rows in the prepared form (4096 x 11008 at 50 %, N = 512: 37.3 against
@@ -450,7 +451,7 @@ MidPlan plan_mid(int M, int V, int Kv, int N, bool canonical) {
       if (!canonical && four && S >= 32 && fills(rows / 4 * b2)) return {4, 2, 4};
       return {2, 2, 4};
     }
-    if (blocks >= 150) return {2, 2, 8};
+    if (blocks > 128) return {2, 2, 8};
   }
   const int64_t blocks = rows * b2;  // 32 x 64; V % 64 != 0 has nothing larger
   if (blocks > 512) return {1, 2, 2};

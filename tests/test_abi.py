@@ -299,3 +299,15 @@ def test_few_columns_run_on_the_kernel_that_is_ahead_with_weights_from_memory(M,
 ])
 def test_packed_arrays_with_few_columns_run_on_the_kernel_that_is_ahead(M, K, V, Kv, N, mid):
     assert bool(hinm.hinm_calib_mid_plan(M, K, V, Kv, "f16", N, 0)) == mid
+
+
+@pytest.mark.parametrize("M,N,block", [
+    (2048, 256, "RB=1,CB=2,NW=8"),      # 128 blocks of 64 x 64, 256 of 32 x 64: one round
+    (2112, 256, "RB=2,CB=2,NW=8"),      # 132 and 264: the smaller ones would need a second round
+    (3072, 160, "RB=2,CB=2,NW=8"),
+])
+def test_blocks_of_the_kernel_for_a_moderate_number_of_columns_fit_one_round(M, N, block):
+    text, n = hinm.hinm_spmm_prepared_plan(M, 4096, 64, 2048, "f16", N, N, N)
+    assert n == 1 and block in text, text
+    for form in (0, 1):
+        assert block in hinm.hinm_calib_mid_plan(M, 4096, 64, 2048, "f16", N, form)
