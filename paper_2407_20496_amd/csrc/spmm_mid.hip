@@ -392,6 +392,9 @@ struct MidCall {
   LaunchPlan* plan;
 };
 
+// An input that a die's L2 (4 MB) holds is shared by all column blocks there; a larger one is taken block by block.
+bool columns_last(int K, int N) { return (double)K * N * 2 > 3.0e6; }
+
 template <int DT, int SRC, int RB, int CB, int NW>
 hipError_t launch_cfg(const MidCall& c, hipStream_t stream) {
   using C = MidCfg<RB, CB, NW>;
@@ -403,8 +406,7 @@ hipError_t launch_cfg(const MidCall& c, hipStream_t stream) {
   p.col_blocks = (c.N + 32 * CB - 1) / (32 * CB);
   p.work = c.M / (32 * RB) * p.col_blocks;
   p.work_per_xcd = (p.work + 7) / 8;
-  // an input that a die's L2 (4 MB) holds is shared by all column blocks there; a larger one is taken block by block
-  p.columns_last = (double)c.K * c.N * 2 > 3.0e6;
+  p.columns_last = columns_last(c.K, c.N);
   p.relu = c.relu;
   p.out_f32 = c.out_f32;
   constexpr auto kernel = spmm_mid_kernel<DT, SRC, RB, CB, NW>;
@@ -521,17 +523,26 @@ static bool beats_rows16(const PreparedArgs& a) {
   return a.N > 128 || S <= 8 || S > 32 || blocks > 64;
 }
 
-// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies
-// at four workgroups per unit (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096,
-// N = 300, 860 blocks: 25 and 38; N = 400, 1204 blocks: 44 and 36).  Layers of 1024 rows and more stay with the tile
-// kernel beyond 1024 columns although this one is faster on some of them (1024 x 1024, N = 1666: 1.8 times): the plan of
-// such products is one that callers of the tile kernel's part measurements rely on.  Smaller ones: 512 x 5904 at 50 %,
-// N = 3488, 440 blocks: 42 -> 24 us.
+// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies at four workgroups per unit
+// (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096, N = 300, 860 blocks: 25 and 38;
+// N = 400, 1204 blocks: 44 and 36; 1024 x 1024, N = 1666, 432 blocks: 7.7 and 13.0; 512 x 5904, N = 3488, 440 blocks: 24 and
+// 42), at three with V % 64 != 0.  Where the tile kernel has one round of 64-row tiles, which is a short one, it is at three
+// for inputs that are taken one column block at a time (8192 x 8192, Kv = 2048, N = 384, 768 blocks: 24.4 and 26.2; N = 448
+// 28.4 and 26.4; 8192 x 4096, N = 512 32.6 and 25.7; 1728 x 6480, N = 2168, 918 blocks: 25.1 and 22.5) unless two of them at
+// a time leave no slot of a unit empty (4096 x 4096, N = 1024, 1024 blocks: 24.5 and 25.8) and for passes of up to 16 steps (7872 x 1248, Kv = 624, N = 417, 861 blocks: 12.2 and 10.7), at two for
+// up to four steps (14400 x 824, Kv = 208, N = 224, 900 blocks: 7.8 and 6.2); else at four (16384 x 4096, N = 256, 1024 blocks:
+// 24.2 and 26.6; 9088 x 1928, Kv = 960, N = 394, 994 blocks and a second round of tiles: 15.4 and 21.3).
 bool spmm_mid_prepared_preferred(const PreparedArgs& a) {
   if (a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   if (a.N <= 128 && !beats_rows16(a)) return false;
-  if (a.N > 1024 && a.s.M >= 1024) return false;
-  return a.N <= 64 || plain_blocks(a.s.M, a.s.V, a.N) <= (a.s.V % 64 == 0 ? 1024 : 768);
+  if (a.N <= 64) return true;
+  const int64_t blocks = plain_blocks(a.s.M, a.s.V, a.N);
+  int64_t line = a.s.V % 64 == 0 ? 1024 : 768;
+  if (a.s.V == 64 && (int64_t)(a.s.M / 64) * ((a.N + 255) / 256) <= 256) {
+    const bool shared = a.s.M <= 4096 && blocks > 960;  // two column blocks of a die share its reads of the weights
+    line = a.s.Kv <= 256 ? 512 : a.s.Kv <= 1024 || (columns_last(a.s.K, a.N) && !shared) ? 768 : 1024;
+  }
+  return blocks <= line;
 }
 
 hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream) {

@@ -311,3 +311,23 @@ def test_blocks_of_the_kernel_for_a_moderate_number_of_columns_fit_one_round(M, 
     assert n == 1 and block in text, text
     for form in (0, 1):
         assert block in hinm.hinm_calib_mid_plan(M, 4096, 64, 2048, "f16", N, form)
+
+
+@pytest.mark.parametrize("M,K,V,Kv,N,kernel", [
+    (1024, 1024, 64, 512, 1666, "spmm_mid_kernel"),
+    (2048, 2048, 128, 1024, 2048, "spmm_mid_kernel"),
+    (2048, 2048, 64, 512, 2056, "spmm_tile_prepared_kernel"),       # 1056 blocks
+    (8192, 4096, 64, 2048, 384, "spmm_mid_kernel"),
+    (8192, 4096, 64, 2048, 512, "spmm_tile_prepared_kernel"),       # one round of 64-row tiles
+    (4096, 4096, 64, 2048, 1024, "spmm_mid_kernel"),                # no empty slot, weights shared by two column blocks
+    (1728, 6480, 64, 1616, 2168, "spmm_tile_prepared_kernel"),
+    (7872, 1248, 64, 624, 417, "spmm_tile_prepared_kernel"),
+    (14400, 824, 64, 208, 224, "spmm_tile_prepared_kernel"),        # four steps
+    (10048, 840, 64, 208, 292, "spmm_mid_kernel"),                  # a second round
+    (9088, 1928, 64, 960, 394, "spmm_mid_kernel"),
+    (16384, 4096, 64, 2048, 256, "spmm_mid_kernel"),                # an input that a die's cache holds
+])
+def test_line_between_a_moderate_number_of_columns_and_the_tile_kernels(M, K, V, Kv, N, kernel):
+    ld = (N + 7) // 8 * 8
+    text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "f16", N, ld, ld)
+    assert n == 1 and text.startswith(kernel + "<"), text

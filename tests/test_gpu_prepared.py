@@ -292,7 +292,7 @@ def test_tile_kernel_parts_run_and_store_nothing():
     import torch
     import paper_2407_20496_amd as hinm
     from tests import gpu_util as gu
-    shapes = [(4096, 1024, 128, 512, 1100, "bf16"), (1024, 2048, 64, 1024, 1032, "f16")]   # both run on the tile kernel
+    shapes = [(4096, 1024, 128, 512, 1100, "bf16"), (2048, 2048, 64, 512, 2056, "f16")]   # both run on the tile kernel
     for (M, K, V, Kv, N, dtype) in shapes:
         ld = (N + 7) // 8 * 8
         assert "spmm_tile_prepared_kernel" in hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld, 0)[0]
@@ -312,7 +312,7 @@ def test_tile_kernel_parts_run_and_store_nothing():
         assert torch.equal(X, before_x) and torch.equal(prep, before_p)
     with pytest.raises(hinm.HinmError):     # a shape served by another kernel has no tile-kernel parts
         hinm.hinm_calib_tile_part(256, 512, 64, 256, "f16", 520, prep, X, 520, 1)
-    _check(synth.small_case(1024, 2048, 64, 1024, 1032, "f16", 77), 1032, [0])
+    _check(synth.small_case(2048, 2048, 64, 512, 2056, "f16", 77), 2056, [0])
 
 
 @pytest.mark.parametrize("forms", ["prepared", "canonical", "mixed"])
