@@ -691,7 +691,8 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t stream) {
   const bool vec2 = (s.K % 2 == 0) && ((reinterpret_cast<uintptr_t>(a.W) & 3u) == 0);
   const bool rho_vec4 = a.rho && (s.K % 4 == 0) && ((reinterpret_cast<uintptr_t>(a.rho) & 15u) == 0);
   // ---- score
-  // eight columns a thread where that leaves sixteen waves for every compute unit, else two (see score_kernel)
+  // eight columns a thread where that leaves sixteen waves for every compute unit, else two (see score_kernel); tiles of fewer
+  // than 32 rows have batches of eight (4096 x 4096, V = 16, all of hinm_pack 34 -> 29 us against rows loaded one by one)
   const bool score8 = vec8 && (int64_t)T * (s.K / 8) >= 256 * 16 * 64;
   const int cols_per_thread = a.rho ? (rho_vec4 ? 4 : 1) : (score8 ? 8 : vec2 ? 2 : 1);
   const int threads_needed = (s.K + cols_per_thread - 1) / cols_per_thread;
@@ -702,11 +703,15 @@ hipError_t launch_pack(const PackArgs& a, hipStream_t stream) {
     else score_rho_kernel<1><<<grid, kScoreThreads, 0, stream>>>(a.rho, a.scores, s.K, s.V);
   } else if (s.dtype == HINM_F16) {
     if (score8) score(score_kernel<HINM_F16, 8, 4>);
+    else if (vec2 && s.V < 32) score(score_kernel<HINM_F16, 2, 8>);
     else if (vec2) score(score_kernel<HINM_F16, 2, 32>);
+    else if (s.V < 32) score(score_kernel<HINM_F16, 1, 8>);
     else score(score_kernel<HINM_F16, 1, 32>);
   } else {
     if (score8) score(score_kernel<HINM_BF16, 8, 4>);
+    else if (vec2 && s.V < 32) score(score_kernel<HINM_BF16, 2, 8>);
     else if (vec2) score(score_kernel<HINM_BF16, 2, 32>);
+    else if (s.V < 32) score(score_kernel<HINM_BF16, 1, 8>);
     else score(score_kernel<HINM_BF16, 1, 32>);
   }
   hipError_t e = hipGetLastError();

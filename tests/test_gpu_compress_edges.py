@@ -15,6 +15,9 @@ pytestmark = pytest.mark.gpu
     (33, 129, 33, 64),         # odd K: one column a thread, rows beyond one batch of 32
     (62, 130, 31, 64),         # two columns a thread, fewer rows than a batch
     (130, 1026, 65, 512),      # ... and a remainder behind two batches
+    (64, 130, 16, 64),         # batches of eight: two, with a remainder, none
+    (40, 129, 20, 64),
+    (14, 130, 7, 64),
     (256, 8192, 1, 64),        # eight columns a thread (enough threads for it)
     (2, 16384, 1, 8192),       # sixteen keys a select thread
     (2, 16392, 1, 8192),       # keys re-read in every pass
