@@ -36,6 +36,21 @@ def test_select_digits(K, values):
     _compare(synth.to_bits(np.ascontiguousarray(W.reshape(32, K)), "bf16"), "bf16", 8, K // 16 * 8)
 
 
+@pytest.mark.parametrize("V", [8, 20, 24])           # rows in batches of eight, with and without a remainder
+@pytest.mark.parametrize("K", [640, 5000, 16392])    # four, sixteen or no keys held per select thread
+@pytest.mark.parametrize("case", ["zeros cut", "zeros below", "ones cut", "near ties cut"])
+def test_select_among_many_equal_scores(case, K, V):
+    """A third to two thirds of the columns tie, in the middle of distinct scores: the threshold among the equal ones, above
+    them, and among scores that differ from them in low bits only."""
+    rng = np.random.default_rng(K + V)
+    W = rng.uniform(0.5, 2.0, size=(2, V, K)).astype(np.float32)
+    tied = rng.random(K) < (0.4 if case == "zeros below" else 0.6)
+    W[:, :, tied] = 0.0 if case.startswith("zeros") else 1.25
+    if case == "near ties cut":
+        W[:, 0, tied & (rng.random(K) < 0.5)] = 1.2578125      # one bf16 step in a single row
+    _compare(synth.to_bits(np.ascontiguousarray(W.reshape(2 * V, K)), "bf16"), "bf16", V, K // 16 * 8)
+
+
 @pytest.mark.parametrize("Kv", [64, 72, 576, 1088])  # whole steps or not; one to nine workgroup-loads of steps
 def test_prepare_does_not_depend_on_alignment(Kv):
     import torch
