@@ -31,13 +31,14 @@ PyObject* s_f16;
 PyObject* s_bf16;
 PyObject* s_layer[12];
 
+// The low 64 bits, as ctypes converts integers: sizes use all of them (2**64 - 1 for "any").
 bool to_i64(PyObject* o, int64_t* out) {
   if (PyLong_Check(o)) {
-    *out = PyLong_AsLongLong(o);
+    *out = (int64_t)PyLong_AsUnsignedLongLongMask(o);
   } else {
     PyObject* n = PyNumber_Long(o);
     if (!n) return false;
-    *out = PyLong_AsLongLong(n);
+    *out = (int64_t)PyLong_AsUnsignedLongLongMask(n);
     Py_DECREF(n);
   }
   return !(*out == -1 && PyErr_Occurred());
@@ -222,10 +223,13 @@ bool field(PyObject* layer, int which, Convert convert, T* out) {
 // (layers, N, X, ldx, Y, ldy, scratch, scratch_bytes, stream)
 PyObject* chain(PyObject*, PyObject* const* a, Py_ssize_t n) {
   if (!takes(n, 9)) return nullptr;
+  if (PyObject_Size(a[0]) < 0) return nullptr;  // an iterator that is used up by one pass is no sequence of layers
   PyObject* seq = PySequence_Fast(a[0], "layers must be a sequence");
   if (!seq) return nullptr;
   const Py_ssize_t count = PySequence_Fast_GET_SIZE(seq);
-  std::vector<hinm_layer> layers((size_t)count);
+  std::vector<hinm_layer> layers;
+  layers.reserve((size_t)count + 1);  // an address also for a chain of no layers, which is an error of shape
+  layers.resize((size_t)count);
   bool ok = true;
   for (Py_ssize_t i = 0; i < count && ok; ++i) {
     PyObject* l = PySequence_Fast_GET_ITEM(seq, i);

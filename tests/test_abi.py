@@ -331,3 +331,22 @@ def test_line_between_a_moderate_number_of_columns_and_the_tile_kernels(M, K, V,
     ld = (N + 7) // 8 * 8
     text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "f16", N, ld, ld)
     assert n == 1 and text.startswith(kernel + "<"), text
+
+
+def test_python_calls_convert_arguments_as_ctypes_does():
+    """Sizes use all 64 bits, a chain of no layers is an error of shape and an iterator no sequence of layers, as in the
+    calls that go through ctypes."""
+    fake = 0x100000
+    with pytest.raises(hinm.HinmError) as err:      # the size passes, the next check refuses the call
+        hinm.hinm_pack(256, 256, 16, 128, "f16", fake, fake, fake, fake, fake + 4, 2**64 - 1, 0)
+    assert err.value.status == 4
+    with pytest.raises(hinm.HinmError) as err:
+        hinm.hinm_spmm(256, 256, 16, 128, "f16", 8, None, fake, fake, None, None, fake, 8, fake, 8, 0, None, 2**64 - 1, 0)
+    assert err.value.status == 1
+    for call in (lambda: hinm.hinm_chain([], 8, fake, 8, fake, 8, fake, 0, 0), lambda: hinm.hinm_chain_sizes([], 8)):
+        with pytest.raises(hinm.HinmError) as err:
+            call()
+        assert err.value.status == 2
+    layer = hinm.Layer(256, 256, 64, 128, "f16", None, None, None, prepared=fake)
+    with pytest.raises(TypeError):
+        hinm.hinm_chain(iter([layer]), 8, fake, 8, fake, 8, fake, 0, 0)
