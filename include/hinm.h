@@ -282,8 +282,10 @@ hinm_status hinm_spmm(const hinm_shape* shape, int32_t N,
  * rounding, pi_in / pi_out, ldx / ldy and alignment rules as for hinm_spmm.  flags: HINM_EPI_RELU,
  * HINM_OUT_F32, HINM_KERNEL_REFERENCE (one thread per output element), the variant bits (1 =
  * register-staged tile kernel, 2 / 3 = direct-to-LDS tile kernel with 256- / 512-column blocks,
- * 4 / 5 = the same with twice as many waves of half the width; 2..5 need Kv % 64 == 0); anything else returns HINM_ERR_UNSUPPORTED.  V in {32, 64, 96, 128}
- * with N > 1 runs on the dense MFMA, other shapes on the plain kernel.  Needs no workspace. */
+ * 4 / 5 = the same with twice as many waves of half the width; 2..5 need Kv % 64 == 0; all of them V in
+ * {32, 64, 96, 128} and N > 1); anything else returns HINM_ERR_UNSUPPORTED.  By shape: N = 1 streams the stored
+ * values once (any V and leading dimensions); V a multiple of 32 with N > 1 runs on the dense MFMA (the kernel for a
+ * moderate number of columns, or a tile kernel up to V = 128); other shapes run on the plain kernel.  Needs no workspace. */
 hinm_status hinm_spmm_vectors(const hinm_shape* shape, int32_t N,
                               const void* vals_v, const int32_t* vec_idx,
                               const int32_t* pi_in, const int32_t* pi_out,
@@ -308,9 +310,10 @@ hinm_status hinm_prepare(const hinm_shape* shape, const void* vals, const uint8_
 
 /* Same product as hinm_spmm, computed from a prepared layer (its pi_in / pi_out are the ones given
  * to hinm_prepare).  Flags: HINM_EPI_RELU, HINM_OUT_F32.
- * Few-column shapes (N <= 64, and small layers up to N = 2048) split each tile's kept columns over
- * the waves of one workgroup, which add their fp32 partial tiles in LDS in a fixed order, so results
- * are reproducible bit for bit.  Columns of X between N and ldx are never used in a result.
+ * Products that do not fill the chip with whole tiles (one column, a moderate number of columns, small layers; which
+ * kernel serves a call: hinm_spmm_prepared_plan) split each tile's kept columns over the waves of one workgroup, which
+ * add their fp32 partial tiles in LDS in a fixed order, so results are reproducible bit for bit.  Columns of X between N
+ * and ldx are never used in a result.
  * hinm_spmm_prepared_workspace gives the bytes of device workspace a shape needs: 0 for every kernel
  * of this build, so `workspace` may be NULL (the argument stays in the ABI for kernels that split a
  * tile over workgroups; one that needs it returns HINM_ERR_WORKSPACE when it is missing, misaligned

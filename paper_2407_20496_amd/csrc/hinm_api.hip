@@ -469,16 +469,16 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     *route = PreparedRoute::Mid;
     return HINM_OK;
   }
-  // up to 16 columns: 16-row workgroups on the 16x16x64 form (measured faster than the 32-row kernel on every
-  // decode shape tried, by 8-10 % with 344 row blocks of 32 and by 15-37 % with 128); variant 11 pins it for any N, 19 its form with
-  // the input rows resident in LDS (16 columns only)
+  // What the kernel for a moderate number of columns leaves: one column, up to 64 columns (128 on the smallest layers) where it
+  // is behind, V % 64 != 0 beyond 768 of its blocks, and many columns.  Up to 64 columns that is the 16-row kernel (16x16x64
+  // form, faster than the 32-row one on every decode shape tried, by 8-10 % with 344 row blocks of 32 and by 15-37 % with
+  // 128); variant 11 pins it for any N, 19 its form with the input rows resident in LDS (16 columns only).
   if (a.tile_variant == 19 && !spmm_rows16_resident_supported(a)) return HINM_ERR_UNSUPPORTED;
-  // ... and for up to 64 columns on every layer tried (one workgroup per 16..64 rows and 16 columns re-reads
-  // the weights for every column block and still wins: 11008 x 4096 at N = 64 23 vs 40 us, 1024 x 4096 6 vs
-  // 33 us), and up to 2048 columns while its cost, which grows with M * Kv * ceil(N / 16), stays under the tile
-  // kernels' floor of one serial pass over the kept columns (about 15 us per 1024 of them, a little more per
-  // column on short passes): layers whose tiles cannot fill the chip.  The constants are fitted to timings of
-  // 42 (layer, N) pairs between 512 x 4608 and 8192 x 8192 and checked on some 250 more at other N.
+  // Beyond, up to 2048 columns, it is the 16-row kernel while its cost, which grows with M * Kv * ceil(N / 16), stays under
+  // the tile kernels' floor of one serial pass over the kept columns (about 15 us per 1024 of them, a little more per column
+  // on short passes): V = 32 and 96 with long passes among products, and every shape for hinm_calib_tile_part, which goes by
+  // the choice between these two alone.  The constants are fitted to timings of 42 (layer, N) pairs between 512 x 4608
+  // and 8192 x 8192 and checked on some 250 more at other N.
   bool few_columns = N <= 64;
   if (!few_columns && N <= 2048) {
     const double units = (double)shape->M * ((N + 15) / 16);
