@@ -145,33 +145,44 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   for (int j = tid; j < m; j += THREADS) col_v[j] = 0.0;
   if (tid == 0) filled[0] = 0;
   __syncthreads();
-  // the smallest cost of every row is taken off it; filled[0] = high word of the largest finite cost that is left
-  for (int i = wave; i < n; i += WAVES) {
-    const double* r = row_of(i);
-    double x[CPL];
-    double least = kInf;
+  // the smallest cost of every row is taken off it (two rows at a time, their chains overlap); filled[0] = high word of
+  // the largest finite cost that is left
+  int largest = 0;
+  for (int i0 = wave; i0 < n; i0 += 2 * WAVES) {
+    double x[2][CPL], least[2];
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      x[c] = r[min(64 * c + lane, m - 1)];
-      least = x[c] < least ? x[c] : least;
-    }
-    least = read_lane(least, wave_argmin_lane(least));
-    const double off = least > -kInf && least < kInf ? least : 0.0;
-    int largest = 0;
+    for (int h = 0; h < 2; ++h) {
+      const double* r = row_of(min(i0 + h * WAVES, n - 1));
+      least[h] = kInf;
 #pragma unroll
-    for (int c = 0; c < CPL; ++c) {
-      x[c] -= off;
-      if (__builtin_fabs(x[c]) < kInf) largest = max(largest, __double2hiint(x[c]) & 0x7fffffff);
-      if constexpr (IN_LDS) {
-        if (64 * c + lane < m) lds_cost[(size_t)i * m + 64 * c + lane] = x[c];
+      for (int c = 0; c < CPL; ++c) {
+        x[h][c] = r[min(64 * c + lane, m - 1)];
+        least[h] = x[h][c] < least[h] ? x[h][c] : least[h];
       }
     }
-    largest = -wave_min(-largest);
-    if (lane == 0) {
-      if constexpr (!IN_LDS) base[i] = off;
-      atomicMax(&filled[0], largest);
+    const int at0 = wave_argmin_lane(least[0]), at1 = wave_argmin_lane(least[1]);
+    least[0] = read_lane(least[0], at0);
+    least[1] = read_lane(least[1], at1);
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int i = i0 + h * WAVES;
+      if (i >= n) break;  // (another wave's row)
+      const double off = least[h] > -kInf && least[h] < kInf ? least[h] : 0.0;
+#pragma unroll
+      for (int c = 0; c < CPL; ++c) {
+        x[h][c] -= off;
+        if (__builtin_fabs(x[h][c]) < kInf) largest = max(largest, __double2hiint(x[h][c]) & 0x7fffffff);
+        if constexpr (IN_LDS) {
+          if (64 * c + lane < m) lds_cost[(size_t)i * m + 64 * c + lane] = x[h][c];
+        }
+      }
+      if constexpr (!IN_LDS) {
+        if (lane == 0) base[i] = off;
+      }
     }
   }
+  largest = -wave_min(-largest);
+  if (lane == 0) atomicMax(&filled[0], largest);
   __syncthreads();
   // powers of two: costs times `scale` are below 2, and the start's potentials are of scaled costs
   const int exponent = max(filled[0] >> 20, 1);
