@@ -428,16 +428,18 @@ struct MidPlan {
   int rb, cb, nw;
 };
 
-// The largest block of which about 150 exist (a block that is alone on its compute unit runs 2 + 0.14 S us with
-// 32 x 32 outputs and eight waves, 2.6 + 0.19 S with 64 x 64, S = 64-column steps; 64 x 64 blocks read 3/8 fewer bytes
-// per output than 64 x 32 ones).  64 x 64 blocks from 129 on: split in two they would be more than 256 of 128 KB of LDS
-// each, a second round (3072 x 8192 at 50 %, N = 160, 144 blocks: 14.2 against 20.9 us; 2304 x 4096, N = 256 8.2 and 11.5).  Beyond 256 blocks of 64 x 64 several share a unit: four waves each leave room for
-// two, two waves for four (11008 x 4096 at 50 %, N = 256, 688 blocks: 20.5 us with two waves, 22.3 with four, 23.3
-// with eight; 16384 x 4096, N = 128, 512 blocks: 21.3, 15.5, 17.7).  Twice the block instead is worth it on long
-// passes where 150 to 256 of them exist: 128 rows in the prepared form (4096 x 11008 at 50 %, N = 512: 37.3 against
-// 41.3 us; with 16 steps 11.2 against 10.0), 128 columns on the packed arrays, whose rows of values cost a cache line
-// each and step (4096 x 4096, N = 512: 19.1 against 24.3; with 8 steps 10.1 against 9.2).  For the same reason the
-// packed arrays take 32-row blocks with 64 columns before 64-row blocks with 32 (8192 x 4096, N = 24: 11.0 and 14.6).
+// The largest block of which about 150 exist (a block that is alone on its compute unit runs 2 + 0.14 S us with 32
+// x 32 outputs and eight waves, 2.6 + 0.19 S with 64 x 64, S = 64-column steps; 64 x 64 blocks read 3/8 fewer bytes
+// per output than 64 x 32 ones).  64 x 64 blocks from 129 on: split in two they would be more than 256 of 128 KB of
+// LDS each, a second round (3072 x 8192 at 50 %, N = 160, 144 blocks: 14.2 against 20.9 us; 2304 x 4096, N = 256
+// 8.2 and 11.5).  Beyond 256 blocks of 64 x 64 several share a unit: four waves each leave room for two, two waves
+// for four (11008 x 4096 at 50 %, N = 256, 688 blocks: 20.5 us with two waves, 22.3 with four, 23.3 with eight;
+// 16384 x 4096, N = 128, 512 blocks: 21.3, 15.5, 17.7).  Twice the block instead is worth it on long passes where
+// 150 to 256 of them exist: 128 rows in the prepared form (4096 x 11008 at 50 %, N = 512: 37.3 against 41.3 us;
+// with 16 steps 11.2 against 10.0), 128 columns on the packed arrays, whose rows of values cost a cache line each
+// and step (4096 x 4096, N = 512: 19.1 against 24.3; with 8 steps 10.1 against 9.2).  For the same reason the
+// packed arrays take 32-row blocks with 64 columns before 64-row blocks with 32 (8192 x 4096, N = 24: 11.0 and
+// 14.6).
 MidPlan plan_mid(int M, int V, int Kv, int N, bool canonical) {
   const int S = (Kv + 63) / 64;
   const int64_t rows = M / 32;
@@ -526,15 +528,17 @@ static bool beats_rows16(const PreparedArgs& a) {
   return a.N > 128 || S <= 8 || S > 32 || blocks > 64;
 }
 
-// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies at four workgroups per unit
-// (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096, N = 300, 860 blocks: 25 and 38;
-// N = 400, 1204 blocks: 44 and 36; 1024 x 1024, N = 1666, 432 blocks: 7.7 and 13.0; 512 x 5904, N = 3488, 440 blocks: 24 and
-// 42), at three with V % 64 != 0.  Where the tile kernel has one round of 64-row tiles, which is a short one, it is at three
-// for inputs that are taken one column block at a time (8192 x 8192, Kv = 2048, N = 384, 768 blocks: 24.4 and 26.2; N = 448
-// 28.4 and 26.4; 8192 x 4096, N = 512 32.6 and 25.7; 1728 x 6480, N = 2168, 918 blocks: 25.1 and 22.5) unless two of them at
-// a time leave no slot of a unit empty (4096 x 4096, N = 1024, 1024 blocks: 24.5 and 25.8) and for passes of up to 16 steps (7872 x 1248, Kv = 624, N = 417, 861 blocks: 12.2 and 10.7), at two for
-// up to four steps (14400 x 824, Kv = 208, N = 224, 900 blocks: 7.8 and 6.2); else at four (16384 x 4096, N = 256, 1024 blocks:
-// 24.2 and 26.6; 9088 x 1928, Kv = 960, N = 394, 994 blocks and a second round of tiles: 15.4 and 21.3).
+// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies at four workgroups per
+// unit (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096, N = 300, 860 blocks: 25
+// and 38; N = 400, 1204 blocks: 44 and 36; 1024 x 1024, N = 1666, 432 blocks: 7.7 and 13.0; 512 x 5904, N = 3488,
+// 440 blocks: 24 and 42), at three with V % 64 != 0.  Where the tile kernel has one round of 64-row tiles, which is
+// a short one, it is at three for inputs that are taken one column block at a time (8192 x 8192, Kv = 2048, N =
+// 384, 768 blocks: 24.4 and 26.2; N = 448 28.4 and 26.4; 8192 x 4096, N = 512 32.6 and 25.7; 1728 x 6480, N = 2168,
+// 918 blocks: 25.1 and 22.5) unless two of them at a time leave no slot of a unit empty (4096 x 4096, N = 1024,
+// 1024 blocks: 24.5 and 25.8) and for passes of up to 16 steps (7872 x 1248, Kv = 624, N = 417, 861 blocks: 12.2
+// and 10.7), at two for up to four steps (14400 x 824, Kv = 208, N = 224, 900 blocks: 7.8 and 6.2); else at four
+// (16384 x 4096, N = 256, 1024 blocks: 24.2 and 26.6; 9088 x 1928, Kv = 960, N = 394, 994 blocks and a second round
+// of tiles: 15.4 and 21.3).
 bool spmm_mid_prepared_preferred(const PreparedArgs& a) {
   if (a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   if (a.N <= 128 && !beats_rows16(a)) return false;
