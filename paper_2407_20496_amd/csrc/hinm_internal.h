@@ -76,6 +76,19 @@ __device__ __forceinline__ uint16_t float_to_bits(float f) {
   }
 }
 
+// two floats -> two storage values in one word, the first in the low half, round-to-nearest-even.
+template <int DT>
+__device__ __forceinline__ uint32_t floats_to_bits(float lo, float hi) {
+  typedef float f32x2 __attribute__((ext_vector_type(2)));
+  if constexpr (DT == HINM_F16) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), f16x2));
+  } else {
+    typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+    return __builtin_bit_cast(uint32_t, __builtin_convertvector((f32x2{lo, hi}), bf16x2));
+  }
+}
+
 // ---- launchers implemented in the kernel translation units -------------------------------------
 // All return hipSuccess or the launch error; all are asynchronous on `stream`.
 

@@ -16,6 +16,7 @@
 #include "hinm_internal.h"
 #include "mfma_types.h"
 #include "prepared_layout.h"
+#include "tile_epilogue.h"
 
 namespace hinm {
 namespace {
@@ -182,13 +183,7 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_panel_prepared_kernel(
     for (int rb = 0; rb < RB; ++rb) {
 #pragma unroll
       for (int cb = 0; cb < 2; ++cb)
-#pragma unroll
-        for (int e = 0; e < 16; ++e) {
-          const int row = 8 * (e >> 2) + 4 * qh + (e & 3);
-          float v = acc[rb][cb][e];
-          if (relu) v = v > 0.f ? v : 0.f;
-          *reinterpret_cast<uint16_t*>(stage + row * kYStride + (cb * 32 + i32) * 2) = float_to_bits<DT>(v);
-        }
+        stage_block<DT, kYStride>(acc[rb][cb], stage + cb * 64, relu);
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
       __builtin_amdgcn_wave_barrier();
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");

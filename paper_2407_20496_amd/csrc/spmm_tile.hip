@@ -28,7 +28,6 @@ constexpr int kWaves = 4;
 constexpr int kThreads = kWaves * 64;
 constexpr int kCB = 2;         // 32-column blocks per wave
 constexpr int kBStride = kNB * 2 + 64;  // bytes per gathered row in LDS (+64: rows 4 apart hit distinct banks)
-constexpr int kYStride = kNB * 2 + 16;  // bytes per staged output row
 
 template <int KSUB>
 struct StageLayout {
@@ -41,7 +40,7 @@ struct StageLayout {
   __host__ __device__ static constexpr int stage_bytes(int V) { return b_bytes + a_bytes(V); }
   __host__ __device__ static constexpr int total_bytes(int V) {
     const int two = 2 * stage_bytes(V);
-    const int epi = V * kYStride;
+    const int epi = V * kStageStride<kNB>;
     return two > epi ? two : epi;
   }
 };
@@ -239,7 +238,7 @@ __global__ __launch_bounds__(kThreads) void spmm_tile_kernel(
   }
 
   // ---- epilogue -----------------------------------------------------------------------------------
-  store_tile_rows<DT, RB, kCB, kNB, 64, kThreads, kYStride>(acc, lds, Y, ldy, N, n0, relu, out_f32,
+  store_tile_rows<DT, RB, kCB, kNB, 64, kThreads>(acc, lds, Y, ldy, N, n0, relu, out_f32,
                                                             [&](int row) -> int64_t { const int r = t * V + row; return pi_out ? pi_out[r] : r; });
 }
 
@@ -274,8 +273,7 @@ struct TileDmaCfg {
   static constexpr int A_NM_INSTR = V / 32;                  // wave-wide 4-byte copies: 64 dwords each
   static constexpr int A_INSTR = A_VAL_INSTR + A_NM_INSTR;
   static constexpr int A_ROUNDS = (A_INSTR + NW - 1) / NW;
-  static constexpr int Y_STRIDE = NB * 2 + 16;
-  static constexpr int EPI_BYTES = V * Y_STRIDE;
+  static constexpr int EPI_BYTES = V * kStageStride<NB>;
   static constexpr int LDS_BYTES = (2 * STAGE_BYTES > EPI_BYTES) ? 2 * STAGE_BYTES : EPI_BYTES;
   static_assert(NB == 256 || NB == 512, "column block");
   static_assert(WC == 64 || WC == 32, "columns per wave");
@@ -441,7 +439,7 @@ __global__ __launch_bounds__(NB / WC * 64) void spmm_tile_dma_kernel(
   }
 
   // ---- epilogue -------------------------------------------------------------------------------------------
-  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS, C::Y_STRIDE>(acc, lds, Y, ldy, N, n0, relu, out_f32,
+  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS>(acc, lds, Y, ldy, N, n0, relu, out_f32,
                                                                   [&](int row) -> int64_t { const int r = t * V + row; return pi_out ? pi_out[r] : r; });
 }
 

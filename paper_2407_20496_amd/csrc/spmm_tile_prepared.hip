@@ -48,8 +48,7 @@ struct TileCfg {
   static constexpr int STAGES_BYTES = ST * (B_BYTES + A_BYTES);
   static constexpr int B_PER_WAVE = (NB == 512 ? KS : KS / 2) / NW;  // wave-wide copies for B per wave and stage
   static constexpr int ROWS_PER_WAVE = KS / NW;
-  static constexpr int Y_STRIDE = NB * 2 + 16;
-  static constexpr int EPI_BYTES = 32 * RB * Y_STRIDE;
+  static constexpr int EPI_BYTES = 32 * RB * kStageStride<NB>;
   static constexpr int LDS_BYTES = (STAGES_BYTES > EPI_BYTES) ? STAGES_BYTES : EPI_BYTES;
   static_assert(NB == 256 || NB == 512, "column block");
   static_assert(WC == 64 || WC == 32, "columns per wave");
@@ -285,7 +284,7 @@ __global__ __launch_bounds__(NB / WC * 64) void spmm_tile_prepared_kernel(
   }
 
   // ---- epilogue -------------------------------------------------------------------------------------
-  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS, C::Y_STRIDE>(
+  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS>(
       acc, lds, Y, ldy, N, n0, relu, out_f32, [&](int row) -> int64_t { return out_rows[t * V + row]; });
 }
 

@@ -34,14 +34,13 @@ constexpr int kThreads = kWaves * 64;
 constexpr int kCB = 2;                  // 32-column blocks per wave
 constexpr int kKS = 32;                 // kept columns per step
 constexpr int kBStride = kNB * 2 + 64;  // bytes per gathered row in LDS (+64: rows 4 apart hit distinct banks)
-constexpr int kYStride = kNB * 2 + 16;  // bytes per staged output row
 constexpr int kAStride = kKS * 2 + 16;  // 80: 16 consecutive rows hit 16 distinct 16-byte bank groups
 constexpr int kBBytes = kKS * kBStride;
 
 __host__ __device__ constexpr int stage_bytes(int V) { return kBBytes + V * kAStride; }
 __host__ __device__ constexpr int total_lds_bytes(int V) {
   const int two = 2 * stage_bytes(V);
-  const int epi = V * kYStride;
+  const int epi = V * kStageStride<kNB>;
   return two > epi ? two : epi;
 }
 
@@ -202,7 +201,7 @@ __global__ __launch_bounds__(kThreads) void spmm_vectors_kernel(
   }
 
   // ---- epilogue -----------------------------------------------------------------------------------
-  store_tile_rows<DT, RB, kCB, kNB, 64, kThreads, kYStride>(acc, lds, Y, ldy, N, n0, relu, out_f32,
+  store_tile_rows<DT, RB, kCB, kNB, 64, kThreads>(acc, lds, Y, ldy, N, n0, relu, out_f32,
                                                             [&](int row) -> int64_t { const int r = t * V + row; return pi_out ? pi_out[r] : r; });
 }
 
@@ -231,8 +230,7 @@ struct DmaCfg {
   static constexpr int B_PER_WAVE = (NB == 512) ? ROWS_PER_WAVE : ROWS_PER_WAVE / 2;
   static constexpr int A_INSTR = V / 8;                      // wave-wide copies of 8 rows x 128 bytes
   static constexpr int A_ROUNDS = (A_INSTR + NW - 1) / NW;
-  static constexpr int Y_STRIDE = NB * 2 + 16;
-  static constexpr int EPI_BYTES = V * Y_STRIDE;
+  static constexpr int EPI_BYTES = V * kStageStride<NB>;
   static constexpr int LDS_BYTES = (2 * STAGE_BYTES > EPI_BYTES) ? 2 * STAGE_BYTES : EPI_BYTES;
   static_assert(NB == 256 || NB == 512, "column block");
   static_assert(WC == 64 || WC == 32, "columns per wave");
@@ -386,7 +384,7 @@ __global__ __launch_bounds__(NB / WC * 64) void spmm_vectors_dma_kernel(
   }
 
   // ---- epilogue -------------------------------------------------------------------------------------------
-  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS, C::Y_STRIDE>(acc, lds, Y, ldy, N, n0, relu, out_f32,
+  store_tile_rows<DT, RB, CBS, NB, WC, C::THREADS>(acc, lds, Y, ldy, N, n0, relu, out_f32,
                                                                   [&](int row) -> int64_t { const int r = t * V + row; return pi_out ? pi_out[r] : r; });
 }
 
