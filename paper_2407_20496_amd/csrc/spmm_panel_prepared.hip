@@ -197,8 +197,7 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_panel_prepared_kernel(
         if (n + 8 <= N) {
           __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
         } else if (n < N) {
-          const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-          for (int e = 0; e < N - n; ++e) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+          store_row_end(dst, v, N - n);
         }
       }
       __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");

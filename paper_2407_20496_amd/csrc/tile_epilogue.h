@@ -19,6 +19,10 @@ namespace hinm {
 template <int NB>
 constexpr int kStageStride = NB * 2 + 64;
 
+// v > 0 ? v : +0, and 0 for NaN: the median of v, 0 and infinity, one instruction (written as a comparison the compiler
+// takes two, one of them for signalling NaN).
+__device__ __forceinline__ float relu_f32(float v) { return __builtin_amdgcn_fmed3f(v, 0.f, __builtin_inff()); }
+
 // One 32x32 block of results into the staging area: `block` is the staged address of its first row and column.  A lane
 // holds one column, and writing its 16 values by themselves (ds_write_b16, 11 clocks each with every wave of a 128 x 512
 // workgroup writing) took 4 to 7 us of a workgroup's life, as much as four 64-row stages of the k loop.  Neighbouring
@@ -29,17 +33,29 @@ __device__ __forceinline__ void stage_block(const f32x16& acc, uint8_t* block, b
   const int lane = threadIdx.x & 63;
   const uint32_t pick = (lane & 1) ? 0x03020706u : 0x05040100u;  // halves of (neighbour, own) that make this lane's word
   uint8_t* const dst = block + (4 * (lane >> 5) + (lane & 1)) * STRIDE + (lane & 30) * 2;
-#pragma unroll
-  for (int e = 0; e < 16; e += 2) {
-    float v0 = acc[e], v1 = acc[e + 1];
-    if (relu) {
-      v0 = v0 > 0.f ? v0 : 0.f;
-      v1 = v1 > 0.f ? v1 : 0.f;
-    }
+  auto put = [&](int e, float v0, float v1) {
     const uint32_t own = floats_to_bits<DT>(v0, v1);
     const uint32_t neighbour = (uint32_t)__builtin_amdgcn_mov_dpp((int)own, 0xB1, 0xf, 0xf, true);  // lane ^ 1
     *reinterpret_cast<uint32_t*>(dst + (8 * (e >> 2) + (e & 3)) * STRIDE) = __builtin_amdgcn_perm(neighbour, own, pick);
+  };
+  if (relu) {
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) put(e, relu_f32(acc[e]), relu_f32(acc[e + 1]));
+  } else {
+#pragma unroll
+    for (int e = 0; e < 16; e += 2) put(e, acc[e], acc[e + 1]);
   }
+}
+
+// The first `left` (1 .. 7) of a lane's eight values to the end of a row, as one store each of four, two and one of them:
+// element by element, in a loop that picks halves of words, this took 8 us of a workgroup of 128 rows (512 x 1192, V = 128,
+// Kv = 592, N = 311 21.5 -> 12.9 us with 512-column blocks).
+__device__ __forceinline__ void store_row_end(uint16_t* dst, u32x4 v, int left) {
+  if (left & 4) *reinterpret_cast<u32x2*>(dst) = u32x2{v.x, v.y};
+  const uint32_t pair = (left & 4) ? v.z : v.x;
+  if (left & 2) *reinterpret_cast<uint32_t*>(dst + (left & 4)) = pair;
+  const uint32_t last = (left & 2) ? ((left & 4) ? v.w : v.y) : pair;
+  if (left & 1) dst[left & 6] = (uint16_t)last;
 }
 
 // Writes `rows` staged rows to Y, every row as one contiguous segment.  The rows' numbers are requested before the first
@@ -74,8 +90,7 @@ __device__ __forceinline__ void store_staged_rows(const uint8_t* lds, void* Y, i
       if (whole) {
         __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
       } else {
-        const uint32_t w[4] = {v.x, v.y, v.z, v.w};
-        for (int e = 0; e < N - n; ++e) dst[e] = (uint16_t)(w[e >> 1] >> (16 * (e & 1)));
+        store_row_end(dst, v, N - n);
       }
     }
   }
