@@ -452,7 +452,7 @@ hinm_status hinm_spmm_prepared_workspace(const hinm_shape* shape, int32_t N, siz
 
 // Which kernel family a prepared call runs on; everything that can make the call fail is decided here, on the
 // host, before anything is launched (hinm_chain validates every layer with it before its first launch).
-enum class PreparedRoute { Mid, Rows16, Skinny, Panel, Tile };
+enum class PreparedRoute { Mid, MidRing, Rows16, Skinny, Panel, Tile, TileRing };
 
 static PreparedArgs prepared_args(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                   void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes) {
@@ -465,8 +465,19 @@ static PreparedArgs prepared_args(const hinm_shape* shape, int32_t N, const void
 static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, bool with_mid = true) {
   const hinm_shape* shape = &a.s;
   const int32_t N = a.N;
+  if (a.tile_variant >= kRingFirstVariant && a.tile_variant <= kRingLastVariant) {
+    if (!spmm_ring_prepared_supported(a)) return HINM_ERR_UNSUPPORTED;
+    *route = PreparedRoute::TileRing;
+    return HINM_OK;
+  }
+  // From 65 columns on: the kernel with private rings wherever it can run, unless one of the kernels for fewer columns is
+  // estimated to take less.  Against the one for a moderate number of columns the estimate has to be 8 % ahead, about what
+  // both estimates miss by (3200 x 10424, V = 128, Kv = 2608, N = 628: 21.6 us there, 22.4 on rings, estimated 24.8 and 23.3),
+  // and up to five steps the two are within a tenth of each other (3008 x 560, Kv = 280, N = 273 5.4 and 5.9 us; 1312 x 1048,
+  // V = 32, Kv = 264, N = 681 5.4 and 5.3).
+  const bool ring = with_mid && a.tile_variant == 0 && N > 64 && spmm_ring_prepared_supported(a);
   if (with_mid && a.tile_variant == 0 && spmm_mid_prepared_preferred(a)) {
-    *route = PreparedRoute::Mid;
+    *route = ring && shape->Kv > 5 * 64 && spmm_ring_prepared_us(a, true) * 1.08 < spmm_mid_prepared_us(a) ? PreparedRoute::MidRing : PreparedRoute::Mid;
     return HINM_OK;
   }
   // What the kernel for a moderate number of columns leaves: one column, up to 64 columns (128 on the smallest layers) where it
@@ -495,7 +506,8 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     // 1024..2048 columns on layers of a few hundred rows)
     const bool x_beyond_l2 = (double)shape->K * N * 2 > 3.5e6;
     const double l2_factor = !x_beyond_l2 ? 1.0 : N > 1024 ? 2.0 : (N > 512 && blocks_per_wg < 4) ? 1.5 : 1.0;
-    few_columns = 2.5 + units * (0.14 * shape->Kv + 40.0) * 1e-6 * l2_factor * pair_factor < tile_floor_us;
+    few_columns = 2.5 + units * (0.14 * shape->Kv + 40.0) * 1e-6 * l2_factor * pair_factor <
+                  (ring ? spmm_ring_prepared_us(a, false) : tile_floor_us);
   }
   if (a.tile_variant == 11 || a.tile_variant == 19 || (a.tile_variant == 0 && few_columns)) {
     if ((N + 15) / 16 > 65535) return HINM_ERR_UNSUPPORTED;
@@ -509,7 +521,7 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     if (N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0 || a.tile_variant == 12) return HINM_ERR_UNSUPPORTED;
     const bool panel = (a.tile_variant == 15) || (a.tile_variant == 0 && spmm_panel_prepared_preferred(a));
     if (panel && !spmm_panel_prepared_supported(a)) return HINM_ERR_UNSUPPORTED;
-    *route = panel ? PreparedRoute::Panel : PreparedRoute::Tile;
+    *route = panel ? PreparedRoute::Panel : ring ? PreparedRoute::TileRing : PreparedRoute::Tile;
   }
   return HINM_OK;
 }
@@ -546,6 +558,8 @@ static hinm_status run_prepared(const hinm_shape* shape, int32_t N, const void* 
     case PreparedRoute::Skinny: e = launch_spmm_skinny_prepared(a, stream); break;
     case PreparedRoute::Panel: e = launch_spmm_panel_prepared(a, stream); break;
     case PreparedRoute::Tile: e = launch_spmm_tile_prepared(a, stream); break;
+    case PreparedRoute::MidRing:
+    case PreparedRoute::TileRing: e = launch_spmm_ring_prepared(a, route == PreparedRoute::MidRing, stream); break;
   }
   return e == hipSuccess ? HINM_OK : HINM_ERR_DEVICE;
 }

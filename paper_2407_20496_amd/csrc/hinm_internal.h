@@ -248,6 +248,12 @@ struct PreparedArgs {
 };
 
 hipError_t launch_spmm_tile_prepared(const PreparedArgs& a, hipStream_t stream);
+// many columns, waves with private rings of gathered rows (spmm_ring_prepared.hip)
+constexpr int kRingFirstVariant = 20, kRingLastVariant = 23;  // that pin one of its forms
+bool spmm_ring_prepared_supported(const PreparedArgs& a);
+// `mid`: in the place of the kernel for a moderate number of columns (under its name, the forms that split the steps)
+double spmm_ring_prepared_us(const PreparedArgs& a, bool mid);  // estimate for the form it would choose
+hipError_t launch_spmm_ring_prepared(const PreparedArgs& a, bool mid, hipStream_t stream);
 // measurement aid: part 1 = only the copy stream of the tile kernel chosen for the shape, part 2 = only its LDS
 // reads and MFMAs; stores nothing; hipErrorNotSupported for shapes outside the named workloads' configurations
 hipError_t launch_spmm_tile_prepared_part(const PreparedArgs& a, int part, hipStream_t stream);
@@ -269,6 +275,7 @@ int spmm_rows16_prepared_blocks_per_wg(const PreparedArgs& a);  // 16-column blo
 // Wave-private kernel for a moderate number of columns (spmm_mid.hip), from every layer form.  V % 32 == 0, N > 1,
 // ldx and ldy multiples of 8; `preferred` includes what it needs.
 bool spmm_mid_prepared_preferred(const PreparedArgs& a);
+double spmm_mid_prepared_us(const PreparedArgs& a);  // estimate, from 65 columns on
 hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream);
 bool spmm_mid_canonical_preferred(const SpmmArgs& a);
 hipError_t launch_spmm_mid_canonical(const SpmmArgs& a, hipStream_t stream);

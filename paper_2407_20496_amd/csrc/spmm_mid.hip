@@ -552,6 +552,13 @@ bool spmm_mid_prepared_preferred(const PreparedArgs& a) {
   return blocks <= line;
 }
 
+// Fitted to 300 random layers with 65 to 4000 columns (error 10 %).
+double spmm_mid_prepared_us(const PreparedArgs& a) {
+  const double steps = (a.s.Kv + 63) / 64;
+  const double units = (double)plain_blocks(a.s.M, a.s.V, a.N) / 256;  // rounds of blocks
+  return a.s.V % 64 == 0 ? 3.5 + 0.046 * steps + units * (0.175 * steps + 0.72) : 3.25 + 0.050 * steps + units * (0.162 * steps + 0.06);
+}
+
 hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
   const uint8_t* base = static_cast<const uint8_t*>(a.prepared);

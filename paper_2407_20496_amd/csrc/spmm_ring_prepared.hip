@@ -1,0 +1,620 @@
+// HiNM sparse GEMM with fused channel permutation, many columns, from the device-tuned layer form, waves with private rings
+// of gathered input rows (arXiv 2407.20496, Section 3.2 and Section 5.3; layout in prepared_layout.h).
+//
+// One workgroup computes one tile of V = 32 * RB output channels for NB = 64 * NWC columns.  Its waves are NWC groups of
+// 64 columns by NWK groups of steps (64 kept columns each, taken in turn).  A wave copies its own 64 columns of the rows its
+// steps name, eight 128-byte row segments to a direct-to-LDS copy, into a ring of R slots of 32 rows that no other wave
+// touches: what it multiplies needs no barrier and the copies behind it are never drained, one slot is refilled the moment
+// its fragments are in registers.  Only the stored values and the row numbers are shared: 9 KB a step (128-row tiles), three
+// slots, copied two stages ahead by all waves, one barrier a stage.
+//
+// Against whole stages behind a barrier (spmm_tile_prepared.hip: all copies of a 64-row stage requested at once, waited for
+// in full): 16384 x 16384 at 50 %, N = 8192 1366 -> 1180 us, 4096 x 11008 at 50 %, N = 2048 83.3 -> 54.3, 11008 x 4096,
+// N = 2048 81 -> 66, 4096 x 4096, V = 64, N = 1024 23.8 -> 18.5.  What bounds it: on large products the power limit.  With
+// all units busy the clock falls from 2.4 GHz to 1.5 .. 1.9 GHz; a 64-row step of 512 columns then takes 1850 clocks, 1024 of
+// them MFMA issue, 1170 the address unit (73 KB at 64 bytes a clock) and about 1000 LDS.  Rows that come from L1 instead
+// of L2 and memory shorten the step by a fifth and the product by a tenth; four waves of 128 columns, which read half as
+// many stored values from LDS, run at a 10 % higher clock and take as long.
+#include "hinm_internal.h"
+#include "mfma_types.h"
+#include "prepared_layout.h"
+#include "direct_lds.h"
+#include "tile_epilogue.h"
+
+#include <type_traits>
+
+namespace hinm {
+namespace {
+
+template <int RB, int NWC, int NWK, int R>
+struct RingCfg {
+  static constexpr int CBS = 2;                      // 32-column blocks of a wave
+  static constexpr int WC = 32 * CBS;                // columns of a wave
+  static constexpr int NB = NWC * WC;                // columns of a workgroup
+  static constexpr int NW = NWC * NWK;               // waves
+  static constexpr int THREADS = NW * 64;
+  static constexpr int ROW_BYTES = WC * 2;
+  static constexpr int COPIES = 32 * ROW_BYTES / 1024;  // wave-wide copies of a substep of 32 kept columns
+  static constexpr int SLOT = 32 * ROW_BYTES;        // ring slot: one substep
+  static constexpr int RING_BYTES = R * SLOT;
+  static constexpr int A_STEP = RB * kPrepBlockBytes;
+  static constexpr int A_STAGE = NWK * A_STEP;       // a stage: one step for every group, contiguous in the layer form
+  static constexpr int A_GRANULES = A_STAGE / 16;
+  static constexpr int A_INSTR = (A_GRANULES + 63) / 64;
+  static constexpr int A_SLOT = A_INSTR * 1024;
+  static constexpr int A_RING = 3;
+  static constexpr int E_SLOT = NWK * 256;           // row numbers of a stage
+  static constexpr int E_RING = 4;
+  static constexpr int SHARED_INSTR = A_INSTR + NWK; // wave-wide copies of a stage that all waves share
+  static constexpr int SHARED_ROUNDS = (SHARED_INSTR + NW - 1) / NW;
+  static constexpr int SHARED_MIN = SHARED_INSTR / NW;  // every wave issues at least that many
+  static constexpr int A_BASE = NW * RING_BYTES;
+  static constexpr int E_BASE = A_BASE + A_RING * A_SLOT;
+  static constexpr int LOOP_BYTES = E_BASE + E_RING * E_SLOT;
+  static constexpr int EPI_BYTES = 32 * RB * kStageStride<NB>;
+  static constexpr int OWN = (RB + NWK - 1) / NWK;   // most row blocks of the result that a wave finishes
+  static constexpr int SUM_BYTES = NWK == 1 ? 0 : NW * OWN * CBS * 4096;
+  static constexpr int LOOP_OR_EPI = LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES;
+  static constexpr int LDS_BYTES = LOOP_OR_EPI > SUM_BYTES ? LOOP_OR_EPI : SUM_BYTES;
+  // 256-column blocks run two side by side on the same tiles of a die: its 32 units then fetch 16 tiles and two column
+  // panels, not 32 tiles and one (4096 x 4096, V = 128, N = 2048 28.3 -> 25.2 us, 4096 x 11008 56.8 -> 55.2).  A panel of
+  // 512 columns is the larger part of what they fetch and stays alone (16384 x 16384, N = 8192 1200 against 1260).
+  static constexpr int BLOCKS_TOGETHER = NB == 256 ? 2 : 1;
+  static_assert(NWK == 1 || NWK == 2, "groups of steps");
+  static_assert(R == 3 || R == 4, "ring");
+  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+};
+
+__device__ __forceinline__ void buffer_copy16_to_lds(__amdgpu_buffer_rsrc_t r, uint32_t offset, uint8_t* lds_wave_base) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_wave_base, 16, (int)offset, 0, 0, 0);
+}
+__device__ __forceinline__ void buffer_copy4_to_lds(__amdgpu_buffer_rsrc_t r, uint32_t offset, uint8_t* lds_wave_base) {
+  __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_wave_base, 4, (int)offset, 0, 0, 0);
+}
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const void* p, uint32_t bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
+}
+
+template <int OFFSET>
+__device__ __forceinline__ void lds_read_b128(uint32_t addr, u32x4& r) {
+  asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(r) : "v"(addr), "n"(OFFSET));
+}
+template <int OFFSET>
+__device__ __forceinline__ void lds_read_tr16(uint32_t addr, uint64_t& r) {
+  asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=&v"(r) : "v"(addr), "n"(OFFSET));
+}
+template <int OFFSET>
+__device__ __forceinline__ void lds_read_b32(uint32_t addr, int& r) {
+  asm volatile("ds_read_b32 %0, %1 offset:%2" : "=&v"(r) : "v"(addr), "n"(OFFSET));
+}
+
+// No use of the register is moved before this point.
+template <class T>
+__device__ __forceinline__ void pin(T& r) {
+  asm volatile("" : "+v"(r));
+}
+
+typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
+
+template <int RB, int CBS>
+struct Fragments {
+  uint64_t part[CBS][4];  // of b, while the reads are in flight
+  u32x8 b[CBS];
+  u32x4 a[RB];
+  int idx[RB];
+};
+
+template <int I, int N, class F>
+__device__ __forceinline__ void unroll(F&& f) {
+  if constexpr (I < N) {
+    f(std::integral_constant<int, I>{});
+    unroll<I + 1, N>(f);
+  }
+}
+
+struct RingParams {
+  const uint8_t* prep_blocks;
+  const int32_t* gather;
+  const int32_t* out_rows;
+  const uint16_t* X;
+  void* Y;
+  int64_t ldy;
+  uint32_t x_bytes;  // what of X may be read, from its first element on
+  int row_bytes;     // of X
+  int T, S, N, n_blocks, work_per_xcd;
+  bool relu, out_f32;
+};
+
+template <int DT, int RB, int NWC, int NWK, int R>
+__device__ __forceinline__ void ring_product(const RingParams& p) {
+  using C = RingCfg<RB, NWC, NWK, R>;
+  constexpr int CBS = C::CBS;
+  constexpr int V = 32 * RB;
+  constexpr int NW = C::NW;
+  const int T = p.T, S = p.S, N = p.N, n_blocks = p.n_blocks, row_bytes = p.row_bytes;
+  const int32_t* const gather = p.gather;
+  const int32_t* const out_rows = p.out_rows;
+  void* const Y = p.Y;
+  const int64_t ldy = p.ldy;
+  const bool relu = p.relu, out_f32 = p.out_f32;
+  extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
+
+  // Consecutive workgroup ids go to different XCDs: every XCD has a contiguous run of the work list, in which the tiles of
+  // BLOCKS_TOGETHER column blocks follow each other.
+  const int xcd = blockIdx.x & 7;
+  const int slot_in_xcd = blockIdx.x >> 3;
+  const int work = xcd * p.work_per_xcd + slot_in_xcd;
+  if (slot_in_xcd >= p.work_per_xcd || work >= n_blocks * T) return;
+  const int group = work / (T * C::BLOCKS_TOGETHER), in_group = work % (T * C::BLOCKS_TOGETHER);
+  const int width = min(C::BLOCKS_TOGETHER, n_blocks - group * C::BLOCKS_TOGETHER);
+  const int t = in_group / width;
+  const int nb = group * C::BLOCKS_TOGETHER + in_group % width;
+
+  const int tid = threadIdx.x;
+  const int lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int wc = wave % NWC, g = wave / NWC;
+  const int n0 = nb * C::NB + wc * C::WC;  // first column of the wave
+  const int stages = (S + NWK - 1) / NWK;
+
+  const auto x_buf = make_buffer(p.X, p.x_bytes);
+  const auto a_buf = make_buffer(p.prep_blocks + (size_t)t * S * C::A_STEP, (uint32_t)S * C::A_STEP);
+  const auto e_buf = make_buffer(gather + (size_t)t * S * 64, (uint32_t)S * 256);
+
+  // ---- copies ----
+  // Copy j of a substep: lane class c = lane / 8 takes row 8 j + c.  Its 32-byte units are stored at unit ^ (row & 3)
+  // (applied to the source address, a direct copy writes LDS linearly): the four rows of a transposing read then fall on
+  // different banks.  Row numbers of padded kept columns are -1, which lies beyond the buffer's end: such lanes write
+  // zeros.  Lanes whose columns lie beyond N re-read the row's first ones; what they feed is never stored.
+  const int c = lane >> 3;
+  const int granule = (lane & 7) ^ ((c & 3) << 1);
+  const int lane_off = (n0 + granule * 8 < N) ? (n0 + granule * 8) * 2 : 0;
+  uint8_t* const ring = lds + wave * C::RING_BYTES;
+  auto issue_row_copy = [&](int row, int slot_off, int j) {
+    buffer_copy16_to_lds(x_buf, (uint32_t)(__mul24(row, row_bytes) + lane_off), ring + slot_off + j * 1024);
+  };
+  // Row numbers of a step in LDS: position e holds the row of lane class e / 8, substep (e / 4) % 2, copy e % 4, so that a
+  // lane reads those of a substep's copies with one 16-byte read.
+  const uint32_t e_src = (uint32_t)(((lane >> 2) & 1) * 32 + 8 * (lane & 3) + (lane >> 3)) * 4;
+  uint32_t a_src[C::SHARED_ROUNDS];
+#pragma unroll
+  for (int m = 0; m < C::SHARED_ROUNDS; ++m) a_src[m] = (uint32_t)min((wave + m * NW) * 64 + lane, C::A_GRANULES - 1) * 16;
+  auto issue_shared = [&](int a_stage, int a_slot, int e_stage) {  // stored values of a_stage, row numbers of e_stage
+#pragma unroll
+    for (int m = 0; m < C::SHARED_ROUNDS; ++m) {
+      const int i = wave + m * NW;
+      if (i < C::A_INSTR)
+        buffer_copy16_to_lds(a_buf, (uint32_t)a_stage * C::A_STAGE + a_src[m], lds + C::A_BASE + a_slot + i * 1024);
+      else if (i < C::SHARED_INSTR)
+        buffer_copy4_to_lds(e_buf, (uint32_t)(e_stage * NWK + (i - C::A_INSTR)) * 256 + e_src,
+                            lds + C::E_BASE + (e_stage & 3) * C::E_SLOT + (i - C::A_INSTR) * 256);
+    }
+  };
+
+  // ---- LDS reads ----
+  const int i32 = lane & 31, qh = lane >> 5, i16 = lane & 15;
+  const uint32_t lds_base = (uint32_t)(uintptr_t)(lds_void_t*)lds;
+  uint32_t b_lane[CBS];
+#pragma unroll
+  for (int cb = 0; cb < CBS; ++cb)
+    b_lane[cb] = lds_base + wave * C::RING_BYTES + (8 * qh + (i16 >> 2)) * C::ROW_BYTES +
+                 (((cb * 2 + (i32 >> 4)) ^ (i16 >> 2)) * 32) + (i16 & 3) * 8;
+  const uint32_t a_lane = lds_base + C::A_BASE + g * C::A_STEP + lane * 16;
+  const uint32_t i_lane = lds_base + C::A_BASE + g * C::A_STEP + kPrepIdxOffset + lane * 4;
+  const uint32_t e_lane = lds_base + C::E_BASE + g * 256 + c * 32;
+
+  Fragments<RB, CBS> f[2];
+  static_assert(C::COPIES == 4, "row numbers of a substep are one vector");
+  u32x4 e0, e1;  // row numbers of the copies to come, by substep
+  // LDS read U of the READS that make a substep's fragments: rows of X first, then the stored values, and at a step's first
+  // substep the nibbles of both
+  auto read_fragment = [&](Fragments<RB, CBS>& fr, int b_slot, int a_slot, auto u_tag, auto sub_tag) {
+    constexpr int U = decltype(u_tag)::value, SUB = decltype(sub_tag)::value;
+    if constexpr (U < 4 * CBS) {
+      constexpr int CB = U / 4, Q = U % 4;
+      lds_read_tr16<((Q >> 1) * 16 + (Q & 1) * 4) * C::ROW_BYTES>(b_lane[CB] + b_slot, fr.part[CB][Q]);
+    } else if constexpr (U < 4 * CBS + RB) {
+      constexpr int I = U - 4 * CBS;
+      lds_read_b128<I * kPrepBlockBytes + SUB * 1024>(a_lane + a_slot, fr.a[I]);
+    } else {
+      constexpr int I = U - 4 * CBS - RB;
+      lds_read_b32<I * kPrepBlockBytes>(i_lane + a_slot, fr.idx[I]);
+    }
+  };
+  auto reads_of = [](int sub) constexpr { return 4 * CBS + RB + (sub == 0 ? RB : 0); };
+  auto tie = [&](Fragments<RB, CBS>& fr, auto sub_tag) {
+    asm volatile("s_waitcnt lgkmcnt(0)" ::);
+    unroll<0, CBS>([&](auto cbt) {
+      constexpr int cb = decltype(cbt)::value;
+      unroll<0, 4>([&](auto q) { pin(fr.part[cb][decltype(q)::value]); });
+    });
+    unroll<0, CBS>([&](auto cbt) {
+      constexpr int cb = decltype(cbt)::value;
+      fr.b[cb] = __builtin_bit_cast(u32x8, u64x4{fr.part[cb][0], fr.part[cb][1], fr.part[cb][2], fr.part[cb][3]});
+      pin(fr.b[cb]);
+    });
+    unroll<0, RB>([&](auto rbt) {
+      constexpr int rb = decltype(rbt)::value;
+      pin(fr.a[rb]);
+      if constexpr (decltype(sub_tag)::value == 0) pin(fr.idx[rb]);
+    });
+  };
+
+  f32x16 acc[RB][CBS];
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb)
+#pragma unroll
+    for (int cb = 0; cb < CBS; ++cb)
+#pragma unroll
+      for (int e = 0; e < 16; ++e) acc[rb][cb][e] = 0.f;
+
+  auto mfma = [&](const Fragments<RB, CBS>& fr, auto m_tag, auto sub_tag) {
+    constexpr int RBI = decltype(m_tag)::value / CBS, CB = decltype(m_tag)::value % CBS;
+    acc[RBI][CB] = smfmac_32x32x32<DT, decltype(sub_tag)::value>(fr.a[RBI], fr.b[CB], acc[RBI][CB], fr.idx[RBI]);
+  };
+
+  // ---- pipeline ----
+  constexpr int NM = RB * CBS;             // MFMAs of a substep
+  constexpr int W = NM >= 8 ? NM / 8 : 1;  // of these, before the wait for the next substep's rows
+  constexpr int BEFORE = (W * C::COPIES + NM - 1) / NM;  // copies issued before that wait: copy j precedes MFMA j NM / COPIES
+  // first two stages' row numbers straight into registers
+  int first_rows[2][2][C::COPIES];
+#pragma unroll
+  for (int st = 0; st < 2; ++st)
+#pragma unroll
+    for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+      for (int j = 0; j < C::COPIES; ++j) {
+        const int step = min(st * NWK + g, S - 1);
+        first_rows[st][sub][j] = gather[(size_t)t * S * 64 + step * 64 + sub * 32 + 8 * j + c];
+      }
+  issue_shared(0, 0, 2);
+#pragma unroll
+  for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[0][0][j], 0, j);
+  issue_shared(1, C::A_SLOT, 3);
+#pragma unroll
+  for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[0][1][j], C::SLOT, j);
+#pragma unroll
+  for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[1][0][j], 2 * C::SLOT, j);
+  if constexpr (R == 4) {
+#pragma unroll
+    for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[1][1][j], 3 * C::SLOT, j);
+  }
+  if constexpr (R == 3) {
+#pragma unroll
+    for (int j = 0; j < C::COPIES; ++j) e1[j] = (uint32_t)first_rows[1][1][j];
+  }
+  wait_copies_outstanding<(R - 1) * C::COPIES + C::SHARED_MIN>();
+  __builtin_amdgcn_s_barrier();
+  issue_shared(2, 2 * C::A_SLOT, 4);
+
+  int b_slot = 0, a_slot = 0;  // of the substep and stage about to be multiplied
+  auto next_b = [&](int s) { return s + C::SLOT == C::RING_BYTES ? 0 : s + C::SLOT; };
+  auto next_a = [&](int s) { return s + C::A_SLOT == C::A_RING * C::A_SLOT ? 0 : s + C::A_SLOT; };
+
+  u32x4 next_e0, next_e1;
+  auto read_rows = [&](int stage) {
+    const uint32_t at = e_lane + (stage & 3) * C::E_SLOT;
+    lds_read_b128<0>(at, next_e0);
+    lds_read_b128<16>(at, next_e1);
+  };
+  auto tie_rows = [&]() {
+    pin(next_e0);
+    pin(next_e1);
+  };
+
+  using I0 = std::integral_constant<int, 0>;
+  using I1 = std::integral_constant<int, 1>;
+  unroll<0, reads_of(0)>([&](auto u) { read_fragment(f[0], 0, 0, u, I0{}); });
+  read_rows(2);
+  tie(f[0], I0{});
+  tie_rows();
+  e0 = next_e0;
+  if constexpr (R == 4) e1 = next_e1;
+
+  // Substep SUB of stage s: the copies of the substep R ahead go into the slot just read, one by one between the MFMAs;
+  // once the next substep's rows have landed, the reads of its fragments are spread over the rest of them.
+  auto substep = [&](int s, auto sub_tag, auto issue_tag, auto shared_tag, auto wait_tag, auto read_tag, bool multiply) {
+    constexpr int SUB = decltype(sub_tag)::value;
+    constexpr bool ISSUE = decltype(issue_tag)::value;
+    constexpr bool SHARED = decltype(shared_tag)::value;
+    constexpr bool READ = decltype(read_tag)::value;
+    // R = 4: rows of stage s + 2, substep SUB; R = 3: substep 0 -> stage s + 1 substep 1, substep 1 -> stage s + 2 substep 0
+    const u32x4 rows = (R == 4) ? (SUB ? e1 : e0) : (SUB ? e0 : e1);
+    const int write_slot = b_slot;
+    b_slot = next_b(b_slot);
+    constexpr int NR = 4 * CBS + RB + (SUB == 1 ? RB : 0);
+    constexpr int PER = (NR + (NM > W + 3 ? NM - W - 2 : 1) - 1) / (NM > W + 3 ? NM - W - 2 : 1);
+    unroll<0, NM>([&](auto m) {
+      constexpr int M = decltype(m)::value;
+      if constexpr (READ && M == W) {
+        wait_copies_outstanding<decltype(wait_tag)::value>();
+        if constexpr (SUB == 1) {
+          __builtin_amdgcn_s_barrier();
+          if constexpr (SHARED) issue_shared(s + 3, a_slot, s + 5);
+          a_slot = next_a(a_slot);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+      }
+      if constexpr (ISSUE) {
+        unroll<0, C::COPIES>([&](auto j) {
+          if constexpr (decltype(j)::value * NM / C::COPIES == M)
+            issue_row_copy((int)rows[decltype(j)::value], write_slot, decltype(j)::value);
+        });
+      }
+      if constexpr (READ && M >= W) {
+        unroll<0, PER>([&](auto p) {
+          constexpr int U = (M - W) * PER + decltype(p)::value;
+          if constexpr (U < NR)
+            read_fragment(f[1 - SUB], b_slot, a_slot, std::integral_constant<int, U>{}, std::integral_constant<int, 1 - SUB>{});
+        });
+        if constexpr (SHARED && M == NM - 1) read_rows(s + 3);
+      }
+      if (multiply) mfma(f[SUB], m, sub_tag);
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    if constexpr (READ) {
+      tie(f[1 - SUB], std::integral_constant<int, 1 - SUB>{});
+      if constexpr (SUB == 0) unroll<0, RB>([&](auto rb) { f[1].idx[decltype(rb)::value] = f[0].idx[decltype(rb)::value]; });
+      if constexpr (SHARED) tie_rows();
+    }
+  };
+  using Yes = std::true_type;
+  using No = std::false_type;
+  // Copies that may be outstanding when the next substep's rows have to be there: those of the substeps behind it, those of
+  // this substep issued so far, and what the wave issued of the shared copies since (at least SHARED_MIN).
+  constexpr int BEHIND = (R - 2) * C::COPIES;
+  using WaitEven = std::integral_constant<int, BEHIND + BEFORE + C::SHARED_MIN>;
+  using WaitOdd = std::integral_constant<int, BEHIND + BEFORE + (R == 4 ? C::SHARED_MIN : 0)>;
+  int s = 0;
+  for (; s < stages - 2; ++s) {
+    substep(s, I0{}, Yes{}, No{}, WaitEven{}, Yes{}, true);
+    if constexpr (R == 3) e1 = next_e1;
+    substep(s, I1{}, Yes{}, Yes{}, WaitOdd{}, Yes{}, true);
+    e0 = next_e0;
+    if constexpr (R == 4) e1 = next_e1;
+  }
+  using WaitTail0 = std::integral_constant<int, BEHIND + (R == 3 ? BEFORE : 0) + C::SHARED_MIN>;
+  using WaitTail1 = std::integral_constant<int, C::COPIES + (R == 4 ? C::SHARED_MIN : 0)>;
+  const bool whole = (stages - 1) * NWK + g < S;  // an odd number of steps: the last group has none in the last stage
+  substep(s, I0{}, std::integral_constant<bool, R == 3>{}, No{}, WaitTail0{}, Yes{}, true);
+  substep(s, I1{}, No{}, No{}, WaitTail1{}, Yes{}, true);
+  substep(s + 1, I0{}, No{}, No{}, I0{}, Yes{}, whole);
+  substep(s + 1, I1{}, No{}, No{}, I0{}, No{}, whole);
+
+  // ---- epilogue ----
+  __builtin_amdgcn_s_barrier();  // every wave is done with the ring and the stored values
+  auto finish = [&](auto g_tag) {
+    constexpr int G = decltype(g_tag)::value;
+    if constexpr (NWK == 2) {
+      const int partner = wc + (1 - G) * NWC;
+      unroll<0, RB>([&](auto rbt) {
+        constexpr int rb = decltype(rbt)::value;
+        if constexpr (rb % 2 != G) {
+#pragma unroll
+          for (int cb = 0; cb < CBS; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              *reinterpret_cast<f32x4*>(lds + ((wave * C::OWN + rb / 2) * CBS + cb) * 4096 + q * 1024 + lane * 16) =
+                  f32x4{acc[rb][cb][4 * q], acc[rb][cb][4 * q + 1], acc[rb][cb][4 * q + 2], acc[rb][cb][4 * q + 3]};
+        }
+      });
+      __syncthreads();
+      unroll<0, RB>([&](auto rbt) {
+        constexpr int rb = decltype(rbt)::value;
+        if constexpr (rb % 2 == G) {
+#pragma unroll
+          for (int cb = 0; cb < CBS; ++cb)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+              const f32x4 v = *reinterpret_cast<const f32x4*>(lds + ((partner * C::OWN + rb / 2) * CBS + cb) * 4096 +
+                                                              q * 1024 + lane * 16);
+#pragma unroll
+              for (int e = 0; e < 4; ++e) acc[rb][cb][4 * q + e] += v[e];
+            }
+        }
+      });
+      __syncthreads();
+    }
+    unroll<0, RB>([&](auto rbt) {
+      constexpr int rb = decltype(rbt)::value;
+      if constexpr (NWK == 1 || rb % 2 == G) {
+        if (out_f32) {
+#pragma unroll
+          for (int e = 0; e < 16; ++e) {
+            const int row = 32 * rb + 8 * (e >> 2) + 4 * qh + (e & 3);
+            float* dst = static_cast<float*>(Y) + (int64_t)out_rows[t * V + row] * ldy;
+#pragma unroll
+            for (int cb = 0; cb < CBS; ++cb) {
+              float v = acc[rb][cb][e];
+              if (relu) v = v > 0.f ? v : 0.f;
+              const int n = n0 + cb * 32 + i32;
+              if (n < N) dst[n] = v;
+            }
+          }
+        } else {
+          unroll<0, CBS>([&](auto cbt) {
+            constexpr int cb = decltype(cbt)::value;
+            stage_block<DT, kStageStride<C::NB>>(acc[rb][cb], lds + 32 * rb * kStageStride<C::NB> + (wc * C::WC + cb * 32) * 2, relu);
+          });
+        }
+      }
+    });
+  };
+  if (NWK == 1 || g == 0) finish(I0{});
+  else finish(I1{});
+  if (out_f32) return;
+  __syncthreads();
+  store_staged_rows<V, C::NB, C::THREADS>(lds, Y, ldy, N, nb * C::NB, [&](int row) -> int64_t { return out_rows[t * V + row]; });
+}
+
+// The two names under which it runs: spmm_mid_kernel where it takes the place of that kernel's own blocks (spmm_mid.hip),
+// spmm_tile_prepared_kernel beyond, for any number of columns.  Two waves a SIMD are asked for where one would do, too: with
+// more than 256 registers at hand the compiler parks fragments in accumulation registers before their LDS reads have landed.
+template <int DT, int RB, int NWC, int NWK, int R>
+__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_mid_kernel(RingParams p) {
+  ring_product<DT, RB, NWC, NWK, R>(p);
+}
+template <int DT, int RB, int NWC, int NWK, int R>
+__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_tile_prepared_kernel(RingParams p) {
+  ring_product<DT, RB, NWC, NWK, R>(p);
+}
+
+// The four forms, by columns and groups of steps (variants 20 to 23), and what a launch of each takes by tile height (us):
+//   start + (rounds of workgroups before the last) * (round + steps * full) + steps * (part + fill * more)
+// where steps are those of a wave and `fill` is the share of the last round's slots that are taken: a step is slower the
+// more units take part (clock, memory).  Fitted to 480 random layers (M, K 256..16384, N 65..8192, all tile heights, both
+// types; error 5 to 15 %); the form chosen by it is 0.7 % off the best of the four on average.  Examples, us in the order
+// below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
+// 4096 x 4096, V = 128, N = 1024 29 / 20 / 20 / 18; 1984 x 6376, V = 64, Kv = 3184, N = 6033 92 / 82 / 77 / 109.
+struct RingForm {
+  int columns, groups, slots;  // slots: workgroups that run at once, by what their LDS leaves room for
+  float start, full, part, more, round;
+};
+constexpr int kRingForms = 4;
+constexpr RingForm kForms[4][kRingForms] = {  // [RB - 1]
+    {{512, 1, 256, 3.2f, 0.76f, 0.55f, 0.21f, 1.4f}, {256, 2, 256, 3.3f, 0.91f, 0.58f, 0.32f, 1.5f},
+     {256, 1, 512, 2.9f, 0.92f, 0.30f, 0.51f, 0.1f}, {128, 2, 512, 3.2f, 1.00f, 0.30f, 0.85f, 3.3f}},
+    {{512, 1, 256, 4.4f, 0.93f, 0.55f, 0.18f, 3.7f}, {256, 2, 256, 4.5f, 0.99f, 0.57f, 0.34f, 2.8f},
+     {256, 1, 512, 4.3f, 0.99f, 0.31f, 0.44f, 2.1f}, {128, 2, 256, 3.8f, 0.59f, 0.38f, 0.20f, 2.3f}},
+    {{512, 1, 256, 5.8f, 0.99f, 0.56f, 0.25f, 6.3f}, {256, 2, 256, 5.2f, 1.15f, 0.63f, 0.38f, 3.9f},
+     {256, 1, 256, 5.0f, 0.55f, 0.38f, 0.10f, 3.6f}, {128, 2, 256, 4.4f, 0.75f, 0.50f, 0.27f, 3.0f}},
+    {{512, 1, 256, 6.4f, 1.04f, 0.66f, 0.43f, 10.8f}, {256, 2, 256, 5.8f, 1.24f, 0.74f, 0.42f, 6.3f},
+     {256, 1, 256, 5.9f, 0.62f, 0.43f, 0.16f, 5.4f}, {128, 2, 256, 4.9f, 0.81f, 0.56f, 0.30f, 4.4f}}};
+
+double form_us(const RingForm& f, int S, int tiles, int N) {
+  const int64_t work = (int64_t)tiles * ((N + f.columns - 1) / f.columns);
+  const int64_t whole = (work - 1) / f.slots, last = work - whole * f.slots;
+  const double steps = (S + f.groups - 1) / f.groups;
+  return f.start + whole * (f.round + steps * f.full) + steps * (f.part + f.more * last / f.slots);
+}
+
+int best_form(const PreparedArgs& a, bool mid, int tiles, double* us) {
+  const PreparedLayout L = prepared_layout(a.s);
+  int best = -1;
+  for (int i = 0; i < kRingForms; ++i) {
+    if (mid && kForms[L.RB - 1][i].groups == 1) continue;  // fewer columns: the forms that split the steps
+    const double t = form_us(kForms[L.RB - 1][i], L.S, tiles, a.N);
+    if (best < 0 || t < *us) *us = t, best = i;
+  }
+  return best;
+}
+
+template <bool MID, int DT, int RB, int NWC, int NWK, int R>
+constexpr auto ring_kernel() {
+  if constexpr (MID) return spmm_mid_kernel<DT, RB, NWC, NWK, R>;
+  else return spmm_tile_prepared_kernel<DT, RB, NWC, NWK, R>;
+}
+
+// The tiles [first, first + count) of the layer.
+template <bool MID, int DT, int RB, int NWC, int NWK, int R>
+hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int count) {
+  using C = RingCfg<RB, NWC, NWK, R>;
+  const PreparedLayout L = prepared_layout(a.s);
+  const int n_blocks = (a.N + C::NB - 1) / C::NB;
+  const int work_per_xcd = (int)(((int64_t)n_blocks * count + 7) / 8);
+  constexpr auto kernel = ring_kernel<MID, DT, RB, NWC, NWK, R>();
+  if (a.plan) {
+    plan_record(a.plan, "%s<DT=%d,RB=%d,NB=%d,NWK=%d,R=%d> private rings, tiles=%d..%d grid=%d block=%d lds=%d",
+                MID ? "spmm_mid_kernel" : "spmm_tile_prepared_kernel", DT, RB, C::NB, NWK, R, first, first + count - 1, work_per_xcd * 8,
+                C::THREADS, C::LDS_BYTES);
+    return hipSuccess;
+  }
+  if (hipError_t e = raise_lds_limit<kernel>(C::LDS_BYTES); e != hipSuccess) return e;
+  const uint8_t* base = static_cast<const uint8_t*>(a.prepared);
+  const int64_t row_bytes = a.ldx * 2;
+  RingParams p;
+  p.prep_blocks = base + L.a_offset + (size_t)first * L.S * C::A_STEP;
+  p.gather = reinterpret_cast<const int32_t*>(base + L.gather_offset) + (size_t)first * L.S * 64;
+  p.out_rows = reinterpret_cast<const int32_t*>(base + L.pi_out_offset) + (size_t)first * a.s.V;
+  p.X = static_cast<const uint16_t*>(a.X);
+  p.Y = a.Y;
+  p.ldy = a.ldy;
+  p.x_bytes = (uint32_t)((a.s.K - 1) * row_bytes + (int64_t)(a.N + 7) / 8 * 16);
+  p.row_bytes = (int)row_bytes;  // checked by spmm_ring_prepared_supported
+  p.T = count;
+  p.S = L.S;
+  p.N = a.N;
+  p.n_blocks = n_blocks;
+  p.work_per_xcd = work_per_xcd;
+  p.relu = a.relu;
+  p.out_f32 = a.out_f32;
+  kernel<<<dim3((unsigned)(work_per_xcd * 8)), C::THREADS, C::LDS_BYTES, stream>>>(p);
+  return hipGetLastError();
+}
+
+template <bool MID, int DT, int RB>
+hipError_t launch_tiles(const PreparedArgs& a, hipStream_t stream, int form, int first, int count) {
+  switch (form) {
+    case 0:
+      if constexpr (!MID) return launch_form<false, DT, RB, 8, 1, 4>(a, stream, first, count);
+      break;
+    case 1: return launch_form<MID, DT, RB, 4, 2, RB <= 2 ? 4 : 3>(a, stream, first, count);
+    case 2:
+      if constexpr (!MID) return launch_form<false, DT, RB, 4, 1, 4>(a, stream, first, count);
+      break;
+    case 3: return launch_form<MID, DT, RB, 2, 2, RB <= 2 ? 4 : 3>(a, stream, first, count);
+    default: break;
+  }
+  return hipErrorInvalidValue;
+}
+
+template <int DT, int RB>
+hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
+  const PreparedLayout L = prepared_layout(a.s);
+  if (a.tile_variant) return launch_tiles<false, DT, RB>(a, stream, a.tile_variant - kRingFirstVariant, 0, L.T);
+  double us = 0;
+  const int form = best_form(a, mid, L.T, &us);
+  if (mid) return launch_tiles<true, DT, RB>(a, stream, form, 0, L.T);
+  // Whole rounds of 512-column blocks, and the tiles that are left over in the form that suits them, behind them
+  // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 66 -> 62 us).
+  const int wide = (a.N + 511) / 512;
+  const int64_t rounds = (int64_t)L.T * wide / 256;
+  const int whole = (int)(rounds * 256 / wide);
+  if (rounds > 0 && whole < L.T) {
+    double rest_us = 0;
+    const int rest_form = best_form(a, false, L.T - whole, &rest_us);
+    if (form_us(kForms[RB - 1][0], L.S, whole, a.N) + rest_us < us) {
+      const hipError_t e = launch_tiles<false, DT, RB>(a, stream, 0, 0, whole);
+      return e != hipSuccess ? e : launch_tiles<false, DT, RB>(a, stream, rest_form, whole, L.T - whole);
+    }
+  }
+  return launch_tiles<false, DT, RB>(a, stream, form, 0, L.T);
+}
+
+}  // namespace
+
+// Two stages at least, and what the copies' 32-bit byte offsets and 24-bit products can address.
+bool spmm_ring_prepared_supported(const PreparedArgs& a) {
+  if (a.N <= 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
+  const PreparedLayout L = prepared_layout(a.s);
+  const uint64_t row = (uint64_t)a.ldx * 2;
+  return L.S >= 3 && a.s.K < (1 << 23) && row < (1u << 23) && ((uint64_t)a.s.K + 1) * row <= (uint64_t{1} << 32) &&
+         (int64_t)L.T * ((a.N + 127) / 128) < (1 << 30);
+}
+
+double spmm_ring_prepared_us(const PreparedArgs& a, bool mid) {
+  double us = 0;
+  best_form(a, mid, a.s.M / a.s.V, &us);
+  return us;
+}
+
+hipError_t launch_spmm_ring_prepared(const PreparedArgs& a, bool mid, hipStream_t stream) {
+  const int RB = a.s.V / 32;
+#define HINM_RB(DT)                                    \
+  switch (RB) {                                        \
+    case 1: return launch_rb<DT, 1>(a, mid, stream);   \
+    case 2: return launch_rb<DT, 2>(a, mid, stream);   \
+    case 3: return launch_rb<DT, 3>(a, mid, stream);   \
+    case 4: return launch_rb<DT, 4>(a, mid, stream);   \
+  }
+  if (a.s.dtype == HINM_F16) {
+    HINM_RB(HINM_F16)
+  } else {
+    HINM_RB(HINM_BF16)
+  }
+#undef HINM_RB
+  return hipErrorInvalidValue;
+}
+
+}  // namespace hinm
