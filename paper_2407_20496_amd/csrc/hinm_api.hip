@@ -323,9 +323,13 @@ hinm_status hinm_spmm_vectors(const hinm_shape* shape, int32_t N, const void* va
   const VectorsArgs a{*shape, N, vals_v, vec_idx, pi_in, pi_out, X, ldx, Y, ldy,
                       (flags & HINM_EPI_RELU) != 0, (flags & HINM_OUT_F32) != 0, variant};
   hipError_t e;
-  if (variant && !spmm_vectors_mfma_supported(a)) return HINM_ERR_UNSUPPORTED;  // a pinned kernel must fit the shape
+  const bool rings = variant >= kRingFirstVariant && variant <= kRingLastVariant;
+  // a pinned kernel must fit the shape
+  if (variant && !(rings ? spmm_ring_vectors_supported(a) : spmm_vectors_mfma_supported(a))) return HINM_ERR_UNSUPPORTED;
   if (!(flags & HINM_KERNEL_REFERENCE) && !variant && N == 1)
     e = launch_spmm_vectors_gemv(a, static_cast<hipStream_t>(stream));
+  else if (rings || (!(flags & HINM_KERNEL_REFERENCE) && !variant && spmm_ring_vectors_preferred(a)))
+    e = launch_spmm_ring_vectors(a, static_cast<hipStream_t>(stream));
   else if (!(flags & HINM_KERNEL_REFERENCE) && !variant && spmm_mid_vectors_preferred(a))
     e = launch_spmm_mid_vectors(a, static_cast<hipStream_t>(stream));
   else if (!(flags & HINM_KERNEL_REFERENCE) && spmm_vectors_mfma_supported(a))
@@ -618,7 +622,7 @@ hinm_status hinm_calib_mid_plan(const hinm_shape* shape, int32_t N, int32_t form
     if (spmm_mid_canonical_preferred(a)) e = launch_spmm_mid_canonical(a, nullptr);
   } else {
     VectorsArgs a{*shape, N, nullptr, nullptr, nullptr, nullptr, nullptr, ld, nullptr, ld, false, false, 0, &plan};
-    if (spmm_mid_vectors_preferred(a)) e = launch_spmm_mid_vectors(a, nullptr);
+    if (spmm_mid_vectors_preferred(a) && !spmm_ring_vectors_preferred(a)) e = launch_spmm_mid_vectors(a, nullptr);
   }
   return e == hipSuccess ? HINM_OK : HINM_ERR_DEVICE;
 }

@@ -248,12 +248,16 @@ struct PreparedArgs {
 };
 
 hipError_t launch_spmm_tile_prepared(const PreparedArgs& a, hipStream_t stream);
-// many columns, waves with private rings of gathered rows (spmm_ring_prepared.hip)
+// many columns, waves with private rings of gathered rows (spmm_rings.hip)
 constexpr int kRingFirstVariant = 20, kRingLastVariant = 23;  // that pin one of its forms
 bool spmm_ring_prepared_supported(const PreparedArgs& a);
 // `mid`: in the place of the kernel for a moderate number of columns (under its name, the forms that split the steps)
 double spmm_ring_prepared_us(const PreparedArgs& a, bool mid);  // estimate for the form it would choose
 hipError_t launch_spmm_ring_prepared(const PreparedArgs& a, bool mid, hipStream_t stream);
+// ... and for a layer before its 2:4 step
+bool spmm_ring_vectors_supported(const VectorsArgs& a);
+bool spmm_ring_vectors_preferred(const VectorsArgs& a);
+hipError_t launch_spmm_ring_vectors(const VectorsArgs& a, hipStream_t stream);
 // measurement aid: part 1 = only the copy stream of the tile kernel chosen for the shape, part 2 = only its LDS
 // reads and MFMAs; stores nothing; hipErrorNotSupported for shapes outside the named workloads' configurations
 hipError_t launch_spmm_tile_prepared_part(const PreparedArgs& a, int part, hipStream_t stream);
@@ -280,6 +284,7 @@ hipError_t launch_spmm_mid_prepared(const PreparedArgs& a, hipStream_t stream);
 bool spmm_mid_canonical_preferred(const SpmmArgs& a);
 hipError_t launch_spmm_mid_canonical(const SpmmArgs& a, hipStream_t stream);
 bool spmm_mid_vectors_preferred(const VectorsArgs& a);
+double spmm_mid_vectors_us(const VectorsArgs& a);  // estimate, from 65 columns on
 hipError_t launch_spmm_mid_vectors(const VectorsArgs& a, hipStream_t stream);
 
 }  // namespace hinm

@@ -26,8 +26,12 @@
 namespace hinm {
 namespace {
 
-template <int RB, int NWC, int NWK, int R>
+// Where the stored values and row numbers come from: the device-tuned form, or the arrays of a layer before its 2:4 step.
+enum RingSource { kRingPrepared = 0, kRingVectors = 1 };
+
+template <int SRC, int RB, int NWC, int NWK, int R>
 struct RingCfg {
+  static constexpr bool SPARSE = SRC == kRingPrepared;
   static constexpr int CBS = 2;                      // 32-column blocks of a wave
   static constexpr int WC = 32 * CBS;                // columns of a wave
   static constexpr int NB = NWC * WC;                // columns of a workgroup
@@ -37,7 +41,7 @@ struct RingCfg {
   static constexpr int COPIES = 32 * ROW_BYTES / 1024;  // wave-wide copies of a substep of 32 kept columns
   static constexpr int SLOT = 32 * ROW_BYTES;        // ring slot: one substep
   static constexpr int RING_BYTES = R * SLOT;
-  static constexpr int A_STEP = RB * kPrepBlockBytes;
+  static constexpr int A_STEP = SPARSE ? RB * kPrepBlockBytes : RB * 4096;  // before 2:4: 32 RB rows of 64 values
   static constexpr int A_STAGE = NWK * A_STEP;       // a stage: one step for every group, contiguous in the layer form
   static constexpr int A_GRANULES = A_STAGE / 16;
   static constexpr int A_INSTR = (A_GRANULES + 63) / 64;
@@ -45,12 +49,14 @@ struct RingCfg {
   static constexpr int A_RING = 3;
   static constexpr int E_SLOT = NWK * 256;           // row numbers of a stage
   static constexpr int E_RING = 4;
-  static constexpr int SHARED_INSTR = A_INSTR + NWK; // wave-wide copies of a stage that all waves share
+  // wave-wide copies of a stage that all waves share (before 2:4 the row numbers are one wave's business)
+  static constexpr int SHARED_INSTR = A_INSTR + (SPARSE ? NWK : 0);
   static constexpr int SHARED_ROUNDS = (SHARED_INSTR + NW - 1) / NW;
   static constexpr int SHARED_MIN = SHARED_INSTR / NW;  // every wave issues at least that many
   static constexpr int A_BASE = NW * RING_BYTES;
   static constexpr int E_BASE = A_BASE + A_RING * A_SLOT;
-  static constexpr int LOOP_BYTES = E_BASE + E_RING * E_SLOT;
+  static constexpr int V_BASE = E_BASE + E_RING * E_SLOT;  // before 2:4: vector indexes on their way to row numbers
+  static constexpr int LOOP_BYTES = V_BASE + (SPARSE ? 0 : 4 * E_SLOT);
   static constexpr int EPI_BYTES = 32 * RB * kStageStride<NB>;
   static constexpr int OWN = (RB + NWK - 1) / NWK;   // most row blocks of the result that a wave finishes
   static constexpr int SUM_BYTES = NWK == 1 ? 0 : NW * OWN * CBS * 4096;
@@ -88,6 +94,10 @@ __device__ __forceinline__ void lds_read_b32(uint32_t addr, int& r) {
   asm volatile("ds_read_b32 %0, %1 offset:%2" : "=&v"(r) : "v"(addr), "n"(OFFSET));
 }
 
+__device__ __forceinline__ void lds_write_b32(uint32_t addr, int v) {
+  asm volatile("ds_write_b32 %0, %1" ::"v"(addr), "v"(v));
+}
+
 // No use of the register is moved before this point.
 template <class T>
 __device__ __forceinline__ void pin(T& r) {
@@ -96,11 +106,11 @@ __device__ __forceinline__ void pin(T& r) {
 
 typedef uint64_t u64x4 __attribute__((ext_vector_type(4)));
 
-template <int RB, int CBS>
+template <int RB, int CBS, bool SPARSE>
 struct Fragments {
   uint64_t part[CBS][4];  // of b, while the reads are in flight
   u32x8 b[CBS];
-  u32x4 a[RB];
+  u32x4 a[SPARSE ? RB : 2 * RB];  // before 2:4: both halves of 16 kept columns
   int idx[RB];
 };
 
@@ -113,21 +123,24 @@ __device__ __forceinline__ void unroll(F&& f) {
 }
 
 struct RingParams {
-  const uint8_t* prep_blocks;
-  const int32_t* gather;
-  const int32_t* out_rows;
+  const uint8_t* values;    // prepared blocks, or the stored values before 2:4
+  const int32_t* gather;    // row numbers, or the vector index
+  const int32_t* pi_in;     // before 2:4 (or NULL)
+  const int32_t* out_rows;  // before 2:4 possibly NULL
   const uint16_t* X;
   void* Y;
   int64_t ldy;
   uint32_t x_bytes;  // what of X may be read, from its first element on
   int row_bytes;     // of X
   int T, S, N, n_blocks, work_per_xcd;
+  int K, Kv;
   bool relu, out_f32;
 };
 
-template <int DT, int RB, int NWC, int NWK, int R>
+template <int SRC, int DT, int RB, int NWC, int NWK, int R>
 __device__ __forceinline__ void ring_product(const RingParams& p) {
-  using C = RingCfg<RB, NWC, NWK, R>;
+  using C = RingCfg<SRC, RB, NWC, NWK, R>;
+  constexpr bool SPARSE = C::SPARSE;
   constexpr int CBS = C::CBS;
   constexpr int V = 32 * RB;
   constexpr int NW = C::NW;
@@ -158,8 +171,10 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   const int stages = (S + NWK - 1) / NWK;
 
   const auto x_buf = make_buffer(p.X, p.x_bytes);
-  const auto a_buf = make_buffer(p.prep_blocks + (size_t)t * S * C::A_STEP, (uint32_t)S * C::A_STEP);
-  const auto e_buf = make_buffer(gather + (size_t)t * S * 64, (uint32_t)S * 256);
+  const int entries = SPARSE ? S * 64 : p.Kv;  // of the tile in `gather`
+  const uint32_t a_bytes = SPARSE ? (uint32_t)S * C::A_STEP : (uint32_t)V * p.Kv * 2;
+  const auto a_buf = make_buffer(p.values + (size_t)t * a_bytes, a_bytes);
+  const auto e_buf = make_buffer(gather + (size_t)t * entries, (uint32_t)entries * 4);
 
   // ---- copies ----
   // Copy j of a substep: lane class c = lane / 8 takes row 8 j + c.  Its 32-byte units are stored at unit ^ (row & 3)
@@ -177,17 +192,44 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   // lane reads those of a substep's copies with one 16-byte read.
   const uint32_t e_src = (uint32_t)(((lane >> 2) & 1) * 32 + 8 * (lane & 3) + (lane >> 3)) * 4;
   uint32_t a_src[C::SHARED_ROUNDS];
+  int a_first[C::SHARED_ROUNDS];  // before 2:4: kept column of the stage that a lane's 16 bytes begin at
 #pragma unroll
-  for (int m = 0; m < C::SHARED_ROUNDS; ++m) a_src[m] = (uint32_t)min((wave + m * NW) * 64 + lane, C::A_GRANULES - 1) * 16;
+  for (int m = 0; m < C::SHARED_ROUNDS; ++m) {
+    const int i = wave + m * NW;
+    if constexpr (SPARSE) {
+      a_src[m] = (uint32_t)min(i * 64 + lane, C::A_GRANULES - 1) * 16;
+    } else {
+      // eight rows of a step at a time, 128 bytes each, 16-byte piece x of row r at position x ^ (r / 2) % 8: the reads of
+      // 32 consecutive rows fall on different banks
+      const int row = i % (4 * RB) * 8 + (lane >> 3), piece = (lane & 7) ^ ((row >> 1) & 7);
+      a_first[m] = i / (4 * RB) * 64 + piece * 8;
+      a_src[m] = (uint32_t)(row * p.Kv + a_first[m]) * 2;
+    }
+  }
+  // Before 2:4 the first wave of every group turns its vector indexes into row numbers: it copies those of the stage three
+  // ahead of e_stage, has those of e_stage in a register by now (`index`) and gathers their input channels into LDS.
+  const auto pi_buf = make_buffer(p.pi_in, (uint32_t)p.K * 4);
+  const bool translates = !SPARSE && wc == 0;
+  int index = 0;
   auto issue_shared = [&](int a_stage, int a_slot, int e_stage) {  // stored values of a_stage, row numbers of e_stage
 #pragma unroll
     for (int m = 0; m < C::SHARED_ROUNDS; ++m) {
       const int i = wave + m * NW;
-      if (i < C::A_INSTR)
-        buffer_copy16_to_lds(a_buf, (uint32_t)a_stage * C::A_STAGE + a_src[m], lds + C::A_BASE + a_slot + i * 1024);
-      else if (i < C::SHARED_INSTR)
+      if (i < C::A_INSTR) {
+        uint32_t off = (uint32_t)a_stage * (SPARSE ? C::A_STAGE : NWK * 128) + a_src[m];
+        if (!SPARSE && a_first[m] + a_stage * NWK * 64 >= p.Kv) off = 0xFFFFFFF0u;  // beyond the row: zeros
+        buffer_copy16_to_lds(a_buf, off, lds + C::A_BASE + a_slot + i * 1024);
+      } else if (i < C::SHARED_INSTR) {
         buffer_copy4_to_lds(e_buf, (uint32_t)(e_stage * NWK + (i - C::A_INSTR)) * 256 + e_src,
                             lds + C::E_BASE + (e_stage & 3) * C::E_SLOT + (i - C::A_INSTR) * 256);
+      }
+    }
+    if (translates) {
+      buffer_copy4_to_lds(e_buf, (uint32_t)((e_stage + 3) * NWK + g) * 256 + e_src,
+                          lds + C::V_BASE + ((e_stage + 3) & 3) * C::E_SLOT + g * 256);
+      uint8_t* const at = lds + C::E_BASE + (e_stage & 3) * C::E_SLOT + g * 256;
+      if (p.pi_in) buffer_copy4_to_lds(pi_buf, (uint32_t)index * 4, at);
+      else lds_write_b32((uint32_t)(uintptr_t)(lds_void_t*)at + lane * 4, index);
     }
   };
 
@@ -199,30 +241,42 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   for (int cb = 0; cb < CBS; ++cb)
     b_lane[cb] = lds_base + wave * C::RING_BYTES + (8 * qh + (i16 >> 2)) * C::ROW_BYTES +
                  (((cb * 2 + (i32 >> 4)) ^ (i16 >> 2)) * 32) + (i16 & 3) * 8;
-  const uint32_t a_lane = lds_base + C::A_BASE + g * C::A_STEP + lane * 16;
+  uint32_t a_lane[SPARSE ? 1 : 4];  // before 2:4: by substep and half
+  if constexpr (SPARSE) {
+    a_lane[0] = lds_base + C::A_BASE + g * C::A_STEP + lane * 16;
+  } else {
+    unroll<0, 4>([&](auto q) {
+      a_lane[decltype(q)::value] =
+          lds_base + C::A_BASE + g * C::A_STEP + i32 * 128 + ((decltype(q)::value * 2 + qh) ^ ((i32 >> 1) & 7)) * 16;
+    });
+  }
   const uint32_t i_lane = lds_base + C::A_BASE + g * C::A_STEP + kPrepIdxOffset + lane * 4;
   const uint32_t e_lane = lds_base + C::E_BASE + g * 256 + c * 32;
+  const uint32_t v_lane = lds_base + C::V_BASE + g * 256 + lane * 4;
 
-  Fragments<RB, CBS> f[2];
+  Fragments<RB, CBS, SPARSE> f[2];
   static_assert(C::COPIES == 4, "row numbers of a substep are one vector");
   u32x4 e0, e1;  // row numbers of the copies to come, by substep
   // LDS read U of the READS that make a substep's fragments: rows of X first, then the stored values, and at a step's first
   // substep the nibbles of both
-  auto read_fragment = [&](Fragments<RB, CBS>& fr, int b_slot, int a_slot, auto u_tag, auto sub_tag) {
+  auto read_fragment = [&](Fragments<RB, CBS, SPARSE>& fr, int b_slot, int a_slot, auto u_tag, auto sub_tag) {
     constexpr int U = decltype(u_tag)::value, SUB = decltype(sub_tag)::value;
     if constexpr (U < 4 * CBS) {
       constexpr int CB = U / 4, Q = U % 4;
       lds_read_tr16<((Q >> 1) * 16 + (Q & 1) * 4) * C::ROW_BYTES>(b_lane[CB] + b_slot, fr.part[CB][Q]);
+    } else if constexpr (!SPARSE) {
+      constexpr int I = U - 4 * CBS;
+      lds_read_b128<I % RB * 4096>(a_lane[SUB * 2 + I / RB] + a_slot, fr.a[I]);
     } else if constexpr (U < 4 * CBS + RB) {
       constexpr int I = U - 4 * CBS;
-      lds_read_b128<I * kPrepBlockBytes + SUB * 1024>(a_lane + a_slot, fr.a[I]);
+      lds_read_b128<I * kPrepBlockBytes + SUB * 1024>(a_lane[0] + a_slot, fr.a[I]);
     } else {
       constexpr int I = U - 4 * CBS - RB;
       lds_read_b32<I * kPrepBlockBytes>(i_lane + a_slot, fr.idx[I]);
     }
   };
-  auto reads_of = [](int sub) constexpr { return 4 * CBS + RB + (sub == 0 ? RB : 0); };
-  auto tie = [&](Fragments<RB, CBS>& fr, auto sub_tag) {
+  auto reads_of = [](int sub) constexpr { return 4 * CBS + (SPARSE ? RB + (sub == 0 ? RB : 0) : 2 * RB); };
+  auto tie = [&](Fragments<RB, CBS, SPARSE>& fr, auto sub_tag) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::);
     unroll<0, CBS>([&](auto cbt) {
       constexpr int cb = decltype(cbt)::value;
@@ -233,11 +287,8 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
       fr.b[cb] = __builtin_bit_cast(u32x8, u64x4{fr.part[cb][0], fr.part[cb][1], fr.part[cb][2], fr.part[cb][3]});
       pin(fr.b[cb]);
     });
-    unroll<0, RB>([&](auto rbt) {
-      constexpr int rb = decltype(rbt)::value;
-      pin(fr.a[rb]);
-      if constexpr (decltype(sub_tag)::value == 0) pin(fr.idx[rb]);
-    });
+    unroll<0, SPARSE ? RB : 2 * RB>([&](auto i) { pin(fr.a[decltype(i)::value]); });
+    if constexpr (SPARSE && decltype(sub_tag)::value == 0) unroll<0, RB>([&](auto rb) { pin(fr.idx[decltype(rb)::value]); });
   };
 
   f32x16 acc[RB][CBS];
@@ -248,13 +299,19 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
 #pragma unroll
       for (int e = 0; e < 16; ++e) acc[rb][cb][e] = 0.f;
 
-  auto mfma = [&](const Fragments<RB, CBS>& fr, auto m_tag, auto sub_tag) {
-    constexpr int RBI = decltype(m_tag)::value / CBS, CB = decltype(m_tag)::value % CBS;
-    acc[RBI][CB] = smfmac_32x32x32<DT, decltype(sub_tag)::value>(fr.a[RBI], fr.b[CB], acc[RBI][CB], fr.idx[RBI]);
+  auto mfma = [&](const Fragments<RB, CBS, SPARSE>& fr, auto m_tag, auto sub_tag) {
+    constexpr int RBI = decltype(m_tag)::value / CBS % RB, CB = decltype(m_tag)::value % CBS;
+    if constexpr (SPARSE) {
+      acc[RBI][CB] = smfmac_32x32x32<DT, decltype(sub_tag)::value>(fr.a[RBI], fr.b[CB], acc[RBI][CB], fr.idx[RBI]);
+    } else {
+      constexpr int H = decltype(m_tag)::value / (RB * CBS);
+      const u32x8 b = fr.b[CB];
+      acc[RBI][CB] = mfma_32x32x16<DT>(fr.a[H * RB + RBI], H ? b.hi : b.lo, acc[RBI][CB]);
+    }
   };
 
   // ---- pipeline ----
-  constexpr int NM = RB * CBS;             // MFMAs of a substep
+  constexpr int NM = RB * CBS * (SPARSE ? 1 : 2);  // MFMAs of a substep
   constexpr int W = NM >= 8 ? NM / 8 : 1;  // of these, before the wait for the next substep's rows
   constexpr int BEFORE = (W * C::COPIES + NM - 1) / NM;  // copies issued before that wait: copy j precedes MFMA j NM / COPIES
   // first two stages' row numbers straight into registers
@@ -265,13 +322,30 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     for (int sub = 0; sub < 2; ++sub)
 #pragma unroll
       for (int j = 0; j < C::COPIES; ++j) {
-        const int step = min(st * NWK + g, S - 1);
-        first_rows[st][sub][j] = gather[(size_t)t * S * 64 + step * 64 + sub * 32 + 8 * j + c];
+        const int entry = min(min(st * NWK + g, S - 1) * 64 + sub * 32 + 8 * j + c, entries - 1);
+        first_rows[st][sub][j] = gather[(size_t)t * entries + entry];
       }
+  int first_index[3] = {0, 0, 0};  // before 2:4: the vector indexes of stages 2 to 4
+  if constexpr (!SPARSE) {
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+      first_index[i] = gather[(size_t)t * entries + min(((i + 2) * NWK + g) * 64 + (int)e_src / 4, entries - 1)];
+    if (p.pi_in) {
+#pragma unroll
+      for (int st = 0; st < 2; ++st)
+#pragma unroll
+        for (int sub = 0; sub < 2; ++sub)
+#pragma unroll
+          for (int j = 0; j < C::COPIES; ++j) first_rows[st][sub][j] = p.pi_in[first_rows[st][sub][j]];
+    }
+  }
+  index = first_index[0];
   issue_shared(0, 0, 2);
 #pragma unroll
   for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[0][0][j], 0, j);
+  index = first_index[1];
   issue_shared(1, C::A_SLOT, 3);
+  index = first_index[2];
 #pragma unroll
   for (int j = 0; j < C::COPIES; ++j) issue_row_copy(first_rows[0][1][j], C::SLOT, j);
 #pragma unroll
@@ -285,6 +359,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     for (int j = 0; j < C::COPIES; ++j) e1[j] = (uint32_t)first_rows[1][1][j];
   }
   wait_copies_outstanding<(R - 1) * C::COPIES + C::SHARED_MIN>();
+  if constexpr (!SPARSE) asm volatile("s_waitcnt lgkmcnt(0)" ::);  // row numbers written to LDS
   __builtin_amdgcn_s_barrier();
   issue_shared(2, 2 * C::A_SLOT, 4);
 
@@ -293,14 +368,17 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   auto next_a = [&](int s) { return s + C::A_SLOT == C::A_RING * C::A_SLOT ? 0 : s + C::A_SLOT; };
 
   u32x4 next_e0, next_e1;
-  auto read_rows = [&](int stage) {
+  int next_index = 0;
+  auto read_rows = [&](int stage) {  // and, before 2:4, the vector indexes of the stage three ahead of it
     const uint32_t at = e_lane + (stage & 3) * C::E_SLOT;
     lds_read_b128<0>(at, next_e0);
     lds_read_b128<16>(at, next_e1);
+    if constexpr (!SPARSE) lds_read_b32<0>(v_lane + ((stage + 3) & 3) * C::E_SLOT, next_index);
   };
   auto tie_rows = [&]() {
     pin(next_e0);
     pin(next_e1);
+    if constexpr (!SPARSE) pin(next_index);
   };
 
   using I0 = std::integral_constant<int, 0>;
@@ -311,6 +389,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   tie_rows();
   e0 = next_e0;
   if constexpr (R == 4) e1 = next_e1;
+  index = next_index;
 
   // Substep SUB of stage s: the copies of the substep R ahead go into the slot just read, one by one between the MFMAs;
   // once the next substep's rows have landed, the reads of its fragments are spread over the rest of them.
@@ -323,7 +402,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     const u32x4 rows = (R == 4) ? (SUB ? e1 : e0) : (SUB ? e0 : e1);
     const int write_slot = b_slot;
     b_slot = next_b(b_slot);
-    constexpr int NR = 4 * CBS + RB + (SUB == 1 ? RB : 0);
+    constexpr int NR = reads_of(1 - SUB);
     constexpr int PER = (NR + (NM > W + 3 ? NM - W - 2 : 1) - 1) / (NM > W + 3 ? NM - W - 2 : 1);
     unroll<0, NM>([&](auto m) {
       constexpr int M = decltype(m)::value;
@@ -355,7 +434,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     });
     if constexpr (READ) {
       tie(f[1 - SUB], std::integral_constant<int, 1 - SUB>{});
-      if constexpr (SUB == 0) unroll<0, RB>([&](auto rb) { f[1].idx[decltype(rb)::value] = f[0].idx[decltype(rb)::value]; });
+      if constexpr (SPARSE && SUB == 0) unroll<0, RB>([&](auto rb) { f[1].idx[decltype(rb)::value] = f[0].idx[decltype(rb)::value]; });
       if constexpr (SHARED) tie_rows();
     }
   };
@@ -373,17 +452,32 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     substep(s, I1{}, Yes{}, Yes{}, WaitOdd{}, Yes{}, true);
     e0 = next_e0;
     if constexpr (R == 4) e1 = next_e1;
+    index = next_index;
   }
   using WaitTail0 = std::integral_constant<int, BEHIND + (R == 3 ? BEFORE : 0) + C::SHARED_MIN>;
   using WaitTail1 = std::integral_constant<int, C::COPIES + (R == 4 ? C::SHARED_MIN : 0)>;
-  const bool whole = (stages - 1) * NWK + g < S;  // an odd number of steps: the last group has none in the last stage
+  const int last_step = (stages - 1) * NWK + g;
+  const bool whole = last_step < S;  // an odd number of steps: the last group has none in the last stage
+  // Before 2:4 the rows of padded kept columns are some row of X: their values are zero, but a row may hold NaN.  Kept columns
+  // come in eights, a lane's registers 4 h .. 4 h + 3 are eight of them.
+  auto clear_padded = [&](Fragments<RB, CBS, SPARSE>& fr, int sub) {
+    if (SPARSE || p.Kv - last_step * 64 >= 64) return;
+    unroll<0, CBS>([&](auto cbt) {
+#pragma unroll
+      for (int i = 0; i < 8; ++i)
+        if (last_step * 64 + 32 * sub + 16 * (i / 4) + 8 * qh >= p.Kv) fr.b[decltype(cbt)::value][i] = 0;
+    });
+  };
   substep(s, I0{}, std::integral_constant<bool, R == 3>{}, No{}, WaitTail0{}, Yes{}, true);
   substep(s, I1{}, No{}, No{}, WaitTail1{}, Yes{}, true);
+  clear_padded(f[0], 0);
   substep(s + 1, I0{}, No{}, No{}, I0{}, Yes{}, whole);
+  clear_padded(f[1], 1);
   substep(s + 1, I1{}, No{}, No{}, I0{}, No{}, whole);
 
   // ---- epilogue ----
   __builtin_amdgcn_s_barrier();  // every wave is done with the ring and the stored values
+  auto out_row = [&](int row) -> int64_t { return SPARSE || out_rows ? out_rows[t * V + row] : t * V + row; };
   auto finish = [&](auto g_tag) {
     constexpr int G = decltype(g_tag)::value;
     if constexpr (NWK == 2) {
@@ -423,7 +517,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
             const int row = 32 * rb + 8 * (e >> 2) + 4 * qh + (e & 3);
-            float* dst = static_cast<float*>(Y) + (int64_t)out_rows[t * V + row] * ldy;
+            float* dst = static_cast<float*>(Y) + out_row(row) * ldy;
 #pragma unroll
             for (int cb = 0; cb < CBS; ++cb) {
               float v = acc[rb][cb][e];
@@ -445,7 +539,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   else finish(I1{});
   if (out_f32) return;
   __syncthreads();
-  store_staged_rows<V, C::NB, C::THREADS>(lds, Y, ldy, N, nb * C::NB, [&](int row) -> int64_t { return out_rows[t * V + row]; });
+  store_staged_rows<V, C::NB, C::THREADS>(lds, Y, ldy, N, nb * C::NB, out_row);
 }
 
 // The two names under which it runs: spmm_mid_kernel where it takes the place of that kernel's own blocks (spmm_mid.hip),
@@ -453,11 +547,15 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
 // more than 256 registers at hand the compiler parks fragments in accumulation registers before their LDS reads have landed.
 template <int DT, int RB, int NWC, int NWK, int R>
 __global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_mid_kernel(RingParams p) {
-  ring_product<DT, RB, NWC, NWK, R>(p);
+  ring_product<kRingPrepared, DT, RB, NWC, NWK, R>(p);
 }
 template <int DT, int RB, int NWC, int NWK, int R>
 __global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_tile_prepared_kernel(RingParams p) {
-  ring_product<DT, RB, NWC, NWK, R>(p);
+  ring_product<kRingPrepared, DT, RB, NWC, NWK, R>(p);
+}
+template <int DT, int RB, int NWC, int NWK, int R>
+__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_vectors_rings_kernel(RingParams p) {
+  ring_product<kRingVectors, DT, RB, NWC, NWK, R>(p);
 }
 
 // The four forms, by columns and groups of steps (variants 20 to 23), and what a launch of each takes by tile height (us):
@@ -489,12 +587,12 @@ double form_us(const RingForm& f, int S, int tiles, int N) {
   return f.start + whole * (f.round + steps * f.full) + steps * (f.part + f.more * last / f.slots);
 }
 
-int best_form(const PreparedArgs& a, bool mid, int tiles, double* us) {
-  const PreparedLayout L = prepared_layout(a.s);
+// `mid`: of the forms that split the steps, for fewer columns
+int best_form(const RingForm (&forms)[kRingForms], bool mid, int S, int tiles, int N, double* us) {
   int best = -1;
   for (int i = 0; i < kRingForms; ++i) {
-    if (mid && kForms[L.RB - 1][i].groups == 1) continue;  // fewer columns: the forms that split the steps
-    const double t = form_us(kForms[L.RB - 1][i], L.S, tiles, a.N);
+    if (forms[i].slots == 0 || (mid && forms[i].groups == 1)) continue;
+    const double t = form_us(forms[i], S, tiles, N);
     if (best < 0 || t < *us) *us = t, best = i;
   }
   return best;
@@ -509,7 +607,7 @@ constexpr auto ring_kernel() {
 // The tiles [first, first + count) of the layer.
 template <bool MID, int DT, int RB, int NWC, int NWK, int R>
 hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int count) {
-  using C = RingCfg<RB, NWC, NWK, R>;
+  using C = RingCfg<kRingPrepared, RB, NWC, NWK, R>;
   const PreparedLayout L = prepared_layout(a.s);
   const int n_blocks = (a.N + C::NB - 1) / C::NB;
   const int work_per_xcd = (int)(((int64_t)n_blocks * count + 7) / 8);
@@ -523,8 +621,8 @@ hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int
   if (hipError_t e = raise_lds_limit<kernel>(C::LDS_BYTES); e != hipSuccess) return e;
   const uint8_t* base = static_cast<const uint8_t*>(a.prepared);
   const int64_t row_bytes = a.ldx * 2;
-  RingParams p;
-  p.prep_blocks = base + L.a_offset + (size_t)first * L.S * C::A_STEP;
+  RingParams p{};
+  p.values = base + L.a_offset + (size_t)first * L.S * C::A_STEP;
   p.gather = reinterpret_cast<const int32_t*>(base + L.gather_offset) + (size_t)first * L.S * 64;
   p.out_rows = reinterpret_cast<const int32_t*>(base + L.pi_out_offset) + (size_t)first * a.s.V;
   p.X = static_cast<const uint16_t*>(a.X);
@@ -564,7 +662,7 @@ hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
   if (a.tile_variant) return launch_tiles<false, DT, RB>(a, stream, a.tile_variant - kRingFirstVariant, 0, L.T);
   double us = 0;
-  const int form = best_form(a, mid, L.T, &us);
+  const int form = best_form(kForms[RB - 1], mid, L.S, L.T, a.N, &us);
   if (mid) return launch_tiles<true, DT, RB>(a, stream, form, 0, L.T);
   // Whole rounds of 512-column blocks, and the tiles that are left over in the form that suits them, behind them
   // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 66 -> 62 us).
@@ -573,7 +671,7 @@ hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
   const int whole = (int)(rounds * 256 / wide);
   if (rounds > 0 && whole < L.T) {
     double rest_us = 0;
-    const int rest_form = best_form(a, false, L.T - whole, &rest_us);
+    const int rest_form = best_form(kForms[RB - 1], false, L.S, L.T - whole, a.N, &rest_us);
     if (form_us(kForms[RB - 1][0], L.S, whole, a.N) + rest_us < us) {
       const hipError_t e = launch_tiles<false, DT, RB>(a, stream, 0, 0, whole);
       return e != hipSuccess ? e : launch_tiles<false, DT, RB>(a, stream, rest_form, whole, L.T - whole);
@@ -595,7 +693,7 @@ bool spmm_ring_prepared_supported(const PreparedArgs& a) {
 
 double spmm_ring_prepared_us(const PreparedArgs& a, bool mid) {
   double us = 0;
-  best_form(a, mid, a.s.M / a.s.V, &us);
+  best_form(kForms[a.s.V / 32 - 1], mid, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us);
   return us;
 }
 
@@ -607,6 +705,114 @@ hipError_t launch_spmm_ring_prepared(const PreparedArgs& a, bool mid, hipStream_
     case 2: return launch_rb<DT, 2>(a, mid, stream);   \
     case 3: return launch_rb<DT, 3>(a, mid, stream);   \
     case 4: return launch_rb<DT, 4>(a, mid, stream);   \
+  }
+  if (a.s.dtype == HINM_F16) {
+    HINM_RB(HINM_F16)
+  } else {
+    HINM_RB(HINM_BF16)
+  }
+#undef HINM_RB
+  return hipErrorInvalidValue;
+}
+
+// ---- before the 2:4 step ------------------------------------------------------------------------------------------------
+
+namespace {
+
+// As kForms, fitted to 260 random layers (M, K up to 8192, N 65..4096; error 4 to 9 %, the form chosen 0.2 % off the best).  Two
+// groups of steps on 256 columns leave no room in LDS for the dense values of 96 rows and more.  us, in the order of the
+// forms: 4096 x 4096, V = 64, Kv = 2048, N = 1000 36 / 27 / 27 / 37 (tile kernel 37); 8192 x 8192, V = 128, Kv = 4096, N = 2048
+// 120 / - / 137 / 179 (165); 4096 x 4096, V = 128, N = 1024 42 / - / 29 / 27 (42).
+constexpr RingForm kVectorForms[4][kRingForms] = {  // [RB - 1]
+    {{512, 1, 256, 4.0f, 1.13f, 0.52f, 0.25f, 1.5f}, {256, 2, 256, 4.2f, 1.13f, 0.54f, 0.41f, 1.8f},
+     {256, 1, 512, 3.9f, 1.07f, 0.29f, 0.52f, 1.1f}, {128, 2, 256, 3.9f, 0.70f, 0.37f, 0.20f, 1.9f}},
+    {{512, 1, 256, 5.4f, 1.59f, 0.58f, 0.52f, 3.7f}, {256, 2, 256, 4.9f, 1.64f, 0.70f, 0.56f, 2.8f},
+     {256, 1, 256, 4.9f, 0.78f, 0.42f, 0.17f, 2.6f}, {128, 2, 256, 4.6f, 1.03f, 0.49f, 0.36f, 2.4f}},
+    {{512, 1, 256, 6.2f, 2.05f, 0.84f, 0.62f, 0.0f}, {256, 2, 0, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f},
+     {256, 1, 256, 5.8f, 0.78f, 0.54f, 0.21f, 6.8f}, {128, 2, 256, 5.4f, 1.32f, 0.73f, 0.30f, 3.1f}},
+    {{512, 1, 256, 7.2f, 1.72f, 1.05f, 0.53f, 10.1f}, {256, 2, 0, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f},
+     {256, 1, 256, 6.4f, 1.02f, 0.68f, 0.37f, 6.2f}, {128, 2, 256, 5.8f, 1.74f, 0.86f, 0.57f, 3.1f}}};
+
+template <int DT, int RB, int NWC, int NWK, int R>
+hipError_t launch_vectors_form(const VectorsArgs& a, hipStream_t stream) {
+  using C = RingCfg<kRingVectors, RB, NWC, NWK, R>;
+  const int T = a.s.M / a.s.V;
+  const int n_blocks = (a.N + C::NB - 1) / C::NB;
+  const int work_per_xcd = (int)(((int64_t)n_blocks * T + 7) / 8);
+  constexpr auto kernel = spmm_vectors_rings_kernel<DT, RB, NWC, NWK, R>;
+  if (hipError_t e = raise_lds_limit<kernel>(C::LDS_BYTES); e != hipSuccess) return e;
+  const int64_t row_bytes = a.ldx * 2;
+  RingParams p{};
+  p.values = static_cast<const uint8_t*>(a.vals_v);
+  p.gather = a.vec_idx;
+  p.pi_in = a.pi_in;
+  p.out_rows = a.pi_out;
+  p.X = static_cast<const uint16_t*>(a.X);
+  p.Y = a.Y;
+  p.ldy = a.ldy;
+  p.x_bytes = (uint32_t)((a.s.K - 1) * row_bytes + (int64_t)(a.N + 7) / 8 * 16);
+  p.row_bytes = (int)row_bytes;  // checked by spmm_ring_vectors_supported
+  p.T = T;
+  p.S = (a.s.Kv + 63) / 64;
+  p.N = a.N;
+  p.n_blocks = n_blocks;
+  p.work_per_xcd = work_per_xcd;
+  p.K = a.s.K;
+  p.Kv = a.s.Kv;
+  p.relu = a.relu;
+  p.out_f32 = a.out_f32;
+  kernel<<<dim3((unsigned)(work_per_xcd * 8)), C::THREADS, C::LDS_BYTES, stream>>>(p);
+  return hipGetLastError();
+}
+
+template <int DT, int RB>
+hipError_t launch_vectors_rb(const VectorsArgs& a, hipStream_t stream) {
+  double us = 0;
+  switch (a.variant ? a.variant - kRingFirstVariant
+                    : best_form(kVectorForms[RB - 1], false, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us)) {
+    case 0: return launch_vectors_form<DT, RB, 8, 1, RB <= 2 ? 4 : 3>(a, stream);
+    case 1:
+      if constexpr (RB <= 2) return launch_vectors_form<DT, RB, 4, 2, RB == 1 ? 4 : 3>(a, stream);
+      break;
+    case 2: return launch_vectors_form<DT, RB, 4, 1, 4>(a, stream);
+    case 3: return launch_vectors_form<DT, RB, 2, 2, RB <= 2 ? 4 : 3>(a, stream);
+    default: break;
+  }
+  return hipErrorInvalidValue;
+}
+
+}  // namespace
+
+bool spmm_ring_vectors_supported(const VectorsArgs& a) {
+  const int V = a.s.V;
+  if (a.variant == kRingFirstVariant + 1 && V > 64) return false;
+  if (!(V == 32 || V == 64 || V == 96 || V == 128) || a.N <= 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
+  const uint64_t row = (uint64_t)a.ldx * 2;
+  return (a.s.Kv + 63) / 64 >= 3 && a.s.K < (1 << 23) && row < (1u << 23) && ((uint64_t)a.s.K + 1) * row <= (uint64_t{1} << 32) &&
+         (int64_t)(a.s.M / V) * ((a.N + 127) / 128) < (1 << 30);
+}
+
+// From 65 columns on.  Against the kernel for a moderate number of columns by estimate, 8 % ahead as for the prepared form, with
+// more than five steps and more than 320 of its 64-column blocks (of 260 random layers two gained below); of
+// what the tile kernel serves all but short passes of whole 64-column steps (2368 x 1536, V = 64, Kv = 384, N = 3856 19.0 us
+// there, 21.4 here; Kv = 256, 3456 x 1040, N = 3943 20.0 and 20.5; but 1344 x 1616, Kv = 400, N = 3873 18.2 and 12.2).
+bool spmm_ring_vectors_preferred(const VectorsArgs& a) {
+  if (a.N <= 64 || !spmm_ring_vectors_supported(a)) return false;
+  if (!spmm_mid_vectors_preferred(a)) return a.s.Kv % 64 != 0 || a.s.Kv > 6 * 64;
+  const int64_t blocks = (int64_t)(a.s.M / (a.s.V % 64 == 0 ? 64 : 32)) * ((a.N + 63) / 64);
+  if (blocks <= 320 || a.s.Kv <= 5 * 64) return false;
+  double us = 0;
+  best_form(kVectorForms[a.s.V / 32 - 1], false, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us);
+  return us * 1.08 < spmm_mid_vectors_us(a);
+}
+
+hipError_t launch_spmm_ring_vectors(const VectorsArgs& a, hipStream_t stream) {
+#define HINM_RB(DT)                                            \
+  switch (a.s.V) {                                             \
+    case 32: return launch_vectors_rb<DT, 1>(a, stream);       \
+    case 64: return launch_vectors_rb<DT, 2>(a, stream);       \
+    case 96: return launch_vectors_rb<DT, 3>(a, stream);       \
+    case 128: return launch_vectors_rb<DT, 4>(a, stream);      \
   }
   if (a.s.dtype == HINM_F16) {
     HINM_RB(HINM_F16)

@@ -1,4 +1,4 @@
-"""The kernel whose waves keep private rings of gathered rows (csrc/spmm_ring_prepared.hip) against the CPU oracle, in all
+"""The kernel whose waves keep private rings of gathered rows (csrc/spmm_rings.hip) against the CPU oracle, in all
 four forms: fewest steps, odd and even counts of them (two groups share the steps), padded kept columns, ragged columns."""
 import numpy as np
 import pytest
@@ -86,3 +86,45 @@ def test_rings_leave_what_they_cannot_address():
         assert err.value.status == 5
     text, _ = hinm.hinm_spmm_prepared_plan(4096, 65528, 128, 1024, "bf16", 32760, 32760, 32760)
     assert "private rings" in text
+
+
+@pytest.mark.gpu
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+@pytest.mark.parametrize("V", [32, 64, 96, 128])
+@pytest.mark.parametrize("Kv,N,orders", [
+    (136, 65, True), (256, 129, False), (320, 511, True), (424, 264, False),
+])
+def test_rings_before_2_4(V, Kv, N, orders, dtype):
+    """The same edges on the dense stored values: row numbers looked up on the way, or taken as they are."""
+    from tests import gpu_util as gu
+    import paper_2407_20496_amd as hinm
+    case = synth.small_case(3 * V, 456, V, Kv, N, dtype, 94)
+    p = gu.gpu_pack_vectors(case.weights(), dtype, V, Kv)
+    pin, pout = (case.pi_in(), case.pi_out()) if orders else (None, None)
+    Xb = case.activations(N)
+    want = gu.gpu_spmm_vectors(p, Xb, pin, pout, hinm.OUT_F32 | hinm.KERNEL_REFERENCE).astype(np.float64)
+    for variant in RINGS:
+        if variant == 21 and V > 64:
+            with pytest.raises(hinm.HinmError):
+                gu.gpu_spmm_vectors(p, Xb, pin, pout, variant << 16)
+            continue
+        got = gu.gpu_spmm_vectors(p, Xb, pin, pout, hinm.OUT_F32 | variant << 16)
+        gu.check_close(got.astype(np.float64), want, what="variant %d" % variant)
+        bits = gu.gpu_spmm_vectors(p, Xb, pin, pout, variant << 16)
+        assert np.array_equal(bits, orc.round_to_storage(got, dtype)), variant
+
+
+@pytest.mark.gpu
+def test_rings_before_2_4_ignore_rows_of_padding():
+    """NaN in a row of X that no kept column names does not reach the result, wherever padding happens to look."""
+    from tests import gpu_util as gu
+    import paper_2407_20496_amd as hinm
+    case = synth.small_case(64, 456, 64, 200, 130, "f16", 95)
+    p = gu.gpu_pack_vectors(case.weights(), "f16", 64, 200)
+    Xb = case.activations(130).copy()
+    Xb[[r for r in range(456) if r not in set(p.vec_idx.cpu().numpy().ravel().tolist())]] = 0x7E00
+    want = gu.gpu_spmm_vectors(p, Xb, None, None, hinm.OUT_F32 | hinm.KERNEL_REFERENCE).astype(np.float64)
+    assert np.isfinite(want).all()
+    for variant in RINGS:
+        got = gu.gpu_spmm_vectors(p, Xb, None, None, hinm.OUT_F32 | variant << 16)
+        gu.check_close(got.astype(np.float64), want, what="variant %d" % variant)
