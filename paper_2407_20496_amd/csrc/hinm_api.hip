@@ -1,6 +1,8 @@
 // C-ABI entry points of libhinm: host-side argument validation and kernel dispatch.
 // Every check here runs before anything is launched, so the error paths need no GPU.
 #include "hinm_internal.h"
+
+#include <algorithm>
 #include "prepared_layout.h"
 #include "hinm_calib.h"
 
@@ -475,13 +477,12 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     return HINM_OK;
   }
   // From 65 columns on: the kernel with private rings wherever it can run, unless one of the kernels for fewer columns is
-  // estimated to take less.  Against the one for a moderate number of columns the estimate has to be 8 % ahead, about what
-  // both estimates miss by (3200 x 10424, V = 128, Kv = 2608, N = 628: 21.6 us there, 22.4 on rings, estimated 24.8 and 23.3),
-  // and up to five steps the two are within a tenth of each other (3008 x 560, Kv = 280, N = 273 5.4 and 5.9 us; 1312 x 1048,
-  // V = 32, Kv = 264, N = 681 5.4 and 5.3).
+  // estimated to take less (with a margin, spmm_rings.hip).  Up to five steps it and the one for a moderate number of columns
+  // are within a tenth of each other (3008 x 560, Kv = 280, N = 273 5.4 us there and 5.9; 1312 x 1048, V = 32, Kv = 264, N = 681
+  // 5.4 and 5.3).
   const bool ring = with_mid && a.tile_variant == 0 && N > 64 && spmm_ring_prepared_supported(a);
   if (with_mid && a.tile_variant == 0 && spmm_mid_prepared_preferred(a)) {
-    *route = ring && shape->Kv > 5 * 64 && spmm_ring_prepared_us(a, true) * 1.08 < spmm_mid_prepared_us(a) ? PreparedRoute::MidRing : PreparedRoute::Mid;
+    *route = ring && shape->Kv > 5 * 64 && spmm_ring_prepared_us(a, true) < spmm_mid_prepared_us(a) ? PreparedRoute::MidRing : PreparedRoute::Mid;
     return HINM_OK;
   }
   // What the kernel for a moderate number of columns leaves: one column, up to 64 columns (128 on the smallest layers) where it
@@ -511,7 +512,7 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     const bool x_beyond_l2 = (double)shape->K * N * 2 > 3.5e6;
     const double l2_factor = !x_beyond_l2 ? 1.0 : N > 1024 ? 2.0 : (N > 512 && blocks_per_wg < 4) ? 1.5 : 1.0;
     few_columns = 2.5 + units * (0.14 * shape->Kv + 40.0) * 1e-6 * l2_factor * pair_factor <
-                  (ring ? spmm_ring_prepared_us(a, false) : tile_floor_us);
+                  (ring ? std::min(spmm_ring_prepared_us(a, false), tile_floor_us) : tile_floor_us);
   }
   if (a.tile_variant == 11 || a.tile_variant == 19 || (a.tile_variant == 0 && few_columns)) {
     if ((N + 15) / 16 > 65535) return HINM_ERR_UNSUPPORTED;

@@ -58,15 +58,16 @@ struct RingCfg {
   static constexpr int V_BASE = E_BASE + E_RING * E_SLOT;  // before 2:4: vector indexes on their way to row numbers
   static constexpr int LOOP_BYTES = V_BASE + (SPARSE ? 0 : 4 * E_SLOT);
   static constexpr int EPI_BYTES = 32 * RB * kStageStride<NB>;
-  static constexpr int OWN = (RB + NWK - 1) / NWK;   // most row blocks of the result that a wave finishes
-  static constexpr int SUM_BYTES = NWK == 1 ? 0 : NW * OWN * CBS * 4096;
+  // 32x32 blocks of the result that a wave leaves to the other groups: block b is finished by group b % NWK
+  static constexpr int GIVEN = (NWK - 1) * ((RB * CBS + NWK - 1) / NWK);
+  static constexpr int SUM_BYTES = NW * GIVEN * 4096;
   static constexpr int LOOP_OR_EPI = LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES;
   static constexpr int LDS_BYTES = LOOP_OR_EPI > SUM_BYTES ? LOOP_OR_EPI : SUM_BYTES;
   // 256-column blocks run two side by side on the same tiles of a die: its 32 units then fetch 16 tiles and two column
   // panels, not 32 tiles and one (4096 x 4096, V = 128, N = 2048 28.3 -> 25.2 us, 4096 x 11008 56.8 -> 55.2).  A panel of
   // 512 columns is the larger part of what they fetch and stays alone (16384 x 16384, N = 8192 1200 against 1260).
   static constexpr int BLOCKS_TOGETHER = NB == 256 ? 2 : 1;
-  static_assert(NWK == 1 || NWK == 2, "groups of steps");
+  static_assert(NWK == 1 || NWK == 2 || NWK == 4, "groups of steps");
   static_assert(R == 3 || R == 4, "ring");
   static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
 };
@@ -134,6 +135,7 @@ struct RingParams {
   int row_bytes;     // of X
   int T, S, N, n_blocks, work_per_xcd;
   int K, Kv;
+  int parts;         // four groups: workgroups that share a tile, 32 RB rows each
   bool relu, out_f32;
 };
 
@@ -173,8 +175,10 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   const auto x_buf = make_buffer(p.X, p.x_bytes);
   const int entries = SPARSE ? S * 64 : p.Kv;  // of the tile in `gather`
   const uint32_t a_bytes = SPARSE ? (uint32_t)S * C::A_STEP : (uint32_t)V * p.Kv * 2;
-  const auto a_buf = make_buffer(p.values + (size_t)t * a_bytes, a_bytes);
-  const auto e_buf = make_buffer(gather + (size_t)t * entries, (uint32_t)entries * 4);
+  const int parts = NWK == 4 ? p.parts : 1, tile = t / parts;  // T and t count parts of tiles
+  const uint32_t step_bytes = (uint32_t)parts * C::A_STEP, part_offset = (uint32_t)(t % parts) * C::A_STEP;
+  const auto a_buf = make_buffer(p.values + (size_t)tile * parts * a_bytes + part_offset, parts * a_bytes - part_offset);
+  const auto e_buf = make_buffer(gather + (size_t)tile * entries, (uint32_t)entries * 4);
 
   // ---- copies ----
   // Copy j of a substep: lane class c = lane / 8 takes row 8 j + c.  Its 32-byte units are stored at unit ^ (row & 3)
@@ -197,7 +201,9 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   for (int m = 0; m < C::SHARED_ROUNDS; ++m) {
     const int i = wave + m * NW;
     if constexpr (SPARSE) {
-      a_src[m] = (uint32_t)min(i * 64 + lane, C::A_GRANULES - 1) * 16;
+      const int piece = min(i * 64 + lane, C::A_GRANULES - 1);  // of 16 bytes
+      a_src[m] = parts == 1 ? (uint32_t)piece * 16
+                            : piece / (C::A_STEP / 16) * step_bytes + (uint32_t)(piece % (C::A_STEP / 16)) * 16;
     } else {
       // eight rows of a step at a time, 128 bytes each, 16-byte piece x of row r at position x ^ (r / 2) % 8: the reads of
       // 32 consecutive rows fall on different banks
@@ -216,7 +222,7 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
     for (int m = 0; m < C::SHARED_ROUNDS; ++m) {
       const int i = wave + m * NW;
       if (i < C::A_INSTR) {
-        uint32_t off = (uint32_t)a_stage * (SPARSE ? C::A_STAGE : NWK * 128) + a_src[m];
+        uint32_t off = (uint32_t)a_stage * (SPARSE ? NWK * step_bytes : NWK * 128) + a_src[m];
         if (!SPARSE && a_first[m] + a_stage * NWK * 64 >= p.Kv) off = 0xFFFFFFF0u;  // beyond the row: zeros
         buffer_copy16_to_lds(a_buf, off, lds + C::A_BASE + a_slot + i * 1024);
       } else if (i < C::SHARED_INSTR) {
@@ -323,13 +329,13 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
 #pragma unroll
       for (int j = 0; j < C::COPIES; ++j) {
         const int entry = min(min(st * NWK + g, S - 1) * 64 + sub * 32 + 8 * j + c, entries - 1);
-        first_rows[st][sub][j] = gather[(size_t)t * entries + entry];
+        first_rows[st][sub][j] = gather[(size_t)tile * entries + entry];
       }
   int first_index[3] = {0, 0, 0};  // before 2:4: the vector indexes of stages 2 to 4
   if constexpr (!SPARSE) {
 #pragma unroll
     for (int i = 0; i < 3; ++i)
-      first_index[i] = gather[(size_t)t * entries + min(((i + 2) * NWK + g) * 64 + (int)e_src / 4, entries - 1)];
+      first_index[i] = gather[(size_t)tile * entries + min(((i + 2) * NWK + g) * 64 + (int)e_src / 4, entries - 1)];
     if (p.pi_in) {
 #pragma unroll
       for (int st = 0; st < 2; ++st)
@@ -480,63 +486,61 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   auto out_row = [&](int row) -> int64_t { return SPARSE || out_rows ? out_rows[t * V + row] : t * V + row; };
   auto finish = [&](auto g_tag) {
     constexpr int G = decltype(g_tag)::value;
-    if constexpr (NWK == 2) {
-      const int partner = wc + (1 - G) * NWC;
-      unroll<0, RB>([&](auto rbt) {
-        constexpr int rb = decltype(rbt)::value;
-        if constexpr (rb % 2 != G) {
+    if constexpr (NWK > 1) {
+      // block b of group h, for group b % NWK: slot (b % NWK - h - 1) mod NWK of the wave's b / NWK-th set
+      auto given = [&](int w, int h, int b) {
+        return lds + (w * C::GIVEN + b / NWK * (NWK - 1) + (b % NWK - h - 1 + NWK) % NWK) * 4096 + lane * 16;
+      };
+      unroll<0, RB * CBS>([&](auto bt) {
+        constexpr int b = decltype(bt)::value;
+        if constexpr (b % NWK != G) {
+          uint8_t* const dst = given(wave, G, b);
 #pragma unroll
-          for (int cb = 0; cb < CBS; ++cb)
-#pragma unroll
-            for (int q = 0; q < 4; ++q)
-              *reinterpret_cast<f32x4*>(lds + ((wave * C::OWN + rb / 2) * CBS + cb) * 4096 + q * 1024 + lane * 16) =
-                  f32x4{acc[rb][cb][4 * q], acc[rb][cb][4 * q + 1], acc[rb][cb][4 * q + 2], acc[rb][cb][4 * q + 3]};
+          for (int q = 0; q < 4; ++q)
+            *reinterpret_cast<f32x4*>(dst + q * 1024) =
+                f32x4{acc[b / CBS][b % CBS][4 * q], acc[b / CBS][b % CBS][4 * q + 1], acc[b / CBS][b % CBS][4 * q + 2],
+                      acc[b / CBS][b % CBS][4 * q + 3]};
         }
       });
       __syncthreads();
-      unroll<0, RB>([&](auto rbt) {
-        constexpr int rb = decltype(rbt)::value;
-        if constexpr (rb % 2 == G) {
-#pragma unroll
-          for (int cb = 0; cb < CBS; ++cb)
+      unroll<0, RB * CBS>([&](auto bt) {
+        constexpr int b = decltype(bt)::value;
+        if constexpr (b % NWK == G) {
+          unroll<1, NWK>([&](auto dt) {
+            constexpr int h = (G + decltype(dt)::value) % NWK;
+            const uint8_t* const src = given(wc + h * NWC, h, b);
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-              const f32x4 v = *reinterpret_cast<const f32x4*>(lds + ((partner * C::OWN + rb / 2) * CBS + cb) * 4096 +
-                                                              q * 1024 + lane * 16);
+              const f32x4 v = *reinterpret_cast<const f32x4*>(src + q * 1024);
 #pragma unroll
-              for (int e = 0; e < 4; ++e) acc[rb][cb][4 * q + e] += v[e];
+              for (int e = 0; e < 4; ++e) acc[b / CBS][b % CBS][4 * q + e] += v[e];
             }
+          });
         }
       });
       __syncthreads();
     }
-    unroll<0, RB>([&](auto rbt) {
-      constexpr int rb = decltype(rbt)::value;
-      if constexpr (NWK == 1 || rb % 2 == G) {
+    unroll<0, RB * CBS>([&](auto bt) {
+      constexpr int b = decltype(bt)::value, rb = b / CBS, cb = b % CBS;
+      if constexpr (b % NWK == G) {
         if (out_f32) {
+          const int n = n0 + cb * 32 + i32;
 #pragma unroll
           for (int e = 0; e < 16; ++e) {
-            const int row = 32 * rb + 8 * (e >> 2) + 4 * qh + (e & 3);
-            float* dst = static_cast<float*>(Y) + out_row(row) * ldy;
-#pragma unroll
-            for (int cb = 0; cb < CBS; ++cb) {
-              float v = acc[rb][cb][e];
-              if (relu) v = v > 0.f ? v : 0.f;
-              const int n = n0 + cb * 32 + i32;
-              if (n < N) dst[n] = v;
-            }
+            float* dst = static_cast<float*>(Y) + out_row(32 * rb + 8 * (e >> 2) + 4 * qh + (e & 3)) * ldy;
+            float v = acc[rb][cb][e];
+            if (relu) v = v > 0.f ? v : 0.f;
+            if (n < N) dst[n] = v;
           }
         } else {
-          unroll<0, CBS>([&](auto cbt) {
-            constexpr int cb = decltype(cbt)::value;
-            stage_block<DT, kStageStride<C::NB>>(acc[rb][cb], lds + 32 * rb * kStageStride<C::NB> + (wc * C::WC + cb * 32) * 2, relu);
-          });
+          stage_block<DT, kStageStride<C::NB>>(acc[rb][cb], lds + 32 * rb * kStageStride<C::NB> + (wc * C::WC + cb * 32) * 2, relu);
         }
       }
     });
   };
-  if (NWK == 1 || g == 0) finish(I0{});
-  else finish(I1{});
+  unroll<0, NWK>([&](auto gt) {
+    if (g == decltype(gt)::value) finish(gt);
+  });
   if (out_f32) return;
   __syncthreads();
   store_staged_rows<V, C::NB, C::THREADS>(lds, Y, ldy, N, nb * C::NB, out_row);
@@ -558,18 +562,18 @@ __global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_vectors_rings_kernel(R
   ring_product<kRingVectors, DT, RB, NWC, NWK, R>(p);
 }
 
-// The four forms, by columns and groups of steps (variants 20 to 23), and what a launch of each takes by tile height (us):
+// The forms, by columns and groups of steps (variants 20 to 24), and what a launch of each takes by tile height (us):
 //   start + (rounds of workgroups before the last) * (round + steps * full) + steps * (part + fill * more)
 // where steps are those of a wave and `fill` is the share of the last round's slots that are taken: a step is slower the
 // more units take part (clock, memory).  Fitted to 480 random layers (M, K 256..16384, N 65..8192, all tile heights, both
-// types; error 5 to 15 %); the form chosen by it is 0.7 % off the best of the four on average.  Examples, us in the order
-// below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
+// types; error 5 to 15 %); the form chosen by it is 0.7 % off the best of the first four on average.  Examples, us in the
+// order below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
 // 4096 x 4096, V = 128, N = 1024 29 / 20 / 20 / 18; 1984 x 6376, V = 64, Kv = 3184, N = 6033 92 / 82 / 77 / 109.
 struct RingForm {
-  int columns, groups, slots;  // slots: workgroups that run at once, by what their LDS leaves room for
+  int columns, groups, slots;  // slots: workgroups that run at once, by what their LDS leaves room for (0: no such form)
   float start, full, part, more, round;
 };
-constexpr int kRingForms = 4;
+constexpr int kRingForms = 5;
 constexpr RingForm kForms[4][kRingForms] = {  // [RB - 1]
     {{512, 1, 256, 3.2f, 0.76f, 0.55f, 0.21f, 1.4f}, {256, 2, 256, 3.3f, 0.91f, 0.58f, 0.32f, 1.5f},
      {256, 1, 512, 2.9f, 0.92f, 0.30f, 0.51f, 0.1f}, {128, 2, 512, 3.2f, 1.00f, 0.30f, 0.85f, 3.3f}},
@@ -578,21 +582,31 @@ constexpr RingForm kForms[4][kRingForms] = {  // [RB - 1]
     {{512, 1, 256, 5.8f, 0.99f, 0.56f, 0.25f, 6.3f}, {256, 2, 256, 5.2f, 1.15f, 0.63f, 0.38f, 3.9f},
      {256, 1, 256, 5.0f, 0.55f, 0.38f, 0.10f, 3.6f}, {128, 2, 256, 4.4f, 0.75f, 0.50f, 0.27f, 3.0f}},
     {{512, 1, 256, 6.4f, 1.04f, 0.66f, 0.43f, 10.8f}, {256, 2, 256, 5.8f, 1.24f, 0.74f, 0.42f, 6.3f},
-     {256, 1, 256, 5.9f, 0.62f, 0.43f, 0.16f, 5.4f}, {128, 2, 256, 4.9f, 0.81f, 0.56f, 0.30f, 4.4f}}};
+     {256, 1, 256, 5.9f, 0.62f, 0.43f, 0.16f, 5.4f}, {128, 2, 256, 4.9f, 0.81f, 0.56f, 0.30f, 4.4f},
+     {128, 4, 256, 4.0f, 1.51f, 0.69f, 0.64f, 1.0f}}};
+
+// Workgroups that share a tile: two of 64 rows each with four groups of steps (tiles of 128 rows only).
+constexpr int form_parts(const RingForm& f) { return f.groups == 4 ? 2 : 1; }
 
 double form_us(const RingForm& f, int S, int tiles, int N) {
-  const int64_t work = (int64_t)tiles * ((N + f.columns - 1) / f.columns);
+  const int64_t work = (int64_t)tiles * form_parts(f) * ((N + f.columns - 1) / f.columns);
   const int64_t whole = (work - 1) / f.slots, last = work - whole * f.slots;
   const double steps = (S + f.groups - 1) / f.groups;
   return f.start + whole * (f.round + steps * f.full) + steps * (f.part + f.more * last / f.slots);
 }
 
-// `mid`: of the forms that split the steps, for fewer columns
+// `mid`: of the forms that split the steps, for fewer columns; against the kernel's own blocks they have to be 8 % ahead, 16 %
+// with 32-row tiles, about what the estimates miss by (2720 x 8992, V = 32, Kv = 1120, N = 576: 12.7 us there, 13.9 here; 3200 x 10424, V = 128, Kv = 2608, N = 628: 21.6 us there, 22.4 here, estimated 24.8 and 23.3).
+// Four groups are the form for the fewest columns, estimated on such products alone, and need no margin; up to 320 of the
+// kernel's own blocks those are as good (11008 x 4096 at 50 %, N = 100, 344 blocks: 14.1 us there, 12.0 with four groups, 15.4
+// with two; 4096 x 4096, N = 512, 512 blocks 17.6, 13.7 and 15.8; N = 256, 256 blocks 8.4 and 9.5).
 int best_form(const RingForm (&forms)[kRingForms], bool mid, int S, int tiles, int N, double* us) {
   int best = -1;
   for (int i = 0; i < kRingForms; ++i) {
-    if (forms[i].slots == 0 || (mid && forms[i].groups == 1)) continue;
-    const double t = form_us(forms[i], S, tiles, N);
+    const bool four = forms[i].groups == 4;
+    if (forms[i].slots == 0 || (mid ? forms[i].groups == 1 : four)) continue;
+    if (four && (S < 5 || (int64_t)tiles * 2 * ((N + 63) / 64) <= 320)) continue;
+    const double t = form_us(forms[i], S, tiles, N) * (!mid || four ? 1.0 : &forms == &kForms[0] ? 1.16 : 1.08);
     if (best < 0 || t < *us) *us = t, best = i;
   }
   return best;
@@ -610,7 +624,8 @@ hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int
   using C = RingCfg<kRingPrepared, RB, NWC, NWK, R>;
   const PreparedLayout L = prepared_layout(a.s);
   const int n_blocks = (a.N + C::NB - 1) / C::NB;
-  const int work_per_xcd = (int)(((int64_t)n_blocks * count + 7) / 8);
+  const int parts = L.RB / RB;
+  const int work_per_xcd = (int)(((int64_t)n_blocks * count * parts + 7) / 8);
   constexpr auto kernel = ring_kernel<MID, DT, RB, NWC, NWK, R>();
   if (a.plan) {
     plan_record(a.plan, "%s<DT=%d,RB=%d,NB=%d,NWK=%d,R=%d> private rings, tiles=%d..%d grid=%d block=%d lds=%d",
@@ -622,7 +637,7 @@ hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int
   const uint8_t* base = static_cast<const uint8_t*>(a.prepared);
   const int64_t row_bytes = a.ldx * 2;
   RingParams p{};
-  p.values = base + L.a_offset + (size_t)first * L.S * C::A_STEP;
+  p.values = base + L.a_offset + (size_t)first * L.S * parts * C::A_STEP;
   p.gather = reinterpret_cast<const int32_t*>(base + L.gather_offset) + (size_t)first * L.S * 64;
   p.out_rows = reinterpret_cast<const int32_t*>(base + L.pi_out_offset) + (size_t)first * a.s.V;
   p.X = static_cast<const uint16_t*>(a.X);
@@ -630,7 +645,8 @@ hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int
   p.ldy = a.ldy;
   p.x_bytes = (uint32_t)((a.s.K - 1) * row_bytes + (int64_t)(a.N + 7) / 8 * 16);
   p.row_bytes = (int)row_bytes;  // checked by spmm_ring_prepared_supported
-  p.T = count;
+  p.T = count * parts;
+  p.parts = parts;
   p.S = L.S;
   p.N = a.N;
   p.n_blocks = n_blocks;
@@ -652,6 +668,9 @@ hipError_t launch_tiles(const PreparedArgs& a, hipStream_t stream, int form, int
       if constexpr (!MID) return launch_form<false, DT, RB, 4, 1, 4>(a, stream, first, count);
       break;
     case 3: return launch_form<MID, DT, RB, 2, 2, RB <= 2 ? 4 : 3>(a, stream, first, count);
+    case 4:
+      if constexpr (RB == 4) return launch_form<true, DT, 2, 2, 4, 3>(a, stream, first, count);
+      break;
     default: break;
   }
   return hipErrorInvalidValue;
@@ -687,8 +706,9 @@ bool spmm_ring_prepared_supported(const PreparedArgs& a) {
   if (a.N <= 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   const PreparedLayout L = prepared_layout(a.s);
   const uint64_t row = (uint64_t)a.ldx * 2;
+  if (a.tile_variant == kRingLastVariant && (L.S < 5 || L.RB != 4)) return false;  // two stages of four steps, two halves
   return L.S >= 3 && a.s.K < (1 << 23) && row < (1u << 23) && ((uint64_t)a.s.K + 1) * row <= (uint64_t{1} << 32) &&
-         (int64_t)L.T * ((a.N + 127) / 128) < (1 << 30);
+         (int64_t)L.T * 2 * ((a.N + 127) / 128) < (1 << 30);
 }
 
 double spmm_ring_prepared_us(const PreparedArgs& a, bool mid) {
@@ -785,7 +805,7 @@ hipError_t launch_vectors_rb(const VectorsArgs& a, hipStream_t stream) {
 
 bool spmm_ring_vectors_supported(const VectorsArgs& a) {
   const int V = a.s.V;
-  if (a.variant == kRingFirstVariant + 1 && V > 64) return false;
+  if (a.variant == kRingLastVariant || (a.variant == kRingFirstVariant + 1 && V > 64)) return false;
   if (!(V == 32 || V == 64 || V == 96 || V == 128) || a.N <= 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   const uint64_t row = (uint64_t)a.ldx * 2;
   return (a.s.Kv + 63) / 64 >= 3 && a.s.K < (1 << 23) && row < (1u << 23) && ((uint64_t)a.s.K + 1) * row <= (uint64_t{1} << 32) &&

@@ -20,7 +20,8 @@ RINGS = [20, 21, 22, 23]
     (424, 264),      # seven, padded; a column block of 8 columns
 ])
 def test_rings(V, Kv, N, dtype):
-    _check(synth.small_case(3 * V, 456, V, Kv, N, dtype, 91), N, RINGS, relu=(Kv == 256))
+    four = [24] if V == 128 and Kv >= 320 else []       # two stages of four steps, some of them without a step
+    _check(synth.small_case(3 * V, 456, V, Kv, N, dtype, 91), N, RINGS + four, relu=(Kv == 256))
 
 
 @pytest.mark.gpu
@@ -66,7 +67,8 @@ def test_rings_read_padding_as_zero_and_relu_clears_nan():
     (16384, 16384, 128, 8192, 8192, "NB=512,NWK=1"),
     (4096, 4096, 64, 2048, 1024, "NB=256,NWK=2"),
     (4096, 4096, 128, 2048, 1024, "NB=128,NWK=2"),
-    (11008, 4096, 128, 2048, 100, "SRC=0,RB=4,CB=2"),   # the small blocks of the other kernel are ahead
+    (11008, 4096, 128, 2048, 100, "RB=2,NB=128,NWK=4"),  # halves of tiles, four groups of steps
+    (4096, 4096, 128, 2048, 256, "SRC=0"),              # the small blocks of the other kernel are ahead
 ])
 def test_form_by_shape(M, K, V, Kv, N, form):
     import paper_2407_20496_amd as hinm
@@ -128,3 +130,14 @@ def test_rings_before_2_4_ignore_rows_of_padding():
     for variant in RINGS:
         got = gu.gpu_spmm_vectors(p, Xb, None, None, hinm.OUT_F32 | variant << 16)
         gu.check_close(got.astype(np.float64), want, what="variant %d" % variant)
+
+
+def test_four_groups_need_two_stages_and_two_halves():
+    import paper_2407_20496_amd as hinm
+    for V, Kv, ok in ((128, 264, True), (128, 256, False), (64, 512, False)):
+        if ok:
+            assert "NWK=4" in hinm.hinm_spmm_prepared_plan(512, 600, V, Kv, "f16", 200, 200, 200, flags=24 << 16)[0]
+            continue
+        with pytest.raises(hinm.HinmError) as err:
+            hinm.hinm_spmm_prepared_plan(512, 600, V, Kv, "f16", 200, 200, 200, flags=24 << 16)
+        assert err.value.status == 5
