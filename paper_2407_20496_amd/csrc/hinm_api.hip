@@ -524,7 +524,11 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     *route = PreparedRoute::Skinny;
   } else {
     if (N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0 || a.tile_variant == 12) return HINM_ERR_UNSUPPORTED;
-    const bool panel = (a.tile_variant == 15) || (a.tile_variant == 0 && spmm_panel_prepared_preferred(a));
+    // 128-row tiles leave the panel kernel's waves two tiles' registers and no depth: rings are ahead on all of 50 drawn layers
+    // (1.24 times; 2304 x 856, Kv = 432, N = 3153 20.5 against 11.4 us); up to 96 rows the two are level or the panel is ahead
+    // (64 rows: 0.99, 13440 x 704, Kv = 176, N = 7601 58 against 82 us).
+    const bool panel = (a.tile_variant == 15) ||
+                       (a.tile_variant == 0 && !(ring && shape->V == 128) && spmm_panel_prepared_preferred(a));
     if (panel && !spmm_panel_prepared_supported(a)) return HINM_ERR_UNSUPPORTED;
     *route = panel ? PreparedRoute::Panel : ring ? PreparedRoute::TileRing : PreparedRoute::Tile;
   }

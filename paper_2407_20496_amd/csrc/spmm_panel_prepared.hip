@@ -18,6 +18,8 @@
 #include "prepared_layout.h"
 #include "tile_epilogue.h"
 
+#include <type_traits>
+
 namespace hinm {
 namespace {
 
@@ -34,7 +36,7 @@ constexpr int kYStride = kRowBytes + 16;   // staged output row
 // layer carries the gather table as ready-made LDS addresses (see prepared_layout.h), padded kept
 // columns pointing at an all-zero row behind the panel, so a B read costs one XOR of address math.
 
-template <int DT, int RB, int kWaves>
+template <int DT, int RB, int kWaves, bool kWholeHalves>
 __global__ __launch_bounds__(kWaves * 64) void spmm_panel_prepared_kernel(
     const uint8_t* __restrict__ prep_blocks, const uint32_t* __restrict__ panel_gather,
     const int32_t* __restrict__ out_rows, const uint16_t* __restrict__ X, int64_t ldx, void* __restrict__ Y,
@@ -195,7 +197,12 @@ __global__ __launch_bounds__(kWaves * 64) void spmm_panel_prepared_kernel(
         const u32x4 v = *reinterpret_cast<const u32x4*>(stage + row * kYStride + chunk * 16);
         uint16_t* dst = Yh + out_row * ldy + n;
         if (n + 8 <= N) {
-          __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+          // A 128-byte piece of a row that is not aligned to 64 bytes leaves parts of lines at both ends; non-temporal, each
+          // part is a write of its own to memory, while L2 joins them with the neighbouring panel's (13440 x 704, V = 64,
+          // Kv = 176, N = 7601 169 -> 58 us; 2560 x 288, N = 7344 24.0 -> 13.9).  Aligned pieces stay non-temporal: 16.5 ->
+          // 12.5 us on 3072 x 768, N = 4096.  Decided on the host: a branch here costs that product a tenth.
+          if constexpr (kWholeHalves) __builtin_nontemporal_store(v, reinterpret_cast<u32x4*>(dst));
+          else *reinterpret_cast<u32x4*>(dst) = v;
         } else if (n < N) {
           store_row_end(dst, v, N - n);
         }
@@ -241,20 +248,25 @@ inline size_t panel_lds_bytes(int K, int waves) {
 template <int DT, int RB, int WAVES>
 hipError_t launch_waves(const PreparedArgs& a, int n_blocks, int tile_groups, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
-  constexpr auto kernel = spmm_panel_prepared_kernel<DT, RB, WAVES>;
   const int nb8 = (n_blocks + 7) / 8 * 8;  // ids are laid out in groups of 8 column blocks
   if (a.plan) {
     plan_record(a.plan, "spmm_panel_prepared_kernel<DT=%d,RB=%d,WAVES=%d> grid=%d block=%d lds=%d", DT, RB, WAVES,
                 nb8 * tile_groups, WAVES * 64, (int)panel_lds_bytes(a.s.K, WAVES));
     return hipSuccess;
   }
-  if (hipError_t e = raise_lds_limit<kernel>(160 * 1024); e != hipSuccess) return e;
   const uint8_t* base = static_cast<const uint8_t*>(a.prepared);
-  kernel<<<dim3((unsigned)(nb8 * tile_groups)), WAVES * 64, panel_lds_bytes(a.s.K, WAVES), stream>>>(
-      base + L.a_offset, reinterpret_cast<const uint32_t*>(base + L.panel_offset),
-      reinterpret_cast<const int32_t*>(base + L.pi_out_offset), static_cast<const uint16_t*>(a.X), a.ldx, a.Y, a.ldy,
-      a.s.K, L.T, L.S, a.N, tile_groups, a.relu, a.out_f32);
-  return hipGetLastError();
+  auto launch = [&](auto whole_halves) {
+    constexpr auto kernel = spmm_panel_prepared_kernel<DT, RB, WAVES, decltype(whole_halves)::value>;
+    if (hipError_t e = raise_lds_limit<kernel>(160 * 1024); e != hipSuccess) return e;
+    kernel<<<dim3((unsigned)(nb8 * tile_groups)), WAVES * 64, panel_lds_bytes(a.s.K, WAVES), stream>>>(
+        base + L.a_offset, reinterpret_cast<const uint32_t*>(base + L.panel_offset),
+        reinterpret_cast<const int32_t*>(base + L.pi_out_offset), static_cast<const uint16_t*>(a.X), a.ldx, a.Y, a.ldy,
+        a.s.K, L.T, L.S, a.N, tile_groups, a.relu, a.out_f32);
+    return hipGetLastError();
+  };
+  // every row of Y begins at a multiple of 64 bytes
+  const bool whole_halves = a.ldy % 32 == 0 && (reinterpret_cast<uintptr_t>(a.Y) & 63) == 0;
+  return whole_halves ? launch(std::true_type{}) : launch(std::false_type{});
 }
 
 // Workgroups per column panel.  The panel fills most of a compute unit's LDS, so a unit holds one workgroup,
