@@ -282,8 +282,9 @@ hinm_status hinm_spmm(const hinm_shape* shape, int32_t N,
  * rounding, pi_in / pi_out, ldx / ldy and alignment rules as for hinm_spmm.  flags: HINM_EPI_RELU,
  * HINM_OUT_F32, HINM_KERNEL_REFERENCE (one thread per output element), the variant bits (1 =
  * register-staged tile kernel, 2 / 3 = direct-to-LDS tile kernel with 256- / 512-column blocks,
- * 4 / 5 = the same with twice as many waves of half the width; 2..5 need Kv % 64 == 0; all of them V in
- * {32, 64, 96, 128} and N > 1); anything else returns HINM_ERR_UNSUPPORTED.  By shape: N = 1 streams the stored
+ * 4 / 5 = the same with twice as many waves of half the width; 2..5 need Kv % 64 == 0; 20..23 = waves with private
+ * rings: 512 columns, 256 with two groups of steps (V <= 64), 256, 128 with two groups, more than 128 kept columns; all
+ * of them V in {32, 64, 96, 128} and N > 1); anything else returns HINM_ERR_UNSUPPORTED.  By shape: N = 1 streams the stored
  * values once (any V and leading dimensions); V a multiple of 32 with N > 1 runs on the dense MFMA (the kernel for a
  * moderate number of columns, or a tile kernel up to V = 128); other shapes run on the plain kernel.  Needs no workspace. */
 hinm_status hinm_spmm_vectors(const hinm_shape* shape, int32_t N,

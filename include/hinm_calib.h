@@ -72,7 +72,8 @@ hinm_status hinm_calib_gather_stream(const void* region, size_t region_bytes, in
                                      int32_t waves, int32_t outstanding, int32_t copies_per_wave,
                                      int32_t workgroups, void* stream);
 
-/* One part of the tile kernel that hinm_spmm_prepared would launch for this shape and N, on a real
+/* One part of the staged tile kernel in the configuration that suits this shape and N (hinm_spmm_prepared itself runs
+ * most such products on waves with private rings, whose two sides do not come apart), on a real
  * prepared layer (hinm_prepare) and a real X: part 1 = only its copy stream (gathered rows of X and the
  * stored values through L2 into LDS, with the kernel's own barriers and waits; no LDS reads, no MFMAs),
  * part 2 = only its LDS reads and MFMAs (no copies after the first stages, so the operands are stale).
