@@ -684,7 +684,7 @@ hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
   const int form = best_form(kForms[RB - 1], mid, L.S, L.T, a.N, &us);
   if (mid) return launch_tiles<true, DT, RB>(a, stream, form, 0, L.T);
   // Whole rounds of 512-column blocks, and the tiles that are left over in the form that suits them, behind them
-  // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 66 -> 62 us).
+  // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 64.8 us, the best single launch 67.9).
   const int wide = (a.N + 511) / 512;
   const int64_t rounds = (int64_t)L.T * wide / 256;
   const int whole = (int)(rounds * 256 / wide);
