@@ -27,7 +27,7 @@ __device__ __forceinline__ float relu_f32(float v) { return __builtin_amdgcn_fme
 // holds one column, and writing its 16 values by themselves (ds_write_b16, 11 clocks each with every wave of a 128 x 512
 // workgroup writing) took 4 to 7 us of a workgroup's life, as much as four 64-row stages of the k loop.  Neighbouring
 // lanes exchange halves first (even lane: row e, odd lane: row e + 1, two columns each), which halves the writes and
-// makes them 32 bits wide: 11100 -> 3400 clocks.
+// makes them 32 bits wide: 11100 -> 4700 clocks.
 template <int DT, int STRIDE>
 __device__ __forceinline__ void stage_block(const f32x16& acc, uint8_t* block, bool relu) {
   const int lane = threadIdx.x & 63;
@@ -49,7 +49,7 @@ __device__ __forceinline__ void stage_block(const f32x16& acc, uint8_t* block, b
 
 // The first `left` (1 .. 7) of a lane's eight values to the end of a row, as one store each of four, two and one of them:
 // element by element, in a loop that picks halves of words, this took 8 us of a workgroup of 128 rows (512 x 1192, V = 128,
-// Kv = 592, N = 311 21.5 -> 12.9 us with 512-column blocks).
+// Kv = 592, N = 311 21.5 -> 14.0 us with 512-column rings; panel kernel, 4416 x 536, V = 64, N = 4119 34.6 -> 30.4).
 __device__ __forceinline__ void store_row_end(uint16_t* dst, u32x4 v, int left) {
   if (left & 4) *reinterpret_cast<u32x2*>(dst) = u32x2{v.x, v.y};
   const uint32_t pair = (left & 4) ? v.z : v.x;
