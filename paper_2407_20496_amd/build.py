@@ -5,6 +5,9 @@
 
 The sanitized library is for CPU runs of the argument-validation tests only (tests/test_sanitize.py): the
 device code in it is the ordinary one and the GPU is never touched under a sanitizer.
+
+Every object's device code is looked at after it is compiled (lds_reads.py): the build fails where a register is used before
+the LDS read that writes it has been waited for.
 """
 from __future__ import annotations
 
@@ -62,6 +65,10 @@ def _compile(src: str, sanitize: bool = False) -> str:
         raise RuntimeError(f"hipcc failed on {src}:\n{err}")
     if err.strip():
         sys.stderr.write(err + "\n")
+    if not sanitize:
+        res = subprocess.run([sys.executable, os.path.join(HERE, "lds_reads.py"), obj], capture_output=True, text=True)
+        if res.returncode != 0:
+            raise RuntimeError(f"{src}: LDS reads in flight:\n{res.stdout}{res.stderr}")
     return obj
 
 

@@ -82,6 +82,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t make_buffer(const void* p, uin
   return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, (int)bytes, 0x00027000);
 }
 
+// LDS reads as raw instructions, not waited for here: the compiler would hold every one until all copies in flight had
+// landed.  To it an output is written at once, so it has to stay in its register until `tie`: lds_reads.py looks at the built
+// code and the build fails where anything touches such a register before the wait.
 template <int OFFSET>
 __device__ __forceinline__ void lds_read_b128(uint32_t addr, u32x4& r) {
   asm volatile("ds_read_b128 %0, %1 offset:%2" : "=&v"(r) : "v"(addr), "n"(OFFSET));
