@@ -2,7 +2,6 @@
 // Every check here runs before anything is launched, so the error paths need no GPU.
 #include "hinm_internal.h"
 
-#include <algorithm>
 #include "prepared_layout.h"
 #include "hinm_calib.h"
 
@@ -511,8 +510,12 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
     // 1024..2048 columns on layers of a few hundred rows)
     const bool x_beyond_l2 = (double)shape->K * N * 2 > 3.5e6;
     const double l2_factor = !x_beyond_l2 ? 1.0 : N > 1024 ? 2.0 : (N > 512 && blocks_per_wg < 4) ? 1.5 : 1.0;
-    few_columns = 2.5 + units * (0.14 * shape->Kv + 40.0) * 1e-6 * l2_factor * pair_factor <
-                  (ring ? std::min(spmm_ring_prepared_us(a, false), tile_floor_us) : tile_floor_us);
+    // on tall layers of 32-row tiles that cost is 1.6 times the estimate (median of 430 drawn ones; 13664 x 3936, Kv = 496,
+    // N = 84 11.1 us, rings 8.7; 12640 x 13784, Kv = 1720, N = 96 31.5 and 17.0): said to the rings alone, whose estimate is
+    // of such layers
+    const double cost = units * (0.14 * shape->Kv + 40.0) * 1e-6 * l2_factor * pair_factor;
+    few_columns = 2.5 + cost < tile_floor_us &&
+                  !(ring && spmm_ring_prepared_us(a, false) <= 2.5 + cost * (shape->V == 32 ? 1.6 : 1.0));
   }
   if (a.tile_variant == 11 || a.tile_variant == 19 || (a.tile_variant == 0 && few_columns)) {
     if ((N + 15) / 16 > 65535) return HINM_ERR_UNSUPPORTED;

@@ -29,9 +29,12 @@ namespace {
 // Where the stored values and row numbers come from: the device-tuned form, or the arrays of a layer before its 2:4 step.
 enum RingSource { kRingPrepared = 0, kRingVectors = 1 };
 
+constexpr int kUnitLds = 160 * 1024;
+
 template <int SRC, int RB, int NWC, int NWK, int R>
 struct RingCfg {
   static constexpr bool SPARSE = SRC == kRingPrepared;
+  static constexpr int ROWS = RB, COLUMN_GROUPS = NWC, STEP_GROUPS = NWK, DEPTH = R;
   static constexpr int CBS = 2;                      // 32-column blocks of a wave
   static constexpr int WC = 32 * CBS;                // columns of a wave
   static constexpr int NB = NWC * WC;                // columns of a workgroup
@@ -69,8 +72,20 @@ struct RingCfg {
   static constexpr int BLOCKS_TOGETHER = NB == 256 ? 2 : 1;
   static_assert(NWK == 1 || NWK == 2 || NWK == 4, "groups of steps");
   static_assert(R == 3 || R == 4, "ring");
-  static_assert(LDS_BYTES <= 160 * 1024, "LDS of a compute unit");
+  static_assert(LDS_BYTES <= kUnitLds, "LDS of a compute unit");
+  static constexpr int SLOTS = 256 * (kUnitLds / LDS_BYTES);  // workgroups that run at once
 };
+
+// The forms (variants 20 to 24): 512 columns; 256, two groups of steps; 256; 128, two groups; 128, four groups on halves of
+// 128-row tiles.  Rings of four slots where the LDS has room for what runs at once.
+constexpr int form_depth(int SRC, int RB, int form) {
+  if (form == 4) return 3;
+  if (SRC == kRingVectors) return form == 2 || RB == 1 || (RB == 2 && form != 1) ? 4 : 3;
+  return form == 0 || form == 2 || RB <= 2 ? 4 : 3;
+}
+constexpr int kFormColumnGroups[5] = {8, 4, 4, 2, 2}, kFormStepGroups[5] = {1, 2, 1, 2, 4};
+template <int SRC, int RB, int FORM>
+using FormCfg = RingCfg<SRC, FORM == 4 ? 2 : RB, kFormColumnGroups[FORM], kFormStepGroups[FORM], form_depth(SRC, RB, FORM)>;
 
 __device__ __forceinline__ void buffer_copy16_to_lds(__amdgpu_buffer_rsrc_t r, uint32_t offset, uint8_t* lds_wave_base) {
   __builtin_amdgcn_raw_ptr_buffer_load_lds(r, (lds_void_t*)lds_wave_base, 16, (int)offset, 0, 0, 0);
@@ -569,17 +584,20 @@ __global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_vectors_rings_kernel(R
 //   start + (rounds of workgroups before the last) * (round + steps * full) + steps * (part + fill * more)
 // where steps are those of a wave and `fill` is the share of the last round's slots that are taken: a step is slower the
 // more units take part (clock, memory).  Fitted to 480 random layers (M, K 256..16384, N 65..8192, all tile heights, both
-// types; error 5 to 15 %); the form chosen by it is 0.7 % off the best of the first four on average.  Examples, us in the
-// order below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
+// types; error 5 to 15 %); the form chosen by it is 0.7 % off the best of the first four on average.  The last two of 32-row
+// tiles are fitted to 804 layers of those (error 11 and 9 %, the choice 0.2 % off the best): two workgroups of 128 columns
+// exceed the LDS of a unit by 2 KB, and two of 256 columns take as long side by side as one behind the other (2880 x 5888,
+// Kv = 2944, N = 256 17.6 us on the kernel for a moderate number of columns, 12.2 on 128 columns; 9856 x 2864, Kv = 720,
+// N = 288 19.4 on 128 columns, 14.6 on 256).  Examples, us in the order below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
 // 4096 x 4096, V = 128, N = 1024 29 / 20 / 20 / 18; 1984 x 6376, V = 64, Kv = 3184, N = 6033 92 / 82 / 77 / 109.
 struct RingForm {
-  int columns, groups, slots;  // slots: workgroups that run at once, by what their LDS leaves room for (0: no such form)
+  int columns, groups, slots;  // slots: workgroups of a round, as many as run at once or fewer (0: no such form)
   float start, full, part, more, round;
 };
 constexpr int kRingForms = 5;
 constexpr RingForm kForms[4][kRingForms] = {  // [RB - 1]
     {{512, 1, 256, 3.2f, 0.76f, 0.55f, 0.21f, 1.4f}, {256, 2, 256, 3.3f, 0.91f, 0.58f, 0.32f, 1.5f},
-     {256, 1, 512, 2.9f, 0.92f, 0.30f, 0.51f, 0.1f}, {128, 2, 512, 3.2f, 1.00f, 0.30f, 0.85f, 3.3f}},
+     {256, 1, 256, 3.3f, 0.39f, 0.31f, 0.07f, 0.35f}, {128, 2, 256, 3.4f, 0.50f, 0.35f, 0.15f, 1.7f}},
     {{512, 1, 256, 4.4f, 0.93f, 0.55f, 0.18f, 3.7f}, {256, 2, 256, 4.5f, 0.99f, 0.57f, 0.34f, 2.8f},
      {256, 1, 512, 4.3f, 0.99f, 0.31f, 0.44f, 2.1f}, {128, 2, 256, 3.8f, 0.59f, 0.38f, 0.20f, 2.3f}},
     {{512, 1, 256, 5.8f, 0.99f, 0.56f, 0.25f, 6.3f}, {256, 2, 256, 5.2f, 1.15f, 0.63f, 0.38f, 3.9f},
@@ -587,6 +605,21 @@ constexpr RingForm kForms[4][kRingForms] = {  // [RB - 1]
     {{512, 1, 256, 6.4f, 1.04f, 0.66f, 0.43f, 10.8f}, {256, 2, 256, 5.8f, 1.24f, 0.74f, 0.42f, 6.3f},
      {256, 1, 256, 5.9f, 0.62f, 0.43f, 0.16f, 5.4f}, {128, 2, 256, 4.9f, 0.81f, 0.56f, 0.30f, 4.4f},
      {128, 4, 256, 4.0f, 1.51f, 0.69f, 0.64f, 1.0f}}};
+
+// No more slots than the LDS of the form's configuration has room for.
+template <int SRC, int RB, int FORM>
+constexpr bool slots_hold(const RingForm& f) {
+  using C = FormCfg<SRC, RB, FORM>;
+  return f.columns == C::NB && f.groups == C::STEP_GROUPS && f.slots <= C::SLOTS;
+}
+template <int RB>
+constexpr bool prepared_forms_hold() {
+  const auto& f = kForms[RB - 1];
+  return slots_hold<kRingPrepared, RB, 0>(f[0]) && slots_hold<kRingPrepared, RB, 1>(f[1]) &&
+         slots_hold<kRingPrepared, RB, 2>(f[2]) && slots_hold<kRingPrepared, RB, 3>(f[3]) &&
+         (RB == 4 ? slots_hold<kRingPrepared, RB, 4>(f[4]) : f[4].slots == 0);
+}
+static_assert(prepared_forms_hold<1>() && prepared_forms_hold<2>() && prepared_forms_hold<3>() && prepared_forms_hold<4>());
 
 // Workgroups that share a tile: two of 64 rows each with four groups of steps (tiles of 128 rows only).
 constexpr int form_parts(const RingForm& f) { return f.groups == 4 ? 2 : 1; }
@@ -603,16 +636,25 @@ double form_us(const RingForm& f, int S, int tiles, int N) {
 // Four groups are the form for the fewest columns, estimated on such products alone, and need no margin; up to 320 of the
 // kernel's own blocks those are as good (11008 x 4096 at 50 %, N = 100, 344 blocks: 14.1 us there, 12.0 with four groups, 15.4
 // with two; 4096 x 4096, N = 512, 512 blocks 17.6, 13.7 and 15.8; N = 256, 256 blocks 8.4 and 9.5).
-int best_form(const RingForm (&forms)[kRingForms], bool mid, int S, int tiles, int N, double* us) {
+// `far_rows`: by rows_are_far.
+int best_form(const RingForm (&forms)[kRingForms], bool mid, int S, int tiles, int N, double* us, bool far_rows = false) {
   int best = -1;
   for (int i = 0; i < kRingForms; ++i) {
     const bool four = forms[i].groups == 4;
     if (forms[i].slots == 0 || (mid ? forms[i].groups == 1 : four)) continue;
     if (four && (S < 5 || (int64_t)tiles * 2 * ((N + 63) / 64) <= 320)) continue;
-    const double t = form_us(forms[i], S, tiles, N) * (!mid || four ? 1.0 : &forms == &kForms[0] ? 1.16 : 1.08);
+    const double t = form_us(forms[i], S, tiles, N) * (!mid || four ? 1.0 : &forms == &kForms[0] ? 1.16 : 1.08) *
+                     (far_rows && i == 2 ? 1.1 : 1.0);
     if (best < 0 || t < *us) *us = t, best = i;
   }
   return best;
+}
+
+// Tiles of 32 rows that keep few of many rows of X find less of what they gather in L2 with 256 columns than with 512: beyond
+// 32 MB of X with an eighth kept the former take 1.33 times their estimate, the latter 1.24 (16 drawn layers; 6336 x 12368,
+// Kv = 1544, N = 4704 222 and 184 us).
+bool rows_are_far(const PreparedArgs& a) {
+  return a.s.V == 32 && a.s.K >= 6 * (int64_t)a.s.Kv && (double)a.s.K * a.N * 2 > 32e6;
 }
 
 template <bool MID, int DT, int RB, int NWC, int NWK, int R>
@@ -622,9 +664,9 @@ constexpr auto ring_kernel() {
 }
 
 // The tiles [first, first + count) of the layer.
-template <bool MID, int DT, int RB, int NWC, int NWK, int R>
+template <bool MID, int DT, class C>
 hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int count) {
-  using C = RingCfg<kRingPrepared, RB, NWC, NWK, R>;
+  constexpr int RB = C::ROWS, NWC = C::COLUMN_GROUPS, NWK = C::STEP_GROUPS, R = C::DEPTH;
   const PreparedLayout L = prepared_layout(a.s);
   const int n_blocks = (a.N + C::NB - 1) / C::NB;
   const int parts = L.RB / RB;
@@ -664,15 +706,15 @@ template <bool MID, int DT, int RB>
 hipError_t launch_tiles(const PreparedArgs& a, hipStream_t stream, int form, int first, int count) {
   switch (form) {
     case 0:
-      if constexpr (!MID) return launch_form<false, DT, RB, 8, 1, 4>(a, stream, first, count);
+      if constexpr (!MID) return launch_form<false, DT, FormCfg<kRingPrepared, RB, 0>>(a, stream, first, count);
       break;
-    case 1: return launch_form<MID, DT, RB, 4, 2, RB <= 2 ? 4 : 3>(a, stream, first, count);
+    case 1: return launch_form<MID, DT, FormCfg<kRingPrepared, RB, 1>>(a, stream, first, count);
     case 2:
-      if constexpr (!MID) return launch_form<false, DT, RB, 4, 1, 4>(a, stream, first, count);
+      if constexpr (!MID) return launch_form<false, DT, FormCfg<kRingPrepared, RB, 2>>(a, stream, first, count);
       break;
-    case 3: return launch_form<MID, DT, RB, 2, 2, RB <= 2 ? 4 : 3>(a, stream, first, count);
+    case 3: return launch_form<MID, DT, FormCfg<kRingPrepared, RB, 3>>(a, stream, first, count);
     case 4:
-      if constexpr (RB == 4) return launch_form<true, DT, 2, 2, 4, 3>(a, stream, first, count);
+      if constexpr (RB == 4) return launch_form<true, DT, FormCfg<kRingPrepared, RB, 4>>(a, stream, first, count);
       break;
     default: break;
   }
@@ -684,17 +726,19 @@ hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
   if (a.tile_variant) return launch_tiles<false, DT, RB>(a, stream, a.tile_variant - kRingFirstVariant, 0, L.T);
   double us = 0;
-  const int form = best_form(kForms[RB - 1], mid, L.S, L.T, a.N, &us);
+  const int form = best_form(kForms[RB - 1], mid, L.S, L.T, a.N, &us, rows_are_far(a));
   if (mid) return launch_tiles<true, DT, RB>(a, stream, form, 0, L.T);
   // Whole rounds of 512-column blocks, and the tiles that are left over in the form that suits them, behind them
-  // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 64.8 us, the best single launch 67.9).
+  // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 64.8 us, the best single launch 67.9).  With 32-row tiles, whose passes are the
+  // shortest, by 1 us more than estimated (61 of 81 drawn splits are left, 0.93 times the best single launch's time on their
+  // mean; without that some lose a tenth: 11584 x 2240, Kv = 1120, N = 352 1.09 times).
   const int wide = (a.N + 511) / 512;
   const int64_t rounds = (int64_t)L.T * wide / 256;
   const int whole = (int)(rounds * 256 / wide);
   if (rounds > 0 && whole < L.T) {
     double rest_us = 0;
-    const int rest_form = best_form(kForms[RB - 1], false, L.S, L.T - whole, a.N, &rest_us);
-    if (form_us(kForms[RB - 1][0], L.S, whole, a.N) + rest_us < us) {
+    const int rest_form = best_form(kForms[RB - 1], false, L.S, L.T - whole, a.N, &rest_us, rows_are_far(a));
+    if (form_us(kForms[RB - 1][0], L.S, whole, a.N) + rest_us + (RB == 1 ? 1.0 : 0.0) < us) {
       const hipError_t e = launch_tiles<false, DT, RB>(a, stream, 0, 0, whole);
       return e != hipSuccess ? e : launch_tiles<false, DT, RB>(a, stream, rest_form, whole, L.T - whole);
     }
@@ -716,7 +760,7 @@ bool spmm_ring_prepared_supported(const PreparedArgs& a) {
 
 double spmm_ring_prepared_us(const PreparedArgs& a, bool mid) {
   double us = 0;
-  best_form(kForms[a.s.V / 32 - 1], mid, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us);
+  best_form(kForms[a.s.V / 32 - 1], mid, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us, rows_are_far(a));
   return us;
 }
 
@@ -756,13 +800,22 @@ constexpr RingForm kVectorForms[4][kRingForms] = {  // [RB - 1]
     {{512, 1, 256, 7.2f, 1.72f, 1.05f, 0.53f, 10.1f}, {256, 2, 0, 0.0f, 0.0f, 0.0f, 0.0f, 0.0f},
      {256, 1, 256, 6.4f, 1.02f, 0.68f, 0.37f, 6.2f}, {128, 2, 256, 5.8f, 1.74f, 0.86f, 0.57f, 3.1f}}};
 
-template <int DT, int RB, int NWC, int NWK, int R>
+template <int RB>
+constexpr bool vector_forms_hold() {
+  const auto& f = kVectorForms[RB - 1];
+  bool second = f[1].slots == 0;
+  if constexpr (RB <= 2) second = slots_hold<kRingVectors, RB, 1>(f[1]);
+  return slots_hold<kRingVectors, RB, 0>(f[0]) && second && slots_hold<kRingVectors, RB, 2>(f[2]) &&
+         slots_hold<kRingVectors, RB, 3>(f[3]) && f[4].slots == 0;
+}
+static_assert(vector_forms_hold<1>() && vector_forms_hold<2>() && vector_forms_hold<3>() && vector_forms_hold<4>());
+
+template <int DT, class C>
 hipError_t launch_vectors_form(const VectorsArgs& a, hipStream_t stream) {
-  using C = RingCfg<kRingVectors, RB, NWC, NWK, R>;
   const int T = a.s.M / a.s.V;
   const int n_blocks = (a.N + C::NB - 1) / C::NB;
   const int work_per_xcd = (int)(((int64_t)n_blocks * T + 7) / 8);
-  constexpr auto kernel = spmm_vectors_rings_kernel<DT, RB, NWC, NWK, R>;
+  constexpr auto kernel = spmm_vectors_rings_kernel<DT, C::ROWS, C::COLUMN_GROUPS, C::STEP_GROUPS, C::DEPTH>;
   if (hipError_t e = raise_lds_limit<kernel>(C::LDS_BYTES); e != hipSuccess) return e;
   const int64_t row_bytes = a.ldx * 2;
   RingParams p{};
@@ -793,12 +846,12 @@ hipError_t launch_vectors_rb(const VectorsArgs& a, hipStream_t stream) {
   double us = 0;
   switch (a.variant ? a.variant - kRingFirstVariant
                     : best_form(kVectorForms[RB - 1], false, (a.s.Kv + 63) / 64, a.s.M / a.s.V, a.N, &us)) {
-    case 0: return launch_vectors_form<DT, RB, 8, 1, RB <= 2 ? 4 : 3>(a, stream);
+    case 0: return launch_vectors_form<DT, FormCfg<kRingVectors, RB, 0>>(a, stream);
     case 1:
-      if constexpr (RB <= 2) return launch_vectors_form<DT, RB, 4, 2, RB == 1 ? 4 : 3>(a, stream);
+      if constexpr (RB <= 2) return launch_vectors_form<DT, FormCfg<kRingVectors, RB, 1>>(a, stream);
       break;
-    case 2: return launch_vectors_form<DT, RB, 4, 1, 4>(a, stream);
-    case 3: return launch_vectors_form<DT, RB, 2, 2, RB <= 2 ? 4 : 3>(a, stream);
+    case 2: return launch_vectors_form<DT, FormCfg<kRingVectors, RB, 2>>(a, stream);
+    case 3: return launch_vectors_form<DT, FormCfg<kRingVectors, RB, 3>>(a, stream);
     default: break;
   }
   return hipErrorInvalidValue;

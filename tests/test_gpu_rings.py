@@ -77,6 +77,23 @@ def test_form_by_shape(M, K, V, Kv, N, form):
     assert n == 1 and form in text, text
 
 
+@pytest.mark.parametrize("M,K,Kv,N,form", [
+    (9856, 2864, 720, 288, "NB=256,NWK=1"),       # 924 workgroups of 128 columns are four rounds, not two
+    (2880, 5888, 2944, 256, "NB=128,NWK=2"),      # 180 of them one short round
+    (12640, 13784, 1720, 96, "NB=128,NWK=2"),     # 395: two rounds, half of what the 16-row kernel takes
+    (11584, 2240, 1120, 352, "NB=256,NWK=1"),     # no launch of its own for a short remainder
+    (6336, 12368, 1544, 4704, "NB=512,NWK=1"),    # few of many rows
+])
+def test_form_of_32_row_tiles(M, K, Kv, N, form):
+    """A unit's LDS holds one workgroup of 128 columns (82944 of 163840 bytes), not two."""
+    import paper_2407_20496_amd as hinm
+    ld = (N + 7) // 8 * 8
+    text, n = hinm.hinm_spmm_prepared_plan(M, K, 32, Kv, "f16", N, ld, ld)
+    assert n == 1 and "RB=1," + form in text and "private rings" in text, text
+    text, _ = hinm.hinm_spmm_prepared_plan(M, K, 32, Kv, "f16", N, ld, ld, flags=23 << 16)
+    assert 2 * int(text.split("lds=")[1]) > 160 * 1024
+
+
 def test_rings_leave_what_they_cannot_address():
     """Byte offsets into X are 32 bits wide: beyond, and below three steps, the staged tile kernel runs."""
     import paper_2407_20496_amd as hinm
