@@ -251,7 +251,7 @@ hipError_t launch_spmm_tile_prepared(const PreparedArgs& a, hipStream_t stream);
 // many columns, waves with private rings of gathered rows (spmm_rings.hip)
 constexpr int kRingFirstVariant = 20, kRingLastVariant = 24;  // that pin one of its forms
 bool spmm_ring_prepared_supported(const PreparedArgs& a);
-// `mid`: in the place of the kernel for a moderate number of columns (under its name, the forms that split the steps)
+// `mid`: in the place of the kernel for a moderate number of columns (the forms that split the steps)
 double spmm_ring_prepared_us(const PreparedArgs& a, bool mid);  // estimate for the form it would choose, with `mid` its margin
 hipError_t launch_spmm_ring_prepared(const PreparedArgs& a, bool mid, hipStream_t stream);
 // ... and for a layer before its 2:4 step

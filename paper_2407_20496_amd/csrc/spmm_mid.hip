@@ -528,17 +528,20 @@ static bool beats_rows16(const PreparedArgs& a) {
   return a.N > 128 || S <= 8 || S > 32 || blocks > 64;
 }
 
-// Many columns belong to the tile kernels, whose larger blocks gather less: the line lies at four workgroups per
-// unit (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there; 11008 x 4096, N = 300, 860 blocks: 25
-// and 38; N = 400, 1204 blocks: 44 and 36; 1024 x 1024, N = 1666, 432 blocks: 7.7 and 13.0; 512 x 5904, N = 3488,
-// 440 blocks: 24 and 42), at three with V % 64 != 0.  Where the tile kernel has one round of 64-row tiles, which is
-// a short one, it is at three for inputs that are taken one column block at a time (8192 x 8192, Kv = 2048, N =
-// 384, 768 blocks: 24.4 and 26.2; N = 448 28.4 and 26.4; 8192 x 4096, N = 512 32.6 and 25.7; 1728 x 6480, N = 2168,
-// 918 blocks: 25.1 and 22.5) unless two of them at a time leave no slot of a unit empty (4096 x 4096, N = 1024,
-// 1024 blocks: 24.5 and 25.8) and for passes of up to 16 steps (7872 x 1248, Kv = 624, N = 417, 861 blocks: 12.2
-// and 10.7), at two for up to four steps (14400 x 824, Kv = 208, N = 224, 900 blocks: 7.8 and 6.2); else at four
-// (16384 x 4096, N = 256, 1024 blocks: 24.2 and 26.6; 9088 x 1928, Kv = 960, N = 394, 994 blocks and a second round
-// of tiles: 15.4 and 21.3).
+// Many columns belong to the kernels with larger blocks, which gather less.  Beyond this line the private rings of
+// spmm_rings.hip serve them all, and within it where they are estimated ahead by a margin (of the examples the rings
+// have taken 8192 x 4096, N = 512 18.0 us; 1728 x 6480 19.3; 4096 x 4096, N = 1024 18.2; 7872 x 1248 9.2; 14400 x 824
+// 6.2; 16384 x 4096 18.3; 9088 x 1928 stays here).  It was drawn against the staged tile kernel, whose times the
+// examples give: at four workgroups per unit (4096 x 11008 at 50 %, N = 1024, 1024 blocks: 58 against 86 us there;
+// 11008 x 4096, N = 300, 860 blocks: 25 and 38; N = 400, 1204 blocks: 44 and 36; 1024 x 1024, N = 1666, 432 blocks:
+// 7.7 and 13.0; 512 x 5904, N = 3488, 440 blocks: 24 and 42), at three with V % 64 != 0.  Where the tile kernel has
+// one round of 64-row tiles, which is a short one, it is at three for inputs that are taken one column block at a
+// time (8192 x 8192, Kv = 2048, N = 384, 768 blocks: 24.4 and 26.2; N = 448 28.4 and 26.4; 8192 x 4096, N = 512 32.6
+// and 25.7; 1728 x 6480, N = 2168, 918 blocks: 25.1 and 22.5) unless two of them at a time leave no slot of a unit
+// empty (4096 x 4096, N = 1024, 1024 blocks: 24.5 and 25.8) and for passes of up to 16 steps (7872 x 1248, Kv = 624,
+// N = 417, 861 blocks: 12.2 and 10.7), at two for up to four steps (14400 x 824, Kv = 208, N = 224, 900 blocks: 7.8
+// and 6.2); else at four (16384 x 4096, N = 256, 1024 blocks: 24.2 and 26.6; 9088 x 1928, Kv = 960, N = 394, 994
+// blocks and a second round of tiles: 15.4 and 21.3).
 bool spmm_mid_prepared_preferred(const PreparedArgs& a) {
   if (a.N == 1 || a.ldx % 8 != 0 || a.ldy % 8 != 0) return false;
   if (a.N <= 128 && !beats_rows16(a)) return false;

@@ -564,15 +564,10 @@ __device__ __forceinline__ void ring_product(const RingParams& p) {
   store_staged_rows<V, C::NB, C::THREADS>(lds, Y, ldy, N, nb * C::NB, out_row);
 }
 
-// The two names under which it runs: spmm_mid_kernel where it takes the place of that kernel's own blocks (spmm_mid.hip),
-// spmm_tile_prepared_kernel beyond, for any number of columns.  Two waves a SIMD are asked for where one would do, too: with
-// more than 256 registers at hand the compiler parks fragments in accumulation registers before their LDS reads have landed.
+// Two waves a SIMD are asked for where one would do, too: with more than 256 registers at hand the compiler parks fragments in
+// accumulation registers before their LDS reads have landed.
 template <int DT, int RB, int NWC, int NWK, int R>
-__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_mid_kernel(RingParams p) {
-  ring_product<kRingPrepared, DT, RB, NWC, NWK, R>(p);
-}
-template <int DT, int RB, int NWC, int NWK, int R>
-__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_tile_prepared_kernel(RingParams p) {
+__global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_rings_kernel(RingParams p) {
   ring_product<kRingPrepared, DT, RB, NWC, NWK, R>(p);
 }
 template <int DT, int RB, int NWC, int NWK, int R>
@@ -657,25 +652,18 @@ bool rows_are_far(const PreparedArgs& a) {
   return a.s.V == 32 && a.s.K >= 6 * (int64_t)a.s.Kv && (double)a.s.K * a.N * 2 > 32e6;
 }
 
-template <bool MID, int DT, int RB, int NWC, int NWK, int R>
-constexpr auto ring_kernel() {
-  if constexpr (MID) return spmm_mid_kernel<DT, RB, NWC, NWK, R>;
-  else return spmm_tile_prepared_kernel<DT, RB, NWC, NWK, R>;
-}
-
 // The tiles [first, first + count) of the layer.
-template <bool MID, int DT, class C>
+template <int DT, class C>
 hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int count) {
-  constexpr int RB = C::ROWS, NWC = C::COLUMN_GROUPS, NWK = C::STEP_GROUPS, R = C::DEPTH;
+  constexpr int RB = C::ROWS, NWK = C::STEP_GROUPS, R = C::DEPTH;
   const PreparedLayout L = prepared_layout(a.s);
   const int n_blocks = (a.N + C::NB - 1) / C::NB;
   const int parts = L.RB / RB;
   const int work_per_xcd = (int)(((int64_t)n_blocks * count * parts + 7) / 8);
-  constexpr auto kernel = ring_kernel<MID, DT, RB, NWC, NWK, R>();
+  constexpr auto kernel = spmm_rings_kernel<DT, RB, C::COLUMN_GROUPS, NWK, R>;
   if (a.plan) {
-    plan_record(a.plan, "%s<DT=%d,RB=%d,NB=%d,NWK=%d,R=%d> private rings, tiles=%d..%d grid=%d block=%d lds=%d",
-                MID ? "spmm_mid_kernel" : "spmm_tile_prepared_kernel", DT, RB, C::NB, NWK, R, first, first + count - 1, work_per_xcd * 8,
-                C::THREADS, C::LDS_BYTES);
+    plan_record(a.plan, "spmm_rings_kernel<DT=%d,RB=%d,NB=%d,NWK=%d,R=%d> private rings, tiles=%d..%d grid=%d block=%d lds=%d", DT,
+                RB, C::NB, NWK, R, first, first + count - 1, work_per_xcd * 8, C::THREADS, C::LDS_BYTES);
     return hipSuccess;
   }
   if (hipError_t e = raise_lds_limit<kernel>(C::LDS_BYTES); e != hipSuccess) return e;
@@ -702,19 +690,15 @@ hipError_t launch_form(const PreparedArgs& a, hipStream_t stream, int first, int
   return hipGetLastError();
 }
 
-template <bool MID, int DT, int RB>
+template <int DT, int RB>
 hipError_t launch_tiles(const PreparedArgs& a, hipStream_t stream, int form, int first, int count) {
   switch (form) {
-    case 0:
-      if constexpr (!MID) return launch_form<false, DT, FormCfg<kRingPrepared, RB, 0>>(a, stream, first, count);
-      break;
-    case 1: return launch_form<MID, DT, FormCfg<kRingPrepared, RB, 1>>(a, stream, first, count);
-    case 2:
-      if constexpr (!MID) return launch_form<false, DT, FormCfg<kRingPrepared, RB, 2>>(a, stream, first, count);
-      break;
-    case 3: return launch_form<MID, DT, FormCfg<kRingPrepared, RB, 3>>(a, stream, first, count);
+    case 0: return launch_form<DT, FormCfg<kRingPrepared, RB, 0>>(a, stream, first, count);
+    case 1: return launch_form<DT, FormCfg<kRingPrepared, RB, 1>>(a, stream, first, count);
+    case 2: return launch_form<DT, FormCfg<kRingPrepared, RB, 2>>(a, stream, first, count);
+    case 3: return launch_form<DT, FormCfg<kRingPrepared, RB, 3>>(a, stream, first, count);
     case 4:
-      if constexpr (RB == 4) return launch_form<true, DT, FormCfg<kRingPrepared, RB, 4>>(a, stream, first, count);
+      if constexpr (RB == 4) return launch_form<DT, FormCfg<kRingPrepared, RB, 4>>(a, stream, first, count);
       break;
     default: break;
   }
@@ -724,10 +708,10 @@ hipError_t launch_tiles(const PreparedArgs& a, hipStream_t stream, int form, int
 template <int DT, int RB>
 hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
-  if (a.tile_variant) return launch_tiles<false, DT, RB>(a, stream, a.tile_variant - kRingFirstVariant, 0, L.T);
+  if (a.tile_variant) return launch_tiles<DT, RB>(a, stream, a.tile_variant - kRingFirstVariant, 0, L.T);
   double us = 0;
   const int form = best_form(kForms[RB - 1], mid, L.S, L.T, a.N, &us, rows_are_far(a));
-  if (mid) return launch_tiles<true, DT, RB>(a, stream, form, 0, L.T);
+  if (mid) return launch_tiles<DT, RB>(a, stream, form, 0, L.T);
   // Whole rounds of 512-column blocks, and the tiles that are left over in the form that suits them, behind them
   // (11008 x 4096 at 50 %, N = 2048, 344 blocks: 64.8 us, the best single launch 67.9).  With 32-row tiles, whose passes are the
   // shortest, by 1 us more than estimated (61 of 81 drawn splits are left, 0.93 times the best single launch's time on their
@@ -739,11 +723,11 @@ hipError_t launch_rb(const PreparedArgs& a, bool mid, hipStream_t stream) {
     double rest_us = 0;
     const int rest_form = best_form(kForms[RB - 1], false, L.S, L.T - whole, a.N, &rest_us, rows_are_far(a));
     if (form_us(kForms[RB - 1][0], L.S, whole, a.N) + rest_us + (RB == 1 ? 1.0 : 0.0) < us) {
-      const hipError_t e = launch_tiles<false, DT, RB>(a, stream, 0, 0, whole);
-      return e != hipSuccess ? e : launch_tiles<false, DT, RB>(a, stream, rest_form, whole, L.T - whole);
+      const hipError_t e = launch_tiles<DT, RB>(a, stream, 0, 0, whole);
+      return e != hipSuccess ? e : launch_tiles<DT, RB>(a, stream, rest_form, whole, L.T - whole);
     }
   }
-  return launch_tiles<false, DT, RB>(a, stream, form, 0, L.T);
+  return launch_tiles<DT, RB>(a, stream, form, 0, L.T);
 }
 
 }  // namespace

@@ -151,9 +151,11 @@ def test_pack_static_rejects_layers_beyond_its_array_before_touching_the_device(
 
 def test_plan_query_names_the_kernels_without_a_device():
     text, n = hinm.hinm_spmm_prepared_plan(16384, 16384, 128, 8192, "bf16", 8192, 8192, 8192)
-    assert n == 1 and text.startswith("spmm_tile_prepared_kernel<") and "NB=512" in text
+    assert n == 1 and text.startswith("spmm_rings_kernel<") and "NB=512" in text
     text, n = hinm.hinm_spmm_prepared_plan(11008, 4096, 128, 2048, "bf16", 2048, 2048, 2048)
-    assert n == 2 and text.count("spmm_tile_prepared_kernel") == 2 and "; " in text   # whole rounds + remainder
+    assert n == 2 and text.count("spmm_rings_kernel") == 2 and "; " in text   # whole rounds + remainder
+    text, n = hinm.hinm_spmm_prepared_plan(4096, 4096, 128, 128, "bf16", 4096, 4096, 4096)    # two steps
+    assert n == 1 and text.startswith("spmm_tile_prepared_kernel<")
     text, n = hinm.hinm_spmm_prepared_plan(3072, 768, 64, 384, "f16", 4096, 4096, 4096)
     assert n == 1 and text.startswith("spmm_panel_prepared_kernel<")
     text, n = hinm.hinm_spmm_prepared_plan(4096, 11008, 128, 5504, "bf16", 1, 1, 1)
@@ -280,7 +282,7 @@ def test_missing_library_fails_loudly(monkeypatch, tmp_path):
     (512, 7048, 128, 1760, 100, "spmm_rows16_prepared_kernel"),
     (4096, 4096, 64, 2048, 64, "spmm_mid_kernel"),
     (4096, 11008, 128, 2752, 32, "spmm_mid_kernel"),
-    (11008, 4096, 128, 2048, 100, "spmm_mid_kernel"),
+    (11008, 4096, 128, 2048, 100, "spmm_rings_kernel"),        # four groups of steps
 ])
 def test_few_columns_run_on_the_kernel_that_is_ahead_with_weights_from_memory(M, K, V, Kv, N, kernel):
     ld = (N + 7) // 8 * 8
@@ -314,23 +316,26 @@ def test_blocks_of_the_kernel_for_a_moderate_number_of_columns_fit_one_round(M, 
 
 
 @pytest.mark.parametrize("M,K,V,Kv,N,kernel", [
-    (1024, 1024, 64, 512, 1666, "spmm_mid_kernel"),
-    (2048, 2048, 128, 1024, 2048, "spmm_mid_kernel"),
-    (2048, 2048, 64, 512, 2056, "spmm_tile_prepared_kernel"),       # 1056 blocks
-    (8192, 4096, 64, 2048, 384, "spmm_mid_kernel"),
-    (8192, 4096, 64, 2048, 512, "spmm_tile_prepared_kernel"),       # one round of 64-row tiles
-    (4096, 4096, 64, 2048, 1024, "spmm_mid_kernel"),                # no empty slot, weights shared by two column blocks
-    (1728, 6480, 64, 1616, 2168, "spmm_tile_prepared_kernel"),
-    (7872, 1248, 64, 624, 417, "spmm_tile_prepared_kernel"),
-    (14400, 824, 64, 208, 224, "spmm_tile_prepared_kernel"),        # four steps
-    (10048, 840, 64, 208, 292, "spmm_mid_kernel"),                  # a second round
-    (9088, 1928, 64, 960, 394, "spmm_mid_kernel"),
-    (16384, 4096, 64, 2048, 256, "spmm_mid_kernel"),                # an input that a die's cache holds
+    # within its line the kernel for a moderate number of columns, unless rings are estimated ahead by a margin
+    (1024, 1024, 64, 512, 1666, "spmm_rings_kernel<DT=0,RB=2,NB=128,NWK=2"),     # 6.6 us, 7.7 on blocks of 64 x 64
+    (2048, 2048, 128, 1024, 2048, "spmm_rings_kernel<DT=0,RB=4,NB=128,NWK=2"),   # 10.8 and 14.6
+    (8192, 4096, 64, 2048, 384, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),     # 17.8 and 23.4
+    (4096, 4096, 64, 2048, 1024, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),    # 18.2 and 24.1
+    (16384, 4096, 64, 2048, 256, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),    # 18.3 and 23.2
+    (10048, 840, 64, 208, 292, "spmm_mid_kernel<DT=0,SRC=0,RB=2,CB=2"),          # four steps: never compared
+    (9088, 1928, 64, 960, 394, "spmm_mid_kernel<DT=0,SRC=0,RB=2,CB=2"),          # 994 blocks, within the margin
+    (4096, 4096, 64, 2048, 256, "spmm_mid_kernel<DT=0,SRC=0,RB=2,CB=2"),
+    # beyond it rings
+    (2048, 2048, 64, 512, 2056, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=1"),     # 1056 blocks; 11.9 us, staged tiles 13.4
+    (8192, 4096, 64, 2048, 512, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),     # 18.0 and 25.2
+    (1728, 6480, 64, 1616, 2168, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),    # 19.3 and 22.2
+    (7872, 1248, 64, 624, 417, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),      # 9.2 and 10.7
+    (14400, 824, 64, 208, 224, "spmm_rings_kernel<DT=0,RB=2,NB=256,NWK=2"),      # four steps; 6.2 and 6.3
 ])
 def test_line_between_a_moderate_number_of_columns_and_the_tile_kernels(M, K, V, Kv, N, kernel):
     ld = (N + 7) // 8 * 8
     text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "f16", N, ld, ld)
-    assert n == 1 and text.startswith(kernel + "<"), text
+    assert n == 1 and text.startswith(kernel + ","), text
 
 
 def test_python_calls_convert_arguments_as_ctypes_does():

@@ -126,12 +126,17 @@ def test_prepared_small_all_variants(M, K, V, Kv, N, dtype):
 
 
 @pytest.mark.parametrize("M,K,V,Kv,N,dtype", [
-    (2752, 1152, 32, 576, 2048, "f16"),      # 86 tiles x 4 wide blocks: 64 tiles in wide blocks, 22 in narrow ones
-    (11008, 1152, 128, 576, 2048, "bf16"),   # the same split with 128-row tiles
+    (2752, 1152, 32, 576, 2048, "f16"),      # 86 tiles x 4 wide blocks: one launch of 256-column blocks is estimated ahead
+    (11008, 1152, 128, 576, 2048, "bf16"),   # 64 tiles in wide blocks, 22 in narrow ones
     (5504, 1280, 64, 640, 1500, "f16"),      # 86 tiles x 3 wide blocks (ragged last block): 85 + 1
 ])
 def test_prepared_remainder_tiles_in_a_second_launch(M, K, V, Kv, N, dtype):
-    """Layers whose wide blocks make whole rounds plus a small remainder are launched in two parts."""
+    """Layers whose wide blocks make whole rounds plus a small remainder are launched in two parts (the staged tile kernel,
+    pinned here, in one)."""
+    import paper_2407_20496_amd as hinm
+    ld = (N + 7) // 8 * 8
+    text, launches = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld)
+    assert launches == (1 if V == 32 else 2) and text.count("spmm_rings_kernel<") == launches, text
     _check(synth.small_case(M, K, V, Kv, N, dtype, 83), N, [0, 3, 16])
 
 
@@ -292,10 +297,11 @@ def test_tile_kernel_parts_run_and_store_nothing():
     import torch
     import paper_2407_20496_amd as hinm
     from tests import gpu_util as gu
-    shapes = [(4096, 1024, 128, 512, 1100, "bf16"), (2048, 2048, 64, 512, 2056, "f16")]   # both run on the tile kernel
+    # the staged tile kernel's parts; the whole products run on private rings
+    shapes = [(4096, 1024, 128, 512, 1100, "bf16"), (2048, 2048, 64, 512, 2056, "f16")]
     for (M, K, V, Kv, N, dtype) in shapes:
         ld = (N + 7) // 8 * 8
-        assert "spmm_tile_prepared_kernel" in hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld, 0)[0]
+        assert "spmm_rings_kernel" in hinm.hinm_spmm_prepared_plan(M, K, V, Kv, dtype, N, ld, ld, 0)[0]
         case = synth.small_case(M, K, V, Kv, N, dtype, 77)
         vals, nm, vec = orc.pack(case.weights(), case.dtype, V, Kv)
         p = gu.upload_packed(M, K, V, Kv, dtype, vals, nm, vec)

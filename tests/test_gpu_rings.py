@@ -75,6 +75,7 @@ def test_form_by_shape(M, K, V, Kv, N, form):
     ld = (N + 7) // 8 * 8
     text, n = hinm.hinm_spmm_prepared_plan(M, K, V, Kv, "bf16", N, ld, ld)
     assert n == 1 and form in text, text
+    assert text.startswith("spmm_mid_kernel<" if form == "SRC=0" else "spmm_rings_kernel<"), text
 
 
 @pytest.mark.parametrize("M,K,Kv,N,form", [
