@@ -295,10 +295,10 @@ class CaseRun:
         return wall / steps, ev / steps
 
     def tile_parts(self, steps):
-        """Where the layer's tile kernel spends its time: the same launch with only its copy stream, and with only
+        """Where the layer's staged tile kernel spends its time: the same launch with only its copy stream, and with only
         its LDS reads and MFMAs (hinm_calib_tile_part), each graph-timed over the rotated buffer sets.  None for a
-        workload that does not run on one tile-kernel launch per layer."""
-        if not self.use_prepared or self.variant or "spmm_tile_prepared_kernel" not in self.kernels \
+        workload that does not run on one launch of that kernel per layer (private rings have no such parts)."""
+        if not self.use_prepared or self.variant or "spmm_tile_prepared_kernel<" not in self.kernels \
                 or self.kernel_launches_per_step != self.n_layers:
             return None
         hinm, c, out = self.hinm, self.c, {}
@@ -357,12 +357,13 @@ class CaseRun:
         self.torch.cuda.empty_cache()
 
 
-def stored_traffic(key, canonical):
-    """HBM bytes per launch from the committed rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summaries."""
+def stored_traffic(key, canonical, kernels):
+    """HBM bytes per launch from the committed rocprofv3 --pmc FETCH_SIZE / WRITE_SIZE summaries, where they are of a kernel
+    that runs now."""
     try:
         with open(os.path.join(ROOT, "profiles", "traffic.json")) as f:
             tr = json.load(f).get(key if not canonical else key + "-canonical")
-        if tr:
+        if tr and tr["kernel"] + "<" in kernels:
             return tr["fetch_bytes"] + tr["write_bytes"], "stored summary, not measured in this run: " + tr.get("source", "")
     except (OSError, ValueError):
         pass
@@ -504,7 +505,7 @@ def main():
         if live_traffic is not None:
             roofline["traffic"], roofline["traffic_source"] = live_traffic
         else:
-            roofline["traffic"], roofline["traffic_source"] = stored_traffic(args.workload, args.canonical)
+            roofline["traffic"], roofline["traffic_source"] = stored_traffic(args.workload, args.canonical, run.kernels)
         if roofline["traffic"]:
             roofline["traffic_over_algorithmic"] = round(roofline["traffic"] / (run.bytes_step / n_layers), 2)
 
