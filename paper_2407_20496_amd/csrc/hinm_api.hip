@@ -340,12 +340,16 @@ hinm_status hinm_spmm_vectors(const hinm_shape* shape, int32_t N, const void* va
   return e == hipSuccess ? HINM_OK : HINM_ERR_DEVICE;
 }
 
+// Which kernel family a prepared call runs on; everything that can make the call fail is decided here, on the
+// host, before anything is launched (hinm_chain validates every layer with it before its first launch).
+enum class PreparedRoute { Mid, MidRing, Rows16, Skinny, Panel, Tile, TileRing };
+
 static hinm_status check_prepared_call(const hinm_shape* shape, int32_t N, const void* prepared, const void* X,
                                        int64_t ldx, const void* Y, int64_t ldy, uint32_t flags, void* workspace,
-                                       size_t workspace_bytes);
+                                       size_t workspace_bytes, PreparedRoute* route);
 static hinm_status run_prepared(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                 void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes,
-                                hipStream_t stream, LaunchPlan* plan);
+                                PreparedRoute route, hipStream_t stream, LaunchPlan* plan);
 
 static hinm_status check_chain(int32_t L, const hinm_layer* layers, int32_t N, size_t* bytes_per_buffer) {
   if (!layers) return HINM_ERR_NULL;
@@ -388,12 +392,14 @@ hinm_status hinm_chain(int32_t L, const hinm_layer* layers, int32_t N, const voi
   // (13.6 -> 8.9 us behind an 11008 x 4096 layer)
   const int64_t ldh = N == 1 ? 1 : (N + 7) / 8 * 8;
   // validate every layer's call before launching the first one
+  constexpr int kKeptRoutes = 8;
+  PreparedRoute routes[kKeptRoutes], route;  // of the first layers; the others' are worked out again
   for (int l = 0; l < L; ++l) {
     const void* in = (l == 0) ? X : scratch;
     void* out = (l == L - 1) ? Y : scratch;
     if (layers[l].prepared)
       st = check_prepared_call(&layers[l].shape, N, layers[l].prepared, in, l == 0 ? ldx : ldh, out,
-                               l == L - 1 ? ldy : ldh, layers[l].flags, nullptr, 0);
+                               l == L - 1 ? ldy : ldh, layers[l].flags, nullptr, 0, &(l < kKeptRoutes ? routes[l] : route));
     else
       st = check_spmm(&layers[l].shape, N, layers[l].vals, layers[l].nm_idx, layers[l].vec_idx, in,
                       l == 0 ? ldx : ldh, out, l == L - 1 ? ldy : ldh, layers[l].flags);
@@ -408,7 +414,9 @@ hinm_status hinm_chain(int32_t L, const hinm_layer* layers, int32_t N, const voi
     const int64_t ld_out = last ? ldy : ldh;
     const hinm_layer& ly = layers[l];
     if (ly.prepared) {
-      st = run_prepared(&ly.shape, N, ly.prepared, in, ld_in, out, ld_out, ly.flags, nullptr, 0,
+      if (l < kKeptRoutes) route = routes[l];
+      else check_prepared_call(&ly.shape, N, ly.prepared, in, ld_in, out, ld_out, ly.flags, nullptr, 0, &route);
+      st = run_prepared(&ly.shape, N, ly.prepared, in, ld_in, out, ld_out, ly.flags, nullptr, 0, route,
                         static_cast<hipStream_t>(stream), nullptr);
     } else {
       SpmmArgs a{ly.shape, N, ly.vals, ly.nm_idx, ly.vec_idx, ly.pi_in, ly.pi_out, in, ld_in, out, ld_out,
@@ -454,10 +462,6 @@ hinm_status hinm_spmm_prepared_workspace(const hinm_shape* shape, int32_t N, siz
   *workspace_bytes = (N <= 32) ? skinny_prepared_workspace_bytes(*shape, N) : 0;
   return HINM_OK;
 }
-
-// Which kernel family a prepared call runs on; everything that can make the call fail is decided here, on the
-// host, before anything is launched (hinm_chain validates every layer with it before its first launch).
-enum class PreparedRoute { Mid, MidRing, Rows16, Skinny, Panel, Tile, TileRing };
 
 static PreparedArgs prepared_args(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                   void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes) {
@@ -540,7 +544,7 @@ static hinm_status route_prepared(const PreparedArgs& a, PreparedRoute* route, b
 
 static hinm_status check_prepared_call(const hinm_shape* shape, int32_t N, const void* prepared, const void* X,
                                        int64_t ldx, const void* Y, int64_t ldy, uint32_t flags, void* workspace,
-                                       size_t workspace_bytes) {
+                                       size_t workspace_bytes, PreparedRoute* route) {
   size_t need = 0;
   hinm_status st = hinm_prepare_sizes(shape, &need);
   if (st != HINM_OK) return st;
@@ -549,20 +553,16 @@ static hinm_status check_prepared_call(const hinm_shape* shape, int32_t N, const
   if (N > 1 && (ldx % 8 != 0 || ldy % 8 != 0)) return HINM_ERR_SHAPE;
   if (!aligned(prepared, 256) || !aligned(X, 16) || !aligned(Y, 16)) return HINM_ERR_SHAPE;
   if (flags & ~(uint32_t)(HINM_EPI_RELU | HINM_OUT_F32 | HINM_VARIANT_MASK)) return HINM_ERR_UNSUPPORTED;
-  PreparedRoute route;
   return route_prepared(prepared_args(shape, N, prepared, X, ldx, const_cast<void*>(Y), ldy, flags, workspace,
-                                      workspace_bytes), &route);
+                                      workspace_bytes), route);
 }
 
-// The call has passed check_prepared_call.
+// The call has passed check_prepared_call, which found its route (once a call: with up to three estimates it costs 0.1 us).
 static hinm_status run_prepared(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                 void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes,
-                                hipStream_t stream, LaunchPlan* plan) {
+                                PreparedRoute route, hipStream_t stream, LaunchPlan* plan) {
   PreparedArgs a = prepared_args(shape, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes);
   a.plan = plan;
-  PreparedRoute route;
-  hinm_status st = route_prepared(a, &route);
-  if (st != HINM_OK) return st;
   hipError_t e = hipSuccess;
   switch (route) {
     case PreparedRoute::Mid: e = launch_spmm_mid_prepared(a, stream); break;
@@ -579,9 +579,10 @@ static hinm_status run_prepared(const hinm_shape* shape, int32_t N, const void* 
 hinm_status hinm_spmm_prepared(const hinm_shape* shape, int32_t N, const void* prepared, const void* X, int64_t ldx,
                                void* Y, int64_t ldy, uint32_t flags, void* workspace, size_t workspace_bytes,
                                void* stream) {
-  hinm_status st = check_prepared_call(shape, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes);
+  PreparedRoute route;
+  hinm_status st = check_prepared_call(shape, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes, &route);
   if (st != HINM_OK) return st;
-  return run_prepared(shape, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes,
+  return run_prepared(shape, N, prepared, X, ldx, Y, ldy, flags, workspace, workspace_bytes, route,
                       static_cast<hipStream_t>(stream), nullptr);
 }
 
@@ -591,10 +592,11 @@ hinm_status hinm_spmm_prepared_plan(const hinm_shape* shape, int32_t N, int64_t 
   text[0] = 0;
   // stand-ins with the alignment of real buffers: a dry run dereferences nothing
   void* const fake = reinterpret_cast<void*>(uintptr_t{1} << 20);
-  hinm_status st = check_prepared_call(shape, N, fake, fake, ldx, fake, ldy, flags, fake, ~size_t{0});
+  PreparedRoute route;
+  hinm_status st = check_prepared_call(shape, N, fake, fake, ldx, fake, ldy, flags, fake, ~size_t{0}, &route);
   if (st != HINM_OK) return st;
   LaunchPlan plan{text, text_bytes};
-  st = run_prepared(shape, N, fake, fake, ldx, fake, ldy, flags, fake, ~size_t{0}, nullptr, &plan);
+  st = run_prepared(shape, N, fake, fake, ldx, fake, ldy, flags, fake, ~size_t{0}, route, nullptr, &plan);
   if (launches) *launches = plan.launches;
   return st;
 }
@@ -603,11 +605,11 @@ hinm_status hinm_calib_tile_part(const hinm_shape* shape, int32_t N, const void*
                                  int32_t part, void* stream) {
   // Y is never written: any aligned non-NULL stand-in passes the checks
   void* const no_y = reinterpret_cast<void*>(uintptr_t{1} << 20);
-  hinm_status st = check_prepared_call(shape, N, prepared, X, ldx, no_y, (N + 7) / 8 * 8, 0, nullptr, 0);
+  PreparedRoute route;
+  hinm_status st = check_prepared_call(shape, N, prepared, X, ldx, no_y, (N + 7) / 8 * 8, 0, nullptr, 0, &route);
   if (st != HINM_OK) return st;
   if (part != 1 && part != 2) return HINM_ERR_UNSUPPORTED;
   PreparedArgs a = prepared_args(shape, N, prepared, X, ldx, no_y, (N + 7) / 8 * 8, 0, nullptr, 0);
-  PreparedRoute route;
   st = route_prepared(a, &route, false);
   if (st != HINM_OK) return st;
   if (route != PreparedRoute::Tile) return HINM_ERR_UNSUPPORTED;

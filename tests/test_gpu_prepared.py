@@ -357,3 +357,30 @@ def test_chain_of_one_column(forms):
     hinm.hinm_chain(layers, 1, gu.dev_bits(Xb), 1, Y, 1, scratch, nbytes)
     torch.cuda.synchronize()
     assert np.array_equal(gu.host_bits(Y), h.reshape(64, 1))
+
+
+def test_chain_of_ten_layers():
+    """More layers than a chain keeps routes of (eight): every layer as its own call, bit for bit."""
+    import torch
+    import paper_2407_20496_amd as hinm
+    from tests import gpu_util as gu
+    dtype, N, RELU = "bf16", 72, 1       # every layer scales by about a tenth: ten of them leave the range of f16
+    sizes = [96, 64, 128, 64, 192, 64, 64, 128, 96, 64, 160]      # K of layer l, M of layer l - 1
+    layers, h, keep = [], None, []
+    for l in range(10):
+        M, K = sizes[l + 1], sizes[l]
+        case = synth.small_case(M, K, 32, K // 2, N, dtype, 140 + l)
+        p = gu.gpu_pack(case.weights(), dtype, 32, K // 2)
+        pr = gu.gpu_prepare(p, case.pi_in(), case.pi_out())
+        if l == 0:
+            Xb = h = case.activations()
+        flags = RELU if l % 2 == 0 else 0
+        h = gu.gpu_spmm_prepared(pr, h, flags)
+        keep.append(pr)
+        layers.append(hinm.Layer(M, K, 32, K // 2, dtype, None, None, None, flags=flags, prepared=pr.buf))
+    nbytes = hinm.hinm_chain_sizes(layers, N)
+    scratch = torch.full((nbytes,), 0x7B, dtype=torch.uint8, device=gu.DEV)
+    Y = torch.full((160, N), 0x7B7B, dtype=torch.int16, device=gu.DEV)
+    hinm.hinm_chain(layers, N, gu.dev_bits(Xb), N, Y, N, scratch, nbytes)
+    torch.cuda.synchronize()
+    assert h.any() and np.array_equal(gu.host_bits(Y), h)
