@@ -794,7 +794,7 @@ def bench_vectors(args, torch, hinm, dev, c):
         ach = flops / (kernel_ms * 1e-3) / 1e12
         roofline = {"bound": "mfma", "achieved": round(ach, 1), "peak": MFMA_DENSE_PEAK_TFLOPS, "unit": "TFLOP/s",
                     "frac": round(ach / MFMA_DENSE_PEAK_TFLOPS, 4), "traffic": None}
-    roofline.update({"kernel": "spmm_vectors_kernel", "kernel_ms_avg": round(kernel_ms, 6),
+    roofline.update({"kernel": "hinm_spmm_vectors (kernel chosen by the library)", "kernel_ms_avg": round(kernel_ms, 6),
                      "algorithmic_bytes_per_launch": bytes_step, "stored_value_flops_per_launch": flops})
     out = {"metric": "hinm_spmm_dense_equiv_tflops", "value": round(2.0 * c.M * c.K * N / (ms_per_step * 1e-3) / 1e12, 3),
            "unit": "TFLOP/s", "n_gpus": 1, "steps": steps, "warmup": warmup, "ms_per_step": round(ms_per_step, 6),
