@@ -67,8 +67,13 @@ struct RingCfg {
   static constexpr int LOOP_OR_EPI = LOOP_BYTES > EPI_BYTES ? LOOP_BYTES : EPI_BYTES;
   static constexpr int LDS_BYTES = LOOP_OR_EPI > SUM_BYTES ? LOOP_OR_EPI : SUM_BYTES;
   // 256-column blocks run two side by side on the same tiles of a die: its 32 units then fetch 16 tiles and two column
-  // panels, not 32 tiles and one (4096 x 4096, V = 128, N = 2048 28.3 -> 25.2 us, 4096 x 11008 56.8 -> 55.2).  A panel of
-  // 512 columns is the larger part of what they fetch and stays alone (16384 x 16384, N = 8192 1200 against 1260).
+  // panels, not 32 tiles and one (4096 x 4096, V = 128, N = 2048 28.6 -> 25.2 us with two groups of steps, 4096 x 11008
+  // 57.0 -> 55.3; V = 64, 8192 x 4096, N = 2048 63.0 -> 60.3 with one).  The smaller the stored values of a tile are beside
+  // the panel, the less there is to share.  Mean over 12 layers (M, K 2048..11008, N 1024..4096) of one block alone over two
+  // together, two groups and one: V = 128 1.04 and 1.02, V = 96 1.01 and 1.00, V = 64 1.01 and 1.01, V = 32 0.99 and 0.97
+  // (2048 x 8192, Kv = 2048, N = 4096 50.0 us alone, 56.4 together; 4096 x 4096, N = 1024 27.6 and 26.6); before 2:4, V = 128
+  // to 32, one group 1.03, 1.01, 1.02, 1.01.  A panel of 512 columns is the larger part of what they fetch and stays alone
+  // (16384 x 16384, N = 8192 1200 against 1260).
   static constexpr int BLOCKS_TOGETHER = NB == 256 ? 2 : 1;
   static_assert(NWK == 1 || NWK == 2 || NWK == 4, "groups of steps");
   static_assert(R == 3 || R == 4, "ring");

@@ -315,11 +315,13 @@ hipError_t launch_cfg(const PreparedArgs& a, hipStream_t stream, int tile_base =
   return hipGetLastError();
 }
 
-// By shape.  Wide column blocks halve the re-reads of the stored values when there are enough of them
-// to fill the chip.  Waves of 32 columns (twice as many waves per workgroup) hide the latency of a stage's
-// copies better and cost 40 % more LDS reads per MFMA: they win wherever a compute unit holds a single
-// workgroup and the layer is not large enough to be bound by LDS and L2 throughput (measured on the
-// encoder, convolution and MLP shapes: 5 to 20 %; the 16384 x 16384 x 8192 layer is 2 % slower with them).
+// By shape.  The lines below were drawn when this kernel served every product with many columns; what reaches it
+// now has one or two steps, or an input beyond the 4 GB that private rings (spmm_rings.hip) address.  Wide column
+// blocks halve the re-reads of the stored values when there are enough of them to fill the chip.  Waves of 32
+// columns (twice as many waves per workgroup) hide the latency of a stage's copies better and cost 40 % more LDS
+// reads per MFMA: they win wherever a compute unit holds a single workgroup and the layer is not large enough to be
+// bound by LDS and L2 throughput (measured on the encoder, convolution and MLP shapes: 5 to 20 %; the 16384 x 16384
+// x 8192 layer is 2 % slower with them).
 // A round of workgroups is one serial pass over the kept columns however few workgroups it holds, and a pass of
 // a 512-column block costs about 1.35 passes of a 256-column block (128-row tiles, whose workgroups sit alone
 // on a compute unit).  True when the 256-column blocks need fewer passes by that count (11008 x 4096 at
