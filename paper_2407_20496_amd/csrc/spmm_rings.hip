@@ -588,8 +588,9 @@ __global__ __launch_bounds__(NWC * NWK * 64, 2) void spmm_vectors_rings_kernel(R
 // tiles are fitted to 804 layers of those (error 11 and 9 %, the choice 0.2 % off the best): two workgroups of 128 columns
 // exceed the LDS of a unit by 2 KB, and two of 256 columns take as long side by side as one behind the other (2880 x 5888,
 // Kv = 2944, N = 256 17.6 us on the kernel for a moderate number of columns, 12.2 on 128 columns; 9856 x 2864, Kv = 720,
-// N = 288 19.4 on 128 columns, 14.6 on 256).  Examples, us in the order below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 / 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723;
-// 4096 x 4096, V = 128, N = 1024 29 / 20 / 20 / 18; 1984 x 6376, V = 64, Kv = 3184, N = 6033 92 / 82 / 77 / 109.
+// N = 288 19.4 on 128 columns, 14.6 on 256).  Examples, us in the order below: 4096 x 11008 at 50 %, N = 2048 67 / 53 / 57 /
+// 75; 16384 x 16384 at 50 %, N = 8192 1178 / 1306 / 1375 / 1723; 4096 x 4096, V = 128, N = 1024 29 / 20 / 20 / 18; 1984 x
+// 6376, V = 64, Kv = 3184, N = 6033 92 / 82 / 77 / 109.
 struct RingForm {
   int columns, groups, slots;  // slots: workgroups of a round, as many as run at once or fewer (0: no such form)
   float start, full, part, more, round;
@@ -632,7 +633,8 @@ double form_us(const RingForm& f, int S, int tiles, int N) {
 }
 
 // `mid`: of the forms that split the steps, for fewer columns; against the kernel's own blocks they have to be 8 % ahead, 16 %
-// with 32-row tiles, about what the estimates miss by (2720 x 8992, V = 32, Kv = 1120, N = 576: 12.7 us there, 13.9 here; 3200 x 10424, V = 128, Kv = 2608, N = 628: 21.6 us there, 22.4 here, estimated 24.8 and 23.3).
+// with 32-row tiles, about what the estimates miss by (2720 x 8992, V = 32, Kv = 1120, N = 576: 12.7 us there, 13.9 here; 3200 x
+// 10424, V = 128, Kv = 2608, N = 628: 21.6 us there, 22.4 here, estimated 24.8 and 23.3).
 // Four groups are the form for the fewest columns, estimated on such products alone, and need no margin; up to 320 of the
 // kernel's own blocks those are as good (11008 x 4096 at 50 %, N = 100, 344 blocks: 14.1 us there, 12.0 with four groups, 15.4
 // with two; 4096 x 4096, N = 512, 512 blocks 17.6, 13.7 and 15.8; N = 256, 256 blocks 8.4 and 9.5).
