@@ -119,3 +119,32 @@ def test_distances_beyond_single_precision(T, n, scale):
     label[clusters.reshape(-1)] = np.repeat(np.arange(T), n)
     assert obj[0] == gyro.kmeans_objective(d, label)
     assert obj[0] <= gyro.kmeans_objective(d, gyro.kmeans_balanced_assignment(d, n)) * (1 + 1e-9)
+
+
+@pytest.mark.parametrize("T,n", [(2, 12), (7, 12), (8, 16), (11, 13), (32, 12), (48, 2), (49, 2), (49, 5), (64, 2), (64, 6), (64, 7), (95, 4),
+                                 (96, 4), (97, 3)])
+def test_edges_of_the_matrix_in_registers(T, n):
+    """128 rows at a time and 6 or 12 columns a lane, up to 384 rows, 96 columns and 12 rows a column; one beyond each."""
+    test_columns_that_take_several_rows(T, n)
+
+
+@pytest.mark.parametrize("P", [4, 48, 50, 62, 94, 96, 98, 126])
+def test_edges_of_the_square_matrix_in_registers(P):
+    test_square_problems(P, False)
+
+
+@pytest.mark.parametrize("T,n", [(48, 8), (96, 4)])
+def test_points_that_share_their_distances(T, n):
+    """Every point twice: ties in every row and column, and columns asked for by twice the rows they take."""
+    c = synth.small_case(T * n, 24, n, 16, 1, "f16", 503)
+    Wb = c.weights()
+    rng = np.random.default_rng(T)
+    rho = np.repeat(rng.integers(0, 3, size=(c.M // 2, c.K)), 2, axis=0).astype(np.float32)
+    sampled = np.tile(np.arange(n, dtype=np.int32), (T, 1))
+    order = np.arange(c.M, dtype=np.int32)
+    clusters, _, obj = _gpu_cluster(c, Wb, rho, order, sampled, 1)
+    assert sorted(clusters.reshape(-1).tolist()) == list(range(T * n))
+    F = gyro.sampled_features(gyro.saliency_matrix(Wb, c.dtype, rho), order.reshape(T, n), sampled)
+    d = gyro.kmeans_distances(F, gyro.kmeans_initial_centroids(F, n))
+    # distances of whole numbers: every total is exact
+    assert obj[0] == gyro.kmeans_objective(d, gyro.kmeans_balanced_assignment(d, n))
