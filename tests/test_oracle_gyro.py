@@ -201,3 +201,14 @@ def test_kmeans_with_one_sample_per_tile_keeps_every_point_alone():
     clusters, C, obj = gyro.balanced_kmeans(F, 1, 2)
     assert clusters.reshape(-1).tolist() == [0, 1, 2, 3, 4] and obj.tolist() == [0.0, 0.0]
     assert np.array_equal(C, F)
+
+
+@pytest.mark.parametrize("T,V,n", [(1, 1, 1), (3, 32, 4), (48, 64, 8), (5, 33, 33), (2, 256, 1)])
+def test_positions_are_those_of_one_permutation_per_tile(T, V, n):
+    from paper_2407_20496_amd.gyro import _draw_positions
+
+    one, all_tiles = np.random.default_rng(T), np.random.default_rng(T)
+    want = np.stack([one.permutation(V)[:n] for _ in range(T)])
+    got = _draw_positions(all_tiles, T, V, n)
+    assert got.dtype == np.int32 and np.array_equal(got, want)
+    assert one.random() == all_tiles.random()
