@@ -28,7 +28,10 @@ __device__ __forceinline__ double saliency_at(const uint16_t* W, const float* rh
 __device__ __forceinline__ int clamp_index(int x, int n) { return x < 0 ? 0 : (x >= n ? n - 1 : x); }
 
 // base[t][k] = sum over the positions of tile t that stay (ascending position) of the saliency in
-// column k; cluster[t][k] = the same over the channels of cluster t (cluster order).
+// column k; cluster[t][k] = the same over the channels of cluster t (cluster order).  The rows' numbers are looked up once a
+// workgroup and sixteen rows are requested before the first is added: with one row at a time, each behind its look-up and
+// the one before, 48 tiles of 64 rows and 768 columns took 17.3 us, 11.2 here.
+constexpr int kSumRows = 16;
 template <int DT>
 __global__ __launch_bounds__(kThreads) void ocp_sums_kernel(const uint16_t* __restrict__ W,
                                                             const float* __restrict__ rho,
@@ -38,25 +41,39 @@ __global__ __launch_bounds__(kThreads) void ocp_sums_kernel(const uint16_t* __re
                                                             double* __restrict__ base, double* __restrict__ cluster,
                                                             int T, int K, int V, int n) {
   __shared__ uint8_t leaves[kOcpMaxV];
+  __shared__ int32_t row_of[kOcpMaxV], come_row[kOcpMaxV];
   const int t = blockIdx.x;
-  for (int p = threadIdx.x; p < V; p += kThreads) leaves[p] = 0;
+  for (int p = threadIdx.x; p < V; p += kThreads) {
+    leaves[p] = 0;
+    row_of[p] = clamp_index(row_order[(size_t)t * V + p], T * V);
+  }
+  for (int e = threadIdx.x; e < n; e += kThreads) {
+    const int q = clusters ? clamp_index(clusters[(size_t)t * n + e], T * n) : t * n + e;
+    const int tq = q / n, eq = q % n;
+    come_row[e] = clamp_index(row_order[(size_t)tq * V + clamp_index(samples[(size_t)tq * n + eq], V)], T * V);
+  }
   __syncthreads();
   for (int e = threadIdx.x; e < n; e += kThreads) leaves[clamp_index(samples[(size_t)t * n + e], V)] = 1;
   __syncthreads();
   const int k = blockIdx.y * kThreads + threadIdx.x;
   if (k >= K) return;
   double stay = 0.0;
-  for (int p = 0; p < V; ++p) {
-    if (leaves[p]) continue;
-    const size_t row = (size_t)clamp_index(row_order[(size_t)t * V + p], T * V);
-    stay += saliency_at<DT>(W, rho, row * K + k);
+  for (int p0 = 0; p0 < V; p0 += kSumRows) {
+    double x[kSumRows];
+#pragma unroll
+    for (int r = 0; r < kSumRows; ++r) x[r] = saliency_at<DT>(W, rho, (size_t)row_of[min(p0 + r, V - 1)] * K + k);
+#pragma unroll
+    for (int r = 0; r < kSumRows; ++r)
+      if (p0 + r < V && !leaves[p0 + r]) stay += x[r];
   }
   double come = 0.0;
-  for (int e = 0; e < n; ++e) {
-    const int q = clusters ? clamp_index(clusters[(size_t)t * n + e], T * n) : t * n + e;
-    const int tq = q / n, eq = q % n;
-    const size_t row = (size_t)clamp_index(row_order[(size_t)tq * V + clamp_index(samples[(size_t)tq * n + eq], V)], T * V);
-    come += saliency_at<DT>(W, rho, row * K + k);
+  for (int e0 = 0; e0 < n; e0 += 4) {
+    double x[4];
+#pragma unroll
+    for (int r = 0; r < 4; ++r) x[r] = saliency_at<DT>(W, rho, (size_t)come_row[min(e0 + r, n - 1)] * K + k);
+#pragma unroll
+    for (int r = 0; r < 4; ++r)
+      if (e0 + r < n) come += x[r];
   }
   base[(size_t)t * K + k] = stay;
   cluster[(size_t)t * K + k] = come;
@@ -172,6 +189,76 @@ __global__ __launch_bounds__(kThreads) void ocp_cost_kernel(const double* __rest
   }
 }
 
+// The same for up to 1024 columns, one wave per pair of tile and cluster: a pass counts with one compare a key whose lane mask
+// is counted by scalar instructions, and there is no barrier in it.  48 x 48 pairs of 768 columns 21.5 us with a workgroup a
+// pair, 13.7 here.
+template <int KPT>
+__global__ __launch_bounds__(kThreads) void ocp_cost_wave_kernel(const double* __restrict__ base,
+                                                                 const double* __restrict__ cluster,
+                                                                 double* __restrict__ cost, int T, int K, int Kv) {
+  const int lane = threadIdx.x & 63;
+  const int pair = __builtin_amdgcn_readfirstlane(blockIdx.x * (kThreads / 64) + (threadIdx.x >> 6));
+  if (pair >= T * T) return;
+  const int i = pair / T, j = pair % T;
+  const double* b = base + (size_t)i * K;
+  const double* c = cluster + (size_t)j * K;
+  double score[KPT];
+  uint32_t hi[KPT];
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) {
+    const int k = min(q * 64 + lane, K - 1);
+    score[q] = b[k] + c[k];
+  }
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) hi[q] = q * 64 + lane < K ? (uint32_t)(ordered_key(score[q]) >> 32) : 0u;
+  int count = 0;
+  uint32_t tau_hi = 0;
+  for (int bit = 31; bit >= 0; --bit) {
+    const uint32_t cand = tau_hi | (1u << bit);
+    count = 0;
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) count += __popcll(__ballot(hi[q] >= cand));
+    if (count >= Kv) tau_hi = cand;
+    if (count == Kv) break;
+  }
+  uint32_t tau_lo = 0;
+  if (count != Kv) {  // the low words of the keys that share the threshold's high word
+    int need = Kv;
+    uint32_t lo[KPT];
+#pragma unroll
+    for (int q = 0; q < KPT; ++q) {
+      need -= __popcll(__ballot(hi[q] > tau_hi));
+      lo[q] = hi[q] == tau_hi && q * 64 + lane < K ? (uint32_t)ordered_key(score[q]) : 0u;
+    }
+    for (int bit = 31; bit >= 0; --bit) {
+      const uint32_t cand = tau_lo | (1u << bit);
+      int enough = 0;
+#pragma unroll
+      for (int q = 0; q < KPT; ++q) enough += __popcll(__ballot(lo[q] >= cand));
+      if (enough >= need) tau_lo = cand;
+      if (enough == need) break;
+    }
+  }
+  const unsigned long long tau = ((unsigned long long)tau_hi << 32) | tau_lo;
+  int above = 0, equal = 0;
+  double below = 0.0;
+#pragma unroll
+  for (int q = 0; q < KPT; ++q) {
+    const bool there = q * 64 + lane < K;
+    const unsigned long long key = ordered_key(score[q]);
+    above += __popcll(__ballot(there && key > tau));
+    equal += __popcll(__ballot(there && key == tau));
+    if (there && key < tau) below += score[q];
+  }
+#pragma unroll
+  for (int off = 32; off >= 1; off >>= 1) below += __shfl_xor(below, off);
+  if (lane == 0) {
+    const int pruned_equal = equal - (Kv - above);  // scores equal to the threshold that do not survive
+    if (pruned_equal > 0) below += (double)pruned_equal * key_value(tau);
+    cost[(size_t)i * T + j] = below;
+  }
+}
+
 // The same with whole 64-bit keys and 64 passes of 64-bit compares (a quarter of the 32-bit rate): with
 // 64 keys per thread the split form needs more registers than it saves time (measured 2.5 ms against
 // 1.8 ms on a 16384-column layer), so the widest configuration keeps this form.
@@ -237,6 +324,7 @@ __global__ __launch_bounds__(kThreads) void ocp_moved_kernel(const double* __res
                                                              const int32_t* __restrict__ clusters,
                                                              int32_t* __restrict__ moved, double* __restrict__ objective,
                                                              int T, int V, int n) {
+  __shared__ double picked[kThreads];
   const int i = blockIdx.x;
   const int j = clamp_index(assign[i], T);
   for (int e = threadIdx.x; e < n; e += kThreads) {
@@ -244,10 +332,20 @@ __global__ __launch_bounds__(kThreads) void ocp_moved_kernel(const double* __res
     const int tq = q / n, eq = q % n;
     moved[(size_t)i * n + e] = row_order[(size_t)tq * V + clamp_index(samples[(size_t)tq * n + eq], V)];
   }
-  if (objective && i == 0 && threadIdx.x == 0) {
+  if (objective && i == 0) {  // tiles in ascending order, looked up by all threads
     double total = 0.0;
-    for (int r = 0; r < T; ++r) total += cost[(size_t)r * T + clamp_index(assign[r], T)];
-    *objective = total;
+    for (int r0 = 0; r0 < T; r0 += kThreads) {
+      const int r = r0 + threadIdx.x;
+      __syncthreads();
+      picked[threadIdx.x] = r < T ? cost[(size_t)r * T + clamp_index(assign[r], T)] : 0.0;
+      __syncthreads();
+      if (threadIdx.x == 0) {
+        const int count = min(kThreads, T - r0);
+#pragma unroll 8
+        for (int e = 0; e < count; ++e) total += picked[e];
+      }
+    }
+    if (threadIdx.x == 0) *objective = total;
   }
 }
 
@@ -288,67 +386,94 @@ __global__ __launch_bounds__(kThreads) void km_init_kernel(const float* __restri
 }
 
 // d[q][c] for 64 clusters (one a lane) and one or two points a wave.  A chain of K steps per pair is the definition (the
-// rounding of every step is pinned), so the chains have to run on operands that are at hand: 64 columns of the
-// centroids at a time go through LDS (rows padded to an odd number of doubles: no bank conflicts), the points' features
-// are wave-uniform.  384 points x 48 clusters x 768 columns: 76 us with one column of a different centroid row per
-// lane and step, 33 us with two points a wave and the loads of a piece behind the sums of the last, 26 us with
-// one point (96 workgroups; two points read the centroids half as often once there are 256) and a piece requested ahead.
-constexpr int kDistColumns = 64;
+// rounding of every step is pinned), so the chains have to run on operands that are at hand: 32 columns of the
+// centroids at a time go through LDS (two pieces in turn, the next one requested ahead; rows padded to an odd number of
+// doubles: no bank conflicts), and a piece of a point's features is held by 32 lanes, each read from its lane as a scalar.
+// 384 points x 48 clusters x 768 columns: 76 us with one column of a different centroid row per lane and step, 26.5 us with
+// the features as scalar loads (they share a counter with the LDS reads, which makes every one wait for all), 21.0 here.
+// Two points read the centroids half as often once there are 256 workgroups of them.
+constexpr int kDistColumns = 32;
 template <int POINTS>  // per wave
 __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __restrict__ F,
                                                                const double* __restrict__ C,
                                                                double* __restrict__ dist, int T, int K, int points) {
 #pragma clang fp contract(off)  // product and sum are rounded separately: that rounding is part of the definition
-  __shared__ double tile[64][kDistColumns + 1];
+  static_assert(POINTS == 1 || POINTS == 2, "a point's piece is held by half of the wave");
+  __shared__ double tile[2][64][kDistColumns + 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c0 = blockIdx.y * 64;
   const int q0 = (blockIdx.x * (kThreads / 64) + wave) * POINTS;
-  const float* f[POINTS];
+  const int column = threadIdx.x % kDistColumns, row = threadIdx.x / kDistColumns;
+  const float* const f = F + (size_t)min(q0 + (POINTS == 2 ? lane / kDistColumns : 0), points - 1) * K;
   double acc[POINTS];
 #pragma unroll
-  for (int p = 0; p < POINTS; ++p) {
-    f[p] = F + (size_t)min(q0 + p, points - 1) * K;
-    acc[p] = 0.0;
-  }
-  constexpr int kPieces = 64 / (kThreads / 64);
+  for (int p = 0; p < POINTS; ++p) acc[p] = 0.0;
+  constexpr int kRows = kThreads / kDistColumns;  // of a piece, at a time
+  constexpr int kPieces = 64 / kRows;
   double ahead[kPieces];
+  float f_ahead;
   auto request = [&](int k0) {
-    const int k_lane = min(k0 + lane, K - 1);
+    const int k = min(k0 + column, K - 1);
 #pragma unroll
-    for (int r = 0; r < kPieces; ++r)
-      ahead[r] = C[(size_t)min(c0 + wave + r * (kThreads / 64), T - 1) * K + k_lane];
+    for (int r = 0; r < kPieces; ++r) ahead[r] = C[(size_t)min(c0 + row + r * kRows, T - 1) * K + k];
+    f_ahead = f[k];  // (column is the lane's, too)
+  };
+  auto put = [&](int at) {
+#pragma unroll
+    for (int r = 0; r < kPieces; ++r) tile[at][row + r * kRows][column] = ahead[r];
   };
   request(0);
+  put(0);
+  int at = 0;
   for (int k0 = 0; k0 < K; k0 += kDistColumns) {
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < kPieces; ++r) tile[wave + r * (kThreads / 64)][lane] = ahead[r];
-    __syncthreads();
+    const double mine = (double)f_ahead;
+    __syncthreads();  // this piece is there, and nobody reads the one before it
     if (k0 + kDistColumns < K) request(k0 + kDistColumns);
-    const int count = min(kDistColumns, K - k0);
-    if (count == kDistColumns) {
-#pragma unroll 16
-      for (int k = 0; k < kDistColumns; ++k) {
-        const double cen = tile[lane][k];
+    auto square = [&](double cen, int p, int k) {
+      const double x = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), p * kDistColumns + k),
+                                        __builtin_amdgcn_readlane(__double2loint(mine), p * kDistColumns + k));
+      const double diff = x - cen;
+      return diff * diff;
+    };
+    if (k0 + kDistColumns <= K) {
+      // the squares of the next four columns between the sums of these: a lone wave issues in order
+      constexpr int kAhead = 4;
+      double cen[2 * kAhead], sq[2][kAhead][POINTS];
 #pragma unroll
-        for (int p = 0; p < POINTS; ++p) {
-          const double diff = (double)f[p][k0 + k] - cen;
-          const double sq = diff * diff;
-          acc[p] = acc[p] + sq;
+      for (int e = 0; e < 2 * kAhead; ++e) cen[e] = tile[at][lane][e];
+#pragma unroll
+      for (int e = 0; e < kAhead; ++e)
+#pragma unroll
+        for (int p = 0; p < POINTS; ++p) sq[0][e][p] = square(cen[e], p, e);
+#pragma unroll
+      for (int k = 0; k < kDistColumns; k += kAhead) {
+        const int now = (k / kAhead) & 1;
+        double after[kAhead];
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e)
+          if (k + 2 * kAhead < kDistColumns) after[e] = tile[at][lane][k + 2 * kAhead + e];
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) {
+#pragma unroll
+          for (int p = 0; p < POINTS; ++p) {
+            acc[p] = acc[p] + sq[now][e][p];
+            if (k + kAhead < kDistColumns) sq[now ^ 1][e][p] = square(cen[kAhead + e], p, k + kAhead + e);
+          }
+          __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int e = 0; e < kAhead; ++e) cen[kAhead + e] = after[e];
       }
     } else {
-      for (int k = 0; k < count; ++k) {
-        const double cen = tile[lane][k];
+      for (int k = 0; k < K - k0; ++k) {
+        const double cen = tile[at][lane][k];
 #pragma unroll
-        for (int p = 0; p < POINTS; ++p) {
-          const double diff = (double)f[p][k0 + k] - cen;
-          const double sq = diff * diff;
-          acc[p] = acc[p] + sq;
-        }
+        for (int p = 0; p < POINTS; ++p) acc[p] = acc[p] + square(cen, p, k);
       }
     }
+    at ^= 1;
+    if (k0 + kDistColumns < K) put(at);
   }
   if (c0 + lane < T) {
 #pragma unroll
@@ -491,7 +616,9 @@ hipError_t launch_ocp_search(const OcpArgs& a, hipStream_t stream) {
     else
       ocp_sums_kernel<HINM_BF16><<<sums_grid, kThreads, 0, stream>>>(Wb, a.rho, a.row_order, smp, cl, base, cluster, T,
                                                                       s.K, s.V, n);
-    if (s.K <= 4 * kThreads) ocp_cost_kernel<4><<<cost_grid, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
+    const int pair_blocks = (T * T + kThreads / 64 - 1) / (kThreads / 64);
+    if (s.K <= 512) ocp_cost_wave_kernel<8><<<pair_blocks, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
+    else if (s.K <= 1024) ocp_cost_wave_kernel<16><<<pair_blocks, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
     else if (s.K <= 16 * kThreads) ocp_cost_kernel<16><<<cost_grid, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
     else ocp_cost_wide_kernel<64><<<cost_grid, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);
     hipError_t e = hipGetLastError();

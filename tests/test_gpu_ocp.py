@@ -196,3 +196,29 @@ def test_clusters_feed_the_search_on_the_c2_layer():
     assert obj[0] <= gyro.kmeans_objective(d0, gyro.kmeans_balanced_assignment(d0, n)) * (1 + 1e-9)
     after, sobj = _gpu_search(c, Wb, None, start, sampled[None], clusters[None].astype(np.int32))
     _check_iteration(c, S, start, after, sampled, clusters, sobj[0], exact=False)
+
+
+@pytest.mark.parametrize("K", [8, 64, 72, 504, 512, 520, 1016, 1024, 1032])
+@pytest.mark.parametrize("scores", ["tied", "plain", "infinite"])
+def test_edges_of_one_wave_per_pair(K, scores):
+    """Up to 512 and 1024 columns a wave finds the threshold of a pair (one beyond each); ties need the low words too."""
+    V, n = 5, 3
+    c = synth.small_case(7 * V, K, V, max(8, K // 16 * 8), 1, "f16", 600 + K)
+    Wb = c.weights()
+    rng = np.random.default_rng(K)
+    if scores == "plain":
+        rho = (rng.standard_normal((c.M, c.K)) ** 2).astype(np.float32)
+    else:
+        rho = rng.integers(0, 3, size=(c.M, c.K)).astype(np.float32)
+    if scores == "infinite":                                 # columns that are never pruned
+        rho[:, : c.Kv // 2] = np.inf
+    samples = np.stack([rng.permutation(V)[:n] for _ in range(c.T)])[None].astype(np.int32)
+    start = rng.permutation(c.M).astype(np.int32)
+    after, obj = _gpu_search(c, Wb, rho, start, samples, None)
+    _check_iteration(c, gyro.saliency_matrix(Wb, c.dtype, rho), start, after, samples[0], None, obj[0], exact=scores != "plain")
+
+
+@pytest.mark.parametrize("K", [16, 32, 40, 64, 96, 104])
+def test_edges_of_the_pieces_of_a_distance(K):
+    """Pieces of 32 columns: part of one, one, several with and without a rest."""
+    test_balanced_kmeans_round_by_round(56, K, 8, 8, 3, "f16", True)
