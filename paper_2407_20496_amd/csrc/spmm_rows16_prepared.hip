@@ -371,6 +371,7 @@ struct Rows16Plan {
   int rbw;
   int nw;
   int blocks_per_wg;  // 16-column blocks: 1, 2 or 4
+  int kb;             // steps of a batch
 };
 
 Rows16Plan plan_rows16(const PreparedArgs& a) {
@@ -415,6 +416,20 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
       while (p.nw > 1 && row_wgs * col_blocks * p.nw > 2048) p.nw >>= 1;
     }
   }
+  p.kb = p.nw == 8 && L.S > 32 && a.N <= kCols ? 6 : p.nw == 16 && L.S > 64 ? 6 : 4;
+  // A wave's steps pass through its slab one after the other and every step of a batch is code to fetch: short layers take
+  // more waves with smaller batches, without dummy steps.  Geometric means over 130 drawn layers with up to 16 columns: 1.19
+  // up to four steps, 1.15 up to eight (four waves with one column, which has little to hide), 1.1 up to sixteen unless several
+  // workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408 workgroups 0.91), 1.07 up to 24, 1.05 up to 40;
+  // 1.09 to 1.26 with more columns where about eight waves a unit are not exceeded by it.
+  if (p.blocks_per_wg == 1 && L.S <= 40) {
+    const int64_t wgs = a.s.M / (kRows * p.rbw) * col_blocks;
+    const int S = L.S;
+    int nw = 8, kb = (S + 7) / 8;
+    if (S <= 4) nw = 4, kb = 1;
+    else if (S <= 8 && a.N == 1) nw = 4, kb = 2;
+    if (kb != 4 && (a.N <= kCols ? S <= 12 || S > 16 || wgs <= 256 : S <= 16 && wgs * nw <= 2048)) p.nw = nw, p.kb = kb;
+  }
   return p;
 }
 
@@ -422,17 +437,20 @@ template <int DT, int RBW>
 void launch_waves(const PreparedArgs& a, const Rows16Plan& plan, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
   const int blocks = plan.blocks_per_wg;
-  const bool deep = L.S > 64;  // batches of six steps for long k loops
-  switch (plan.nw) {
-    case 1: return launch_modes<DT, 1, 4, RBW>(a, L, blocks, stream);
-    case 2: return launch_modes<DT, 2, 4, RBW>(a, L, blocks, stream);
-    case 4: return launch_modes<DT, 4, 4, RBW>(a, L, blocks, stream);
-    case 8:
-      if (L.S > 32 && a.N <= kCols) return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
-      return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
-    default:
-      if (deep) launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);
-      else launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
+  switch (plan.nw * 8 + plan.kb) {
+    case 1 * 8 + 4: return launch_modes<DT, 1, 4, RBW>(a, L, blocks, stream);
+    case 2 * 8 + 4: return launch_modes<DT, 2, 4, RBW>(a, L, blocks, stream);
+    case 4 * 8 + 1: return launch_modes<DT, 4, 1, RBW>(a, L, 1, stream);
+    case 4 * 8 + 2: return launch_modes<DT, 4, 2, RBW>(a, L, 1, stream);
+    case 4 * 8 + 4: return launch_modes<DT, 4, 4, RBW>(a, L, blocks, stream);
+    case 8 * 8 + 1: return launch_modes<DT, 8, 1, RBW>(a, L, 1, stream);
+    case 8 * 8 + 2: return launch_modes<DT, 8, 2, RBW>(a, L, 1, stream);
+    case 8 * 8 + 3: return launch_modes<DT, 8, 3, RBW>(a, L, 1, stream);
+    case 8 * 8 + 4: return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
+    case 8 * 8 + 5: return launch_modes<DT, 8, 5, RBW>(a, L, 1, stream);
+    case 8 * 8 + 6: return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
+    case 16 * 8 + 4: return launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
+    default: return launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);
   }
 }
 

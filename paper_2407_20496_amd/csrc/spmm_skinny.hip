@@ -262,9 +262,18 @@ void launch_modes(const SpmmArgs& a, hipStream_t stream) {
 template <int DT, int RBW>
 void launch_waves(const SpmmArgs& a, hipStream_t stream) {
   const int full_steps = a.s.Kv / kStep;
-  // Prefer one batch per wave (every load of the wave in flight at once): waves x batch >= steps.
-  if (full_steps <= 4) launch_modes<DT, 1, 4, RBW>(a, stream);
+  // One batch per wave (every load of the wave in flight at once): waves x batch >= steps.  A wave's steps pass through its
+  // slab one after the other and every step of a batch is code to fetch, so short layers take a wave a step, and four waves at
+  // least, which share the epilogue: 256 x 256, V = 16, Kv = 128, N = 64 3.21 us with one wave and batches of four, 2.67 with two
+  // waves, 2.36 with four.  Geometric means over 130 drawn layers: 1.36 up to two steps, 1.3 up to four, 1.17 up to eight (one
+  // column: four waves, 1.15 against 1.13) and, with batches of two, 1.08 up to twelve (13 to 16 steps 0.95 to 1.09).  Up to 32
+  // steps sixteen waves with batches of two are ahead with one column (1.09; 0.96 with up to 16).
+  if (full_steps <= 4) launch_modes<DT, 4, 1, RBW>(a, stream);
+  else if (full_steps <= 8 && a.N == 1) launch_modes<DT, 4, 2, RBW>(a, stream);
+  else if (full_steps <= 8) launch_modes<DT, 8, 1, RBW>(a, stream);
+  else if (full_steps <= 12) launch_modes<DT, 8, 2, RBW>(a, stream);
   else if (full_steps <= 16) launch_modes<DT, 4, 4, RBW>(a, stream);
+  else if (full_steps <= 32 && a.N == 1) launch_modes<DT, 16, 2, RBW>(a, stream);
   else if (full_steps <= 32) launch_modes<DT, 8, 4, RBW>(a, stream);
   // (4096 x 11008, Kv = 2752, N = 16 11.7 -> 10.4 us from memory, 10.1 -> 8.4 cached, against sixteen waves)
   else if (full_steps <= 48 && a.N <= kCols) launch_modes<DT, 8, 6, RBW>(a, stream);

@@ -384,3 +384,16 @@ def test_chain_of_ten_layers():
     hinm.hinm_chain(layers, N, gu.dev_bits(Xb), N, Y, N, scratch, nbytes)
     torch.cuda.synchronize()
     assert h.any() and np.array_equal(gu.host_bits(Y), h)
+
+
+@pytest.mark.parametrize("S", [1, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41])
+@pytest.mark.parametrize("N", [1, 6, 16, 40])
+def test_waves_and_batches_of_the_16_row_kernel(S, N):
+    """Waves and batches change at 4, 8, 12, 16, 24, 32 and 40 steps; the last step is ragged."""
+    _check(synth.small_case(96, 64 * S + 8, 32, 64 * S - 24, N, "bf16" if S % 2 else "f16", 700 + S), N, [0, 11], relu=S % 3 == 0)
+
+
+@pytest.mark.parametrize("S", [1, 7, 12, 13, 20])
+def test_waves_of_the_16_row_kernel_with_many_workgroups(S):
+    """Both halves of a 32-row block in a workgroup (256 of them and more); above 12 steps the count of workgroups decides."""
+    _check(synth.small_case(8320, 64 * S, 64, 64 * S - 8, 9, "f16", 720 + S), 9, [11])
