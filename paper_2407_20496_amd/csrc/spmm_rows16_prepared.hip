@@ -374,61 +374,78 @@ struct Rows16Plan {
   int kb;             // steps of a batch
 };
 
+// Waves and batch with one column block.  A wave's steps pass through its slab one after the other and every step of a batch is
+// code to fetch and registers to hold, so short layers take a wave a step (four at least, which share the epilogue; one column
+// has little to hide, eight steps on four waves do), and no batch has dummy steps.  Against one to sixteen waves with batches of
+// four and six, geometric means over 130 drawn layers with up to 16 columns: 1.19 up to four steps, 1.15 up to eight, 1.1 up to
+// sixteen unless several workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408 workgroups 0.91), 1.07 up
+// to 24, 1.05 up to 40.  Beyond (us): 4096 x 11008, 43 steps, N = 1 5.10 -> 4.95, N = 16 6.42 -> 6.14 (twelve waves;
+// with eight as fast on 16 workgroups, 4 % faster on 384 and with up to four columns); 8192 x 8192, 64 steps, N = 1
+// 12.6 -> 8.35 (9.5 of it from both halves of a block); 86 steps, N = 1 8.64 -> 7.12 (eight waves 7.61), 5120 x 13824, 108 steps,
+// 320 workgroups 19.6 -> 11.8 (sixteen waves 14.6), N = 3 34.7 -> 27.0; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3; 86 steps with
+// more than one column stay one batch of six (11.9, in batches of four 14.0).
+void one_block_waves(Rows16Plan& p, int S, int N, int64_t wgs) {
+  if (S <= 4) p.nw = 4, p.kb = 1;
+  else if (S <= 8 && N == 1) p.nw = 4, p.kb = 2;
+  else if (S > 12 && S <= 16 && wgs > 256) p.nw = 4, p.kb = 4;
+  else if (S > 40 && S <= 48 && N > 4 && wgs >= 128 && wgs <= 256) p.nw = 12, p.kb = 4;
+  else if (S > 40 && S <= 48 && N == 1) p.nw = 8, p.kb = 3;
+  else if (S <= 48) p.nw = 8, p.kb = (S + 7) / 8;
+  else if (S <= 64) p.nw = 8, p.kb = 4;
+  else if (N == 1) p.nw = wgs <= 256 ? 16 : 8, p.kb = 3;
+  else p.nw = 16, p.kb = S <= 96 ? 6 : 4;
+}
+
 Rows16Plan plan_rows16(const PreparedArgs& a) {
   const PreparedLayout L = prepared_layout(a.s);
   Rows16Plan p;
   // Several 16-row blocks in one workgroup share the gathered input rows: both halves of a 32-row block when
-  // the grid then still holds 256 workgroups (column blocks count: 4096 x 4096 at N = 128 22.8 -> 17.1 us), two
+  // the grid then still holds 256 workgroups (column blocks count: 4096 x 4096 at N = 128 22.8 -> 17.1 us; one column: 16384 x
+  // 4096, 32 steps 10.0 -> 8.8, 13824 x 5120, 40 steps 12.1 -> 9.5), two
   // neighbouring 32-row blocks under the same condition on layers of at least 2048 rows and beyond one column
   // block (-> 13.0 us; 8192 x 8192 at N = 128 62.8 -> 47.8 us; with fewer rows the shorter grid loses: 768 x 3072
   // at N = 384 9.2 -> 12.0 us).
   const int64_t col_blocks = (a.N + kCols - 1) / kCols;
   const bool quad = a.N > kCols && a.s.V % 64 == 0 && a.s.M >= 2048 && (a.s.M / 64) * col_blocks >= 256;
-  const bool both = a.N > 4 && (a.s.M / 32) * col_blocks >= 256;
+  const bool both = (a.s.M / 32) * col_blocks >= 256;
   p.rbw = quad ? 4 : both ? 2 : 1;
-  // one batch per wave where possible (every load of the wave in flight at once): waves x batch >= steps ... (33 to 48
-  // steps as eight waves with batches of six, up to 16 columns: 4096 x 11008, Kv = 2752, N = 16 9.4 -> 8.1 us from memory, 7.7 ->
-  // 6.4 from the cache, against sixteen with four; beyond 48 steps sixteen waves are ahead, 13.7 and 14.0 with 86)
-  const int nw_steps = L.S <= 4 ? 1 : L.S <= 16 ? 4 : L.S <= (a.N <= kCols ? 48 : 32) ? 8 : 16;
-  p.nw = nw_steps;
   p.blocks_per_wg = 1;
-  if (a.N > kCols) {
-    // ... but no more waves than the chip can hold at once: with many workgroups (several column blocks, or
-    // a tall layer) the parallelism is already there, and fewer waves per workgroup mean fewer partial tiles
-    // to sum and more of each wave's own loads in flight one after another (4096 x 4096 at N = 128, 2048
-    // workgroups: 32.8 us with eight waves, 22.7 us with one).  About eight waves per compute unit in total.
-    const int64_t row_wgs = a.s.M / (kRows * p.rbw);
-    // Two or four column blocks per workgroup: a step's weights, gather entries and the 128-byte cache lines of
-    // its input rows then serve 32 or 64 columns (11008 x 4096 at N = 128 42.3 -> 31.1 -> 24.8 us, 8192 x 8192
-    // at N = 256 89.5 -> 69.3 -> 45.0 us).  It needs a grid that still covers most of the chip (160 workgroups;
-    // with 96..159 it measured slower: 4096 x 4096 at N = 64, 128 workgroups left, 7.9 -> 9.5 us) and at least
-    // eight steps (from there on never slower under that condition; 8192 x 1024 with 512 kept columns at
-    // N = 256: 17.7 -> 13.5 us).
-    if (a.ldx % 8 == 0 && L.S >= 8) {
-      if (col_blocks >= 3 && row_wgs * ((col_blocks + 3) / 4) >= 160) p.blocks_per_wg = 4;
-      else if (row_wgs * ((col_blocks + 1) / 2) >= 160) p.blocks_per_wg = 2;
-    }
-    const int64_t wgs = row_wgs * ((col_blocks + p.blocks_per_wg - 1) / p.blocks_per_wg);
-    while (p.nw > 1 && wgs * p.nw > 2048) p.nw >>= 1;
-    if (p.blocks_per_wg > 1 && p.nw > 8) {  // sixteen waves leave too few registers for several blocks
-      p.blocks_per_wg = 1;
-      p.nw = nw_steps;
-      while (p.nw > 1 && row_wgs * col_blocks * p.nw > 2048) p.nw >>= 1;
-    }
+  const int64_t row_wgs = a.s.M / (kRows * p.rbw);
+  if (a.N <= kCols) {
+    one_block_waves(p, L.S, a.N, row_wgs);
+    return p;
   }
-  p.kb = p.nw == 8 && L.S > 32 && a.N <= kCols ? 6 : p.nw == 16 && L.S > 64 ? 6 : 4;
-  // A wave's steps pass through its slab one after the other and every step of a batch is code to fetch: short layers take
-  // more waves with smaller batches, without dummy steps.  Geometric means over 130 drawn layers with up to 16 columns: 1.19
-  // up to four steps, 1.15 up to eight (four waves with one column, which has little to hide), 1.1 up to sixteen unless several
-  // workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408 workgroups 0.91), 1.07 up to 24, 1.05 up to 40;
-  // 1.09 to 1.26 with more columns where about eight waves a unit are not exceeded by it.
-  if (p.blocks_per_wg == 1 && L.S <= 40) {
-    const int64_t wgs = a.s.M / (kRows * p.rbw) * col_blocks;
-    const int S = L.S;
-    int nw = 8, kb = (S + 7) / 8;
-    if (S <= 4) nw = 4, kb = 1;
-    else if (S <= 8 && a.N == 1) nw = 4, kb = 2;
-    if (kb != 4 && (a.N <= kCols ? S <= 12 || S > 16 || wgs <= 256 : S <= 16 && wgs * nw <= 2048)) p.nw = nw, p.kb = kb;
+  // One batch per wave where possible (every load of the wave in flight at once): waves x batch >= steps ...
+  const int nw_steps = L.S <= 4 ? 1 : L.S <= 16 ? 4 : L.S <= 32 ? 8 : 16;
+  p.nw = nw_steps;
+  // ... but no more waves than the chip can hold at once: with many workgroups (several column blocks, or
+  // a tall layer) the parallelism is already there, and fewer waves per workgroup mean fewer partial tiles
+  // to sum and more of each wave's own loads in flight one after another (4096 x 4096 at N = 128, 2048
+  // workgroups: 32.8 us with eight waves, 22.7 us with one).  About eight waves per compute unit in total.
+  //
+  // Two or four column blocks per workgroup: a step's weights, gather entries and the 128-byte cache lines of
+  // its input rows then serve 32 or 64 columns (11008 x 4096 at N = 128 42.3 -> 31.1 -> 24.8 us, 8192 x 8192
+  // at N = 256 89.5 -> 69.3 -> 45.0 us).  It needs a grid that still covers most of the chip (160 workgroups;
+  // with 96..159 it measured slower: 4096 x 4096 at N = 64, 128 workgroups left, 7.9 -> 9.5 us) and at least
+  // eight steps (from there on never slower under that condition; 8192 x 1024 with 512 kept columns at
+  // N = 256: 17.7 -> 13.5 us).
+  if (a.ldx % 8 == 0 && L.S >= 8) {
+    if (col_blocks >= 3 && row_wgs * ((col_blocks + 3) / 4) >= 160) p.blocks_per_wg = 4;
+    else if (row_wgs * ((col_blocks + 1) / 2) >= 160) p.blocks_per_wg = 2;
+  }
+  const int64_t wgs = row_wgs * ((col_blocks + p.blocks_per_wg - 1) / p.blocks_per_wg);
+  while (p.nw > 1 && wgs * p.nw > 2048) p.nw >>= 1;
+  if (p.blocks_per_wg > 1 && p.nw > 8) {  // sixteen waves leave too few registers for several blocks
+    p.blocks_per_wg = 1;
+    p.nw = nw_steps;
+    while (p.nw > 1 && row_wgs * col_blocks * p.nw > 2048) p.nw >>= 1;
+  }
+  p.kb = p.nw == 16 && L.S > 64 ? 6 : 4;
+  // Short layers as with one column block while that makes no more than eight waves a unit (1.09 to 1.26 times).
+  if (p.blocks_per_wg == 1 && L.S <= 16) {
+    Rows16Plan q = p;
+    one_block_waves(q, L.S, a.N, row_wgs * col_blocks);
+    if (row_wgs * col_blocks * q.nw <= 2048) p = q;
   }
   return p;
 }
@@ -449,6 +466,8 @@ void launch_waves(const PreparedArgs& a, const Rows16Plan& plan, hipStream_t str
     case 8 * 8 + 4: return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
     case 8 * 8 + 5: return launch_modes<DT, 8, 5, RBW>(a, L, 1, stream);
     case 8 * 8 + 6: return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
+    case 12 * 8 + 4: return launch_modes<DT, 12, 4, RBW>(a, L, 1, stream);
+    case 16 * 8 + 3: return launch_modes<DT, 16, 3, RBW>(a, L, 1, stream);
     case 16 * 8 + 4: return launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
     default: return launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);
   }

@@ -386,14 +386,25 @@ def test_chain_of_ten_layers():
     assert h.any() and np.array_equal(gu.host_bits(Y), h)
 
 
-@pytest.mark.parametrize("S", [1, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41])
+@pytest.mark.parametrize("S", [1, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49, 64, 65, 96, 97])
 @pytest.mark.parametrize("N", [1, 6, 16, 40])
 def test_waves_and_batches_of_the_16_row_kernel(S, N):
-    """Waves and batches change at 4, 8, 12, 16, 24, 32 and 40 steps; the last step is ragged."""
+    """Waves and batches change at 4, 8, 12, 16, 24, 32, 40, 48, 64 and 96 steps; the last step is ragged."""
     _check(synth.small_case(96, 64 * S + 8, 32, 64 * S - 24, N, "bf16" if S % 2 else "f16", 700 + S), N, [0, 11], relu=S % 3 == 0)
 
 
 @pytest.mark.parametrize("S", [1, 7, 12, 13, 20])
-def test_waves_of_the_16_row_kernel_with_many_workgroups(S):
+@pytest.mark.parametrize("N", [1, 9])
+def test_waves_of_the_16_row_kernel_with_many_workgroups(S, N):
     """Both halves of a 32-row block in a workgroup (256 of them and more); above 12 steps the count of workgroups decides."""
-    _check(synth.small_case(8320, 64 * S, 64, 64 * S - 8, 9, "f16", 720 + S), 9, [11])
+    _check(synth.small_case(8320, 64 * S, 64, 64 * S - 8, N, "f16", 720 + S), N, [11])
+
+
+@pytest.mark.parametrize("S", [40, 41, 48, 49])
+def test_twelve_waves_where_there_are_128_workgroups(S):
+    _check(synth.small_case(2048, 64 * S, 32, 64 * S - 8, 11, "bf16", 742), 11, [11])
+
+
+def test_eight_waves_on_long_layers_of_one_column():
+    """More than 256 workgroups beyond 64 steps."""
+    _check(synth.small_case(4128, 64 * 66, 32, 64 * 66 - 8, 1, "bf16", 741), 1, [11])
