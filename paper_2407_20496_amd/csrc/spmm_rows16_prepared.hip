@@ -379,8 +379,7 @@ struct Rows16Plan {
 // has little to hide, eight steps on four waves do), and no batch has dummy steps.  Against one to sixteen waves with batches of
 // four and six, geometric means over 130 drawn layers with up to 16 columns: 1.19 up to four steps, 1.15 up to eight, 1.1 up to
 // sixteen unless several workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408 workgroups 0.91), 1.07 up
-// to 24, 1.05 up to 40.  Beyond (us): 4096 x 11008, 43 steps, N = 1 5.10 -> 4.95, N = 16 6.42 -> 6.14 (twelve waves;
-// with eight as fast on 16 workgroups, 4 % faster on 384 and with up to four columns); 8192 x 8192, 64 steps, N = 1
+// to 24, 1.05 up to 40.  Beyond (us): 4096 x 11008, 43 steps, N = 1 5.10 -> 4.95; 8192 x 8192, 64 steps, N = 1
 // 12.6 -> 8.35 (9.5 of it from both halves of a block); 86 steps, N = 1 8.64 -> 7.12 (eight waves 7.61), 5120 x 13824, 108 steps,
 // 320 workgroups 19.6 -> 11.8 (sixteen waves 14.6), N = 3 34.7 -> 27.0; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3; 86 steps with
 // more than one column stay one batch of six (11.9, in batches of four 14.0).
@@ -388,10 +387,9 @@ void one_block_waves(Rows16Plan& p, int S, int N, int64_t wgs) {
   if (S <= 4) p.nw = 4, p.kb = 1;
   else if (S <= 8 && N == 1) p.nw = 4, p.kb = 2;
   else if (S > 12 && S <= 16 && wgs > 256) p.nw = 4, p.kb = 4;
-  else if (S > 40 && S <= 48 && N > 4 && wgs >= 128 && wgs <= 256) p.nw = 12, p.kb = 4;
   else if (S > 40 && S <= 48 && N == 1) p.nw = 8, p.kb = 3;
   else if (S <= 48) p.nw = 8, p.kb = (S + 7) / 8;
-  else if (S <= 64) p.nw = 8, p.kb = 4;
+  else if (S <= 64) p.nw = N == 1 || wgs >= 128 ? 8 : 16, p.kb = 4;
   else if (N == 1) p.nw = wgs <= 256 ? 16 : 8, p.kb = 3;
   else p.nw = 16, p.kb = S <= 96 ? 6 : 4;
 }
@@ -466,7 +464,6 @@ void launch_waves(const PreparedArgs& a, const Rows16Plan& plan, hipStream_t str
     case 8 * 8 + 4: return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
     case 8 * 8 + 5: return launch_modes<DT, 8, 5, RBW>(a, L, 1, stream);
     case 8 * 8 + 6: return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
-    case 12 * 8 + 4: return launch_modes<DT, 12, 4, RBW>(a, L, 1, stream);
     case 16 * 8 + 3: return launch_modes<DT, 16, 3, RBW>(a, L, 1, stream);
     case 16 * 8 + 4: return launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
     default: return launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);

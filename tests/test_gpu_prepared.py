@@ -401,7 +401,7 @@ def test_waves_of_the_16_row_kernel_with_many_workgroups(S, N):
 
 
 @pytest.mark.parametrize("S", [40, 41, 48, 49])
-def test_twelve_waves_where_there_are_128_workgroups(S):
+def test_waves_of_the_16_row_kernel_with_128_workgroups(S):
     _check(synth.small_case(2048, 64 * S, 32, 64 * S - 8, 11, "bf16", 742), 11, [11])
 
 
