@@ -275,8 +275,11 @@ void launch_waves(const SpmmArgs& a, hipStream_t stream) {
   else if (full_steps <= 16) launch_modes<DT, 4, 4, RBW>(a, stream);
   else if (full_steps <= 32 && a.N == 1) launch_modes<DT, 16, 2, RBW>(a, stream);
   else if (full_steps <= 32) launch_modes<DT, 8, 4, RBW>(a, stream);
-  // (4096 x 11008, Kv = 2752, N = 16 11.7 -> 10.4 us from memory, 10.1 -> 8.4 cached, against sixteen waves)
-  else if (full_steps <= 48 && a.N <= kCols) launch_modes<DT, 8, 6, RBW>(a, stream);
+  // Sixteen waves with batches of three, weights from memory, against eight with six (batches of two and four are slower than
+  // either): 768 x 5000, 36 steps, N = 1 6.63 -> 5.90 us, 4480 x 5200, V = 32, 40 steps 12.6 -> 12.1, 896 x 4300, 33 steps, N = 11
+  // 7.49 -> 6.85, 256 x 6000, V = 16, 40 steps, N = 40 10.5 -> 9.2; but 1024 x 6000, V = 32, 46 steps, N = 9 9.92 -> 10.49.
+  else if (full_steps <= 48 && (full_steps <= 40 || a.N > kCols)) launch_modes<DT, 16, 3, RBW>(a, stream);
+  else if (full_steps <= 48) launch_modes<DT, 8, 6, RBW>(a, stream);
   else if (full_steps <= 64) launch_modes<DT, 16, 4, RBW>(a, stream);
   else launch_modes<DT, 16, 6, RBW>(a, stream);
 }

@@ -236,9 +236,9 @@ def test_c5_sampled():
     _check_sampled(c, c.N, rows_per_tile=2, whole_tiles=(64,))
 
 
-@pytest.mark.parametrize("S", [0, 1, 4, 5, 8, 9, 12, 13, 16, 17, 32, 33])
+@pytest.mark.parametrize("S", [0, 1, 4, 5, 8, 9, 12, 13, 16, 17, 32, 33, 40, 41, 48, 49, 64, 65])
 @pytest.mark.parametrize("V,N", [(16, 1), (16, 21), (32, 1), (64, 7)])
 def test_waves_and_batches_of_the_kernel_for_few_columns(S, V, N):
-    """Waves and batches change at 4, 8, 12, 16 and 32 whole steps; with and without a ragged one behind them."""
+    """Waves and batches change at 4, 8, 12, 16, 32, 40, 48 and 64 whole steps; with and without a ragged one behind them."""
     Kv = 64 * S + (24 if S % 2 == 0 else 0)
     _check_full(synth.small_case(2 * V, Kv + 16, V, Kv, N, "f16" if S % 2 else "bf16", 730 + S), N, [0], relu=S % 3 == 0)
