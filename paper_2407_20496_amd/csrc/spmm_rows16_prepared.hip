@@ -405,7 +405,12 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   // at N = 384 9.2 -> 12.0 us).
   const int64_t col_blocks = (a.N + kCols - 1) / kCols;
   const bool quad = a.N > kCols && a.s.V % 64 == 0 && a.s.M >= 2048 && (a.s.M / 64) * col_blocks >= 256;
-  const bool both = (a.s.M / 32) * col_blocks >= 256;
+  // One batch of eight waves, one column: everything is requested at once either way, and blocks of 16 rows are kept where
+  // they spread more evenly over the units (11008 x 4096, 32 steps, weights from HBM 8.3 us against 8.7; 20 and 40 steps 6.5
+  // against 6.1 and 10.6 against 9.8).
+  const int64_t halves = a.s.M / 16;
+  const bool spread = a.N == 1 && L.S > 24 && L.S <= 32 && (halves / 2 + 255) / 256 * 2 > (halves + 255) / 256;
+  const bool both = (a.s.M / 32) * col_blocks >= 256 && !spread;
   p.rbw = quad ? 4 : both ? 2 : 1;
   p.blocks_per_wg = 1;
   const int64_t row_wgs = a.s.M / (kRows * p.rbw);
