@@ -25,8 +25,9 @@ constexpr int kStep = 64;   // kept columns per MFMA
 // private LDS slab of one wave: 64 rows x 16 columns, 8-row blocks padded so that the four lane
 // groups of a transposing read fall on different banks
 constexpr int kSlabBytes = 8 * 384;
-constexpr int kXPieces = 4;                 // XMODE 3: 16-byte pieces of the input vector per thread
-constexpr int kXLdsMaxBytes = 48 * 1024;
+constexpr int kXLdsMaxBytes = 48 * 1024;    // XMODE 3: the input vector in LDS, up to 24568 elements,
+template <int NW>
+constexpr int x_pieces = (kXLdsMaxBytes / 16 + NW * 64 - 1) / (NW * 64);  // ... and 16-byte pieces of it per thread
 
 __device__ __forceinline__ int slab_row_offset(int row) { return row * 32 + (row >> 3) * 128; }
 
@@ -116,11 +117,12 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
 
   // XMODE 3: this thread's 16-byte pieces of the input vector (requested now, written to LDS after the first
   // batch of weight loads has been issued); every wave passes the barrier exactly once
-  u32x4 x_mine[kXPieces];
+  u32x4 x_mine[x_pieces<NW>];
   bool x_staged = XMODE != 3 && XMODE != 4;
   if constexpr (XMODE == 3) {
 #pragma unroll
-    for (int r = 0; r < kXPieces; ++r) {
+    for (int r = 0; r < x_pieces<NW>; ++r) {
+      if (r * NW * 64 >= K / 8) break;
       const int piece = min((int)threadIdx.x + r * NW * 64, K / 8 - 1);  // beyond the vector: its last piece again
       x_mine[r] = reinterpret_cast<const u32x4*>(X)[piece];
     }
@@ -143,7 +145,7 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
     }
     if constexpr (XMODE == 3) {
 #pragma unroll
-      for (int r = 0; r < kXPieces; ++r) {
+      for (int r = 0; r < x_pieces<NW>; ++r) {
         const int piece = (int)threadIdx.x + r * NW * 64;
         if (piece < K / 8) reinterpret_cast<u32x4*>(x_lds)[piece] = x_mine[r];
       }
@@ -306,10 +308,12 @@ void launch_modes(const PreparedArgs& a, const PreparedLayout& L, int blocks_per
           a.ldy, a.s.V, L.RB, L.S, a.N - (Y_OFF), a.s.K, a.relu, a.out_f32)
   if (a.N == 1) {
     // staging the input vector pays once a wave gathers for more than four steps (4096 x 11008 at 50 %:
-    // 10.4 -> 9.9 us; with four steps per wave and 688 workgroups it costs 0.8 us instead)
+    // 10.4 -> 9.9 us; with four steps per wave and 688 workgroups it costs 0.8 us instead), with any vector that fits (us, not
+    // staged -> staged on eight waves: 6656 x 17920, 140 steps 31.5 -> 17.2, 9216 x 20000, 157 steps 46.5 -> 27.0, 5120 x 24560,
+    // 192 steps 43.3 -> 20.4, 8192 x 20480, 40 steps 7.9 -> 7.6; sixteen waves with batches of six, staged: 22.9, 33.3, 24.0 and 11.7)
     const size_t x_bytes = ((size_t)a.s.K + 8) * 2;
     const bool stage = a.ldx == 1 && a.s.K % 8 == 0 && (reinterpret_cast<uintptr_t>(a.X) & 15u) == 0 &&
-                       a.s.K <= 8 * kXPieces * NW * 64 && x_bytes <= (size_t)kXLdsMaxBytes && L.S > 4 * NW;
+                       x_bytes <= (size_t)kXLdsMaxBytes && L.S > 4 * NW;
     if (stage) {
       // slabs (static) plus the vector (dynamic) can exceed the default 64 KB of a workgroup
       if (!a.plan && raise_lds_limit<spmm_rows16_prepared_kernel<DT, NW, 3, KB, RBW>>(kXLdsMaxBytes) != hipSuccess)

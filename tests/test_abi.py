@@ -355,3 +355,12 @@ def test_python_calls_convert_arguments_as_ctypes_does():
     layer = hinm.Layer(256, 256, 64, 128, "f16", None, None, None, prepared=fake)
     with pytest.raises(TypeError):
         hinm.hinm_chain(iter([layer]), 8, fake, 8, fake, 8, fake, 0, 0)
+
+
+@pytest.mark.parametrize("M,K,Kv,staged", [(6656, 17920, 8960, True), (9216, 20000, 10000, True), (5120, 24560, 12280, True),
+                                           (2048, 24568, 5000, True), (4096, 20480, 3584, True), (8192, 16392, 2560, True),
+                                           (4096, 24576, 12288, False), (8192, 24560, 2048, False)])
+def test_one_column_is_staged_whenever_it_fits(M, K, Kv, staged):
+    """More than four steps a wave and at most 48 KB: the input vector goes through LDS, whatever the number of waves."""
+    text, _ = hinm.hinm_spmm_prepared_plan(M, K, 128, Kv, "bf16", 1, 1, 1)
+    assert ("XMODE=3," if staged else "XMODE=2,") in text, text

@@ -408,3 +408,12 @@ def test_waves_of_the_16_row_kernel_with_128_workgroups(S):
 def test_eight_waves_on_long_layers_of_one_column():
     """More than 256 workgroups beyond 64 steps."""
     _check(synth.small_case(4128, 64 * 66, 32, 64 * 66 - 8, 1, "bf16", 741), 1, [11])
+
+
+@pytest.mark.parametrize("K", [16384, 16392, 20480, 20488, 24560, 24568, 24576])
+def test_vectors_of_up_to_six_pieces_a_thread(K):
+    """Eight waves stage four pieces of 4096 elements, five or six; beyond 48 KB none."""
+    import paper_2407_20496_amd as hinm
+    c = synth.small_case(64, K, 32, 64 * 40 - 8, 1, "bf16", 750)
+    assert f"NW=8,XMODE={3 if K <= 24568 else 2}," in hinm.hinm_spmm_prepared_plan(c.M, K, c.V, c.Kv, c.dtype, 1, 1, 1)[0]
+    _check(c, 1, [0])
