@@ -380,22 +380,28 @@ struct Rows16Plan {
 
 // Waves and batch with one column block.  A wave's steps pass through its slab one after the other and every step of a batch is
 // code to fetch and registers to hold, so short layers take a wave a step (four at least, which share the epilogue; one column
-// has little to hide, eight steps on four waves do), and no batch has dummy steps.  Against one to sixteen waves with batches of
-// four and six, geometric means over 130 drawn layers with up to 16 columns: 1.19 up to four steps, 1.15 up to eight, 1.1 up to
-// sixteen unless several workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408 workgroups 0.91), 1.07 up
-// to 24, 1.05 up to 40.  Beyond (us): 4096 x 11008, 43 steps, N = 1 5.10 -> 4.95; 8192 x 8192, 64 steps, N = 1
-// 12.6 -> 8.35 (9.5 of it from both halves of a block); 86 steps, N = 1 8.64 -> 7.12 (eight waves 7.61), 5120 x 13824, 108 steps,
-// 320 workgroups 19.6 -> 11.8 (sixteen waves 14.6), N = 3 34.7 -> 27.0; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3; 86 steps with
-// more than one column stay one batch of six (11.9, in batches of four 14.0).
-void one_block_waves(Rows16Plan& p, int S, int N, int64_t wgs) {
+// has little to hide, eight steps on four waves do), and up to 48 steps a wave's steps are one batch (two with 41 to 48 steps of one
+// column; a wave has as many steps as the others or fewer, and what a batch has beyond them is multiplied by zero).  Against one
+// to sixteen waves with batches of four and six, geometric means over 130 drawn layers with up to 16 columns: 1.19 up to four
+// steps, 1.15 up to eight, 1.1 up to sixteen unless several workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408
+// workgroups 0.91), 1.07 up to 24, 1.05 up to 40.  Beyond (us, weights from memory): one column, 41 to 48 steps, batches of three
+// against one of six on ten layers 0.77 to 0.90 of the time (11008 x 5632, 44 steps 9.8 and 12.8); 49 to 56 steps are one batch
+// on sixteen waves, which are ahead while the workgroups fit the units in one round (1600 x 6256, 49 steps 5.49 and 5.81; 8000 x 6400,
+// 50 steps 11.2 and 9.5) and as long as their gathers find the vector nearby (eight waves stage it: 0.97 times over 24 layers of
+// twice the kept columns, 1.03 with three times, 9408 and more, 1.12 with four: 1024 x 14336, 56 steps 7.00 and 5.89), with 57 to 64
+// eight are (2464 x 8064 6.84 -> 6.51, 8192 x 8192 13.5 -> 10.2; 9.5 of it from both halves of a block); 86 steps 10.0 -> 8.8, 5120 x 13824, 108 steps, 320 workgroups 21.6 -> 13.0 (sixteen waves 14.6).  With more columns
+// sixteen waves are ahead throughout (60 layers with 49 to 64 steps; 4992 x 6512, N = 4 13.6 and 15.3), in batches of six up to 96
+// steps (4096 x 11008, N = 16 11.9 and 14.0) and beyond 128, where four make three of them (30 layers, 1.03 times; 2112 x 10872, N = 2 21.1
+// and 22.4), of four between (97 to 128 steps, 16 layers 1.22 times; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3).
+void one_block_waves(Rows16Plan& p, int S, int K, int N, int64_t wgs) {
   if (S <= 4) p.nw = 4, p.kb = 1;
   else if (S <= 8 && N == 1) p.nw = 4, p.kb = 2;
   else if (S > 12 && S <= 16 && wgs > 256) p.nw = 4, p.kb = 4;
   else if (S > 40 && S <= 48 && N == 1) p.nw = 8, p.kb = 3;
   else if (S <= 48) p.nw = 8, p.kb = (S + 7) / 8;
-  else if (S <= 64) p.nw = N == 1 || wgs >= 128 ? 8 : 16, p.kb = 4;
+  else if (S <= 64) p.nw = N == 1 && (S > 56 || K > 9216 || wgs > 256) ? 8 : 16, p.kb = 4;
   else if (N == 1) p.nw = wgs <= 256 ? 16 : 8, p.kb = 3;
-  else p.nw = 16, p.kb = S <= 96 ? 6 : 4;
+  else p.nw = 16, p.kb = S <= 96 || S > 128 ? 6 : 4;
 }
 
 Rows16Plan plan_rows16(const PreparedArgs& a) {
@@ -419,7 +425,7 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   p.blocks_per_wg = 1;
   const int64_t row_wgs = a.s.M / (kRows * p.rbw);
   if (a.N <= kCols) {
-    one_block_waves(p, L.S, a.N, row_wgs);
+    one_block_waves(p, L.S, a.s.K, a.N, row_wgs);
     return p;
   }
   // One batch per wave where possible (every load of the wave in flight at once): waves x batch >= steps ...
@@ -451,7 +457,7 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   // Short layers as with one column block while that makes no more than eight waves a unit (1.09 to 1.26 times).
   if (p.blocks_per_wg == 1 && L.S <= 16) {
     Rows16Plan q = p;
-    one_block_waves(q, L.S, a.N, row_wgs * col_blocks);
+    one_block_waves(q, L.S, a.s.K, a.N, row_wgs * col_blocks);
     if (row_wgs * col_blocks * q.nw <= 2048) p = q;
   }
   return p;

@@ -364,3 +364,15 @@ def test_one_column_is_staged_whenever_it_fits(M, K, Kv, staged):
     """More than four steps a wave and at most 48 KB: the input vector goes through LDS, whatever the number of waves."""
     text, _ = hinm.hinm_spmm_prepared_plan(M, K, 128, Kv, "bf16", 1, 1, 1)
     assert ("XMODE=3," if staged else "XMODE=2,") in text, text
+
+
+@pytest.mark.parametrize("M,K,S,N,waves,batch", [
+    (4096, 8192, 49, 1, 16, 4), (4096, 9216, 56, 1, 16, 4), (4128, 9216, 56, 1, 8, 4), (4096, 9224, 56, 1, 8, 4),  # 256, 258 workgroups
+    (4096, 4096, 57, 1, 8, 4), (4096, 4096, 64, 1, 8, 4),
+    (2048, 8192, 49, 2, 16, 4), (4096, 8192, 56, 16, 16, 4), (4096, 8192, 64, 8, 16, 4),
+    (1024, 8192, 65, 2, 16, 6), (1024, 8192, 96, 16, 16, 6), (1024, 8192, 97, 2, 16, 4), (1024, 8192, 128, 16, 16, 4),
+    (1024, 16384, 129, 2, 16, 6), (1024, 16384, 160, 16, 16, 6)])
+def test_waves_and_batches_of_long_layers(M, K, S, N, waves, batch):
+    ld = 1 if N == 1 else 16
+    text, _ = hinm.hinm_spmm_prepared_plan(M, K, 32, 64 * S, "bf16", N, ld, ld)
+    assert f"NW={waves}," in text and f"KB={batch}," in text, text

@@ -417,3 +417,14 @@ def test_vectors_of_up_to_six_pieces_a_thread(K):
     c = synth.small_case(64, K, 32, 64 * 40 - 8, 1, "bf16", 750)
     assert f"NW=8,XMODE={3 if K <= 24568 else 2}," in hinm.hinm_spmm_prepared_plan(c.M, K, c.V, c.Kv, c.dtype, 1, 1, 1)[0]
     _check(c, 1, [0])
+
+
+@pytest.mark.parametrize("S,K,N,waves,batch", [(49, 9216, 1, 16, 4), (56, 9216, 1, 16, 4), (56, 9224, 1, 8, 4), (57, 4096, 1, 8, 4),
+                                               (64, 4096, 9, 16, 4), (128, 8192, 9, 16, 4), (129, 8256, 9, 16, 6), (193, 12352, 16, 16, 6)])
+def test_waves_and_batches_of_long_layers(S, K, N, waves, batch):
+    import paper_2407_20496_amd as hinm
+    c = synth.small_case(64, K, 32, 64 * S - 8, N, "f16", 760)
+    ld = 1 if N == 1 else 16
+    text = hinm.hinm_spmm_prepared_plan(c.M, K, c.V, c.Kv, c.dtype, N, ld, ld)[0]
+    assert f"NW={waves}," in text and f"KB={batch}," in text, text
+    _check(c, N, [0])
