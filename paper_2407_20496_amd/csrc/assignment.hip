@@ -17,7 +17,8 @@
 //            (the low words only where those tie).
 // With capacities the matrix is n x m instead of n x n with every column repeated.
 // Measured, against one augmenting-path search per row from column minima on two to four waves: 64 problems of 512 x 512
-// (four iterations of the tile-wise search on 4096 x 4096) 161 -> 16 ms.  Small problems have a kernel of their own, below.
+// (four iterations of the tile-wise search on 4096 x 4096) 161 -> 15 ms, 12 with `row_paths` (129 to 512 columns of one row
+// each 1.09 to 1.21 times).  Small problems have a kernel of their own, below.
 // Every loop is bounded by the problem's size.  Costs may be of any finite size below 1e300: a row's smallest cost is
 // taken off the row first (a constant of a row changes no choice, but next to one of 1e39 the other rows' costs would
 // be rounded away), and the start, which works in single precision, scales what is left by the power of two of
@@ -490,21 +491,24 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
     n_free += __popcll(mask);
   }
   bool failed = false;
-  if constexpr (!CAPACITY) {
+  // `row_paths` keeps two more values a column, which sixteen columns a lane leave no registers for: 64 spilled ones in the chain of
+  // links took 31 ms against 19.6 (4 problems of 1024 x 1024; of 600 x 600 9.4 against 6.6).
+  if constexpr (!CAPACITY && CPL <= 8) {
     failed = !row_paths<CPL>([&](int i, int j) { return row_of(i)[j] - base_of(i); }, col_v, filled, members, list, n_free,
                              row_col, m);
     for (int i = lane; i < n; i += 64) out[i] = failed ? i : row_col[i];
     return;
   }
   double v[CPL];
-  int y[CPL];  // how many rows the column holds
+  int y[CPL];  // how many rows the column holds; where it takes one, that row or -1
   int col[CPL];
 #pragma unroll
   for (int c = 0; c < CPL; ++c) {
     const int j = 64 * c + lane;
     col[c] = min(j, m - 1);
     v[c] = j < m ? col_v[j] : 0.0;
-    y[c] = j < m ? filled[col[c]] : 0;
+    const int count = j < m ? filled[col[c]] : 0;
+    y[c] = CAPACITY ? count : (count ? members[col[c]] : -1);
   }
   auto reduced_row = [&](int i, double (&x)[CPL]) {
     const double* r = row_of(i);
@@ -544,7 +548,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       const int at_c = CPL == 1 ? 0 : __builtin_amdgcn_readlane(least_c, at);
       const int j1 = 64 * at_c + at;
       const int held = at_column(y, j1);
-      if (held < cap) {
+      if (CAPACITY ? held < cap : held < 0) {
         end = j1;
         break;
       }
@@ -561,23 +565,29 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
           pred[c] = better ? i : pred[c];
         }
       };
-      const int* who = members + j1 * cap;
-      int e = 0;
-      for (; e + 4 <= cap; e += 4) {  // four rows in flight
-        int i4[4];
-        double x4[4][CPL];
+      if constexpr (CAPACITY) {
+        const int* who = members + j1 * cap;
+        int e = 0;
+        for (; e + 4 <= cap; e += 4) {  // four rows in flight
+          int i4[4];
+          double x4[4][CPL];
 #pragma unroll
-        for (int q = 0; q < 4; ++q) i4[q] = __builtin_amdgcn_readfirstlane(who[e + q]);
+          for (int q = 0; q < 4; ++q) i4[q] = __builtin_amdgcn_readfirstlane(who[e + q]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) reduced_row(i4[q], x4[q]);
+          for (int q = 0; q < 4; ++q) reduced_row(i4[q], x4[q]);
 #pragma unroll
-        for (int q = 0; q < 4; ++q) relax(i4[q], x4[q]);
-      }
-      for (; e < cap; ++e) {
-        const int i = __builtin_amdgcn_readfirstlane(who[e]);
+          for (int q = 0; q < 4; ++q) relax(i4[q], x4[q]);
+        }
+        for (; e < cap; ++e) {
+          const int i = __builtin_amdgcn_readfirstlane(who[e]);
+          double x[CPL];
+          reduced_row(i, x);
+          relax(i, x);
+        }
+      } else {
         double x[CPL];
-        reduced_row(i, x);
-        relax(i, x);
+        reduced_row(held, x);
+        relax(held, x);
       }
     }
     if (end < 0) {
@@ -589,28 +599,37 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
       if (d[c] < open[c]) v[c] += d[c] - reach;
     // shift the rows along the path
     int j = end;
-    int slot = at_column(y, end);
-    set_column(y, end, lane, slot + 1);
+    int slot = 0;
+    if constexpr (CAPACITY) {
+      slot = at_column(y, end);
+      set_column(y, end, lane, slot + 1);
+    }
     for (int guard = 0; guard <= m; ++guard) {
       const int i = at_column(pred, j);
       const int from = __builtin_amdgcn_readfirstlane(row_col[i]);
       row_col[i] = j;
-      int freed = 0;
-      if (i != start) {
-        const int* who = members + from * cap;
-        for (int e = 0; e < cap; ++e)
-          if (__builtin_amdgcn_readfirstlane(who[e]) == i) freed = e;
+      if constexpr (CAPACITY) {
+        int freed = 0;
+        if (i != start) {
+          const int* who = members + from * cap;
+          for (int e = 0; e < cap; ++e)
+            if (__builtin_amdgcn_readfirstlane(who[e]) == i) freed = e;
+        }
+        members[j * cap + slot] = i;
+        slot = freed;
+      } else {
+        set_column(y, j, lane, i);
       }
-      members[j * cap + slot] = i;
-      slot = freed;
       if (i == start) break;
       j = from;
     }
   }
   if (failed) {
     for (int i = lane; i < n; i += 64) out[i] = i;
-  } else {
+  } else if constexpr (CAPACITY) {
     for (int e = lane; e < n; e += 64) out[members[e]] = e;
+  } else {
+    for (int i = lane; i < n; i += 64) out[i] = row_col[i];
   }
 }
 

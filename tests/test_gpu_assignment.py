@@ -148,3 +148,11 @@ def test_points_that_share_their_distances(T, n):
     d = gyro.kmeans_distances(F, gyro.kmeans_initial_centroids(F, n))
     # distances of whole numbers: every total is exact
     assert obj[0] == gyro.kmeans_objective(d, gyro.kmeans_balanced_assignment(d, n))
+
+
+def test_sixteen_columns_a_lane_with_costs_of_all_kinds():
+    """The path loop of its own that problems of more than 512 columns have, at its largest and next to its smallest size."""
+    test_square_problems(1024, False)
+    test_costs_beyond_single_precision(514, "some")
+    test_infinite_scores_are_pairs_that_cannot_be_taken(514, True)
+    test_infinite_scores_are_pairs_that_cannot_be_taken(514, False)

@@ -82,3 +82,15 @@ def test_built_library(tmp_path):
         planted += len(lds_reads.violations(re.sub(r"s_waitcnt lgkmcnt\(0\) ", "s_nop 0 ", first)))
     assert rings >= 60 and planted > 100
     assert lds_reads.check(build.LIB) == []
+
+
+def test_chains_of_the_assignment_solver_keep_their_registers(tmp_path):
+    """One row a column: a link of a path is a dependent chain on one wave, and no form of it spills."""
+    forms = 0
+    for code in lds_reads.code_objects(build.LIB, str(tmp_path)):
+        notes = lds_reads._run(lds_reads.LLVM + "/llvm-readelf", "--notes", code)
+        for name, (_, spilled, _) in lds_reads.resources(notes).items():
+            if re.search(r"assign_kernelILi\d+ELi\d+ELb[01]ELb0E", name) or re.search(r"assign_tile_kernelILi\dELi\dELi\d+ELb0E", name):
+                forms += 1
+                assert spilled == 0, (name, spilled)
+    assert forms >= 8
