@@ -187,7 +187,7 @@ hipError_t launch_assignment(const double* cost, int32_t* assign, int problems, 
 
 // ---- output-channel permutation search ---------------------------------------------------------------
 constexpr int kOcpMaxK = 16384;   // columns one workgroup of the cost kernel holds in registers
-constexpr int kOcpMaxV = 4096;    // positions of a tile (flags in LDS)
+constexpr int kOcpMaxV = 4096;    // positions of a tile (flags and row numbers in LDS)
 struct OcpWorkspace {
   size_t base, cluster, cost, assign, moved, total_bytes;
 };

@@ -30,8 +30,11 @@ __device__ __forceinline__ int clamp_index(int x, int n) { return x < 0 ? 0 : (x
 // base[t][k] = sum over the positions of tile t that stay (ascending position) of the saliency in
 // column k; cluster[t][k] = the same over the channels of cluster t (cluster order).  The rows' numbers are looked up once a
 // workgroup and sixteen rows are requested before the first is added: with one row at a time, each behind its look-up and
-// the one before, 48 tiles of 64 rows and 768 columns took 17.3 us, 11.2 here.
+// the one before, 48 tiles of 64 rows and 768 columns took 17.3 us, 11.2 here (16384 x 16384, V = 128 367 -> 231).  LDS for what
+// the tile has and no more: with room for 4096 rows a unit held four workgroups (256 tiles of 32 rows, 2048 columns 25.7 us, 17.9
+// here, 8192 columns 72 and 59).
 constexpr int kSumRows = 16;
+inline size_t ocp_sums_lds_bytes(int V, int n) { return (size_t)V * 5 + (size_t)n * 4; }
 template <int DT>
 __global__ __launch_bounds__(kThreads) void ocp_sums_kernel(const uint16_t* __restrict__ W,
                                                             const float* __restrict__ rho,
@@ -40,8 +43,10 @@ __global__ __launch_bounds__(kThreads) void ocp_sums_kernel(const uint16_t* __re
                                                             const int32_t* __restrict__ clusters,
                                                             double* __restrict__ base, double* __restrict__ cluster,
                                                             int T, int K, int V, int n) {
-  __shared__ uint8_t leaves[kOcpMaxV];
-  __shared__ int32_t row_of[kOcpMaxV], come_row[kOcpMaxV];
+  extern __shared__ int32_t sums_lds[];  // ocp_sums_lds_bytes
+  int32_t* const row_of = sums_lds;
+  int32_t* const come_row = row_of + V;
+  uint8_t* const leaves = reinterpret_cast<uint8_t*>(come_row + n);
   const int t = blockIdx.x;
   for (int p = threadIdx.x; p < V; p += kThreads) {
     leaves[p] = 0;
@@ -606,15 +611,16 @@ hipError_t launch_ocp_search(const OcpArgs& a, hipStream_t stream) {
   int32_t* moved = reinterpret_cast<int32_t*>(ws + w.moved);
   const uint16_t* Wb = static_cast<const uint16_t*>(a.W);
   const dim3 sums_grid(T, (s.K + kThreads - 1) / kThreads);
+  const size_t sums_lds = ocp_sums_lds_bytes(s.V, n);
   const dim3 cost_grid(T, T);
   for (int it = 0; it < a.iters; ++it) {
     const int32_t* smp = a.samples + (size_t)it * T * n;
     const int32_t* cl = a.clusters ? a.clusters + (size_t)it * T * n : nullptr;
     if (s.dtype == HINM_F16)
-      ocp_sums_kernel<HINM_F16><<<sums_grid, kThreads, 0, stream>>>(Wb, a.rho, a.row_order, smp, cl, base, cluster, T,
+      ocp_sums_kernel<HINM_F16><<<sums_grid, kThreads, sums_lds, stream>>>(Wb, a.rho, a.row_order, smp, cl, base, cluster, T,
                                                                      s.K, s.V, n);
     else
-      ocp_sums_kernel<HINM_BF16><<<sums_grid, kThreads, 0, stream>>>(Wb, a.rho, a.row_order, smp, cl, base, cluster, T,
+      ocp_sums_kernel<HINM_BF16><<<sums_grid, kThreads, sums_lds, stream>>>(Wb, a.rho, a.row_order, smp, cl, base, cluster, T,
                                                                       s.K, s.V, n);
     const int pair_blocks = (T * T + kThreads / 64 - 1) / (kThreads / 64);
     if (s.K <= 512) ocp_cost_wave_kernel<8><<<pair_blocks, kThreads, 0, stream>>>(base, cluster, cost, T, s.K, s.Kv);

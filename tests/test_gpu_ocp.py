@@ -222,3 +222,16 @@ def test_edges_of_one_wave_per_pair(K, scores):
 def test_edges_of_the_pieces_of_a_distance(K):
     """Pieces of 32 columns: part of one, one, several with and without a rest."""
     test_balanced_kmeans_round_by_round(56, K, 8, 8, 3, "f16", True)
+
+
+@pytest.mark.parametrize("V,n", [(4096, 4096), (4096, 1), (4093, 7), (1, 1)])
+def test_sums_of_the_tallest_tiles(V, n):
+    """The row numbers of a tile and of its samples in LDS, up to 4096 of each."""
+    c = synth.small_case(2 * V, 16, V, 8, 1, "bf16", 610)
+    Wb = c.weights()
+    rng = np.random.default_rng(V + n)
+    rho = rng.integers(0, 3, size=(c.M, c.K)).astype(np.float32)
+    samples = np.stack([rng.permutation(V)[:n] for _ in range(c.T)])[None].astype(np.int32)
+    start = rng.permutation(c.M).astype(np.int32)
+    after, obj = _gpu_search(c, Wb, rho, start, samples, None)
+    _check_iteration(c, gyro.saliency_matrix(Wb, c.dtype, rho), start, after, samples[0], None, obj[0], exact=True)

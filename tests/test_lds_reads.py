@@ -94,3 +94,14 @@ def test_chains_of_the_assignment_solver_keep_their_registers(tmp_path):
                 forms += 1
                 assert spilled == 0, (name, spilled)
     assert forms >= 8
+
+
+def test_sums_of_the_row_search_take_lds_by_the_tile(tmp_path):
+    """No room for the tallest tile at every launch: eight workgroups share a unit."""
+    sizes = []
+    for code in lds_reads.code_objects(build.LIB, str(tmp_path)):
+        notes = lds_reads._run(lds_reads.LLVM + "/llvm-readelf", "--notes", code)
+        for entry in re.split(r"\n\s*- \.agpr_count:", notes)[1:]:
+            if "ocp_sums_kernel" in re.search(r"\n\s*\.name:\s*(\S+)", entry)[1]:
+                sizes.append(int(re.search(r"\.group_segment_fixed_size:\s*(\d+)", entry)[1]))
+    assert len(sizes) == 2 and max(sizes) == 0, sizes
