@@ -390,30 +390,25 @@ __global__ __launch_bounds__(kThreads) void km_init_kernel(const float* __restri
   if (k < K) C[(size_t)c * K + k] = (double)F[(size_t)c * n * K + k];
 }
 
-// d[q][c] for 64 clusters (one a lane) and one or two points a wave.  A chain of K steps per pair is the definition (the
+// d[q][c] for 64 clusters (one a lane) and one point a wave.  A chain of K steps per pair is the definition (the
 // rounding of every step is pinned), so the chains have to run on operands that are at hand: 32 columns of the
 // centroids at a time go through LDS (two pieces in turn, the next one requested ahead; rows padded to an odd number of
 // doubles: no bank conflicts), and a piece of a point's features is held by 32 lanes, each read from its lane as a scalar.
 // 384 points x 48 clusters x 768 columns: 76 us with one column of a different centroid row per lane and step, 26.5 us with
 // the features as scalar loads (they share a counter with the LDS reads, which makes every one wait for all), 21.0 here.
-// Two points read the centroids half as often once there are 256 workgroups of them.
 constexpr int kDistColumns = 32;
-template <int POINTS>  // per wave
 __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __restrict__ F,
                                                                const double* __restrict__ C,
                                                                double* __restrict__ dist, int T, int K, int points) {
 #pragma clang fp contract(off)  // product and sum are rounded separately: that rounding is part of the definition
-  static_assert(POINTS == 1 || POINTS == 2, "a point's piece is held by half of the wave");
   __shared__ double tile[2][64][kDistColumns + 1];
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int c0 = blockIdx.y * 64;
-  const int q0 = (blockIdx.x * (kThreads / 64) + wave) * POINTS;
+  const int q = blockIdx.x * (kThreads / 64) + wave;
   const int column = threadIdx.x % kDistColumns, row = threadIdx.x / kDistColumns;
-  const float* const f = F + (size_t)min(q0 + (POINTS == 2 ? lane / kDistColumns : 0), points - 1) * K;
-  double acc[POINTS];
-#pragma unroll
-  for (int p = 0; p < POINTS; ++p) acc[p] = 0.0;
+  const float* const f = F + (size_t)min(q, points - 1) * K;
+  double acc = 0.0;
   constexpr int kRows = kThreads / kDistColumns;  // of a piece, at a time
   constexpr int kPieces = 64 / kRows;
   double ahead[kPieces];
@@ -435,22 +430,20 @@ __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __re
     const double mine = (double)f_ahead;
     __syncthreads();  // this piece is there, and nobody reads the one before it
     if (k0 + kDistColumns < K) request(k0 + kDistColumns);
-    auto square = [&](double cen, int p, int k) {
-      const double x = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), p * kDistColumns + k),
-                                        __builtin_amdgcn_readlane(__double2loint(mine), p * kDistColumns + k));
+    auto square = [&](double cen, int k) {
+      const double x = __hiloint2double(__builtin_amdgcn_readlane(__double2hiint(mine), k),
+                                        __builtin_amdgcn_readlane(__double2loint(mine), k));
       const double diff = x - cen;
       return diff * diff;
     };
     if (k0 + kDistColumns <= K) {
       // the squares of the next four columns between the sums of these: a lone wave issues in order
       constexpr int kAhead = 4;
-      double cen[2 * kAhead], sq[2][kAhead][POINTS];
+      double cen[2 * kAhead], sq[2][kAhead];
 #pragma unroll
       for (int e = 0; e < 2 * kAhead; ++e) cen[e] = tile[at][lane][e];
 #pragma unroll
-      for (int e = 0; e < kAhead; ++e)
-#pragma unroll
-        for (int p = 0; p < POINTS; ++p) sq[0][e][p] = square(cen[e], p, e);
+      for (int e = 0; e < kAhead; ++e) sq[0][e] = square(cen[e], e);
 #pragma unroll
       for (int k = 0; k < kDistColumns; k += kAhead) {
         const int now = (k / kAhead) & 1;
@@ -460,29 +453,84 @@ __global__ __launch_bounds__(kThreads) void km_distance_kernel(const float* __re
           if (k + 2 * kAhead < kDistColumns) after[e] = tile[at][lane][k + 2 * kAhead + e];
 #pragma unroll
         for (int e = 0; e < kAhead; ++e) {
-#pragma unroll
-          for (int p = 0; p < POINTS; ++p) {
-            acc[p] = acc[p] + sq[now][e][p];
-            if (k + kAhead < kDistColumns) sq[now ^ 1][e][p] = square(cen[kAhead + e], p, k + kAhead + e);
-          }
+          acc = acc + sq[now][e];
+          if (k + kAhead < kDistColumns) sq[now ^ 1][e] = square(cen[kAhead + e], k + kAhead + e);
           __builtin_amdgcn_sched_barrier(0);
         }
 #pragma unroll
         for (int e = 0; e < kAhead; ++e) cen[kAhead + e] = after[e];
       }
     } else {
-      for (int k = 0; k < K - k0; ++k) {
-        const double cen = tile[at][lane][k];
-#pragma unroll
-        for (int p = 0; p < POINTS; ++p) acc[p] = acc[p] + square(cen, p, k);
-      }
+      for (int k = 0; k < K - k0; ++k) acc = acc + square(tile[at][lane][k], k);
     }
     at ^= 1;
     if (k0 + kDistColumns < K) put(at);
   }
+  if (c0 + lane < T && q < points) dist[(size_t)q * T + c0 + lane] = acc;
+}
+
+// The same with two points a wave, for more than three workgroups a unit of the kernel above: there instructions count, and features
+// as scalar loads cost none.  256 x 4 points to 256 clusters, 2048 columns 131 us above, 125 here, 512 x 2 to 512 244 and 209; but 192 x
+// 5 to 192 (720 workgroups above) 105 and 125, 128 x 8 to 128 78 and 119.
+constexpr int kManyColumns = 64, kManyPoints = 2;
+__global__ __launch_bounds__(kThreads) void km_distance_many_kernel(const float* __restrict__ F,
+                                                                    const double* __restrict__ C,
+                                                                    double* __restrict__ dist, int T, int K, int points) {
+#pragma clang fp contract(off)  // product and sum are rounded separately: that rounding is part of the definition
+  __shared__ double tile[64][kManyColumns + 1];
+  const int lane = threadIdx.x & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int c0 = blockIdx.y * 64;
+  const int q0 = (blockIdx.x * (kThreads / 64) + wave) * kManyPoints;
+  const float* f[kManyPoints];
+  double acc[kManyPoints];
+#pragma unroll
+  for (int p = 0; p < kManyPoints; ++p) {
+    f[p] = F + (size_t)min(q0 + p, points - 1) * K;
+    acc[p] = 0.0;
+  }
+  constexpr int kPieces = 64 / (kThreads / 64);
+  double ahead[kPieces];
+  auto request = [&](int k0) {
+    const int k_lane = min(k0 + lane, K - 1);
+#pragma unroll
+    for (int r = 0; r < kPieces; ++r)
+      ahead[r] = C[(size_t)min(c0 + wave + r * (kThreads / 64), T - 1) * K + k_lane];
+  };
+  request(0);
+  for (int k0 = 0; k0 < K; k0 += kManyColumns) {
+    __syncthreads();
+#pragma unroll
+    for (int r = 0; r < kPieces; ++r) tile[wave + r * (kThreads / 64)][lane] = ahead[r];
+    __syncthreads();
+    if (k0 + kManyColumns < K) request(k0 + kManyColumns);
+    const int count = min(kManyColumns, K - k0);
+    if (count == kManyColumns) {
+#pragma unroll 16
+      for (int k = 0; k < kManyColumns; ++k) {
+        const double cen = tile[lane][k];
+#pragma unroll
+        for (int p = 0; p < kManyPoints; ++p) {
+          const double diff = (double)f[p][k0 + k] - cen;
+          const double sq = diff * diff;
+          acc[p] = acc[p] + sq;
+        }
+      }
+    } else {
+      for (int k = 0; k < count; ++k) {
+        const double cen = tile[lane][k];
+#pragma unroll
+        for (int p = 0; p < kManyPoints; ++p) {
+          const double diff = (double)f[p][k0 + k] - cen;
+          const double sq = diff * diff;
+          acc[p] = acc[p] + sq;
+        }
+      }
+    }
+  }
   if (c0 + lane < T) {
 #pragma unroll
-    for (int p = 0; p < POINTS; ++p)
+    for (int p = 0; p < kManyPoints; ++p)
       if (q0 + p < points) dist[(size_t)(q0 + p) * T + c0 + lane] = acc[p];
   }
 }
@@ -570,11 +618,11 @@ hipError_t launch_ocp_cluster(const KmeansArgs& a, hipStream_t stream) {
   for (int r = 0; r < a.rounds; ++r) {
     constexpr int kWaves = kThreads / 64;
     const int cluster_blocks = (T + 63) / 64;
-    if ((points + 2 * kWaves - 1) / (2 * kWaves) * cluster_blocks >= 256)
-      km_distance_kernel<2><<<dim3((points + 2 * kWaves - 1) / (2 * kWaves), cluster_blocks), kThreads, 0, stream>>>(
-          F, a.centroids, dist, T, s.K, points);
+    const int ones = (points + kWaves - 1) / kWaves;
+    if (ones * cluster_blocks <= 3 * 256)
+      km_distance_kernel<<<dim3(ones, cluster_blocks), kThreads, 0, stream>>>(F, a.centroids, dist, T, s.K, points);
     else
-      km_distance_kernel<1><<<dim3((points + kWaves - 1) / kWaves, cluster_blocks), kThreads, 0, stream>>>(
+      km_distance_many_kernel<<<dim3((ones + kManyPoints - 1) / kManyPoints, cluster_blocks), kThreads, 0, stream>>>(
           F, a.centroids, dist, T, s.K, points);
     e = hipGetLastError();
     if (e != hipSuccess) return e;

@@ -148,7 +148,7 @@ def _gpu_cluster(c, Wb, rho, row_order, sampled, rounds, centroids=None):
     (48, 40, 8, 16, 3, "f16", False),
     (64, 300, 16, 152, 5, "bf16", True),
     (40, 24, 1, 8, 1, "f16", True),
-    (1040, 72, 8, 32, 7, "f16", True),       # 910 points, 130 clusters: two points a wave
+    (1040, 72, 8, 32, 7, "f16", True),       # 910 points, 130 clusters: three groups of 64
 ])
 def test_balanced_kmeans_round_by_round(M, K, V, Kv, n, dtype, scored):
     c = synth.small_case(M, K, V, Kv, 1, dtype, 101)
@@ -235,3 +235,9 @@ def test_sums_of_the_tallest_tiles(V, n):
     start = rng.permutation(c.M).astype(np.int32)
     after, obj = _gpu_search(c, Wb, rho, start, samples, None)
     _check_iteration(c, gyro.saliency_matrix(Wb, c.dtype, rho), start, after, samples[0], None, obj[0], exact=True)
+
+
+@pytest.mark.parametrize("T,n,K", [(192, 5, 72), (200, 5, 24), (200, 5, 64), (200, 5, 72), (256, 4, 136), (341, 3, 40)])
+def test_distances_with_one_and_two_points_a_wave(T, n, K):
+    """Up to three workgroups a unit (192 x 5 to 192: 720) and more; pieces of 64 columns with and without a rest."""
+    test_balanced_kmeans_round_by_round(T * 5, K, 5, 8, n, "bf16", True)
