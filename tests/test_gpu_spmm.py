@@ -242,3 +242,10 @@ def test_waves_and_batches_of_the_kernel_for_few_columns(S, V, N):
     """Waves and batches change at 4, 8, 12, 16, 32, 40, 48 and 64 whole steps; with and without a ragged one behind them."""
     Kv = 64 * S + (24 if S % 2 == 0 else 0)
     _check_full(synth.small_case(2 * V, Kv + 16, V, Kv, N, "f16" if S % 2 else "bf16", 730 + S), N, [0], relu=S % 3 == 0)
+
+
+@pytest.mark.parametrize("S", [24, 25, 28, 29])
+@pytest.mark.parametrize("tail", [0, 24])
+def test_one_column_with_25_to_28_steps(S, tail):
+    """Eight waves with batches of four, sixteen with two on both sides."""
+    _check_full(synth.small_case(48, 64 * S + 40, 16, 64 * S + tail, 1, "f16" if tail else "bf16", 770 + S), 1, [0])
