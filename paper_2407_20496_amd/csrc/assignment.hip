@@ -694,9 +694,8 @@ __device__ __forceinline__ double dpp(double x) {
 // lane ^ 1, lane ^ 2, the other four of eight (once those agree), lane ^ 8
 constexpr int kDppXor1 = 0xB1, kDppXor2 = 0x4E, kDppHalfMirror = 0x141, kDppXor8 = 0x128;
 
-// Minimum and maximum as medians: one instruction, where fminf first quiets operands that come from another lane.
+// Minimum as a median: one instruction, where fminf first quiets operands that come from another lane.
 __device__ __forceinline__ float least_of(float x, float y) { return __builtin_amdgcn_fmed3f(x, y, -__builtin_inff()); }
-__device__ __forceinline__ float most_of(float x, float y) { return __builtin_amdgcn_fmed3f(x, y, __builtin_inff()); }
 // two smallest of (s1 <= s2) and (t1 <= t2)
 __device__ __forceinline__ void merge_two(float& s1, float& s2, float t1, float t2) {
   s2 = least_of(__builtin_amdgcn_fmed3f(s1, s2, t1), t2);
@@ -1252,15 +1251,16 @@ hipError_t launch_cfg(const double* cost, int32_t* assign, int problems, int n, 
   return hipGetLastError();
 }
 
+// Problems that `tile_holds` leaves: with one row a column those have more than 128 columns.
 template <bool CAPACITY>
 hipError_t launch(const double* cost, int32_t* assign, int problems, int n, int m, int cap, hipStream_t stream) {
-  if (m <= 256 && assign_lds(n, m, 1024, true).total <= kLdsBytes) {
-    if (m <= 64) return launch_cfg<1, true, CAPACITY>(cost, assign, problems, n, m, cap, stream);
-    if (m <= 128) return launch_cfg<2, true, CAPACITY>(cost, assign, problems, n, m, cap, stream);
-    return launch_cfg<4, true, CAPACITY>(cost, assign, problems, n, m, cap, stream);  // at most some 135 x 135
+  const bool in_lds = assign_lds(n, m, 1024, true).total <= kLdsBytes;
+  if constexpr (CAPACITY) {
+    if (m <= 64) return (in_lds ? launch_cfg<1, true, true> : launch_cfg<1, false, true>)(cost, assign, problems, n, m, cap, stream);
+    if (m <= 128) return (in_lds ? launch_cfg<2, true, true> : launch_cfg<2, false, true>)(cost, assign, problems, n, m, cap, stream);
+  } else {
+    if (in_lds) return launch_cfg<4, true, false>(cost, assign, problems, n, m, cap, stream);  // at most some 135 x 135
   }
-  if (m <= 64) return launch_cfg<1, false, CAPACITY>(cost, assign, problems, n, m, cap, stream);
-  if (m <= 128) return launch_cfg<2, false, CAPACITY>(cost, assign, problems, n, m, cap, stream);
   if (m <= 256) return launch_cfg<4, false, CAPACITY>(cost, assign, problems, n, m, cap, stream);
   if (m <= 512) return launch_cfg<8, false, CAPACITY>(cost, assign, problems, n, m, cap, stream);
   if constexpr (!CAPACITY) return launch_cfg<16, false, false>(cost, assign, problems, n, m, cap, stream);

@@ -54,7 +54,7 @@ __device__ __forceinline__ u32x8 read_b_operand(const uint8_t* slab, int i, int 
   return b;
 }
 
-// XMODE: 0 = any N / ld (element loads, slow), 1 = rows are 16-byte aligned (ld % 8 == 0; columns beyond N
+// XMODE: 1 = rows are 16-byte aligned (ld % 8 == 0; columns beyond N
 // are computed on whatever the padding holds and never stored), 2 = N == 1, 3 = N == 1 with the input vector staged in LDS (a 64-lane gather of 2-byte
 // elements from global memory costs the address unit one cycle per lane; the vector is small, so the
 // workgroup copies it whole, requested before everything else, and picks from LDS), 4 = 16 columns with all K
@@ -214,16 +214,9 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
           b_lo[u][cb] = *reinterpret_cast<const u32x4*>(r_lo + 8 * (lane & 1));
           b_hi[u][cb] = *reinterpret_cast<const u32x4*>(r_hi + 8 * (lane & 1));
         }
-      } else if constexpr (XMODE == 2) {
+      } else {
         b_lo[u][0] = u32x4{(uint32_t)xr[0], 0, 0, 0};
         b_hi[u][0] = u32x4{0, 0, 0, 0};
-      } else {
-        uint32_t w[8] = {0, 0, 0, 0, 0, 0, 0, 0};
-#pragma unroll
-        for (int e = 0; e < 16; ++e)
-          if (n0 + e < N) w[e >> 1] |= (uint32_t)xr[e] << (16 * (e & 1));
-        b_lo[u][0] = u32x4{w[0], w[1], w[2], w[3]};
-        b_hi[u][0] = u32x4{w[4], w[5], w[6], w[7]};
       }
     }
     // phase 4: multiply
@@ -288,25 +281,23 @@ __global__ __launch_bounds__(NW * 64) void spmm_rows16_prepared_kernel(
   }
 }
 
-template <int DT, int NW, int KB, int RBW>
-void launch_modes(const PreparedArgs& a, const PreparedLayout& L, int blocks_per_wg, hipStream_t stream) {
+template <int DT, int NW, int XMODE, int KB, int RBW, int CB = 1>
+void launch_form(const PreparedArgs& a, const PreparedLayout& L, int grid_y, size_t lds, hipStream_t stream) {
+  if (a.plan) {
+    plan_record(a.plan, "spmm_rows16_prepared_kernel<DT=%d,NW=%d,XMODE=%d,KB=%d,RBW=%d,CB=%d> grid=%dx%d block=%d", DT, NW, XMODE,
+                KB, RBW, CB, a.s.M / (kRows * RBW), grid_y, NW * 64);
+    return;
+  }
   const uint8_t* base = static_cast<const uint8_t*>(a.prepared);
-  auto x = static_cast<const uint16_t*>(a.X);
-  const int col_blocks = (a.N + kCols - 1) / kCols;
-#define HINM_ROWS16(MODE, GRID_Y, X_PTR, Y_OFF, LDS) HINM_ROWS16_CB(MODE, 1, KB, GRID_Y, X_PTR, Y_OFF, LDS)
-#define HINM_ROWS16_CB(MODE, CBV, KBV, GRID_Y, X_PTR, Y_OFF, LDS)                                                \
-  if (a.plan)                                                                                                    \
-    plan_record(a.plan, "spmm_rows16_prepared_kernel<DT=%d,NW=%d,XMODE=%d,KB=%d,RBW=%d,CB=%d> grid=%dx%d block=%d", \
-                DT, NW, MODE, KBV, RBW, CBV, a.s.M / (kRows * RBW), (int)(GRID_Y), NW * 64);                     \
-  else                                                                                                           \
-    spmm_rows16_prepared_kernel<DT, NW, MODE, KBV, RBW, CBV>                                                     \
-      <<<dim3(a.s.M / (kRows * RBW), GRID_Y), NW * 64, LDS, stream>>>(                                           \
-          base + L.a_offset, reinterpret_cast<const int32_t*>(base + L.gather_offset),                           \
-          reinterpret_cast<const int32_t*>(base + L.pi_out_offset), base + L.zero_offset, X_PTR, a.ldx,          \
-          a.out_f32 ? static_cast<void*>(static_cast<float*>(a.Y) + (Y_OFF))                                     \
-                    : static_cast<void*>(static_cast<uint16_t*>(a.Y) + (Y_OFF)),                                 \
-          a.ldy, a.s.V, L.RB, L.S, a.N - (Y_OFF), a.s.K, a.relu, a.out_f32)
-  if (a.N == 1) {
+  spmm_rows16_prepared_kernel<DT, NW, XMODE, KB, RBW, CB><<<dim3(a.s.M / (kRows * RBW), grid_y), NW * 64, lds, stream>>>(
+      base + L.a_offset, reinterpret_cast<const int32_t*>(base + L.gather_offset),
+      reinterpret_cast<const int32_t*>(base + L.pi_out_offset), base + L.zero_offset, static_cast<const uint16_t*>(a.X), a.ldx,
+      a.Y, a.ldy, a.s.V, L.RB, L.S, a.N, a.s.K, a.relu, a.out_f32);
+}
+
+template <int DT, int NW, int KB, int RBW>
+void launch_one_column(const PreparedArgs& a, const PreparedLayout& L, hipStream_t stream) {
+  if constexpr (KB == 3 || (NW == 8 && KB >= 4)) {  // (the others never have more than four steps a wave)
     // staging the input vector pays once a wave gathers for more than four steps (4096 x 11008 at 50 %:
     // 10.4 -> 9.9 us; with four steps per wave and 688 workgroups it costs 0.8 us instead), with any vector that fits (us, not
     // staged -> staged on eight waves: 6656 x 17920, 140 steps 31.5 -> 17.2, 9216 x 20000, 157 steps 46.5 -> 27.0, 5120 x 24560,
@@ -318,30 +309,24 @@ void launch_modes(const PreparedArgs& a, const PreparedLayout& L, int blocks_per
       // slabs (static) plus the vector (dynamic) can exceed the default 64 KB of a workgroup
       if (!a.plan && raise_lds_limit<spmm_rows16_prepared_kernel<DT, NW, 3, KB, RBW>>(kXLdsMaxBytes) != hipSuccess)
         return;  // the error stays pending and is reported by the caller's hipGetLastError
-      HINM_ROWS16(3, 1, x, 0, x_bytes);
-    } else {
-      HINM_ROWS16(2, 1, x, 0, 0);
-    }
-    return;
-  }
-  // rows of X that start on 16-byte boundaries: vector loads for every block, the ragged last one included
-  if constexpr (NW <= 8 && KB <= 4) {  // (sixteen waves leave 128 registers per lane: not enough for several blocks)
-    if (blocks_per_wg == 4 && a.ldx % 8 == 0) {  // (batches of two steps: four blocks of input rows per step)
-      HINM_ROWS16_CB(1, 4, 2, (col_blocks + 3) / 4, x, 0, 0);
-      return;
-    }
-    if (blocks_per_wg == 2 && a.ldx % 8 == 0) {
-      HINM_ROWS16_CB(1, 2, KB, (col_blocks + 1) / 2, x, 0, 0);
+      launch_form<DT, NW, 3, KB, RBW>(a, L, 1, x_bytes, stream);
       return;
     }
   }
-  if (a.ldx % 8 == 0) {
-    HINM_ROWS16(1, col_blocks, x, 0, 0);
-  } else {
-    HINM_ROWS16(0, col_blocks, x, 0, 0);
+  launch_form<DT, NW, 2, KB, RBW>(a, L, 1, 0, stream);
+}
+
+// Several columns: rows of X start on 16-byte boundaries (the calls ask for it), vector loads for every block, the ragged last
+// one included.
+template <int DT, int NW, int KB, int RBW>
+void launch_columns(const PreparedArgs& a, const PreparedLayout& L, int blocks_per_wg, hipStream_t stream) {
+  const int col_blocks = (a.N + kCols - 1) / kCols;
+  if constexpr (NW <= 8 && KB == 4) {  // (sixteen waves leave 128 registers per lane: not enough for several blocks)
+    // (batches of two steps: four blocks of input rows per step)
+    if (blocks_per_wg == 4) return launch_form<DT, NW, 1, 2, RBW, 4>(a, L, (col_blocks + 3) / 4, 0, stream);
+    if (blocks_per_wg == 2) return launch_form<DT, NW, 1, KB, RBW, 2>(a, L, (col_blocks + 1) / 2, 0, stream);
   }
-#undef HINM_ROWS16
-#undef HINM_ROWS16_CB
+  launch_form<DT, NW, 1, KB, RBW>(a, L, col_blocks, 0, stream);
 }
 
 // The layer's input rows resident in LDS (XMODE 4): 16 columns, 64 rows per workgroup.
@@ -463,25 +448,42 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   return p;
 }
 
+// The forms that `plan_rows16` chooses: four 16-row blocks only beyond 16 columns, and then eight waves at most.
 template <int DT, int RBW>
 void launch_waves(const PreparedArgs& a, const Rows16Plan& plan, hipStream_t stream) {
   const PreparedLayout L = prepared_layout(a.s);
-  const int blocks = plan.blocks_per_wg;
-  switch (plan.nw * 8 + plan.kb) {
-    case 1 * 8 + 4: return launch_modes<DT, 1, 4, RBW>(a, L, blocks, stream);
-    case 2 * 8 + 4: return launch_modes<DT, 2, 4, RBW>(a, L, blocks, stream);
-    case 4 * 8 + 1: return launch_modes<DT, 4, 1, RBW>(a, L, 1, stream);
-    case 4 * 8 + 2: return launch_modes<DT, 4, 2, RBW>(a, L, 1, stream);
-    case 4 * 8 + 4: return launch_modes<DT, 4, 4, RBW>(a, L, blocks, stream);
-    case 8 * 8 + 1: return launch_modes<DT, 8, 1, RBW>(a, L, 1, stream);
-    case 8 * 8 + 2: return launch_modes<DT, 8, 2, RBW>(a, L, 1, stream);
-    case 8 * 8 + 3: return launch_modes<DT, 8, 3, RBW>(a, L, 1, stream);
-    case 8 * 8 + 4: return launch_modes<DT, 8, 4, RBW>(a, L, blocks, stream);
-    case 8 * 8 + 5: return launch_modes<DT, 8, 5, RBW>(a, L, 1, stream);
-    case 8 * 8 + 6: return launch_modes<DT, 8, 6, RBW>(a, L, 1, stream);
-    case 16 * 8 + 3: return launch_modes<DT, 16, 3, RBW>(a, L, 1, stream);
-    case 16 * 8 + 4: return launch_modes<DT, 16, 4, RBW>(a, L, 1, stream);
-    default: return launch_modes<DT, 16, 6, RBW>(a, L, 1, stream);
+  const int blocks = plan.blocks_per_wg, form = plan.nw * 8 + plan.kb;
+  if constexpr (RBW <= 2) {
+    if (a.N == 1) {
+      switch (form) {
+        case 4 * 8 + 1: return launch_one_column<DT, 4, 1, RBW>(a, L, stream);
+        case 4 * 8 + 2: return launch_one_column<DT, 4, 2, RBW>(a, L, stream);
+        case 4 * 8 + 4: return launch_one_column<DT, 4, 4, RBW>(a, L, stream);
+        case 8 * 8 + 2: return launch_one_column<DT, 8, 2, RBW>(a, L, stream);
+        case 8 * 8 + 3: return launch_one_column<DT, 8, 3, RBW>(a, L, stream);
+        case 8 * 8 + 4: return launch_one_column<DT, 8, 4, RBW>(a, L, stream);
+        case 8 * 8 + 5: return launch_one_column<DT, 8, 5, RBW>(a, L, stream);
+        case 16 * 8 + 4: return launch_one_column<DT, 16, 4, RBW>(a, L, stream);
+        default: return launch_one_column<DT, 16, 3, RBW>(a, L, stream);
+      }
+    }
+    switch (form) {
+      case 8 * 8 + 3: return launch_columns<DT, 8, 3, RBW>(a, L, 1, stream);
+      case 8 * 8 + 5: return launch_columns<DT, 8, 5, RBW>(a, L, 1, stream);
+      case 8 * 8 + 6: return launch_columns<DT, 8, 6, RBW>(a, L, 1, stream);
+      case 16 * 8 + 4: return launch_columns<DT, 16, 4, RBW>(a, L, 1, stream);
+      case 16 * 8 + 6: return launch_columns<DT, 16, 6, RBW>(a, L, 1, stream);
+      default: break;
+    }
+  }
+  switch (form) {
+    case 1 * 8 + 4: return launch_columns<DT, 1, 4, RBW>(a, L, blocks, stream);
+    case 2 * 8 + 4: return launch_columns<DT, 2, 4, RBW>(a, L, blocks, stream);
+    case 4 * 8 + 1: return launch_columns<DT, 4, 1, RBW>(a, L, 1, stream);
+    case 4 * 8 + 4: return launch_columns<DT, 4, 4, RBW>(a, L, blocks, stream);
+    case 8 * 8 + 1: return launch_columns<DT, 8, 1, RBW>(a, L, 1, stream);
+    case 8 * 8 + 2: return launch_columns<DT, 8, 2, RBW>(a, L, 1, stream);
+    default: return launch_columns<DT, 8, 4, RBW>(a, L, blocks, stream);
   }
 }
 
