@@ -283,7 +283,7 @@ def test_prepared_c3_decode_full(idx):
 @pytest.mark.parametrize("N", [1, 5, 16])
 @pytest.mark.parametrize("Kv", [2056, 2112, 3072])
 def test_sixteen_row_kernel_with_33_to_48_steps(Kv, N, dtype):
-    """Eight waves with batches of six: one step beyond 32 (the last one padded), whole ones, and the longest pass."""
+    """Eight waves: one step beyond 32 (the last one padded), whole ones, and the longest pass."""
     import paper_2407_20496_amd as hinm
     M, K, V = 96, 3080, 32
     ld = N if N == 1 else (N + 7) // 8 * 8
@@ -386,45 +386,95 @@ def test_chain_of_ten_layers():
     assert h.any() and np.array_equal(gu.host_bits(Y), h)
 
 
-@pytest.mark.parametrize("S", [1, 4, 5, 8, 9, 12, 13, 16, 17, 24, 25, 32, 33, 40, 41, 48, 49, 64, 65, 96, 97])
+def _rows16_form(c, N, variant=11):
+    """What the 16-row kernel is launched with: waves, steps of a batch, 16-row blocks, and how it reads X (2: gathers of one
+    column, 3: that column staged in LDS)."""
+    import paper_2407_20496_amd as hinm
+    ld = N if N == 1 else (N + 7) // 8 * 8
+    text, launches = hinm.hinm_spmm_prepared_plan(c.M, c.K, c.V, c.Kv, c.dtype, N, ld, ld, variant << 16)
+    assert launches == 1 and text.startswith("spmm_rows16_prepared_kernel<"), text
+    form = dict(item.split("=") for item in text[text.index("<") + 1:text.index(">")].split(","))
+    return {k: int(v) for k, v in form.items()}
+
+
+# steps: (waves, batch) of one column, of 2 to 16; three column blocks differ above 16 steps
+WAVES_AND_BATCH = {
+    1: ((4, 1), (4, 1)), 4: ((4, 1), (4, 1)), 5: ((4, 2), (8, 1)), 8: ((4, 2), (8, 1)), 9: ((8, 2), (8, 2)), 12: ((8, 2), (8, 2)),
+    13: ((8, 2), (8, 2)), 16: ((8, 2), (8, 2)), 17: ((8, 3), (8, 3)), 24: ((8, 3), (8, 3)), 25: ((8, 4), (8, 4)),
+    32: ((8, 4), (8, 4)), 33: ((8, 5), (8, 5)), 40: ((8, 5), (8, 5)), 41: ((8, 3), (8, 6)), 48: ((8, 3), (8, 6)),
+    49: ((16, 4), (16, 4)), 64: ((8, 4), (16, 4)), 65: ((16, 3), (16, 6)), 96: ((16, 3), (16, 6)), 97: ((16, 3), (16, 4))}
+
+
+@pytest.mark.parametrize("S", list(WAVES_AND_BATCH))
 @pytest.mark.parametrize("N", [1, 6, 16, 40])
 def test_waves_and_batches_of_the_16_row_kernel(S, N):
     """Waves and batches change at 4, 8, 12, 16, 24, 32, 40, 48, 64 and 96 steps; the last step is ragged."""
-    _check(synth.small_case(96, 64 * S + 8, 32, 64 * S - 24, N, "bf16" if S % 2 else "f16", 700 + S), N, [0, 11], relu=S % 3 == 0)
+    c = synth.small_case(96, 64 * S + 8, 32, 64 * S - 24, N, "bf16" if S % 2 else "f16", 700 + S)
+    form = _rows16_form(c, N)
+    want = WAVES_AND_BATCH[S][N > 1] if N <= 16 or S <= 16 else (8, 4) if S <= 32 else (16, 4) if S <= 64 else (16, 6)
+    assert (form["NW"], form["KB"], form["RBW"]) == (*want, 1), form
+    assert form["XMODE"] == (1 if N > 1 else 3 if S > 4 * form["NW"] else 2), form
+    _check(c, N, [0, 11], relu=S % 3 == 0)
 
 
-@pytest.mark.parametrize("S", [1, 7, 12, 13, 20])
+@pytest.mark.parametrize("S,one,several", [(1, (4, 1), (4, 1)), (7, (4, 2), (8, 1)), (12, (8, 2), (8, 2)), (13, (4, 4), (4, 4)),
+                                           (20, (8, 3), (8, 3))])
 @pytest.mark.parametrize("N", [1, 9])
-def test_waves_of_the_16_row_kernel_with_many_workgroups(S, N):
+def test_waves_of_the_16_row_kernel_with_many_workgroups(S, one, several, N):
     """Both halves of a 32-row block in a workgroup (256 of them and more); above 12 steps the count of workgroups decides."""
-    _check(synth.small_case(8320, 64 * S, 64, 64 * S - 8, N, "f16", 720 + S), N, [11])
+    c = synth.small_case(8320, 64 * S, 64, 64 * S - 8, N, "f16", 720 + S)
+    form = _rows16_form(c, N)
+    assert (form["NW"], form["KB"]) == (several if N > 1 else one) and form["RBW"] == 2, form
+    _check(c, N, [11])
 
 
-@pytest.mark.parametrize("S", [40, 41, 48, 49])
-def test_waves_of_the_16_row_kernel_with_128_workgroups(S):
-    _check(synth.small_case(2048, 64 * S, 32, 64 * S - 8, 11, "bf16", 742), 11, [11])
+@pytest.mark.parametrize("S,waves,batch", [(40, 8, 5), (41, 8, 6), (48, 8, 6), (49, 16, 4)])
+def test_waves_of_the_16_row_kernel_with_128_workgroups(S, waves, batch):
+    c = synth.small_case(2048, 64 * S, 32, 64 * S - 8, 11, "bf16", 742)
+    form = _rows16_form(c, 11)
+    assert (form["NW"], form["KB"], form["RBW"]) == (waves, batch, 1), form
+    _check(c, 11, [11])
 
 
 def test_eight_waves_on_long_layers_of_one_column():
     """More than 256 workgroups beyond 64 steps."""
-    _check(synth.small_case(4128, 64 * 66, 32, 64 * 66 - 8, 1, "bf16", 741), 1, [11])
+    c = synth.small_case(4128, 64 * 66, 32, 64 * 66 - 8, 1, "bf16", 741)
+    form = _rows16_form(c, 1)
+    assert (form["NW"], form["KB"], form["RBW"], form["XMODE"]) == (8, 3, 1, 3), form
+    _check(c, 1, [11])
+
+
+@pytest.mark.parametrize("M,S,waves,batch", [(8192, 33, 8, 5), (8192, 40, 8, 5), (8192, 41, 8, 3), (8192, 48, 8, 3), (8192, 57, 8, 4),
+                                             (8192, 64, 8, 4), (8192, 66, 16, 3), (8224, 52, 8, 4), (8224, 66, 8, 3)])
+def test_both_halves_with_one_staged_column(M, S, waves, batch):
+    """256 and 257 workgroups of 32 rows, the input vector in LDS."""
+    c = synth.small_case(M, 64 * S, 32, 64 * S - 8, 1, "bf16" if S % 2 else "f16", 780 + S)
+    form = _rows16_form(c, 1, 0)
+    assert (form["NW"], form["KB"], form["RBW"], form["XMODE"]) == (waves, batch, 2, 3), form
+    _check(c, 1, [0])
+
+
+@pytest.mark.parametrize("M,S,rows", [(8224, 24, 2), (8224, 25, 1), (8224, 32, 1), (8224, 33, 2), (8192, 32, 2)])
+def test_halves_of_one_batch_that_spread_more_evenly(M, S, rows):
+    """One column, 25 to 32 steps: 514 workgroups of 16 rows rather than 257 of 32; 512 and 256 make one round each."""
+    c = synth.small_case(M, 64 * S, 32, 64 * S - 8, 1, "f16", 790 + S)
+    assert _rows16_form(c, 1, 0)["RBW"] == rows
+    _check(c, 1, [0])
 
 
 @pytest.mark.parametrize("K", [16384, 16392, 20480, 20488, 24560, 24568, 24576])
 def test_vectors_of_up_to_six_pieces_a_thread(K):
     """Eight waves stage four pieces of 4096 elements, five or six; beyond 48 KB none."""
-    import paper_2407_20496_amd as hinm
     c = synth.small_case(64, K, 32, 64 * 40 - 8, 1, "bf16", 750)
-    assert f"NW=8,XMODE={3 if K <= 24568 else 2}," in hinm.hinm_spmm_prepared_plan(c.M, K, c.V, c.Kv, c.dtype, 1, 1, 1)[0]
+    form = _rows16_form(c, 1, 0)
+    assert (form["NW"], form["XMODE"]) == (8, 3 if K <= 24568 else 2), form
     _check(c, 1, [0])
 
 
 @pytest.mark.parametrize("S,K,N,waves,batch", [(49, 9216, 1, 16, 4), (56, 9216, 1, 16, 4), (56, 9224, 1, 8, 4), (57, 4096, 1, 8, 4),
                                                (64, 4096, 9, 16, 4), (128, 8192, 9, 16, 4), (129, 8256, 9, 16, 6), (193, 12352, 16, 16, 6)])
 def test_waves_and_batches_of_long_layers(S, K, N, waves, batch):
-    import paper_2407_20496_amd as hinm
     c = synth.small_case(64, K, 32, 64 * S - 8, N, "f16", 760)
-    ld = 1 if N == 1 else 16
-    text = hinm.hinm_spmm_prepared_plan(c.M, K, c.V, c.Kv, c.dtype, N, ld, ld)[0]
-    assert f"NW={waves}," in text and f"KB={batch}," in text, text
+    form = _rows16_form(c, N, 0)
+    assert (form["NW"], form["KB"]) == (waves, batch), form
     _check(c, N, [0])

@@ -249,3 +249,10 @@ def test_waves_and_batches_of_the_kernel_for_few_columns(S, V, N):
 def test_one_column_with_25_to_28_steps(S, tail):
     """Eight waves with batches of four, sixteen with two on both sides."""
     _check_full(synth.small_case(48, 64 * S + 40, 16, 64 * S + tail, 1, "f16" if tail else "bf16", 770 + S), 1, [0])
+
+
+@pytest.mark.parametrize("S,tail", [(0, 24), (4, 0), (4, 24), (8, 0), (12, 24), (16, 0), (24, 24), (28, 24), (32, 0), (40, 0), (40, 24), (48, 24)])
+def test_two_row_blocks_of_the_kernel_for_few_columns(S, tail):
+    """From 10240 rows on a workgroup owns both 16-row halves of 32 rows; the ragged step behind the whole ones then has its
+    own loads."""
+    _check_full(synth.small_case(10240, 64 * S + 40, 32, 64 * S + tail, 1, "f16" if S % 8 else "bf16", 800 + S), 1, [0])
