@@ -502,10 +502,8 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 // "a / b -> c / d us" is the 16-row kernel and then this one, with buffers rotated past that cache / from it.  A compute
 // unit fetches from memory at a bounded rate (neither more waves per workgroup nor requests further ahead change it), so
 // what counts there is how many units take part and for how many rounds.
-//   2 .. 4 columns: this one on tall layers of more than twelve steps (9600 rows and more).  Against the 16-row kernel's form
-//     with both halves of a 32-row block it is ahead from 49 steps on (7 layers 0.84 to 0.95 of the time from memory, 0.57 to 0.62 from
-//     the cache), level from memory between (14 to 48: 0.91 to 1.12) and ahead from the cache (0.67 to 1.01: 14208 x 12032, 47 steps,
-//     N = 4 17.1 / 16.4 -> 17.6 / 11.8); up to twelve steps the other is (26 layers 1.05 to 1.38: 11008 x 1280, 10 steps, N = 4 4.9 -> 6.7).
+//   2 .. 4 columns: the 16-row kernel has one row block per workgroup (11008 x 4096 at 50 %, N = 2: 13.3 / 12.0 ->
+//     10.6 / 5.9).
 //   5 .. 16: that kernel is ahead where its workgroups fit the chip in one round (4096 x 11008 at 50 %, N = 16: 13.7 / 12.1 ->
 //     17.5 / 8.8; 4096 x 4096: 6.3 / 4.9 -> 8.5 / 5.1; 8192 x 8192, Kv = 2048: 8.2 / 6.5 -> 9.6 / 6.2), this one with a second
 //     round (5120 x 5120: 13.4 / 11.7 -> 10.1 / 5.9; 7296 x 13240, N = 15: 37.9 / 34.7 -> 22.8 / 14.9) unless its workgroups have
@@ -521,7 +519,7 @@ static bool beats_rows16(const PreparedArgs& a) {
   const int64_t blocks = (int64_t)(a.s.M / 32) * ((a.N + 31) / 32);
   const int64_t others = spmm_rows16_prepared_workgroups(a);
   const bool tall = a.s.V % 64 == 0 && a.s.M / 64 >= 150;
-  if (a.N <= 4) return tall && S > 12;
+  if (a.N <= 4) return tall;
   if (a.N <= 16)
     return !spmm_rows16_resident_preferred(a) && others > 256 && (tall ? S >= 16 : a.N > 8 && S > 16);
   if (a.N <= 64)

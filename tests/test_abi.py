@@ -376,11 +376,3 @@ def test_waves_and_batches_of_long_layers(M, K, S, N, waves, batch):
     ld = 1 if N == 1 else 16
     text, _ = hinm.hinm_spmm_prepared_plan(M, K, 32, 64 * S, "bf16", N, ld, ld)
     assert f"NW={waves}," in text and f"KB={batch}," in text, text
-
-
-@pytest.mark.parametrize("M,S,N,kernel", [(9600, 12, 2, "rows16"), (9600, 13, 2, "mid"), (16384, 4, 4, "rows16"), (11008, 32, 3, "mid"),
-                                          (9472, 32, 4, "rows16"), (11008, 12, 1, "rows16")])
-def test_tall_layers_of_two_to_four_columns(M, S, N, kernel):
-    ld = 1 if N == 1 else 8
-    text, _ = hinm.hinm_spmm_prepared_plan(M, 128 * S, 128, 64 * S, "bf16", N, ld, ld)
-    assert text.startswith(f"spmm_{kernel}_"), text
