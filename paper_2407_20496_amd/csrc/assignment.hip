@@ -9,8 +9,9 @@
 //            way to the midpoint between its cap-th and (cap + 1)-th smallest (cost[i][j] - v[j]) - o[i][j] (damped
 //            max-product message passing; the midpoint is where exactly cap rows prefer the column).  This part is
 //            parallel over the matrix and runs on the whole workgroup.  Rows then take the column of their minimum
-//            while it has room.  On the 96 x 96 problems of the tile-wise search 2 to 6 rows stay free, on
-//            384 points x 48 clusters of 8 about 5 (60 and 300 from plain column and row minima).
+//            while it has room.  On 96 x 96 problems of the tile-wise search 2 to 6 rows stayed free, on 384 points x
+//            48 clusters of 8 about 5 (60 and 300 from plain column and row minima), before these sizes had a kernel
+//            of their own, below.
 //   paths  : for the free rows, on one wave that holds column 64 c + lane in register c: no barrier and no shared
 //            minimum in a link; a row arrives with one read per 64 columns from LDS (matrices up to some 150 KB) or
 //            L2, and the minimum over the lanes is six data-parallel-primitive moves on the high words of the costs
@@ -18,7 +19,7 @@
 // With capacities the matrix is n x m instead of n x n with every column repeated.
 // Measured, against one augmenting-path search per row from column minima on two to four waves: 64 problems of 512 x 512
 // (four iterations of the tile-wise search on 4096 x 4096) 161 -> 15 ms, 12 with `row_paths` (129 to 512 columns of one row
-// each 1.09 to 1.21 times).  Small problems have a kernel of their own, below.
+// each 1.09 to 1.21 times).
 // Every loop is bounded by the problem's size.  Costs may be of any finite size below 1e300: a row's smallest cost is
 // taken off the row first (a constant of a row changes no choice, but next to one of 1e39 the other rows' costs would
 // be rounded away), and the start, which works in single precision, scales what is left by the power of two of
@@ -30,7 +31,7 @@
 namespace hinm {
 namespace {
 
-constexpr int kStartRounds = 12;  // 384 x 48: path steps 62 after 10 rounds, 96 x 96: 30 .. 70 after 10, 15 .. 30 after 20
+constexpr int kStartRounds = 12;  // (chosen on 384 x 48: path steps 62 after 10 rounds; 96 x 96: 30 .. 70 after 10, 15 .. 30 after 20)
 constexpr double kInf = 1e300;  // distance of a column that is closed; costs are below
 constexpr double kFar = 5e299;  // distance of a column that cannot be reached yet
 constexpr int kFarHigh = 0x7e27e43c, kInfHigh = 0x7e37e43c;  // their high words
@@ -633,7 +634,7 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
   }
 }
 
-// ---- the same for problems whose matrix fits the workgroup's registers ------------------------------------------------
+// ---- the same for problems whose matrix fits the workgroup's registers, or nearly -------------------------------------
 //
 // What bounds the general kernel on these is the start: a row comes from LDS twice a round, one wave a row, with three
 // reductions over 64 lanes behind each other.  Here the matrix stays in registers, in single precision: eight lanes a row
@@ -645,8 +646,11 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
 // the other costs: that m x m matrix is worked out by the whole workgroup, held in LDS, and only the columns of a path are
 // worked out again after it.  A link of a path is one read instead of `cap`.
 // Per call, against the general kernel (3072 x 768, V = 64, us): 48 problems of 96 x 96 105 -> 62; 384, 192 and 96 points to 48
-// clusters 148 -> 24 on average, 35 to 53 the first round of a clustering, 7 to 15 the second; 48 x 48 45 -> 18.  What is left is
-// the chain of the paths, some 700 clocks a link with two columns a lane, 450 with one, and 3300 to 8500 clocks a round.
+// clusters 148 -> 24 on average, 35 to 53 the first round of a clustering, 7 to 15 the second; 48 x 48 45 -> 18.  The forms for 49 to 96
+// columns of up to 256 and 384 rows have 24 and 36 entries a thread and spill 43 and 98 registers; still, first and second round: 256
+// points to 64 clusters 190 -> 88 and 170 -> 31, 384 to 64 334 -> 121 and 255 -> 50, 384 to 96 462 -> 142 and 334 -> 50.  512 points (438
+// and 313 to 64 clusters) are the general kernel's.  What is left is the chain of the paths, some 700 clocks a link with two columns a lane,
+// 450 with one, and 3300 to 8500 clocks a round.
 
 constexpr int kTileThreads = 1024;
 constexpr int kTileWaves = kTileThreads / 64;
@@ -1221,7 +1225,7 @@ hipError_t launch_tile(const double* cost, int32_t* assign, int problems, int n,
   return hipGetLastError();
 }
 
-// Matrices of up to 36 entries a thread (of up to 16 without capacities, and 132 KB in LDS).
+// Matrices of up to 36 entries a thread (of up to 16 without capacities, and 132 KB in LDS); larger ones were not tried.
 bool tile_holds(int n, int m, int cap) {
   return cap == 1 ? m <= 128 : n <= 3 * kTileRows && m <= 96 && cap <= kTileMaxCap;
 }

@@ -502,8 +502,11 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 // "a / b -> c / d us" is the 16-row kernel and then this one, with buffers rotated past that cache / from it.  A compute
 // unit fetches from memory at a bounded rate (neither more waves per workgroup nor requests further ahead change it), so
 // what counts there is how many units take part and for how many rounds.
-//   2 .. 4 columns: the 16-row kernel has one row block per workgroup (11008 x 4096 at 50 %, N = 2: 13.3 / 12.0 ->
-//     10.6 / 5.9).
+//   2 .. 4 columns: this one on tall layers (9600 rows and more).  Against the 16-row kernel's form with both halves of a 32-row
+//     block it is ahead from 49 steps on (7 layers 0.84 to 0.95 of the time from memory, 0.57 to 0.62 from the cache), level from
+//     memory between 14 and 48 steps (0.91 to 1.12) and ahead from the cache (0.67 to 1.01: 14208 x 12032, 47 steps, N = 4 17.1 / 16.4 ->
+//     17.6 / 11.8); up to twelve steps it is behind (26 layers 1.05 to 1.38 of the time from memory, 0.92 to 1.23 from the cache:
+//     11008 x 1280, 10 steps, N = 4 4.9 -> 6.7 from memory), which the line does not go by.
 //   5 .. 16: that kernel is ahead where its workgroups fit the chip in one round (4096 x 11008 at 50 %, N = 16: 13.7 / 12.1 ->
 //     17.5 / 8.8; 4096 x 4096: 6.3 / 4.9 -> 8.5 / 5.1; 8192 x 8192, Kv = 2048: 8.2 / 6.5 -> 9.6 / 6.2), this one with a second
 //     round (5120 x 5120: 13.4 / 11.7 -> 10.1 / 5.9; 7296 x 13240, N = 15: 37.9 / 34.7 -> 22.8 / 14.9) unless its workgroups have
@@ -513,6 +516,9 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 //     short, where the other's last round is no more than 3/4 full (2176 x 10488, Kv = 2624, N = 32 1.06 / 1.7 times), where
 //     it needs sixteen waves (4096 x 11008, Kv = 2752, N = 32: 10.3 / 9.0 -> 10.3 / 5.5) or two batches per wave; else the
 //     16-row kernel (2048 x 8192, V = 32, Kv = 2048, N = 32: 5.9 / 4.9 -> 8.3 / 4.5; 768 x 3072 at 50 %: 4.9 / 3.6 -> 6.4 / 4.0).
+//     These examples are of the 16-row kernel before its layers of up to sixteen steps took a wave a step.  With those, 22 drawn layers of
+//     up to 16 steps that come here: up to seven steps 0.70 to 1.29 of its time, eight to 16 steps 0.72 to 1.11 (from memory: 1280 rows, 4
+//     steps, N = 40 3.0 there, 3.9 here; 10560 rows, 1 step, N = 64 6.2 and 4.4).
 //   65 .. 128: that kernel on the smallest layers (512 x 7048, Kv = 1760, N = 100: 5.7 / 4.6 -> 7.2 / 4.8).
 static bool beats_rows16(const PreparedArgs& a) {
   const int S = (a.s.Kv + 63) / 64;

@@ -400,9 +400,11 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   // at N = 384 9.2 -> 12.0 us).
   const int64_t col_blocks = (a.N + kCols - 1) / kCols;
   const bool quad = a.N > kCols && a.s.V % 64 == 0 && a.s.M >= 2048 && (a.s.M / 64) * col_blocks >= 256;
-  // One batch of eight waves, one column: everything is requested at once either way, and blocks of 16 rows are kept where
-  // they spread more evenly over the units (11008 x 4096, 32 steps, weights from HBM 8.3 us against 8.7; 20 and 40 steps 6.5
-  // against 6.1 and 10.6 against 9.8).
+  // One batch of eight waves, one column: everything is requested at once either way, and blocks of 16 rows are kept where they spread
+  // more evenly over the units.  From memory 25 layers of 8448 to 12288 rows with 25 to 32 steps 0.98 to 1.06 times (11008 x 4096, 32
+  // steps 8.9 -> 8.5 us; 8448 rows, 30 steps 8.2 -> 7.8), from the memory-side cache 0.90 to 1.01 (8.5 and 8.7): a layer is one of many.
+  // With 13 to 24 steps both are nearer to level (0.98 to 1.06 and 0.93 to 1.01; 11008 rows, 24 steps 7.3 and 7.1) and the line leaves them;
+  // beyond 32 the blocks of 16 lose either way (from memory 0.87 to 0.99).
   const int64_t halves = a.s.M / 16;
   const bool spread = a.N == 1 && L.S > 24 && L.S <= 32 && (halves / 2 + 255) / 256 * 2 > (halves + 255) / 256;
   const bool both = (a.s.M / 32) * col_blocks >= 256 && !spread;
