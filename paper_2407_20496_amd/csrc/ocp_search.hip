@@ -30,9 +30,10 @@ __device__ __forceinline__ int clamp_index(int x, int n) { return x < 0 ? 0 : (x
 // base[t][k] = sum over the positions of tile t that stay (ascending position) of the saliency in
 // column k; cluster[t][k] = the same over the channels of cluster t (cluster order).  The rows' numbers are looked up once a
 // workgroup and sixteen rows are requested before the first is added: with one row at a time, each behind its look-up and
-// the one before, 48 tiles of 64 rows and 768 columns took 17.3 us, 11.2 here (16384 x 16384, V = 128 367 -> 231).  LDS for what
-// the tile has and no more: with room for 4096 rows a unit held four workgroups (256 tiles of 32 rows, 2048 columns 25.7 us, 17.9
-// here, 8192 columns 72 and 59).
+// the one before, 96 tiles of 32 rows and 768 columns took 13.9 us, 6.6 here (16384 x 16384, V = 128 365 -> 237, magnitudes of W
+// 312 -> 115).  Which of the two is read is settled outside the loops: chosen at every read, each read of W waited for the one
+// before (16384 x 16384 317 us, 512 tiles of 32 rows, 2048 columns 36 against 21).  LDS for what the tile has and no more: with room
+// for 4096 rows a unit held four workgroups (256 tiles of 32 rows, 8192 columns 72 us, 57 here; W 139 and 39).
 constexpr int kSumRows = 16;
 inline size_t ocp_sums_lds_bytes(int V, int n) { return (size_t)V * 5 + (size_t)n * 4; }
 template <int DT>
@@ -62,24 +63,29 @@ __global__ __launch_bounds__(kThreads) void ocp_sums_kernel(const uint16_t* __re
   __syncthreads();
   const int k = blockIdx.y * kThreads + threadIdx.x;
   if (k >= K) return;
-  double stay = 0.0;
-  for (int p0 = 0; p0 < V; p0 += kSumRows) {
-    double x[kSumRows];
+  double stay = 0.0, come = 0.0;
+  auto add_rows = [&](auto load, auto saliency) {
+    for (int p0 = 0; p0 < V; p0 += kSumRows) {
+      decltype(load(0)) x[kSumRows];
 #pragma unroll
-    for (int r = 0; r < kSumRows; ++r) x[r] = saliency_at<DT>(W, rho, (size_t)row_of[min(p0 + r, V - 1)] * K + k);
+      for (int r = 0; r < kSumRows; ++r) x[r] = load(row_of[min(p0 + r, V - 1)]);
 #pragma unroll
-    for (int r = 0; r < kSumRows; ++r)
-      if (p0 + r < V && !leaves[p0 + r]) stay += x[r];
-  }
-  double come = 0.0;
-  for (int e0 = 0; e0 < n; e0 += 4) {
-    double x[4];
+      for (int r = 0; r < kSumRows; ++r)
+        if (p0 + r < V && !leaves[p0 + r]) stay += saliency(x[r]);
+    }
+    for (int e0 = 0; e0 < n; e0 += 4) {
+      decltype(load(0)) x[4];
 #pragma unroll
-    for (int r = 0; r < 4; ++r) x[r] = saliency_at<DT>(W, rho, (size_t)come_row[min(e0 + r, n - 1)] * K + k);
+      for (int r = 0; r < 4; ++r) x[r] = load(come_row[min(e0 + r, n - 1)]);
 #pragma unroll
-    for (int r = 0; r < 4; ++r)
-      if (e0 + r < n) come += x[r];
-  }
+      for (int r = 0; r < 4; ++r)
+        if (e0 + r < n) come += saliency(x[r]);
+    }
+  };
+  if (rho) add_rows([&](int row) { return rho[(size_t)row * K + k]; }, [](float x) { return (double)x; });
+  else
+    add_rows([&](int row) { return W[(size_t)row * K + k]; },
+             [](uint16_t x) { return (double)__builtin_fabsf(bits_to_float<DT>(x)); });
   base[(size_t)t * K + k] = stay;
   cluster[(size_t)t * K + k] = come;
 }

@@ -241,3 +241,16 @@ def test_sums_of_the_tallest_tiles(V, n):
 def test_distances_with_one_and_two_points_a_wave(T, n, K):
     """Up to three workgroups a unit (192 x 5 to 192: 720) and more; pieces of 64 columns with and without a rest."""
     test_balanced_kmeans_round_by_round(T * 5, K, 5, 8, n, "bf16", True)
+
+
+@pytest.mark.parametrize("V,n", [(15, 3), (16, 4), (17, 5), (40, 8), (40, 40)])
+@pytest.mark.parametrize("dtype", ["f16", "bf16"])
+def test_sums_of_magnitudes(V, n, dtype):
+    """No saliency given: the magnitudes of W, sixteen rows requested at a time, samples four at a time."""
+    c = synth.small_case(6 * V, 264, V, 128, 1, dtype, 620)
+    Wb = c.weights()
+    rng = np.random.default_rng(V + n)
+    samples = np.stack([rng.permutation(V)[:n] for _ in range(c.T)])[None].astype(np.int32)
+    start = rng.permutation(c.M).astype(np.int32)
+    after, obj = _gpu_search(c, Wb, None, start, samples, None)
+    _check_iteration(c, gyro.saliency_matrix(Wb, dtype, None), start, after, samples[0], None, obj[0], exact=False)
