@@ -649,8 +649,8 @@ __global__ __launch_bounds__(THREADS) void assign_kernel(const double* __restric
 // clusters 148 -> 24 on average, 35 to 53 the first round of a clustering, 7 to 15 the second; 48 x 48 45 -> 18.  The forms for 49 to 96
 // columns of up to 256 and 384 rows have 24 and 36 entries a thread and spill 43 and 98 registers; still, first and second round: 256
 // points to 64 clusters 190 -> 88 and 170 -> 31, 384 to 64 334 -> 121 and 255 -> 50, 384 to 96 462 -> 142 and 334 -> 50.  512 points (438
-// and 313 to 64 clusters) are the general kernel's.  What is left is the chain of the paths, some 700 clocks a link with two columns a lane,
-// 450 with one, and 3300 to 8500 clocks a round.
+// and 313 to 64 clusters) are the general kernel's.  What is left is the chain of the paths, some 700 clocks a link with two
+// columns a lane, 450 with one, and 3300 to 8500 clocks a round.
 
 constexpr int kTileThreads = 1024;
 constexpr int kTileWaves = kTileThreads / 64;

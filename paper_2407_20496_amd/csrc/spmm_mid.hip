@@ -516,9 +516,9 @@ hipError_t launch_planned(const MidCall& c, hipStream_t stream) {
 //     short, where the other's last round is no more than 3/4 full (2176 x 10488, Kv = 2624, N = 32 1.06 / 1.7 times), where
 //     it needs sixteen waves (4096 x 11008, Kv = 2752, N = 32: 10.3 / 9.0 -> 10.3 / 5.5) or two batches per wave; else the
 //     16-row kernel (2048 x 8192, V = 32, Kv = 2048, N = 32: 5.9 / 4.9 -> 8.3 / 4.5; 768 x 3072 at 50 %: 4.9 / 3.6 -> 6.4 / 4.0).
-//     These examples are of the 16-row kernel before its layers of up to sixteen steps took a wave a step.  With those, 22 drawn layers of
-//     up to 16 steps that come here: up to seven steps 0.70 to 1.29 of its time, eight to 16 steps 0.72 to 1.11 (from memory: 1280 rows, 4
-//     steps, N = 40 3.0 there, 3.9 here; 10560 rows, 1 step, N = 64 6.2 and 4.4).
+//     These examples are of the 16-row kernel before its layers of up to sixteen steps took a wave a step.  With those, 22 drawn
+//     layers of up to 16 steps that come here: up to seven steps 0.70 to 1.29 of its time, eight to 16 steps 0.72 to 1.11 (from
+//     memory: 1280 rows, 4 steps, N = 40 3.0 there, 3.9 here; 10560 rows, 1 step, N = 64 6.2 and 4.4).
 //   65 .. 128: that kernel on the smallest layers (512 x 7048, Kv = 1760, N = 100: 5.7 / 4.6 -> 7.2 / 4.8).
 static bool beats_rows16(const PreparedArgs& a) {
   const int S = (a.s.Kv + 63) / 64;

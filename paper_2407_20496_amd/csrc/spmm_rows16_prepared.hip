@@ -371,13 +371,14 @@ struct Rows16Plan {
 // steps, 1.15 up to eight, 1.1 up to sixteen unless several workgroups of eight waves share a unit (6528 x 7512, 15 steps, N = 16, 408
 // workgroups 0.91), 1.07 up to 24, 1.05 up to 40.  Beyond (us, weights from memory): one column, 41 to 48 steps, batches of three
 // against one of six on ten layers 0.77 to 0.90 of the time (11008 x 5632, 44 steps 9.8 and 12.8); 49 to 56 steps are one batch
-// on sixteen waves, which are ahead while the workgroups fit the units in one round (1600 x 6256, 49 steps 5.49 and 5.81; 8000 x 6400,
-// 50 steps 11.2 and 9.5) and as long as their gathers find the vector nearby (eight waves stage it: 0.97 times over 24 layers of
-// twice the kept columns, 1.03 with three times, 9408 and more, 1.12 with four: 1024 x 14336, 56 steps 7.00 and 5.89), with 57 to 64
-// eight are (2464 x 8064 6.84 -> 6.51, 8192 x 8192 13.5 -> 10.2; 9.5 of it from both halves of a block); 86 steps 10.0 -> 8.8, 5120 x 13824, 108 steps, 320 workgroups 21.6 -> 13.0 (sixteen waves 14.6).  With more columns
-// sixteen waves are ahead throughout (60 layers with 49 to 64 steps; 4992 x 6512, N = 4 13.6 and 15.3), in batches of six up to 96
-// steps (4096 x 11008, N = 16 11.9 and 14.0) and beyond 128, where four make three of them (30 layers, 1.03 times; 2112 x 10872, N = 2 21.1
-// and 22.4), of four between (97 to 128 steps, 16 layers 1.22 times; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3).
+// on sixteen waves, which are ahead while the workgroups fit the units in one round (1600 x 6256, 49 steps 5.49 and 5.81; 8000 x
+// 6400, 50 steps 11.2 and 9.5) and as long as their gathers find the vector nearby (eight waves stage it: 0.97 times over 24
+// layers of twice the kept columns, 1.03 with three times, 9408 and more, 1.12 with four: 1024 x 14336, 56 steps 7.00 and 5.89);
+// with 57 to 64 steps eight are (2464 x 8064 6.84 -> 6.51, 8192 x 8192 13.5 -> 10.2); 86 steps 10.0 -> 8.8, 5120 x 13824, 108
+// steps, 320 workgroups 21.6 -> 13.0 (sixteen waves 14.6).  With more columns sixteen waves are ahead throughout (60 layers with
+// 49 to 64 steps; 4992 x 6512, N = 4 13.6 and 15.3), in batches of six up to 96 steps (4096 x 11008, N = 16 11.9 and 14.0) and
+// beyond 128, where four make three of them (30 layers, 1.03 times; 2112 x 10872, N = 2 21.1 and 22.4), of four between (97 to 128
+// steps, 16 layers 1.22 times; 3072 x 16384, 128 steps, N = 16 19.6 -> 16.3).
 void one_block_waves(Rows16Plan& p, int S, int K, int N, int64_t wgs) {
   if (S <= 4) p.nw = 4, p.kb = 1;
   else if (S <= 8 && N == 1) p.nw = 4, p.kb = 2;
@@ -403,8 +404,8 @@ Rows16Plan plan_rows16(const PreparedArgs& a) {
   // One batch of eight waves, one column: everything is requested at once either way, and blocks of 16 rows are kept where they spread
   // more evenly over the units.  From memory 25 layers of 8448 to 12288 rows with 25 to 32 steps 0.98 to 1.06 times (11008 x 4096, 32
   // steps 8.9 -> 8.5 us; 8448 rows, 30 steps 8.2 -> 7.8), from the memory-side cache 0.90 to 1.01 (8.5 and 8.7): a layer is one of many.
-  // With 13 to 24 steps both are nearer to level (0.98 to 1.06 and 0.93 to 1.01; 11008 rows, 24 steps 7.3 and 7.1) and the line leaves them;
-  // beyond 32 the blocks of 16 lose either way (from memory 0.87 to 0.99).
+  // With 13 to 24 steps both are nearer to level (0.98 to 1.06 and 0.93 to 1.01; 11008 rows, 24 steps 7.3 and 7.1) and the line
+  // leaves them; beyond 32 the blocks of 16 lose either way (from memory 0.87 to 0.99).
   const int64_t halves = a.s.M / 16;
   const bool spread = a.N == 1 && L.S > 24 && L.S <= 32 && (halves / 2 + 255) / 256 * 2 > (halves + 255) / 256;
   const bool both = (a.s.M / 32) * col_blocks >= 256 && !spread;

@@ -268,8 +268,9 @@ void launch_waves(const SpmmArgs& a, hipStream_t stream) {
   // waves, 2.36 with four.  Geometric means over 130 drawn layers: 1.36 up to two steps, 1.3 up to four, 1.17 up to eight (one
   // column: four waves, 1.15 against 1.13) and, with batches of two, 1.08 up to twelve (13 to 16 steps 0.95 to 1.09).  Up to 32
   // steps sixteen waves with batches of two are ahead with one column (1.09; 0.96 with up to 16), except at 25 to 28 (0.94 to 1.02 on 16
-  // layers, weights from memory: 12544 x 3584, V = 16 13.1 us on eight, 14.0 on sixteen).  Grids do not change the order: 16-row
-  // tiles with up to 36080 workgroups 1.09 to 1.6 times up to eight steps (3200 x 896, 7 steps, N = 2764 190 -> 118 us), 1.05 to 1.14 up to twelve.
+  // layers, weights from memory: 12544 x 3584, V = 16 13.1 us on eight, 14.0 on sixteen).  Grids do not change the
+  // order: 16-row tiles with up to 36080 workgroups 1.01 to 1.6 times up to eight steps (3200 x 896, 7 steps, N = 2764 190 -> 118
+  // us), 1.05 to 1.14 up to twelve.
   if (full_steps <= 4) launch_modes<DT, 4, 1, RBW>(a, stream);
   else if (full_steps <= 8 && a.N == 1) launch_modes<DT, 4, 2, RBW>(a, stream);
   else if (full_steps <= 8) launch_modes<DT, 8, 1, RBW>(a, stream);
